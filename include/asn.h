@@ -314,9 +314,10 @@ asn_status asn_contraction_work(asn_problem p, double* dense_flops, double* tile
 /* The contraction's own arithmetic: nonzero_flops = 2 C times the number of nonzero
  * entries of K in the stored operand type (FP32, or the BF16/FP16 copy), the products
  * the method needs (paper Section 3.5: S_as^+ is sparse).  The banded step
- * (ASN_FORM_BANDED) multiplies every stored nonzero of a pair's run plus the zeros that
- * pad wide runs to a multiple of four, which asn_contraction_work reports as its
- * tile_flops.  Errors: ASN_E_INVALID (NULL problem or pointer). */
+ * (ASN_FORM_BANDED) is counted in asn_contraction_work's tile_flops by every stored nonzero
+ * of a pair's run plus the zeros that pad wide runs to a multiple of four; in FP32 it adds
+ * the two ordinates at offsets +-d first, so it multiplies about half as often.
+ * Errors: ASN_E_INVALID (NULL problem or pointer). */
 asn_status asn_contraction_nonzero(asn_problem p, double* nonzero_flops);
 
 /* Free the handle and any memory the library allocated.  NULL is accepted. */

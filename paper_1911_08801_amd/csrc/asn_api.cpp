@@ -48,17 +48,17 @@ struct Layout {
     bool banded = false; // banded step: one kernel per step for a product ordinate set
     int ktab_len = 0;
     size_t off_psi0, off_psi1, off_Y, off_Kt, off_Klp, off_rdef, off_ktab, off_qi, off_coef, off_iso,
-        off_band, off_brange, off_bcoef, off_bfrag,
+        off_band, off_bcoef5, off_bcoef7, off_bcxy, off_bfrag,
         off_phi64, off_phipart, off_blk, off_fin, off_ypart, off_fix, off_delta, off_bmax0, off_bmax1, off_rec,
         off_tab, off_off, off_base, off_left, off_imp,
         total;
 };
 
-// Coefficients the banded form of a set of `levels` polar levels of `azim` azimuths
-// can need at most (reach up to kBandMaxReach, runs padded to 4).
+// Coefficients either table of band_scatter_tables can need at most for `levels` polar
+// levels of `azim` azimuths: offsets 0 .. azim / 2 (a multiple of 4), 7 columns each; and 16
+// more (the kernel reads whole scalar loads).
 static size_t band_coef_capacity(int levels, int azim) {
-    const int span = 2 * asn::kBandMaxReach + 1;
-    return (size_t)levels * span * (size_t)round_up(azim, 4);
+    return (size_t)levels * 7 * (size_t)(1 + round_up(azim / 2, 4)) + 16;
 }
 
 // log2 of an accepted operand scale block (0 selects the default), else -1.
@@ -141,11 +141,11 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
         L.ktab_len = mt + 1 + 2 * mt * (L.Qp / bk);   // offsets, k-steps, sub-block masks
         L.off_ktab = take((size_t)L.ktab_len * 4);
     }
-    // level descriptors, 8 words, and 8 zero words after them (the kernel may read one
-    // descriptor word past the last level's)
+    // level descriptors, 8 words (reduced precision: one more)
     L.off_band = take(L.banded ? (size_t)(band_levels + 1) * 32 : 0);
-    L.off_brange = take(L.banded ? (size_t)band_levels * 8 : 0);    // coefficient ranges, int2
-    L.off_bcoef = take(L.banded && !L.lowp ? band_coef_capacity(band_levels, band_azim) * 4 : 0);
+    L.off_bcoef5 = take(L.banded && !L.lowp ? band_coef_capacity(band_levels, band_azim) * 4 : 0);
+    L.off_bcoef7 = take(L.banded && !L.lowp ? band_coef_capacity(band_levels, band_azim) * 4 : 0);
+    L.off_bcxy = take(L.banded && !L.lowp ? (size_t)Q * 8 : 0);
     // reduced-precision banded step: per level and one more, 2 kBandLpMaxReach + 1 pair
     // slots of n_az / 16 A operands of 1 KiB and a (cx, cy) table of n_az float pairs, and
     // 1 KiB after them
@@ -211,12 +211,11 @@ struct asn_problem_s {
     StepArgs tab[2];          // step arguments when psi buffer 0 / 1 holds the state
     int blocks[asn::KT_COUNT];
     std::unique_ptr<asn::ImplicitSolver> imp;   // the implicit scheme's solver (else null)
-    int band_levels = 0, band_azim = 0, band_reach = 0, band_cmax = 0;   // banded step (else 0)
+    int band_levels = 0, band_azim = 0, band_reach = 0;   // banded step (else 0)
     size_t band_lds() const {
-        return dtype == ASN_GEMM_F32 ? asn::band_lds_bytes(band_azim, band_reach, band_cmax)
+        return dtype == ASN_GEMM_F32 ? asn::band_lds_bytes(band_azim)
                                      : asn::band_lp_lds_bytes(band_azim, band_reach, dtype);
     }
-    bool band_wide_rows() const { return nx >= asn::kBandWideRowCells; }
 };
 
 struct asn_batch_s {
@@ -225,8 +224,7 @@ struct asn_batch_s {
     int launch_scheme = 0;   // scheme, or its flat-chunk stencil form
     int band_az = 0;         // banded batches: the azimuth count and LDS bytes per block
     size_t band_lds = 0;
-    int band_reach = 0;      // the largest reach of a banded reduced-precision batch
-    bool band_wide = false;  // every problem's rows are wide (asn::kBandWideRowCells)
+    int band_reach = 0;      // the largest reach of a banded batch
     hipStream_t stream = nullptr;
     std::vector<StepArgs> tab;
     std::vector<int> off;
@@ -284,13 +282,13 @@ StepArgs make_args(asn_problem p, int cur) {
     a.rec = reinterpret_cast<double*>(b + L.off_rec);
     if (L.banded) {
         a.band = reinterpret_cast<const uint4*>(b + L.off_band);   // two per level
-        a.brange = reinterpret_cast<const int2*>(b + L.off_brange);
-        a.bcoef = reinterpret_cast<const float*>(b + L.off_bcoef);
+        a.bcoef5 = reinterpret_cast<const float*>(b + L.off_bcoef5);
+        a.bcoef7 = reinterpret_cast<const float*>(b + L.off_bcoef7);
+        a.bcxy = reinterpret_cast<const float2*>(b + L.off_bcxy);
         a.bfrag = reinterpret_cast<const uint4*>(b + L.off_bfrag);
         a.n_lev = p->band_levels;
         a.n_az = p->band_azim;
         a.reach = p->band_reach;
-        a.bcmax = p->band_cmax;
     }
     return a;
 }
@@ -591,6 +589,8 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
     // banded step when K has that form (ASN_FORM_AUTO) or on request (ASN_FORM_BANDED)
     asn::BandForm bf;
     bool banded = false;
+    std::vector<uint32_t> sdesc;   // FP32 kernel: level descriptors and coefficients
+    std::vector<float> coef5, coef7;
     if (band_candidate(p->dtype, p->scheme, opt.step_form, quad, C)) {
         // the values the kernel multiplies: FP32 K, or its BF16 / FP16 rounding
         std::vector<float> K32((size_t)Q * Q);
@@ -605,6 +605,7 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         }
         banded = asn::band_form(quad->n_polar, quad->n_azim, K32.data(), asn::kBandMaxReach,
                                 asn::kBandNarrow, bf);
+        if (banded && p->dtype == ASN_GEMM_F32) banded = asn::band_scatter_tables(bf, sdesc, coef5, coef7);
         if (banded && p->dtype != ASN_GEMM_F32) {
             // the reduced-precision kernel takes one row defect per level (the rows of a
             // level hold the same values, so their FP64 sums agree; checked) and must fit
@@ -629,7 +630,6 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         p->band_levels = bf.levels;
         p->band_azim = bf.azim;
         p->band_reach = bf.reach;
-        p->band_cmax = bf.cmax;
         p->L = make_layout(p->nx, p->ny, Q, p->dtype, p->scheme, false, bf.levels, bf.azim);
     } else {
         p->L = make_layout(p->nx, p->ny, Q, p->dtype, p->scheme,
@@ -757,15 +757,17 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         coef[c].w = source ? (float)(p->dt * (double)source[c]) : 0.f;
     }
 
-    // the banded kernel's descriptors: counts as built, pair codes in its decoded form
     std::vector<uint32_t> ddesc;
+    std::vector<float> dcxy;   // FP32 banded kernel: (cx, cy) per ordinate
     std::vector<uint16_t> bfrag;
     if (banded && !L.lowp) {
-        ddesc = bf.desc;
+        ddesc = sdesc;   // and the FP64 weight of the level's ordinates
         for (int i = 0; i < bf.levels; ++i)
-            for (int t = 0; t < (int)bf.desc[(size_t)i * 8]; ++t)
-                ddesc[(size_t)i * 8 + 1 + t] =
-                    asn::band_device_code(bf.desc[(size_t)i * 8 + 1 + t], i, bf.reach, bf.azim);
+            std::memcpy(&ddesc[8 * (size_t)i + 4], &qi[(size_t)i * bf.azim].w, 8);
+        for (const QInfo& v : qi) {
+            dcxy.push_back(v.cx);
+            dcxy.push_back(v.cy);
+        }
     } else if (banded) {
         // per level and one more {pairs, first uint4 of its block, the level offsets k of its
         // pair slots (4 bits each), 0}.  Block l: 2 kBandLpMaxReach + 1 pair slots of
@@ -819,11 +821,12 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         (banded && !L.lowp &&
          (hipMemcpyAsync(b + L.off_band, ddesc.data(), ddesc.size() * 4, hipMemcpyHostToDevice,
                          p->stream) != hipSuccess ||
-          hipMemcpyAsync(b + L.off_brange, bf.range.data(), bf.range.size() * 4,
-                         hipMemcpyHostToDevice, p->stream) != hipSuccess ||
-          hipMemcpyAsync(b + L.off_bcoef, bf.coef.data(), bf.coef.size() * 4, hipMemcpyHostToDevice,
+          (!coef5.empty() && hipMemcpyAsync(b + L.off_bcoef5, coef5.data(), coef5.size() * 4,
+                                            hipMemcpyHostToDevice, p->stream) != hipSuccess) ||
+          hipMemcpyAsync(b + L.off_bcoef7, coef7.data(), coef7.size() * 4, hipMemcpyHostToDevice,
                          p->stream) != hipSuccess ||
-          asn::prepare_banded(bf.azim, p->band_lds()) != hipSuccess)) ||
+          hipMemcpyAsync(b + L.off_bcxy, dcxy.data(), dcxy.size() * 4, hipMemcpyHostToDevice,
+                         p->stream) != hipSuccess)) ||
         (banded && L.lowp &&
          (hipMemcpyAsync(b + L.off_band, ddesc.data(), ddesc.size() * 4, hipMemcpyHostToDevice,
                          p->stream) != hipSuccess ||
@@ -970,7 +973,7 @@ asn_status asn_step(asn_problem p, int64_t n_steps) {
     for (int64_t i = 0; i < n_steps; ++i) {
         b.s_par = (int)(i & 1);
         HIP_TRY(asn::launch_step(b, p->blocks, p->dtype, launch_scheme(p), p->stream, nullptr,
-                                 p->band_azim, lds, p->band_wide_rows(), p->band_reach));
+                                 p->band_azim, lds, p->band_reach));
     }
     p->cur ^= state_flip(p->scheme, n_steps);
     p->steps_done += n_steps;
@@ -1013,7 +1016,7 @@ asn_status asn_step_timed(asn_problem p, int64_t n_steps, double kernel_ms[5]) {
         bt.s_par = (int)(i & 1);
         const hipError_t e = asn::launch_step(
             bt, p->blocks, p->dtype, launch_scheme(p), p->stream, &ev[(size_t)i * per], p->band_azim,
-            p->L.banded ? p->band_lds() : 0, p->band_wide_rows(), p->band_reach);
+            p->L.banded ? p->band_lds() : 0, p->band_reach);
         if (e != hipSuccess) {
             st = fail(ASN_E_HIP, std::string("step launch failed: ") + hipGetErrorString(e));
             break;
@@ -1091,11 +1094,9 @@ asn_status asn_batch_create(asn_problem* probs, int32_t n, asn_batch* out) {
     b->scheme = probs[0]->scheme;
     b->launch_scheme = launch_scheme(probs[0]);
     b->band_az = probs[0]->band_azim;
-    b->band_wide = true;
     for (int32_t i = 0; i < n; ++i) {
         if (probs[i]->L.banded)
             b->band_lds = std::max(b->band_lds, probs[i]->band_lds());
-        b->band_wide = b->band_wide && probs[i]->band_wide_rows();
         b->band_reach = std::max(b->band_reach, probs[i]->band_reach);
     }
     b->stream = probs[0]->stream;
@@ -1162,7 +1163,7 @@ asn_status asn_batch_step(asn_batch b, int64_t n_steps, const int64_t* limit) {
             for (int64_t j = 0; j < n_steps && e == hipSuccess; ++j) {
                 args.s_par = (int)(j & 1);
                 e = asn::launch_step(args, b->grid, b->dtype, b->launch_scheme, b->stream, nullptr,
-                                     b->band_az, b->band_lds, b->band_wide, b->band_reach);
+                                     b->band_az, b->band_lds, b->band_reach);
             }
             const hipError_t e2 = hipStreamEndCapture(b->stream, &g);
             if (e != hipSuccess || e2 != hipSuccess) {
@@ -1181,7 +1182,7 @@ asn_status asn_batch_step(asn_batch b, int64_t n_steps, const int64_t* limit) {
         for (int64_t j = 0; j < n_steps; ++j) {
             args.s_par = (int)(j & 1);
             HIP_TRY(asn::launch_step(args, b->grid, b->dtype, b->launch_scheme, b->stream, nullptr,
-                                     b->band_az, b->band_lds, b->band_wide, b->band_reach));
+                                     b->band_az, b->band_lds, b->band_reach));
         }
     }
     for (int i = 0; i < b->n; ++i) {
@@ -1247,7 +1248,6 @@ asn_status asn_step_batch_noalloc(asn_problem* probs, int32_t n, int64_t n_steps
     int grid[asn::KT_COUNT];
     for (int k = 0; k < asn::KT_COUNT; ++k) off[k * (n + 1)] = 0;
     size_t band_lds = 0;
-    bool band_wide = true;
     int band_reach = 0;
     for (int32_t i = 0; i < n; ++i) {
         tab[2 * i] = probs[i]->tab[0];
@@ -1255,7 +1255,6 @@ asn_status asn_step_batch_noalloc(asn_problem* probs, int32_t n, int64_t n_steps
         for (int k = 0; k < asn::KT_COUNT; ++k)
             off[k * (n + 1) + i + 1] = off[k * (n + 1) + i] + probs[i]->blocks[k];
         if (probs[i]->L.banded) band_lds = std::max(band_lds, probs[i]->band_lds());
-        band_wide = band_wide && probs[i]->band_wide_rows();
         band_reach = std::max(band_reach, probs[i]->band_reach);
     }
     for (int k = 0; k < asn::KT_COUNT; ++k) grid[k] = off[k * (n + 1) + n];
@@ -1285,7 +1284,7 @@ asn_status asn_step_batch_noalloc(asn_problem* probs, int32_t n, int64_t n_steps
     for (int64_t j = 0; j < n_steps; ++j) {
         args.s_par = (int)(j & 1);
         HIP_TRY(asn::launch_step(args, grid, probs[0]->dtype, scheme, stream, nullptr,
-                                 probs[0]->band_azim, band_lds, band_wide, band_reach));
+                                 probs[0]->band_azim, band_lds, band_reach));
     }
     for (int i = 0; i < n; ++i) {
         probs[i]->cur ^= state_flip(probs[i]->scheme, n_steps);

@@ -400,6 +400,61 @@ bool band_form(int levels, int azim, const float* K32, int max_reach, int narrow
     return true;
 }
 
+bool band_scatter_tables(const BandForm& bf, std::vector<uint32_t>& desc, std::vector<float>& coef5,
+                         std::vector<float>& coef7) {
+    const int azim = bf.azim, half = azim / 2;
+    desc.assign((size_t)bf.levels * 8, 0u);
+    coef5.clear();
+    coef7.clear();
+    for (int j = 0; j < bf.levels; ++j) {
+        std::array<std::vector<float>, 7> col;   // c_ij(d), d = 0 .. s, of output i = j + m - 3
+        for (int m = 0; m < 7; ++m) {
+            const int i = j + m - 3;
+            if (i < 0 || i >= bf.levels) continue;
+            const int n = (int)bf.desc[(size_t)i * 8];
+            for (int t = 0; t < n; ++t) {
+                const uint32_t code = bf.desc[(size_t)i * 8 + 1 + t];
+                if (i + (int)((code >> 8) & 7u) - bf.reach != j) continue;
+                int lo = 0, len = 0;
+                band_run(code, azim, lo, len);
+                const float* run = &bf.coef[(size_t)bf.range[2 * (size_t)i] + 4 * ((code >> 11) & 127u)];
+                for (int d = 0; d < lo + len; ++d) {
+                    const float plus = run[d - lo], minus = -d >= lo ? run[-d - lo] : plus;
+                    if (plus != minus && std::nextafter(plus, minus) != minus) return false;
+                    col[(size_t)m].push_back(2 * d == azim ? 0.5f * plus : plus);
+                }
+            }
+        }
+        int D = 0;
+        int outer = 0;
+        for (int m = 0; m < 7; ++m) {
+            const int w = (int)col[(size_t)m].size() - 1;
+            D = std::max(D, w);
+            if (m < 2 || m > 4) outer = std::max(outer, w);
+        }
+        if (D > half) return false;
+        uint32_t* d8 = &desc[(size_t)j * 8];
+        d8[0] = (uint32_t)coef5.size();
+        d8[1] = (uint32_t)coef7.size();
+        d8[2] = (uint32_t)((D + 3) / 4) | (D > 2 ? kBandBeyond2 : 0u) | (outer > 1 ? kBandOuter2 : 0u) |
+                (outer > 2 ? kBandOuter3 : 0u);
+        const int rows = D <= 2 ? 3 : 1 + (D + 3) / 4 * 4;
+        for (int N = 7; N >= (bf.reach <= 2 ? 5 : 7); N -= 2) {
+            std::vector<float>& out = N == 7 ? coef7 : coef5;
+            const size_t base = out.size();
+            out.resize(base + (size_t)rows * N, 0.f);
+            for (int m = (7 - N) / 2; m < 7 - (7 - N) / 2; ++m) {
+                const std::vector<float>& c = col[(size_t)m];
+                if (c.empty()) continue;
+                const int r = m - (7 - N) / 2;
+                for (size_t d = 0; d < c.size(); ++d) out[base + d * N + r] = c[d];
+                d8[N == 7 ? 6 : 3] |= (uint32_t)((c.size() + 2) / 4) << (4 * r);
+            }
+        }
+    }
+    return true;
+}
+
 void band_lp_fragments(const BandForm& bf, int level, int pair, int dtype,
                        std::vector<uint16_t>& out) {
     const int azim = bf.azim;

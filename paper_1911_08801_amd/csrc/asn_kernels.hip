@@ -11,6 +11,10 @@
 // bitwise reproducible.
 #include "asn_kernels.hpp"
 
+#include <type_traits>
+
+#include "asn_host.hpp"
+
 namespace asn {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -858,6 +862,26 @@ __device__ __forceinline__ void block_sum_waves(double (&v)[NV], OutPtr out) {
             double t = red[0][k];
 #pragma unroll
             for (int w = 1; w < NW; ++w) t += red[w][k];
+            out[k] = t;
+        }
+}
+
+// The same for a block of nw <= MAXW waves.
+template <int MAXW, int NV, typename OutPtr>
+__device__ __forceinline__ void block_sum_n(double (&v)[NV], int nw, OutPtr out) {
+    __shared__ double red[MAXW][NV];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) red[wave][k] = v[k];
+    __syncthreads();
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            double t = red[0][k];
+            for (int w = 1; w < nw; ++w) t += red[w][k];
             out[k] = t;
         }
 }
@@ -1878,26 +1902,32 @@ __global__ void broadcast_kernel(float* psi, const float* cell, int Q, int64_t C
 
 // ---------------------------------------------------------------------------
 // 5. Banded forward-Euler step for product ordinate sets (FP32).
-//    The set is invariant under rotations by 2 pi / n_az about the polar axis, so
-//    Y_(i,k) = sum_j sum_delta c_ij(delta) psi_(j, k + delta): per output level a
-//    short circular convolution along the azimuth with each of the levels within
-//    `reach`.  Block = kBandCells consecutive cells (flat index) x every ordinate,
-//    walking the levels in order.  Ring slot l % (2 reach + 2) holds level l of the
-//    block's cells (and the cell before and after them); while output level i is
-//    computed, level i + reach + 1 is written into the slot level i - reach - 1 left
-//    and level i + reach + 2 is loaded into registers, so one LDS barrier per level
-//    suffices and each cell-ordinate of psi^n is read from memory once by its own
-//    block (the y-upwind values are read again by the block below or above).  Level
-//    i's coefficients sit in one of two LDS buffers (written a level ahead); its pair
-//    codes, decoded on the host (band_device_code), come with its descriptor, a scalar
-//    load made a level ahead.  A lane's outputs of a level are kBandO consecutive azimuths of one cell.
-//    Narrow pairs (coupling azimuths at most kBandNarrow apart) are unrolled per width
-//    with their LDS rows at compile-time offsets (the slot carries wrapped copies of
-//    the rows at either end); wide pairs go in steps of four offsets from the wrapped
-//    start row.  The epilogue is the donor-cell stream + collide update as one FMA
-//    chain; the x-upwind value comes from the slot, the y-upwind value from memory
-//    (loaded a level ahead).  The block writes each cell's complete Phi^{n+1} (one
-//    partial, G = 1) and its defect and outflow partials, in a fixed order.
+//    The set is invariant under rotations by 2 pi / n_az about the polar axis and under
+//    reflection of the azimuth, so Y_(i,k) = sum_j sum_d c_ij(d) (psi_(j, k + d) + psi_(j, k - d)):
+//    per pair of levels a short symmetric circular convolution along the azimuth.  The
+//    kernel goes by source level: level j's sums over +-d are formed once and serve
+//    every output level within `reach`, whose partial sums stay in registers until their
+//    last source has passed.  That halves the multiplications of the direct form, reads
+//    each LDS row once per source level instead of once per level pair, and keeps two
+//    levels in LDS.  Block = kBandCells consecutive cells (flat index) x every ordinate;
+//    wave w owns azimuths 4 w .. 4 w + 3 of every level, lane c cell c, so coefficients,
+//    (cx, cy) and the flow direction are uniform over a wave (scalar registers).
+//    Pass j: convolve level j (LDS slot j & 1); its stream + collide terms but for the
+//    in-scattering (x-upwind values from the slot); write level j + 1 into the other slot;
+//    finish and store level j - RT; load level j + 2 and the y-upwind values of level
+//    j + 1; one LDS barrier.  A pass's scalar loads come in one round trip with its LDS
+//    rows (awaited one by one they cost a tenth).  The value and the terms of a level wait in
+//    registers for its in-scattering; the pass is written 2 RT + 1 times, so that these
+//    and the partial sums rotate by renaming.
+//    What bounds it: memory and VALU issue together.  At 1024^2 x 2048 the pass without its
+//    loads and stores takes 3.7 ms (203 VALU instructions a wave and level, half of them in
+//    the four levels at either pole, which couple up to the whole ring), without its
+//    convolution 4.4 ms, as a whole 5.2 ms (3.3 TB/s on 8 B per update; a 4 GiB copy
+//    reaches 4.9); 400^2 x 512 0.172 ms (3.8 TB/s), 700^2 x 1152 1.36 ms.  The direct form
+//    (gathering per output level, all levels within reach in LDS) took 6.85, 0.289 and
+//    2.23 ms.  Two levels of loads in flight, flags between neighbouring waves instead of
+//    the barrier, and loads issued at the start of a pass instead of its end were all
+//    slower: what they add in registers and instructions costs more than they hide.
 // ---------------------------------------------------------------------------
 // The band tables are written by the host before any step and only read by the
 // kernels: reached through the constant address space, their uniform loads are scalar
@@ -1912,82 +1942,161 @@ __device__ __forceinline__ const ASN_K T* kp(const T* p) {
     return (const ASN_K T*)p;
 }
 
-// A narrow pair: offsets -S .. S.  row: the lane's column in the row of its first
-// output azimuth; cf: the run's coefficients in LDS (16-byte aligned, the same words
-// for every lane).
-template <int S>
-__device__ __forceinline__ void band_narrow(float (&acc)[kBandO], const float* row,
-                                            const float* cf) {
-    constexpr int O = kBandO, N = O + 2 * S, NC = (2 * S + 4) / 4;
-    float in[N];
+// Awaits scalar loads here (and what is in flight in LDS), so that they are issued together
+// and not one by one where each is used.
+template <int M>
+__device__ __forceinline__ void await(const float (&k)[M]) {
 #pragma unroll
-    for (int j = 0; j < N; ++j) in[j] = row[(j - S) * kBandStride];
-    float k[4 * NC];
-#pragma unroll
-    for (int t = 0; t < NC; ++t) {
-        const float4 v = reinterpret_cast<const float4*>(cf)[t];
-        k[4 * t] = v.x;
-        k[4 * t + 1] = v.y;
-        k[4 * t + 2] = v.z;
-        k[4 * t + 3] = v.w;
-    }
-#pragma unroll
-    for (int d = 0; d <= 2 * S; ++d)
-#pragma unroll
-        for (int o = 0; o < O; ++o) acc[o] = fmaf(k[d], in[o + d], acc[o]);
+    for (int i = 0; i < M; ++i) asm volatile("" ::"s"(k[i]));
 }
 
-// A wide pair: offsets lo .. lo + len - 1 in steps of four (coefficients past len are
-// zero), from the slot row of azimuth a0 + lo wrapped into [0, A).  A step reads the
-// rows m .. m + kBandO + 2 of its start m in [0, A) (the trailing copies cover those
-// past A - 1); the start advances by four rows and wraps once it passes the last
-// azimuth.  slot: the lane's column in row 0 of the slot.
-template <int A>
-__device__ __forceinline__ void band_wide(float (&acc)[kBandO], const float* slot, int a0, int lo,
-                                          int len, const float* cf) {
+// The convolution of one source level j: acc[i mod N] += c_ij(d) (v[k + d] + v[k - d]) for
+// the output levels i = j - RT .. j + RT (N = 2 RT + 1; P = j mod N, so nothing moves from
+// level to level).  Most levels couple the three middle outputs to azimuths at most 2 apart
+// and the others to at most 1: those products always; the rest by the level's flags, offsets
+// beyond 4 in steps of four, each output as many as it needs (steps: 4 bits each).  lo / hi:
+// the lane's column in the four rows before / after its wave's; col: in row 0.
+template <int RT, int P>
+__device__ __forceinline__ void scatter(float (&acc)[2 * RT + 1][kBandO], const float (&v)[kBandO],
+                                        const float (&near)[4], const float (&k0)[3 * (2 * RT + 1)],
+                                        const float* lo, const float* hi, const float* col, int a0,
+                                        int A, uint32_t form, uint32_t steps, const ASN_K float* kc) {
+    constexpr int O = kBandO, N = 2 * RT + 1;
+    auto add = [&](int m, float k, const float (&s)[O]) {
+        const int r = (P + m - RT + N) % N;
+#pragma unroll
+        for (int o = 0; o < O; ++o) acc[r][o] = fmaf(k, s[o], acc[r][o]);
+    };
+    auto outer = [](int m) { return m < RT - 1 || m > RT + 1; };
+    float up[2 * O], dn[2 * O];   // azimuths a0 .. a0 + 7 and a0 - 4 .. a0 + 3
+    auto sum = [&](int d, float (&s)[O]) {
+#pragma unroll
+        for (int o = 0; o < O; ++o) s[o] = up[o + d] + dn[O + o - d];
+    };
+#pragma unroll
+    for (int o = 0; o < O; ++o) up[o] = dn[O + o] = v[o];
+    dn[O - 2] = near[0];
+    dn[O - 1] = near[1];
+    up[O] = near[2];
+    up[O + 1] = near[3];
+#pragma unroll
+    for (int m = 0; m < N - 1; ++m) add(m, k0[m], v);
+#pragma unroll
+    for (int o = 0; o < O; ++o) acc[(P + RT) % N][o] = k0[N - 1] * v[o];   // its first source
+    float s[O];
+    sum(1, s);
+#pragma unroll
+    for (int m = 0; m < N; ++m) add(m, k0[N + m], s);
+    sum(2, s);
+#pragma unroll
+    for (int m = RT - 1; m <= RT + 1; ++m) add(m, k0[2 * N + m], s);
+    if (form & kBandOuter2)
+#pragma unroll
+        for (int m = 0; m < N; ++m)
+            if (outer(m)) add(m, k0[2 * N + m], s);
+    if (form & kBandBeyond2) {
+        float k[2 * N], s4[O];
+#pragma unroll
+        for (int i = 0; i < 2 * N; ++i) k[i] = kc[3 * N + i];
+        up[O + 2] = hi[2 * kBandRow];
+        up[O + 3] = hi[3 * kBandRow];
+        dn[1] = lo[kBandRow];
+        dn[0] = lo[0];
+        await(k);
+        sum(3, s);
+        sum(4, s4);
+#pragma unroll
+        for (int m = RT - 1; m <= RT + 1; ++m) {
+            add(m, k[m], s);
+            add(m, k[N + m], s4);
+        }
+        if (form & kBandOuter3)
+#pragma unroll
+            for (int m = 0; m < N; ++m)
+                if (outer(m)) {
+                    add(m, k[m], s);
+                    add(m, k[N + m], s4);
+                }
+        // the window's halves change roles from step to step
+        const int ns = (int)(form & kBandSteps);
+        int ah = a0 + O, al = a0 - O;
+        float ua[O], ub[O], da[O], db[O];
+#pragma unroll
+        for (int o = 0; o < O; ++o) {
+            ua[o] = up[O + o];
+            da[o] = dn[o];
+        }
+        auto step = [&](int n, float (&u0)[O], float (&u1)[O], float (&d0)[O], float (&d1)[O]) {
+            ah = ah >= A - O ? ah + O - A : ah + O;
+            al = al < O ? al - O + A : al - O;
+            kc += 4 * N;
+            const float* ph = col + ah * kBandRow;
+            const float* pl = col + al * kBandRow;
+            float kw[4 * N];
+#pragma unroll
+            for (int i = 0; i < 4 * N; ++i) kw[i] = kc[N + i];
+#pragma unroll
+            for (int o = 0; o < O; ++o) {
+                u1[o] = ph[o * kBandRow];
+                d1[o] = pl[o * kBandRow];
+            }
+            await(kw);
+#pragma unroll
+            for (int d = 1; d <= 3; d += 2) {
+#pragma unroll
+                for (int o = 0; o < O; ++o) {
+                    s[o] = (o + d < O ? u0[(o + d) % O] : u1[(o + d) % O]) + (o >= d ? d0[(o - d + O) % O] : d1[(o - d + O) % O]);
+                    s4[o] = (o + d + 1 < O ? u0[(o + d + 1) % O] : u1[(o + d + 1) % O]) +
+                            (o >= d + 1 ? d0[(o - d - 1 + O) % O] : d1[(o - d - 1 + O) % O]);
+                }
+#pragma unroll
+                for (int m = 0; m < N; ++m)
+                    if ((int)((steps >> (4 * m)) & 15u) > n) {
+                        add(m, kw[(d - 1) * N + m], s);
+                        add(m, kw[d * N + m], s4);
+                    }
+            }
+        };
+        for (int n = 1; n < ns; n += 2) {
+            step(n, ua, ub, da, db);
+            if (n + 1 >= ns) break;
+            step(n + 1, ub, ua, db, da);
+        }
+    }
+}
+
+// A level's descriptor: the first of its coefficients, the form of its convolution, the
+// steps of four offsets of each output level (band_scatter_tables).
+struct BandLevel {
+    uint32_t coef, form, steps;
+};
+template <int RT>
+__device__ __forceinline__ BandLevel band_level(const uint4* band, int l) {
+    const ASN_K uint4* p = kp(band) + 2 * l;
+    return {RT == 2 ? p[0].x : p[0].y, p[0].z, RT == 2 ? p[0].w : p[1].z};
+}
+// ... and the weight of its ordinates.
+__device__ __forceinline__ double band_weight(const uint4* band, int l) {
+    return *reinterpret_cast<const ASN_K double*>(kp(band) + 2 * l + 1);
+}
+
+// T: the largest block (512 threads up to 32 azimuths: the reach-3 instance then keeps its
+// queue in registers).
+template <int RT, int T>
+__global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     constexpr int O = kBandO;
-    const int m0 = a0 + lo;   // >= 1 - A / 2 - ... > -A
-    const float* r = slot + (m0 < 0 ? m0 + A + kBandLead : m0 + kBandLead) * kBandStride;
-    const float* const rend = slot + (A + kBandLead) * kBandStride;
-    const float4* k4 = reinterpret_cast<const float4*>(cf);
-    for (int j0 = 0; j0 < len; j0 += 4) {
-        float in[O + 3];
-#pragma unroll
-        for (int u = 0; u < O + 3; ++u) in[u] = r[u * kBandStride];
-        const float4 k = *k4++;
-        const float kk[4] = {k.x, k.y, k.z, k.w};
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int o = 0; o < O; ++o) acc[o] = fmaf(kk[d], in[o + d], acc[o]);
-        r += 4 * kBandStride;
-        r = r >= rend ? r - A * kBandStride : r;
-    }
-}
-
-template <int A, bool YNT>
-__global__ __launch_bounds__(8 * A) void banded_euler_kernel(BatchArgs B) {
-    constexpr int O = kBandO, NW = A / (2 * O), ROWS = kBandLead + A + kBandTrail;
-    constexpr int SLOT = ROWS * kBandStride;
-    extern __shared__ float ring[];
+    extern __shared__ float slots[];
     int pi, local;
     if (!locate(B, KT_SC, xcd_remap(blockIdx.x, gridDim.x), pi, local)) return;
     const StepArgs a = args_of(B, pi);   // by value: no reloads after stores
-    const int tid = threadIdx.x, wave = tid >> 6, h = (tid >> 5) & 1, c = tid & 31;
-    const int a0 = (2 * wave + h) * O;
-    const int nx = a.nx, ny = a.ny, L = a.n_lev, R = a.reach, NS = 2 * R + 2;
-    const int C = (int)a.C, CM = a.bcmax;
-    const int64_t P = a.P;
-    const int c0 = local * kBandCells, cell = c0 + c;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int A = a.n_az, NW = A / O, a0 = wave * O;
+    const int nx = a.nx, ny = a.ny, L = a.n_lev, C = (int)a.C;
+    const int c0 = local * kBandCells, cell = c0 + lane;
     const bool in = cell < C;
-    float* stage = ring + NS * SLOT;   // two buffers of CM coefficients
-    // then two (cx, cy) tables of the level's ordinates (8-byte aligned)
-    float2* cxys = reinterpret_cast<float2*>(stage + 2 * ((CM + 1) & ~1));
-    const ASN_G QInfo* __restrict__ qtab = gp(a.qi);
-    const ASN_K QInfo* qk = kp(a.qi);
-    const ASN_K uint4* ldesc = kp(a.band);
-    const ASN_K int2* lrange = kp(a.brange);
-    const ASN_G float* __restrict__ bcoef = gp(a.bcoef);
+    const ASN_K float* bcoef = kp(RT == 2 ? a.bcoef5 : a.bcoef7);
+    const ASN_K float2* bcxy = kp(a.bcxy) + a0;
 
     float4 cf = make_float4(0.f, 0.f, 0.f, 0.f);
     float isov = 0.f;
@@ -1995,322 +2104,208 @@ __global__ __launch_bounds__(8 * A) void banded_euler_kernel(BatchArgs B) {
         cf = gp(a.coef)[cell];
         isov = gp(a.iso)[cell];
     }
+    // boundary of the lane's cell: 1 / 2 first / last column, 4 / 8 first / last row; 16 a
+    // padding cell
     const int y = cell / nx, x = cell - y * nx;
-    const int e = in ? ((x == 0 ? 1 : 0) | (x == nx - 1 ? 2 : 0) | (y == 0 ? 4 : 0) |
-                        (y == ny - 1 ? 8 : 0))
-                     : 0;
-    const bool wedge = __ballot(e != 0) != 0;   // some lane of the wave is on the boundary
-    // Memory is reached through one buffer descriptor per level (uniform; the two
-    // halves of a wave hold different azimuths) and a per-lane byte offset within the
-    // level, (a0 + o) P + cell floats; offsets at or beyond the level read 0.
-    const uint32_t lvl_bytes = (uint32_t)(A * P * 4);
-    const uint32_t pb = (uint32_t)(P * 4);   // bytes of an azimuth plane
-    // the lane's cell in its first azimuth plane (plane o: + o pb)
-    const uint32_t off0 = 4u * (uint32_t)(a0 * P) + 4u * (uint32_t)cell;
-    // its y-upwind cell; kOOB (reads 0, the vacuum ghost) where that lies outside the grid
-    uint32_t yoff[O];
-    // per output azimuth (the direction is the same on every level): the x-upwind value
-    // is the left neighbour (tl), the right one (tr) or a ghost (neither); ox / oy: the
-    // cell's x / y face is an outflow face
-    bool tl[O], tr[O], ox[O], oy[O];
+    int at = in ? (x == 0 ? 1 : 0) | (x == nx - 1 ? 2 : 0) | (y == 0 ? 4 : 0) | (y == ny - 1 ? 8 : 0) : 16;
+    const bool edge = __ballot(at != 0) != 0;
+    // Memory is reached through one buffer descriptor per level, a lane's byte offset in a
+    // plane and the (uniform) offset of the plane; kOOB reads 0 (the vacuum ghost).
+    const uint32_t pb = (uint32_t)(a.P * 4);   // bytes of an azimuth plane
+    const uint32_t lvl_bytes = (uint32_t)A * pb, s0 = (uint32_t)a0 * pb;
+    const size_t lvl_floats = (size_t)A * (size_t)a.P;
+    const uint32_t voff = 4u * (uint32_t)cell;
+    // n_az / 4 is even, so the flow direction is the same for azimuths 0, 1 and for 2, 3 of the
+    // wave (index o / 2)
+    uint32_t dir[2], yoff[2];
 #pragma unroll
-    for (int o = 0; o < O; ++o) {
-        const int d = qtab[a0 + o].dir;
-        const int yc = (d & 4) ? cell - nx : cell + nx;
-        yoff[o] = (in && yc >= 0 && yc < C) ? off0 + (uint32_t)o * pb + 4u * (uint32_t)(yc - cell)
-                                             : kOOB;
-        const bool gx = !in || (d & e & 3) != 0;
-        tl[o] = !gx && (d & 1);
-        tr[o] = !gx && !(d & 1);
-        const int go = (((d & 5) << 1) | ((d & 10) >> 1)) & e;   // outflow faces of d
-        ox[o] = in && (go & 3);
-        oy[o] = in && (go & 12);
+    for (int h = 0; h < 2; ++h) {
+        dir[h] = (uint32_t)kp(a.qi)[a0 + 2 * h].dir;
+        const int yc = (dir[h] & 4) ? cell - nx : cell + nx;
+        yoff[h] = (in && yc >= 0 && yc < C) ? 4u * (uint32_t)yc : kOOB;
     }
+    // lane l also fetches azimuth a0 + l % 4's upwind cell beyond the block's end, and keeps it
+    // in the column before / after the cells of that row (every lane: no branch on lanes, so
+    // the kernel's branches all stay scalar)
+    const int hd = gp(a.qi)[a0 + (lane & 3)].dir;
+    const int hc = (hd & 1) ? c0 - 1 : c0 + kBandCells;
+    const uint32_t hoff = hc >= 0 ? (uint32_t)(lane & 3) * pb + 4u * (uint32_t)hc : kOOB;
+    const int hrow = (a0 + (lane & 3)) * kBandRow + ((hd & 1) ? 0 : kBandCells + 1);
+    const int SF = A * kBandRow;
+    const int own = a0 * kBandRow + 1 + lane;
+    const int lo = (a0 == 0 ? A - O : a0 - O) * kBandRow + 1 + lane;
+    const int hi = (a0 + O == A ? 0 : a0 + O) * kBandRow + 1 + lane;
+    const int xup[2] = {own + ((dir[0] & 1) ? -1 : 1), own + ((dir[1] & 1) ? -1 : 1)};
 
-    const size_t lvl_floats = (size_t)A * (size_t)P;
+    struct Entry {
+        float v[O], t[O];     // value, terms but the in-scattering
+    };
+    float pre[O], preh;   // the next level, on its way into LDS (lanes 0 .. 3: a halo value)
+    float uy[O];          // its y-upwind values
     auto level_rsrc = [&](const float* base) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)lvl_bytes,
                                                  kRsrcWord3);
     };
-
-    // Ring fill: the lane's kBandO azimuths of level l, cell c.  Lanes 0 and 31 also
-    // fetch the cell before / after the block (the other lanes' halo offsets lie
-    // outside the level and read 0) into column 0 / 33 of the row; the other lanes
-    // write theirs into a padding column.  The first kBandTrail and the last kBandLead
-    // azimuths are also written to their wrapped copy (other rows: to themselves
-    // again).  No branches.
-    struct Fill {
-        float v[O], lo[O];   // the cell, and the block's halo cell (lanes 0 and 31)
+    auto load = [&](__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t plane) {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, plane, 0));
     };
-    const int hcol = c == 0 ? 0 : (c == 31 ? 33 : 34);
-    // the halo cell's offset in plane o (kOOB: reads 0)
-    const bool hvalid = (c == 0 && c0 > 0) || c == 31;
-    const uint32_t hdel = c == 0 ? (uint32_t)-4 : 4u;
-    uint32_t hoff[O];
-#pragma unroll
-    for (int o = 0; o < O; ++o) hoff[o] = hvalid ? off0 + (uint32_t)o * pb + hdel : kOOB;
-    // the lane's rows for azimuth a0 + o: own (rrow0 + o kBandStride), wrapped copies
-    // after the last and before the first azimuth (at most one unless A < lead + trail)
-    constexpr bool kTwoCopies = A < kBandLead + kBandTrail;
-    const int rrow0 = (a0 + kBandLead) * kBandStride;
-    // byte distance from the row of azimuth a0 + o to its (first) wrapped copy
-    int cpy[O];
-#pragma unroll
-    for (int o = 0; o < O; ++o) {
-        const int az = a0 + o;
-        const int up = az < kBandTrail ? A * kBandStride : 0;
-        const int dn = az >= A - kBandLead ? -A * kBandStride : 0;
-        cpy[o] = 4 * (kTwoCopies ? up : (up != 0 ? up : dn));
-    }
-    auto fetch = [&](const float* base, Fill& f) {
+    auto fetch = [&](const float* base) {
         const __amdgpu_buffer_rsrc_t r = level_rsrc(base);
 #pragma unroll
-        for (int o = 0; o < O; ++o) {
-            f.v[o] = load_plane(r, off0 + (uint32_t)o * pb);
-            f.lo[o] = load_plane(r, hoff[o]);
-        }
+        for (int o = 0; o < O; ++o) pre[o] = load(r, voff, s0 + (uint32_t)o * pb);
+        preh = load(r, hoff, s0);
     };
-    auto put = [&](int slot, const Fill& f) {
-        float* s = ring + slot * SLOT;
+    auto put = [&](int slot) {
+        float* s = slots + slot * SF;
 #pragma unroll
-        for (int o = 0; o < O; ++o) {
-            const int az = a0 + o, rr = rrow0 + o * kBandStride;
-            const int dn = az >= A - kBandLead ? rr - A * kBandStride : rr;
-            float* pv = s + rr + c + 1;
-            float* ph = s + rr + hcol;
-            *pv = f.v[o];
-            *ph = f.lo[o];
-            *reinterpret_cast<float*>(reinterpret_cast<char*>(pv) + cpy[o]) = f.v[o];
-            *reinterpret_cast<float*>(reinterpret_cast<char*>(ph) + cpy[o]) = f.lo[o];
-            if constexpr (kTwoCopies) {
-                s[dn + c + 1] = f.v[o];
-                s[dn + hcol] = f.lo[o];
-            }
-        }
+        for (int o = 0; o < O; ++o) s[own + o * kBandRow] = pre[o];
+        s[hrow] = preh;
     };
-    // a level's coefficients: thread t holds number t (the count is below the block
-    // size: at most 2 reach + 1 runs of at most n_az), and threads 0 .. 2 n_az - 1 the
-    // level's cx, cy (thread 2 m + k: component k of azimuth m)
-    struct Coef {
-        float k, c;
-    };
-    auto fetch_coef = [&](int l) {
-        const int2 rg = lrange[l];
-        Coef v;
-        v.k = bcoef[rg.x + min(tid, rg.y - 1)];
-        v.c = reinterpret_cast<const ASN_G float*>(qtab + l * A + min(tid >> 1, A - 1))[tid & 1];
-        return v;
-    };
-    auto put_coef = [&](int l, const Coef& v) {
-        if (tid < CM) stage[(l & 1) * CM + tid] = v.k;
-        if (tid < 2 * A) reinterpret_cast<float*>(cxys + (l & 1) * A)[tid] = v.c;
-    };
-    // per level, loaded one level ahead (after the level's stores, so that the wait
-    // for them in the next epilogue does not also wait for the prefetches, which are
-    // issued later): the y-upwind values and the ordinates' constants (the weight w_q
-    // of a product set depends on the level only: a scalar load)
-    struct Ahead {
-        float y[O];
-        double w;
-    };
-    // base: the level's planes; q0: its first ordinate
-    // The y-upwind row belongs to the block nx / kBandCells blocks away.  With YNT (rows
-    // of kBandWideRowCells or more) that block runs about half a block's time apart (an
-    // XCD holds 64 blocks) and its lines are no longer in the L2: they are read
-    // non-temporally, so they do not push out lines that are (1024^2 x 2048: -0.8 %, with
-    // the non-temporal stores -3.9 %; on narrower rows the L2 still serves them and the
-    // same reads cost 2 to 3 %; measured).
-    auto fetch_ahead = [&](const float* base, int q0, Ahead& ah) {
+    auto fetch_y = [&](const float* base) {
         const __amdgpu_buffer_rsrc_t r = level_rsrc(base);
 #pragma unroll
-        for (int o = 0; o < O; ++o)
-            ah.y[o] = YNT ? load_plane_nt(r, yoff[o]) : load_plane(r, yoff[o]);
-        ah.w = qk[q0].w;
+        for (int o = 0; o < O; ++o) uy[o] = load(r, yoff[o / 2], s0 + (uint32_t)o * pb);
     };
 
-    {   // prologue: levels 0 .. reach into the ring, level 0's coefficients staged
-        Fill f;
-        for (int l = 0; l <= R && l < L; ++l) {
-            fetch(a.psi + (uint32_t)l * lvl_floats, f);
-            put(l, f);   // slot l
-        }
-        put_coef(0, fetch_coef(0));
+    // (level j's at j mod N, of which RT + 1 are in use at a time)
+    constexpr int N = 2 * RT + 1;
+    Entry q[N];
+    float acc[N][O];
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+#pragma unroll
+        for (int o = 0; o < O; ++o) acc[m][o] = 0.f;
+    double phacc = 0.0, defect = 0.0, outflow = 0.0;
+    const float* pf = a.psi;   // planes of the level fetched next
+    const float* py = a.psi;   // and of the one whose y-upwind values are
+    float* po = a.psi_new;     // planes of the level finished next
+    BandLevel d = band_level<RT>(a.band, 0);   // of level j
+    fetch(pf);
+    fetch_y(py);
+    put(0);
+    if (L > 1) {
+        pf += lvl_floats;
+        fetch(pf);
     }
-    // The values loaded a level ahead alternate between two register sets (the loop
-    // body is written twice), and every load is unconditional (the last level again
-    // near the end), so no loop-carried copy of a load in flight forces a wait.
-    Coef cpre = fetch_coef(min(1, L - 1));
-    Fill pre;
-    // level cursors (uniform), advanced once per level and held at the last level:
-    // pf the planes of the level fetched next, pa / qa those and the first ordinate of
-    // the level whose constants are loaded next, po the output planes of level i
-    const float* pf = a.psi + (uint32_t)min(R + 1, L - 1) * lvl_floats;
-    fetch(pf, pre);
-    pf += (R + 2 <= L - 1) ? lvl_floats : 0;
-    const float* pa = a.psi;
-    int qa = 0;
-    float* po = a.psi_new;
-    Ahead ahA, ahB;
-    uint4 dA = ldesc[0], dB = ldesc[1];   // level 0's descriptor
-    uint4 eA = dA, eB = dB;               // level 1's (set in the loop)
-    fetch_ahead(pa, qa, ahA);
-    const bool more_levels = L > 1;
-    pa += more_levels ? lvl_floats : 0;
-    qa += more_levels ? A : 0;
     lds_barrier();
 
-    double phacc = 0.0, defect = 0.0, outflow = 0.0;
-    // level i in ring slot si, level i + reach + 1 goes into slot sp: `pre` holds level
-    // i + reach + 1 and is refilled with level i + reach + 2, `cpre` holds level i + 1's
-    // coefficients and is refilled with level i + 2's; `d0`, `d1` / `ah` hold level i's
-    // descriptor / constants and y-upwind values, `n0`, `n1` / `ah_next` receive level
-    // i + 1's
-    auto level = [&](int i, int si, int sp, const uint4& d0, const uint4& d1, uint4& n0,
-                     uint4& n1, const Ahead& ah, Ahead& ah_next) {
-        // into the slot level i - reach - 1 held and the buffer level i - 1's coefficients
-        // held (their last readers passed the barrier)
-        if (i + R + 1 < L) put(sp, pre);
-        put_coef(i + 1, cpre);
-        cpre = fetch_coef(min(i + 2, L - 1));
-        fetch(pf, pre);
-        pf += (i + R + 3 <= L - 1) ? lvl_floats : 0;
-        // contraction, one pair of levels at a time
-        const float* cbuf = stage + (i & 1) * CM;
-        float acc[O];
-#pragma unroll
-        for (int o = 0; o < O; ++o) acc[o] = 0.f;
-        const int n_pairs = (int)d0.x;
-        // pair codes in the kernel's form (band_device_code), loaded with the level's
-        // descriptor a level ahead and shifted through scalar registers (no scalar load
-        // in flight in the loop, so the waits for a pair's LDS rows can be partial)
-        uint32_t c0 = d0.y, c1 = d0.z, c2 = d0.w, c3 = d1.x, c4 = d1.y, c5 = d1.z, c6 = d1.w;
-        for (int p = 0; p < n_pairs; ++p) {
-            const uint32_t code = c0;
-            c0 = c1;
-            c1 = c2;
-            c2 = c3;
-            c3 = c4;
-            c4 = c5;
-            c5 = c6;
-            const uint32_t w = code >> 24;
-            const float* slot =
-                reinterpret_cast<const float*>(reinterpret_cast<const char*>(ring) + (code & 0x1FFFFu)) +
-                c + 1;
-            const float* cfp = cbuf + 4 * ((code >> 17) & 127u);
-            if (w <= (uint32_t)kBandNarrow) {
-                const float* row = slot + (a0 + kBandLead) * kBandStride;
-                switch (w) {
-                    case 0: band_narrow<0>(acc, row, cfp); break;
-                    case 1: band_narrow<1>(acc, row, cfp); break;
-                    case 2: band_narrow<2>(acc, row, cfp); break;
-                    case 3: band_narrow<3>(acc, row, cfp); break;
-                    case 4: band_narrow<4>(acc, row, cfp); break;
-                    case 5: band_narrow<5>(acc, row, cfp); break;
-                    case 6: band_narrow<6>(acc, row, cfp); break;
-                    case 7: band_narrow<7>(acc, row, cfp); break;
-                    default: band_narrow<8>(acc, row, cfp); break;
-                }
-            } else {
-                const bool whole = w == kBandRingTag;
-                const int s = (int)w - (int)kBandWideTag;
-                band_wide<A>(acc, slot, a0, whole ? 1 - A / 2 : -s, whole ? A : 2 * s + 1, cfp);
-            }
-        }
-        // level i + 1's descriptor, after the contraction: a scalar load in flight there
-        // would make every wait for LDS rows a full one
-        n0 = ldesc[2 * min(i + 1, L - 1)];
-        n1 = ldesc[2 * min(i + 1, L - 1) + 1];
-        // stream + collide of the lane's outputs:
-        //   psi' = psi + [cx (ux - psi) + cy (uy - psi) - aa psi + gs (Y - psi) + bs (iso - psi) + ss]
-        // (aa = dt sigma_a, bs = dt sigma_s, gs = dt sigma_as, ss = dt q), the bracket
-        // in one chain of FMAs; no coefficient of psi is folded into a per-cell constant,
-        // whose rounding would bias every ordinate of the cell alike.  Phi takes each new
-        // value in FP64; the collision term's sum over the outputs, gs sum (Y - psi) +
-        // bs sum (iso - psi), is formed in FP32 (small terms) and added once per level.
-        const float* own = ring + si * SLOT + (a0 + kBandLead) * kBandStride + c + 1;
-        const float2* cxy = cxys + (i & 1) * A + a0;   // the outputs' (cx, cy)
-        const __amdgpu_buffer_rsrc_t ro = level_rsrc(po);
-        po += lvl_floats;
-        // The cells and both x neighbours of every output read first (one LDS round
-        // trip), or each output's as it is updated (the upwind one only): the first is
-        // faster where a SIMD holds three waves of this kernel (n_az 32, 48), the second
-        // at four (n_az 64; measured)
-        constexpr bool kEarly = NW < 8;
-        float vl[O], vv[O], vr[O];
-        if constexpr (kEarly) {
+    auto pass = [&](int j, auto phase) {   // phase: j mod N
+        constexpr int PJ = decltype(phase)::value;
+        Entry& e = q[PJ];                   // level j
+        Entry& n = q[(PJ + N - RT) % N];    // level j - RT
+        BandLevel dn = d;
+        // the weight of the level finished here
+        const double w = band_weight(a.band, max(j - RT, 0));
+        if (j < L) {
+            const float* s = slots + (j & 1) * SF;
+            float ux[O];
 #pragma unroll
             for (int o = 0; o < O; ++o) {
-                const float* pc = own + o * kBandStride;
-                vl[o] = pc[-1];
-                vv[o] = pc[0];
-                vr[o] = pc[1];
+                e.v[o] = s[own + o * kBandRow];
+                ux[o] = s[xup[o / 2] + o * kBandRow];
             }
-        }
-        float sd = 0.f;
+            const float near[4] = {s[lo + 2 * kBandRow], s[lo + 3 * kBandRow], s[hi], s[hi + kBandRow]};
+            // the level's uniform values, in one round trip with the LDS rows
+            const ASN_K float* kc = bcoef + d.coef;
+            const ASN_K float* kcc = reinterpret_cast<const ASN_K float*>(bcxy + j * A);
+            float k0[3 * N], cc[2 * O];
 #pragma unroll
-        for (int o = 0; o < O; ++o) {
-            const float* pc = own + o * kBandStride;
-            if constexpr (!kEarly) vv[o] = pc[0];
-            const float v = vv[o];
-            const float ux = kEarly ? (tl[o] ? vl[o] : (tr[o] ? vr[o] : 0.f))
-                                    : (tl[o] ? pc[-1] : (tr[o] ? pc[1] : 0.f));
-            const float uy = ah.y[o];
-            const float dy = acc[o] - v;
-            float t = fmaf(cf.y, isov - v, cf.w);
-            t = fmaf(cf.z, dy, t);
-            t = fmaf(-cf.x, v, t);
-            const float2 cc = cxy[o];
-            t = fmaf(cc.y, uy - v, t);
-            t = fmaf(cc.x, ux - v, t);
-            // a padding cell (not in) has psi = 0, zero coefficients and zero upwind
-            // values, so it stays zero
-            const float nv = v + t;
-            store_plane_nt(nv, ro, off0 + (uint32_t)o * pb);   // read next step, not from L2
-            phacc += ah.w * (double)nv;
-            sd += dy;
-        }
-        defect += ah.w * (double)(in ? cf.z * sd : 0.f);
-        if (wedge) {
-            float ob = 0.f;
+            for (int i = 0; i < 3 * N; ++i) k0[i] = kc[i];
 #pragma unroll
-            for (int o = 0; o < O; ++o)
-                ob += (ox[o] ? cxy[o].x * vv[o] : 0.f) + (oy[o] ? cxy[o].y * vv[o] : 0.f);
-            outflow += ah.w * (double)ob;
+            for (int i = 0; i < 2 * O; ++i) cc[i] = kcc[i];
+            dn = band_level<RT>(a.band, min(j + 1, L - 1));
+            await(k0);
+            await(cc);
+            asm volatile("" ::"s"(w));
+            scatter<RT, PJ>(acc, e.v, near, k0, s + lo, s + hi, s + 1 + lane, a0, A, d.form, d.steps, kc);
+            // stream + collide without the in-scattering, one chain of FMAs:
+            //   psi' = psi + [bs (iso - psi) + ss - aa psi + cy (uy - psi) + cx (ux - psi) + gs (Y - psi)]
+            // (aa = dt sigma_a, bs = dt sigma_s, gs = dt sigma_as, ss = dt q); no coefficient
+            // of psi is folded into a per-cell constant, whose rounding would bias every
+            // ordinate of the cell alike.  A padding cell (not in) has psi = 0, zero
+            // coefficients and zero upwind values, so it stays zero.
+            if (edge) {   // ghosts along x, outflow through the faces on the boundary
+                asm volatile("" : "+v"(at));   // (evaluated here, not kept in masks)
+                float ob = 0.f;
+#pragma unroll
+                for (int o = 0; o < O; ++o) {
+                    const int dx = (dir[o / 2] & 1) ? 1 : 2, dy = (dir[o / 2] & 4) ? 8 : 4;
+                    if (at & (dx | 16)) ux[o] = 0.f;
+                    ob += (at & (3 - dx) ? cc[2 * o] * e.v[o] : 0.f) + (at & dy ? cc[2 * o + 1] * e.v[o] : 0.f);
+                }
+                outflow += band_weight(a.band, j) * (double)ob;
+            }
+#pragma unroll
+            for (int o = 0; o < O; ++o) {
+                float t = fmaf(cf.y, isov - e.v[o], cf.w);
+                t = fmaf(-cf.x, e.v[o], t);
+                t = fmaf(cc[2 * o + 1], uy[o] - e.v[o], t);
+                e.t[o] = fmaf(cc[2 * o], ux[o] - e.v[o], t);
+            }
+            if (j + 1 < L) put((j + 1) & 1);   // this slot's readers passed the last barrier
         }
-        fetch_ahead(pa, qa, ah_next);
-        const bool adv = i + 2 <= L - 1;
-        pa += adv ? lvl_floats : 0;
-        qa += adv ? A : 0;
+        if (j >= RT) {
+            // finish level j - RT (entry n); Phi takes each new value in FP64; the
+            // in-scattering's sum over the outputs, gs sum (Y - psi), is formed in FP32
+            // (small terms) and added once per level
+            const __amdgpu_buffer_rsrc_t r = level_rsrc(po);
+            po += lvl_floats;
+            float sd = 0.f;
+#pragma unroll
+            for (int o = 0; o < O; ++o) {
+                const float dy = acc[(PJ + N - RT) % N][o] - n.v[o];
+                const float nv = n.v[o] + fmaf(cf.z, dy, n.t[o]);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(nv), r, voff, s0 + (uint32_t)o * pb,
+                                                      kCachePolicyNT);   // read next step, not from L2
+                phacc += w * (double)nv;
+                sd += dy;
+            }
+            defect += w * (double)(cf.z * sd);
+        }
+        if (j + 1 < L) {
+            py += lvl_floats;
+            fetch_y(py);
+        }
+        if (j + 2 < L) {
+            pf += lvl_floats;
+            fetch(pf);
+        }
+        d = dn;
         lds_barrier();
     };
-    int si = 0, sp = R + 1;   // ring slots of levels i and i + reach + 1
-    auto next_slot = [NS](int s) { return s + 1 == NS ? 0 : s + 1; };
-    for (int i = 0; i < L; i += 2) {
-        level(i, si, sp, dA, dB, eA, eB, ahA, ahB);
-        si = next_slot(si);
-        sp = next_slot(sp);
-        if (i + 1 >= L) break;
-        level(i + 1, si, sp, eA, eB, dA, dB, ahB, ahA);
-        si = next_slot(si);
-        sp = next_slot(sp);
+    for (int j = 0; j < L + RT; j += N) {
+        pass(j, std::integral_constant<int, 0>{});
+        if (j + 1 >= L + RT) break;
+        pass(j + 1, std::integral_constant<int, 1>{});
+        if (j + 2 >= L + RT) break;
+        pass(j + 2, std::integral_constant<int, 2>{});
+        if (j + 3 >= L + RT) break;
+        pass(j + 3, std::integral_constant<int, 3>{});
+        if (j + 4 >= L + RT) break;
+        pass(j + 4, std::integral_constant<int, 4>{});
+        if constexpr (RT == 3) {
+            if (j + 5 >= L + RT) break;
+            pass(j + 5, std::integral_constant<int, 5 % N>{});
+            if (j + 6 >= L + RT) break;
+            pass(j + 6, std::integral_constant<int, 6 % N>{});
+        }
     }
 
-    // Phi^{n+1} of each cell: the 2 NW lane groups' partials in a fixed order
-    double* red = reinterpret_cast<double*>(ring);
-    red[(2 * wave + h) * kBandCells + c] = phacc;
+    // Phi^{n+1} of each cell: the waves' partials in a fixed order
+    double* red = reinterpret_cast<double*>(slots);
+    red[wave * kBandCells + lane] = phacc;
     lds_barrier();
-    if (tid < kBandCells && in) {
-        double s = red[c];
-#pragma unroll
-        for (int g = 1; g < 2 * NW; ++g) s += red[g * kBandCells + c];
+    if (wave == 0 && in) {
+        double s = red[lane];
+        for (int g = 1; g < NW; ++g) s += red[g * kBandCells + lane];
         gp(a.phi_part)[cell] = s;
     }
     // the physical scattering's part of the collision defect, sum_q w_q bs (iso - psi_q)
     // = bs (W iso - Phi), once per cell (Phi of psi^n in FP64)
-    if (wave == 0 && h == 0 && in)
+    if (wave == 0 && in)
         defect += (double)cf.y * (a.W * (double)isov - gp(a.phi64)[cell]);
     double sums[2] = {defect, outflow};
-    block_sum_waves<NW, 2>(sums, gp(a.blk_part) + 2 * (size_t)local);
+    block_sum_n<16, 2>(sums, NW, gp(a.blk_part) + 2 * (size_t)local);
 }
 
 // ---------------------------------------------------------------------------
@@ -2782,25 +2777,15 @@ void blocks_per_kind(const StepArgs& a, int out[KT_COUNT]) {
     out[KT_BUDGET] = 1;
 }
 
-template <int A>
-static void launch_banded_az(const BatchArgs& b, int blocks, size_t lds, hipStream_t s, bool wide) {
-    if (wide) banded_euler_kernel<A, true><<<blocks, 8 * A, lds, s>>>(b);
-    else banded_euler_kernel<A, false><<<blocks, 8 * A, lds, s>>>(b);
-}
-
+// The instance for reach 2 also serves smaller reaches (zero coefficients), the one for
+// reach 3 any.
 static hipError_t launch_banded(const BatchArgs& b, int blocks, int az, size_t lds, hipStream_t s,
-                                bool wide) {
-    switch (az) {
-        case 8: launch_banded_az<8>(b, blocks, lds, s, wide); break;
-        case 16: launch_banded_az<16>(b, blocks, lds, s, wide); break;
-        case 24: launch_banded_az<24>(b, blocks, lds, s, wide); break;
-        case 32: launch_banded_az<32>(b, blocks, lds, s, wide); break;
-        case 40: launch_banded_az<40>(b, blocks, lds, s, wide); break;
-        case 48: launch_banded_az<48>(b, blocks, lds, s, wide); break;
-        case 56: launch_banded_az<56>(b, blocks, lds, s, wide); break;
-        case 64: launch_banded_az<64>(b, blocks, lds, s, wide); break;
-        default: return hipErrorInvalidValue;
-    }
+                                int reach) {
+    if (!band_azimuths_supported(az) || reach < 0 || reach > kBandMaxReach) return hipErrorInvalidValue;
+    const int threads = az / kBandO * 64;
+    if (reach <= 2) banded_euler_kernel<2, 1024><<<blocks, threads, lds, s>>>(b);
+    else if (threads <= 512) banded_euler_kernel<3, 512><<<blocks, threads, lds, s>>>(b);
+    else banded_euler_kernel<3, 1024><<<blocks, threads, lds, s>>>(b);
     return hipSuccess;
 }
 
@@ -2855,29 +2840,6 @@ hipError_t prepare_banded_lp(int band_az, int dtype, int reach, size_t band_lds)
     return hipErrorInvalidValue;
 }
 
-template <int A>
-static hipError_t prepare_banded_az(size_t lds) {
-    const hipError_t e = hipFuncSetAttribute((const void*)banded_euler_kernel<A, false>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute((const void*)banded_euler_kernel<A, true>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-
-hipError_t prepare_banded(int az, size_t lds) {
-    switch (az) {
-        case 8: return prepare_banded_az<8>(lds);
-        case 16: return prepare_banded_az<16>(lds);
-        case 24: return prepare_banded_az<24>(lds);
-        case 32: return prepare_banded_az<32>(lds);
-        case 40: return prepare_banded_az<40>(lds);
-        case 48: return prepare_banded_az<48>(lds);
-        case 56: return prepare_banded_az<56>(lds);
-        case 64: return prepare_banded_az<64>(lds);
-        default: return hipErrorInvalidValue;
-    }
-}
-
 // Stencil kinds of a pass: 0 donor-cell strips, 1 / 2 Heun stages (strips), 3 donor-cell
 // flat chunks, 4 / 5 Heun stages (flat chunks), kStencilBanded the banded step (its
 // contraction and stencil are one kernel).
@@ -2886,15 +2848,14 @@ constexpr int kStencilBanded = 16;
 // One pass: contraction, stencil, finalize, budget.
 static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, int stencil,
                               int bud, hipStream_t s, hipEvent_t* ev, int band_az = 0,
-                              size_t band_lds = 0, bool band_wide_rows = false,
-                              int band_reach = 0) {
+                              size_t band_lds = 0, int band_reach = 0) {
     hipError_t e = hipSuccess;
     auto mark = [&](int k) {
         if (ev && e == hipSuccess) e = hipEventRecord(ev[k], s);
     };
     if (stencil == kStencilBanded) {   // contraction and stencil in one kernel
         mark(0);
-        e = dtype == 0 ? launch_banded(b, grid[KT_SC], band_az, band_lds, s, band_wide_rows)
+        e = dtype == 0 ? launch_banded(b, grid[KT_SC], band_az, band_lds, s, band_reach)
                        : launch_banded_lp(b, grid[KT_SC], band_az, dtype, band_lds, s, band_reach);
         mark(1);
         mark(2);
@@ -2952,11 +2913,10 @@ static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, in
 }
 
 hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int scheme, hipStream_t s,
-                       hipEvent_t* ev, int band_az, size_t band_lds, bool band_wide_rows,
-                       int band_reach) {
+                       hipEvent_t* ev, int band_az, size_t band_lds, int band_reach) {
     if (scheme == SCHEME_EULER_BANDED)
         return launch_pass(b, grid, dtype, kStencilBanded, BUD_STEP, s, ev, band_az, band_lds,
-                           band_wide_rows, band_reach);
+                           band_reach);
     if (scheme != SCHEME_HEUN && scheme != SCHEME_HEUN_FLAT)
         return launch_pass(b, grid, dtype, scheme == SCHEME_EULER_FLAT ? 3 : 0, BUD_STEP, s, ev);
     const int st = scheme == SCHEME_HEUN_FLAT ? 4 : 1;   // stencil of the first pass

@@ -57,54 +57,21 @@ constexpr int kFlatMaxNxM = (kFlatRounds * kFlatCells - kFlatCells - 8) / 3;
 
 // Banded forward-Euler step (product ordinate sets, FP32): one kernel per step does
 // the contraction, the stream + collide update, the moments and the budget partials.
-// A block owns kBandCells consecutive cells (flat index) and every ordinate: it walks
-// the polar levels in order with a ring of 2 reach + 2 level slots in LDS, each slot
-// kBandLead + n_az + kBandTrail azimuth rows (wrapped copies of the last kBandLead and
-// the first kBandTrail azimuths around the n_az rows) of kBandStride floats (the cells
-// plus one neighbour on each side, padded), and the current level's coefficients
-// staged in LDS.  Lane (wave w, half h, cell c) produces azimuths (2 w + h) kBandO ..
-// + kBandO - 1 of every level for cell c, so a block has n_az / (2 kBandO) waves.
-// Level pairs coupling azimuths at most kBandNarrow apart are unrolled per width;
-// wider ones run in steps of four offsets.
+// A block owns kBandCells consecutive cells (flat index) and every ordinate and walks
+// the polar levels in order; a wave owns kBandO consecutive azimuths of every level, a
+// lane one cell, so a block has n_az / kBandO waves.  LDS holds two levels: n_az rows of
+// kBandRow floats (the cells, with the neighbour on either side at the ends).
 constexpr int SCHEME_EULER_BANDED = 5;
-constexpr int kBandCells = 32;
+constexpr int kBandCells = 64;
 constexpr int kBandO = 4;
-constexpr int kBandNarrow = 8;
-// Rows before azimuth 0 and after the last azimuth.  A narrow pair of width s reads
-// the azimuths a0 - s .. a0 + kBandO - 1 + s of outputs a0 .. a0 + kBandO - 1, a wide
-// step the rows m .. m + kBandO + 2 from a wrapped start m in [0, n_az).
-constexpr int kBandLead = kBandNarrow;
-constexpr int kBandTrail = kBandNarrow > kBandO + 2 ? kBandNarrow : kBandO + 2;
-static_assert(kBandLead >= kBandNarrow && kBandTrail >= kBandNarrow && kBandTrail >= kBandO + 2,
-              "banded ring rows must cover every narrow and wide read");
-constexpr int kBandStride = 40;
+constexpr int kBandRow = kBandCells + 2;
 constexpr int kBandMaxReach = 3;
-// Azimuth counts with a kernel instance.
+// Largest half-width of the pair codes marked narrow by band_form (asn_host.hpp).
+constexpr int kBandNarrow = 8;
+// Azimuth counts the kernel takes.
 inline bool band_azimuths_supported(int az) { return az >= 8 && az <= 64 && az % 8 == 0; }
-// Floats of one ring slot of the banded kernel.
-inline int band_slot_floats(int az) { return (kBandLead + az + kBandTrail) * kBandStride; }
-// The kernel's form of a pair code of band_form (asn_host.hpp), decoded on the host so the
-// kernel spends few scalar instructions per pair:
-//   bits 0-16   byte offset of the partner level's ring slot (level j sits in slot j mod
-//               (2 reach + 2); at most 8 slots of (16 + 64) x 40 floats: < 2^17)
-//   bits 17-23  start of the pair's run in the level's staged coefficients, in units of 4
-//   bits 24-31  narrow run: its half-width s (<= kBandNarrow); wider run: kBandWideTag + s;
-//               whole ring: kBandRingTag
-constexpr uint32_t kBandWideTag = 32, kBandRingTag = 128;
-inline uint32_t band_device_code(uint32_t code, int level, int reach, int az) {
-    const int s = (int)(code & 63u), k = (int)((code >> 8) & 7u);
-    const int j = level + k - reach;
-    const uint32_t slot = (uint32_t)(j % (2 * reach + 2)) * (uint32_t)band_slot_floats(az) * 4u;
-    const uint32_t w = (code & 128u) ? kBandRingTag : ((code & 64u) ? kBandWideTag + (uint32_t)s
-                                                                     : (uint32_t)s);
-    return slot | ((code >> 11) & 127u) << 17 | w << 24;
-}
-// Dynamic LDS of a banded block: the ring, then two level-coefficient buffers of cmax
-// floats (cmax a multiple of 4) and two tables of the level's (cx, cy).
-inline size_t band_lds_bytes(int az, int reach, int cmax) {
-    return (size_t)(2 * reach + 2) * (kBandLead + az + kBandTrail) * kBandStride * 4 +
-           2 * (size_t)((cmax + 1) & ~1) * 4 + 2 * (size_t)az * 8;
-}
+// Dynamic LDS of a banded block (the final sums reuse them).
+inline size_t band_lds_bytes(int az) { return (size_t)2 * az * kBandRow * 4; }
 
 // Banded reduced-precision step (BF16 / FP16 operands on MFMA 16x16x32, FP32 accumulate)
 // for product sets of 32, 48 or 64 azimuths: a block owns kBandLpCells consecutive cells and
@@ -207,13 +174,14 @@ struct StepArgs {
     unsigned* bmax_next;    // block max |psi^{n+1}| (written by the stencil)
     double* rec;
     // banded step (product ordinate sets): n_lev levels of n_az azimuths, coupling
-    // levels up to `reach` apart; per level the descriptor (band, two uint4), the
-    // coefficient range {first, count} (brange) and the coefficients (bcoef) as built by
-    // band_form (asn_host.hpp); bcmax the largest count of a level
+    // levels up to `reach` apart; per level a descriptor (band, two uint4) and its coefficients for
+    // the kernel's instances of reach 2 and 3 (bcoef5, bcoef7) as built by
+    // band_scatter_tables (asn_host.hpp), and per ordinate (cx, cy) (bcxy)
     const uint4* band;
-    const int2* brange;
-    const float* bcoef;
-    int n_lev, n_az, reach, bcmax;
+    const float* bcoef5;
+    const float* bcoef7;
+    const float2* bcxy;
+    int n_lev, n_az, reach;
     // banded reduced-precision step: per level pair and 16-azimuth offset the A operand
     // of MFMA 16x16x32 as 64 lanes x 8 16-bit values (band_lp_fragments); band then holds
     // per level {pairs, first fragment, level offsets k of the pairs (4 bits each), 0}
@@ -252,19 +220,13 @@ inline bool can_fuse(int dtype, int scheme) { (void)dtype; return scheme == SCHE
 // If ev is given, ev[5 k .. 5 k + 4] are recorded before, between and after
 // the four kernels of pass k.
 // band_az / band_lds: the banded step's azimuth count and dynamic LDS bytes (every
-// problem of a banded batch has that azimuth count); band_wide_rows: every problem's
-// rows hold at least kBandWideRowCells cells (selects the FP32 banded kernel's instance
-// that reads the y-upwind rows non-temporally); band_reach: the reach the banded
-// reduced-precision kernel is instantiated for (at least every problem's).
+// problem of a banded batch has that azimuth count); band_reach: the reach the banded
+// kernel is instantiated for (at least every problem's).
 hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int scheme, hipStream_t s,
                        hipEvent_t* ev = nullptr, int band_az = 0, size_t band_lds = 0,
-                       bool band_wide_rows = false, int band_reach = 0);
-// Rows from this many cells on: the banded kernel's y-upwind row belongs to a block at
-// least 32 blocks away, which runs about half a block's time apart on its XCD.
-constexpr int kBandWideRowCells = 32 * kBandCells;
-// Raise the dynamic LDS limit of the banded kernel for an azimuth count (once per device).
-hipError_t prepare_banded(int band_az, size_t band_lds);
-// The same for the banded reduced-precision kernel of an azimuth count, operand type
+                       int band_reach = 0);
+// Raise the dynamic LDS limit of the banded reduced-precision kernel of an azimuth count,
+// operand type
 // and reach.
 hipError_t prepare_banded_lp(int band_az, int dtype, int reach, size_t band_lds);
 // Passes per step of a scheme.

@@ -90,6 +90,44 @@ def test_line_source_50_q128_full_run():
     assert bud["max_residual"] <= max(1e-10, 64 * fp32_budget_floor(state, st.w))
 
 
+# (n_polar, n_azim, beta) by what their levels' convolutions take: steps of four offsets 2 .. 8 in
+# odd and even numbers, outputs two levels away coupling 0 .. 3 and more azimuths, reach 3 with
+# blocks of up to 8 waves and of more
+FORMS = [(32, 64, 4.5), (24, 56, 6.0), (20, 48, 6.0), (7, 48, 14.0), (10, 8, 4.5), (16, 24, 6.0),
+         (16, 40, 14.0)]
+
+
+@pytest.mark.parametrize("nx,ny", [(63, 2), (64, 3), (65, 4)])
+@pytest.mark.parametrize("n_polar,n_azim,beta", FORMS)
+def test_convolution_forms(nx, ny, n_polar, n_azim, beta):
+    # as test_one_step_matches_oracle, around one 64-cell block
+    spec = wl.random_problem(nx + ny + n_azim, nx, ny, n_polar=n_polar, n_azim=n_azim, beta=beta)
+    psi0 = wl.random_state(nx + n_polar, spec.q, ny, nx)
+    state, phi, _, _ = gpu_run(asn, spec, 1, psi0=psi0, form="banded")
+    ref, phi_ref, _ = oracle_run(spec, 1, psi0=psi0)
+    assert np.max(np.abs(state - ref)) <= 4e-6 * np.abs(ref).max()
+    assert np.max(np.abs(phi - phi_ref)) <= 4e-6 * np.abs(phi_ref).max()
+
+
+def test_batch_of_different_reach_equals_alone():
+    # the batch takes the kernel of the largest reach (3); alone the first takes that of 2
+    specs = [wl.random_problem(7 + i, 30 + i, 5, n_polar=16, n_azim=24, beta=b)
+             for i, b in enumerate((4.5, 6.0))]
+    assert [_band_reach(16, 24, b) for b in (4.5, 6.0)] == [2, 3]
+    states = [wl.random_state(30 + i, sp.q, sp.ny, sp.nx) for i, sp in enumerate(specs)]
+    alone = [gpu_run(asn, sp, 3, psi0=s0, form="banded")[0] for sp, s0 in zip(specs, states)]
+    probs = [asn.from_spec(sp, set_initial_state=False, form="banded") for sp in specs]
+    try:
+        for p, s0 in zip(probs, states):
+            asn.asn_set_state(p, s0)
+        asn.asn_step_batch(probs, 3)
+        for p, ref in zip(probs, alone):
+            assert np.array_equal(asn.asn_get_state(p), ref)
+    finally:
+        for p in probs:
+            p.close()
+
+
 def test_automatic_form_takes_the_banded_step_and_agrees_with_fused():
     spec = wl.random_problem(8, 45, 38, n_polar=8, n_azim=16, beta=4.5)
     psi0 = wl.random_state(4, spec.q, 38, 45)
