@@ -269,7 +269,8 @@ asn_status asn_iteration_counts(asn_problem p, int64_t* sweeps, int64_t* matvecs
  * stream between its kernels; synchronises.  kernel_ms[k] receives the average
  * duration per step of kernel k: 0 the ordinate contraction Y = K Psi, 1 stream
  * + collide, 2 moment finalize, 3 budget fold (for ASN_SCHEME_HEUN, the sum over
- * its two passes); kernel_ms[4] the average span of a whole step.  Measurement
+ * its two passes; the FP32 ASN_FORM_BANDED step does all of it in kernel 0, but for the
+ * last step's fold); kernel_ms[4] the average span of a whole step.  Measurement
  * support for benchmarks; results equal asn_step.
  * Errors: ASN_E_INVALID (n_steps < 1), ASN_E_HIP. */
 asn_status asn_step_timed(asn_problem p, int64_t n_steps, double kernel_ms[5]);

@@ -159,8 +159,10 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
     L.off_iso = take(plane * 4);
     L.off_phi64 = take(plane * 8);
     L.off_phipart = take((size_t)L.G * plane * 8);
-    L.off_blk = take((size_t)tiles * L.G * 2 * 8);
-    L.off_fin = take((size_t)L.fin_blocks * 4 * 8);
+    // banded FP32: the partials of a step are read in the next one, so once per state buffer
+    const size_t sets = L.banded && !L.lowp ? 2 : 1;
+    L.off_blk = take(sets * tiles * L.G * 2 * 8);
+    L.off_fin = take(sets * std::max<size_t>(L.fin_blocks, L.banded ? tiles : 0) * 4 * 8);
     L.off_ypart = take(L.lowp ? (size_t)(L.Qp / asn::kGemmBM) * plane * 8 : 0);
     L.off_fix = take(L.lowp && !fused ? plane * 4 : 0);
     L.off_delta = take(L.lowp && fused ? plane * 4 : 0);
@@ -230,7 +232,7 @@ struct asn_batch_s {
     std::vector<int> off;
     char* dev = nullptr;
     asn::BatchArgs args{};
-    int grid[asn::KT_COUNT] = {0, 0, 0, 0, 0};
+    int grid[asn::KT_COUNT] = {};
     std::map<int64_t, std::pair<hipGraph_t, hipGraphExec_t>> graphs;
 };
 
@@ -280,6 +282,10 @@ StepArgs make_args(asn_problem p, int cur) {
     a.bmax_cur = cur == 0 ? bm0 : bm1;
     a.bmax_next = cur == 0 ? bm1 : bm0;
     a.rec = reinterpret_cast<double*>(b + L.off_rec);
+    if (L.banded && !L.lowp && cur) {
+        a.blk_part += 2 * (size_t)L.tiles_x;
+        a.fin_part += 4 * (size_t)L.tiles_x;
+    }
     if (L.banded) {
         a.band = reinterpret_cast<const uint4*>(b + L.off_band);   // two per level
         a.bcoef5 = reinterpret_cast<const float*>(b + L.off_bcoef5);
@@ -300,9 +306,8 @@ asn::BatchArgs single_batch(asn_problem p) {
     b.tab = reinterpret_cast<const StepArgs*>(p->base + L.off_tab);
     b.off = reinterpret_cast<const int*>(p->base + L.off_off);
     b.base = reinterpret_cast<const int*>(p->base + L.off_base);
-    b.steps_left = reinterpret_cast<int*>(p->base + L.off_left);
+    b.limit = reinterpret_cast<const int*>(p->base + L.off_left);
     b.n = 1;
-    b.s_par = 0;
     return b;
 }
 
@@ -971,10 +976,12 @@ asn_status asn_step(asn_problem p, int64_t n_steps) {
     asn::BatchArgs b = single_batch(p);
     const size_t lds = p->L.banded ? p->band_lds() : 0;
     for (int64_t i = 0; i < n_steps; ++i) {
+        b.step = (int)i;
         b.s_par = (int)(i & 1);
         HIP_TRY(asn::launch_step(b, p->blocks, p->dtype, launch_scheme(p), p->stream, nullptr,
                                  p->band_azim, lds, p->band_reach));
     }
+    HIP_TRY(asn::launch_last_budget(b, (int)n_steps, p->dtype, launch_scheme(p), p->stream));
     p->cur ^= state_flip(p->scheme, n_steps);
     p->steps_done += n_steps;
     return ASN_OK;
@@ -1013,6 +1020,7 @@ asn_status asn_step_timed(asn_problem p, int64_t n_steps, double kernel_ms[5]) {
         st = fail(ASN_E_HIP, "arming the step counter failed");
     asn::BatchArgs bt = single_batch(p);
     for (int64_t i = 0; st == ASN_OK && i < n_steps; ++i) {
+        bt.step = (int)i;
         bt.s_par = (int)(i & 1);
         const hipError_t e = asn::launch_step(
             bt, p->blocks, p->dtype, launch_scheme(p), p->stream, &ev[(size_t)i * per], p->band_azim,
@@ -1022,6 +1030,8 @@ asn_status asn_step_timed(asn_problem p, int64_t n_steps, double kernel_ms[5]) {
             break;
         }
     }
+    if (st == ASN_OK && asn::launch_last_budget(bt, (int)n_steps, p->dtype, launch_scheme(p), p->stream) != hipSuccess)
+        st = fail(ASN_E_HIP, "budget launch failed");
     if (st == ASN_OK) {
         p->cur ^= state_flip(p->scheme, n_steps);
         p->steps_done += n_steps;
@@ -1129,7 +1139,7 @@ asn_status asn_batch_create(asn_problem* probs, int32_t n, asn_batch* out) {
     b->args.tab = reinterpret_cast<const StepArgs*>(b->dev);
     b->args.off = reinterpret_cast<const int*>(b->dev + tab_b);
     b->args.base = reinterpret_cast<const int*>(b->dev + tab_b + off_b);
-    b->args.steps_left = reinterpret_cast<int*>(b->dev + tab_b + off_b + asn::kMaxArm * sizeof(int));
+    b->args.limit = reinterpret_cast<const int*>(b->dev + tab_b + off_b + asn::kMaxArm * sizeof(int));
     b->args.n = n;
     b->args.s_par = 0;
     *out = b;
@@ -1149,8 +1159,8 @@ asn_status asn_batch_step(asn_batch b, int64_t n_steps, const int64_t* limit) {
         any = any || take[i] > 0;
     }
     if (!any) return ASN_OK;
-    int* left = b->args.steps_left;
-    HIP_TRY(asn::launch_arm(left, const_cast<int*>(b->args.base), b->n, v, b->stream));
+    HIP_TRY(asn::launch_arm(const_cast<int*>(b->args.limit), const_cast<int*>(b->args.base), b->n, v,
+                            b->stream));
     asn::BatchArgs args = b->args;
     if (b->stream != nullptr && n_steps >= 2) {
         // Capture the step sequence once per length; later calls replay it.
@@ -1161,10 +1171,13 @@ asn_status asn_batch_step(asn_batch b, int64_t n_steps, const int64_t* limit) {
             HIP_TRY(hipStreamBeginCapture(b->stream, hipStreamCaptureModeRelaxed));
             hipError_t e = hipSuccess;
             for (int64_t j = 0; j < n_steps && e == hipSuccess; ++j) {
+                args.step = (int)j;
                 args.s_par = (int)(j & 1);
                 e = asn::launch_step(args, b->grid, b->dtype, b->launch_scheme, b->stream, nullptr,
                                      b->band_az, b->band_lds, b->band_reach);
             }
+            if (e == hipSuccess)
+                e = asn::launch_last_budget(args, (int)n_steps, b->dtype, b->launch_scheme, b->stream);
             const hipError_t e2 = hipStreamEndCapture(b->stream, &g);
             if (e != hipSuccess || e2 != hipSuccess) {
                 if (g) (void)hipGraphDestroy(g);
@@ -1180,10 +1193,12 @@ asn_status asn_batch_step(asn_batch b, int64_t n_steps, const int64_t* limit) {
         HIP_TRY(hipGraphLaunch(it->second.second, b->stream));
     } else {
         for (int64_t j = 0; j < n_steps; ++j) {
+            args.step = (int)j;
             args.s_par = (int)(j & 1);
             HIP_TRY(asn::launch_step(args, b->grid, b->dtype, b->launch_scheme, b->stream, nullptr,
                                      b->band_az, b->band_lds, b->band_reach));
         }
+        HIP_TRY(asn::launch_last_budget(args, (int)n_steps, b->dtype, b->launch_scheme, b->stream));
     }
     for (int i = 0; i < b->n; ++i) {
         b->probs[i]->cur ^= state_flip(b->scheme, take[i]);
@@ -1272,20 +1287,22 @@ asn_status asn_step_batch_noalloc(asn_problem* probs, int32_t n, int64_t n_steps
     args.tab = reinterpret_cast<const StepArgs*>(dev);
     args.off = reinterpret_cast<const int*>(dev + tab_b);
     args.base = reinterpret_cast<const int*>(dev + tab_b + off_b);
-    args.steps_left = reinterpret_cast<int*>(dev + tab_b + off_b + kN * sizeof(int));
+    args.limit = reinterpret_cast<const int*>(dev + tab_b + off_b + kN * sizeof(int));
     args.n = n;
     asn::ArmArgs v{};
     for (int i = 0; i < n; ++i) {
         v.limit[i] = (int)n_steps;
         v.cur[i] = probs[i]->cur;
     }
-    HIP_TRY(asn::launch_arm(args.steps_left, const_cast<int*>(args.base), n, v, stream));
+    HIP_TRY(asn::launch_arm(const_cast<int*>(args.limit), const_cast<int*>(args.base), n, v, stream));
     const int scheme = launch_scheme(probs[0]);
     for (int64_t j = 0; j < n_steps; ++j) {
+        args.step = (int)j;
         args.s_par = (int)(j & 1);
         HIP_TRY(asn::launch_step(args, grid, probs[0]->dtype, scheme, stream, nullptr,
                                  probs[0]->band_azim, band_lds, band_reach));
     }
+    HIP_TRY(asn::launch_last_budget(args, (int)n_steps, probs[0]->dtype, scheme, stream));
     for (int i = 0; i < n; ++i) {
         probs[i]->cur ^= state_flip(probs[i]->scheme, n_steps);
         probs[i]->steps_done += n_steps;

@@ -43,7 +43,7 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
 }
 
 // Problem i and its local block for hardware block b of kernel kind `kind`;
-// false if that problem has no steps left in this batch.
+// false if that problem takes no such step in this batch.
 __device__ __forceinline__ bool locate(const BatchArgs& B, int kind, int b, int& i, int& local) {
     const ASN_G int* off = gp(B.off) + kind * (B.n + 1);
     int lo = 0, hi = B.n - 1;
@@ -54,7 +54,7 @@ __device__ __forceinline__ bool locate(const BatchArgs& B, int kind, int b, int&
     }
     i = lo;
     local = b - off[lo];
-    return gp(B.steps_left)[lo] > 0;
+    return gp(B.limit)[lo] > B.step;
 }
 
 __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
@@ -1770,22 +1770,18 @@ __global__ void materialize_done_kernel(StepArgs a) {
 // threads in a fixed order.  Thread 0 reads the record while the partials arrive and
 // writes it back whole.
 constexpr int kBudgetThreads = 1024;
-__global__ __launch_bounds__(kBudgetThreads) void budget_kernel(BatchArgs B, int mode) {
-    int pi, local;
-    if (!locate(B, KT_BUDGET, blockIdx.x, pi, local)) return;
-    const StepArgs a = args_of(B, pi);   // by value: no reloads after stores
+// T: threads of the block (at most kBudgetThreads); n_fin, n_blk: partials of either kind.
+__device__ __forceinline__ void budget_fold(const StepArgs& a, int n_fin, int n_blk, int T, int mode) {
     const bool init = mode == BUD_INIT;
     ASN_G double* rec = gp(a.rec);
     double r[REC_LEN];
     if (threadIdx.x == 0)
 #pragma unroll
         for (int k = 0; k < REC_LEN; ++k) r[k] = rec[k];
-    const int n_fin = a.fin_blocks;
-    const int n_blk = init ? 0 : a.tiles_x * a.tiles_y * a.G;
     double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const ASN_G double4* fp = reinterpret_cast<const ASN_G double4*>(gp(a.fin_part));
     const ASN_G double2* bp = reinterpret_cast<const ASN_G double2*>(gp(a.blk_part));
-    constexpr int T = kBudgetThreads, U = 4;
+    constexpr int U = 4;
     for (int i0 = threadIdx.x; i0 < max(n_fin, n_blk); i0 += T * U) {
         double4 v[U];
         double2 w[U];
@@ -1812,10 +1808,9 @@ __global__ __launch_bounds__(kBudgetThreads) void budget_kernel(BatchArgs B, int
         }
     }
     __shared__ double tot[6];
-    block_sum_waves<T / 64, 6>(s, tot);
+    block_sum_n<kBudgetThreads / 64, 6>(s, T / 64, tot);
     __syncthreads();
     if (threadIdx.x != 0) return;
-    if (mode == BUD_STEP || mode == BUD_STAGE2) gp(B.steps_left)[pi] -= 1;
     const double m_next = a.area * tot[0];
     const double abs_next = a.area * tot[1];
     auto store = [&]() {
@@ -1870,6 +1865,18 @@ __global__ __launch_bounds__(kBudgetThreads) void budget_kernel(BatchArgs B, int
         r[REC_ABS_NEXT] = abs_next;
     }
     store();
+}
+
+// One block per problem.  A banded step's partials are one of either kind per block of the
+// step, written by step B.step - 1 (the fold of the call's last step).
+__global__ __launch_bounds__(kBudgetThreads) void budget_kernel(BatchArgs B, int mode) {
+    const int pi = blockIdx.x;
+    if (gp(B.limit)[pi] <= (mode == BUD_BANDED ? B.step - 1 : B.step)) return;
+    const StepArgs a = args_of(B, pi);   // by value: no reloads after stores
+    if (mode == BUD_BANDED)
+        budget_fold(a, a.tiles_x, a.tiles_x, kBudgetThreads, BUD_STEP);
+    else
+        budget_fold(a, a.fin_blocks, mode == BUD_INIT ? 0 : a.tiles_x * a.tiles_y * a.G, kBudgetThreads, mode);
 }
 
 // ---------------------------------------------------------------------------
@@ -2087,7 +2094,16 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     constexpr int O = kBandO;
     extern __shared__ float slots[];
     int pi, local;
-    if (!locate(B, KT_SC, xcd_remap(blockIdx.x, gridDim.x), pi, local)) return;
+    if ((int)blockIdx.x < B.n) {   // the last step's budget, one block per problem
+        pi = blockIdx.x;
+        if (B.step == 0 || gp(B.limit)[pi] < B.step) return;
+        BatchArgs P = B;
+        P.s_par ^= 1;
+        const StepArgs a = args_of(P, pi);
+        budget_fold(a, a.tiles_x, a.tiles_x, (int)blockDim.x, BUD_STEP);
+        return;
+    }
+    if (!locate(B, KT_SC, xcd_remap(blockIdx.x - B.n, gridDim.x - B.n), pi, local)) return;
     const StepArgs a = args_of(B, pi);   // by value: no reloads after stores
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2291,19 +2307,32 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
         }
     }
 
-    // Phi^{n+1} of each cell: the waves' partials in a fixed order
+    // Phi^{n+1} of each cell: the waves' partials in a fixed order.  Wave 0 holds the block's
+    // cells, so it takes over what finalize_kernel does for the other forms: Phi, Phi / W and
+    // the mass partials.
     double* red = reinterpret_cast<double*>(slots);
     red[wave * kBandCells + lane] = phacc;
     lds_barrier();
-    if (wave == 0 && in) {
-        double s = red[lane];
-        for (int g = 1; g < NW; ++g) s += red[g * kBandCells + lane];
-        gp(a.phi_part)[cell] = s;
+    if (wave == 0) {
+        double fin[4] = {0.0, 0.0, 0.0, 0.0};
+        if (in) {
+            double phi = red[lane];
+            for (int g = 1; g < NW; ++g) phi += red[g * kBandCells + lane];
+            // the physical scattering's part of the collision defect, sum_q w_q bs (iso -
+            // psi_q) = bs (W iso - Phi), once per cell (Phi of psi^n in FP64)
+            defect += (double)cf.y * (a.W * (double)isov - gp(a.phi64)[cell]);
+            gp(a.iso)[cell] = (float)(phi / a.W);
+            gp(a.phi64)[cell] = phi;
+            fin[0] = phi;
+            fin[1] = (double)cf.x * phi;
+            fin[2] = (double)cf.w;
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) fin[k] = wave_sum(fin[k]);
+        if (lane == 0)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) gp(a.fin_part)[4 * (size_t)local + k] = fin[k];
     }
-    // the physical scattering's part of the collision defect, sum_q w_q bs (iso - psi_q)
-    // = bs (W iso - Phi), once per cell (Phi of psi^n in FP64)
-    if (wave == 0 && in)
-        defect += (double)cf.y * (a.W * (double)isov - gp(a.phi64)[cell]);
     double sums[2] = {defect, outflow};
     block_sum_n<16, 2>(sums, NW, gp(a.blk_part) + 2 * (size_t)local);
 }
@@ -2774,15 +2803,21 @@ void blocks_per_kind(const StepArgs& a, int out[KT_COUNT]) {
     out[KT_FIX] = (a.dtype != 0 && !a.fused) ? a.fin_blocks : 0;
     out[KT_SC] = (a.fused && !banded) ? 0 : a.tiles_x * a.tiles_y * a.G;
     out[KT_FIN] = a.fin_blocks;
-    out[KT_BUDGET] = 1;
 }
 
 // The instance for reach 2 also serves smaller reaches (zero coefficients), the one for
 // reach 3 any.
+// One launch per step: each block finishes its cells' moments, and the fold of a step's budget
+// partials, which nothing in the next step waits for, runs in n more blocks of that step's
+// launch (the partials alternate with the state buffers; the call's last fold is a launch of
+// its own, launch_last_budget).  With finalize_kernel and budget_kernel after every step
+// 24 steps of 50^2 x 128, set-up and results included, took 726 us instead of 516, 40 steps of
+// 311 x 173 x 288 3.13 ms instead of 2.76, a step of 400^2 x 512 187 us instead of 175.
 static hipError_t launch_banded(const BatchArgs& b, int blocks, int az, size_t lds, hipStream_t s,
                                 int reach) {
     if (!band_azimuths_supported(az) || reach < 0 || reach > kBandMaxReach) return hipErrorInvalidValue;
     const int threads = az / kBandO * 64;
+    blocks += b.n;   // and the last step's budget
     if (reach <= 2) banded_euler_kernel<2, 1024><<<blocks, threads, lds, s>>>(b);
     else if (threads <= 512) banded_euler_kernel<3, 512><<<blocks, threads, lds, s>>>(b);
     else banded_euler_kernel<3, 1024><<<blocks, threads, lds, s>>>(b);
@@ -2859,9 +2894,9 @@ static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, in
                        : launch_banded_lp(b, grid[KT_SC], band_az, dtype, band_lds, s, band_reach);
         mark(1);
         mark(2);
-        if (e == hipSuccess) finalize_kernel<<<grid[KT_FIN], 256, 0, s>>>(b, 0);
+        if (e == hipSuccess && dtype != 0) finalize_kernel<<<grid[KT_FIN], 256, 0, s>>>(b, 0);
         mark(3);
-        if (e == hipSuccess) budget_kernel<<<grid[KT_BUDGET], kBudgetThreads, 0, s>>>(b, BUD_STEP);
+        if (e == hipSuccess && dtype != 0) budget_kernel<<<b.n, kBudgetThreads, 0, s>>>(b, BUD_STEP);
         mark(4);
         if (e != hipSuccess) return e;
         return hipGetLastError();
@@ -2906,7 +2941,7 @@ static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, in
     mark(2);
     finalize_kernel<<<grid[KT_FIN], 256, 0, s>>>(b, 0);
     mark(3);
-    budget_kernel<<<grid[KT_BUDGET], kBudgetThreads, 0, s>>>(b, bud);
+    budget_kernel<<<b.n, kBudgetThreads, 0, s>>>(b, bud);
     mark(4);
     if (e != hipSuccess) return e;
     return hipGetLastError();
@@ -2928,17 +2963,26 @@ hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int schem
     return launch_pass(b1, grid, dtype, st + 1, BUD_STAGE2, s, ev ? ev + 5 : nullptr);
 }
 
-__global__ void arm_kernel(int* steps_left, int* base, int n, ArmArgs v) {
+hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int dtype, int scheme, hipStream_t s) {
+    if (scheme != SCHEME_EULER_BANDED || dtype != 0 || n_steps < 1) return hipSuccess;
+    BatchArgs l = b;
+    l.step = n_steps;
+    l.s_par = (n_steps - 1) & 1;
+    budget_kernel<<<l.n, kBudgetThreads, 0, s>>>(l, BUD_BANDED);
+    return hipGetLastError();
+}
+
+__global__ void arm_kernel(int* limit, int* base, int n, ArmArgs v) {
     const int i = threadIdx.x;
     if (i < n) {
-        steps_left[i] = v.limit[i];
+        limit[i] = v.limit[i];
         base[i] = v.cur[i];
     }
 }
 
-hipError_t launch_arm(int* steps_left, int* base, int n, const ArmArgs& v, hipStream_t s) {
+hipError_t launch_arm(int* limit, int* base, int n, const ArmArgs& v, hipStream_t s) {
     if (n < 1 || n > kMaxArm) return hipErrorInvalidValue;
-    arm_kernel<<<1, kMaxArm, 0, s>>>(steps_left, base, n, v);
+    arm_kernel<<<1, kMaxArm, 0, s>>>(limit, base, n, v);
     return hipGetLastError();
 }
 

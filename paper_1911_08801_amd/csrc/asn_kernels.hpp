@@ -103,7 +103,7 @@ inline size_t band_lp_lds_bytes(int az, int reach, int dtype) {
 constexpr size_t kMaxBlockLds = 160 * 1024 - 1024;
 
 // Modes of the budget kernel.
-enum { BUD_STEP = 0, BUD_INIT = 1, BUD_STAGE1 = 2, BUD_STAGE2 = 3 };
+enum { BUD_STEP = 0, BUD_INIT = 1, BUD_STAGE1 = 2, BUD_STAGE2 = 3, BUD_BANDED = 4 };
 
 // Cells per block of the reduced-precision operand scale: the default, and the range
 // of powers of two a problem may choose (StepArgs::sb_log).  A block holds at least 64
@@ -164,7 +164,8 @@ struct StepArgs {
     double* phi64;          // Phi (FP64)
     double* phi_part;       // [G][P]
     double* blk_part;       // stencil block partials [G * tiles][2]
-    double* fin_part;       // finalize block partials [fin_blocks][4]
+    double* fin_part;       // finalize block partials [fin_blocks][4] (banded FP32: [tiles][4], and
+                            // both kinds once per state buffer)
     double* ypart;          // [Qp / kGemmBM][P] weighted row sums of Y (reduced precision)
     float* fix;             // [P] per-cell particle correction of the reduced-precision Y
     float* delta;           // [P] fused reduced precision: pending isotropic correction of the
@@ -189,23 +190,23 @@ struct StepArgs {
 };
 
 // Kernel kinds of one step, each with its own block decomposition.
-enum { KT_GEMM = 0, KT_FIX = 1, KT_SC = 2, KT_FIN = 3, KT_BUDGET = 4, KT_COUNT = 5 };
+enum { KT_GEMM = 0, KT_FIX = 1, KT_SC = 2, KT_FIN = 3, KT_COUNT = 4 };
 
 // Launch view of a batch of problems that share Q, K and the operand type.
 // Every kernel covers all problems in one launch: block b of kernel kind k
 // belongs to problem i with off[k * (n + 1) + i] <= b < off[k * (n + 1) + i + 1].
 // tab[2 i + c] are the step arguments of problem i when psi buffer c holds its
-// current state; at batch step s problem i uses c = base[i] ^ s_par.  A problem
-// whose steps_left[i] is not positive is skipped (its blocks exit at once); the
-// budget kernel decrements steps_left[i] after each step.  A single problem is a
+// current state; at batch step s problem i uses c = base[i] ^ s_par.  A problem takes the
+// steps below limit[i]; at later ones its blocks exit at once.  A single problem is a
 // batch of one, so a problem computes bitwise the same alone and in a batch.
 struct BatchArgs {
     const StepArgs* tab;
     const int* off;
     const int* base;
-    int* steps_left;
+    const int* limit;
     int n;
-    int s_par;
+    int step;    // steps of the call before this one
+    int s_par;   // buffer parity: of the step (Euler), of the pass (Heun)
 };
 
 // Blocks of each kernel kind for one problem.
@@ -233,13 +234,16 @@ hipError_t prepare_banded_lp(int band_az, int dtype, int reach, size_t band_lds)
 inline int passes_per_step(int scheme) {
     return scheme == SCHEME_HEUN || scheme == SCHEME_HEUN_FLAT ? 2 : 1;
 }
-// Arm a batch: steps_left[i] = limit[i] and base[i] = cur[i], i < n <= kMaxArm.
+// After the last of a call's n_steps steps: what the next step's launch would do for it (the
+// banded step's budget).
+hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int dtype, int scheme, hipStream_t s);
+// Arm a batch: limit[i] and base[i] = cur[i], i < n <= kMaxArm.
 constexpr int kMaxArm = 64;
 struct ArmArgs {
     int limit[kMaxArm];
     int cur[kMaxArm];
 };
-hipError_t launch_arm(int* steps_left, int* base, int n, const ArmArgs& v, hipStream_t s);
+hipError_t launch_arm(int* limit, int* base, int n, const ArmArgs& v, hipStream_t s);
 // Moments of the current state (after set_state): phi64, iso, bmax, budget record.
 hipError_t launch_init(const StepArgs& a, const BatchArgs& one, hipStream_t s);
 // Fused reduced precision: fold the pending correction into the stored state.
