@@ -33,7 +33,7 @@ PEAK_FP32_MFMA_TFLOPS = 157.3
 PEAK_FP32_VALU_TFLOPS = 78.6     # FMA on 16 lanes per SIMD, no packed FP32 (not used here)
 PEAK_LP_MFMA_TFLOPS = 2500.0     # dense BF16 / FP16 MFMA
 BYTES_PER_UPDATE = 8.0           # read psi^n and write psi^{n+1} once, FP32
-BAND_WIDE_ROW_CELLS = 1024       # rows from this width on take the banded kernel's wide-row instance
+BAND_WIDE_ROW_CELLS = 1024       # rows from this width on are labelled wide
 
 
 def parse():
@@ -195,11 +195,13 @@ def measured_traffic(kernel, spec):
     return None if k is None else k["fetch_bytes"] + k["write_bytes"]
 
 
-# the dominant kernel of each kernel form (its event slot in asn_step_timed)
+# the dominant kernel of each kernel form (its event slot in asn_step_timed).  The banded step is
+# one kernel, instantiated by reach and operand type; here it goes by its workload's azimuth count
+# and row width (FP32) or operand type.
 def dominant_kernel(res, spec, dtype):
     form = res["form"]
     lp = {"f32": 0, "bf16": 1, "f16": 2}[dtype]
-    if form == "banded" and lp:   # instantiated per reach of K
+    if form == "banded" and lp:
         return f"banded_lp_kernel<{spec.n_azim}, {lp}, R>", "contraction"
     if form == "banded":
         wide = "true" if spec.nx >= BAND_WIDE_ROW_CELLS else "false"
@@ -227,7 +229,7 @@ def roofline(res, spec, dtype):
     ach = bytes_ / t / 1e9
     nz = res["work"]["nonzero_flops"]
     executed = res["work"]["tile_flops"]
-    compute_peak = (PEAK_FP32_VALU_TFLOPS if res["form"] == "banded" and dtype == "f32" else
+    compute_peak = (PEAK_FP32_VALU_TFLOPS if res["form"] == "banded" else
                     PEAK_FP32_MFMA_TFLOPS if dtype == "f32" else PEAK_LP_MFMA_TFLOPS)
     traffic = measured_traffic(name, spec)
     return {"bound": "hbm", "kernel": name, "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",

@@ -104,14 +104,13 @@ enum { ASN_DT_STREAMING = 0, ASN_DT_STIFF = 1 };
  *                    2 pi / n_azim about the polar axis, so K restricted to two polar
  *                    levels is circulant along the azimuth, and K couples only nearby
  *                    levels (forward peak, Section 3.5 notes S_as^+ is sparse).  One kernel
- *                    per step applies K level pair by level pair and the update, reading
- *                    psi^n once.  FP32: short circular convolutions on the vector units,
- *                    n_azim in {8, 16, ..., 64}.  BF16 / FP16: each coupled pair's
- *                    n_azim x n_azim circulant block of the rounded K on the matrix
- *                    cores, the update as ASN_FORM_FUSED (the same rounding recipe and
- *                    pending per-cell correction), n_azim 32, 48 or 64.  Needs levels at
- *                    most 3 apart coupled (BF16 at 48 or 64 azimuths: 2) and the stored K exactly
- *                    circulant (checked at asn_create; ASN_E_UNSUPPORTED otherwise).
+ *                    per step applies K as short circular convolutions on the vector units
+ *                    and the update, reading psi^n once.  FP32: n_azim in {8, 16, ..., 64}.
+ *                    BF16 / FP16: the rounded operands and the rounded K (the same rounding
+ *                    recipe and pending per-cell correction as ASN_FORM_FUSED), n_azim 32,
+ *                    48 or 64.  Needs levels at most 3 apart coupled (BF16 at 48 or 64
+ *                    azimuths: 2) and the stored K exactly circulant (checked at asn_create;
+ *                    ASN_E_UNSUPPORTED otherwise).
  * ASN_FORM_AUTO:     the banded form where it applies; else BF16/FP16 fuse, and FP32
  *                    runs separate kernels from 2^25 cell-ordinates (nx <= 4088) and
  *                    fuses smaller problems, the faster forms on MI355X at the sizes
@@ -269,7 +268,7 @@ asn_status asn_iteration_counts(asn_problem p, int64_t* sweeps, int64_t* matvecs
  * stream between its kernels; synchronises.  kernel_ms[k] receives the average
  * duration per step of kernel k: 0 the ordinate contraction Y = K Psi, 1 stream
  * + collide, 2 moment finalize, 3 budget fold (for ASN_SCHEME_HEUN, the sum over
- * its two passes; the FP32 ASN_FORM_BANDED step does all of it in kernel 0, but for the
+ * its two passes; the ASN_FORM_BANDED step does all of it in kernel 0, but for the
  * last step's fold); kernel_ms[4] the average span of a whole step.  Measurement
  * support for benchmarks; results equal asn_step.
  * Errors: ASN_E_INVALID (n_steps < 1), ASN_E_HIP. */
@@ -302,9 +301,8 @@ asn_status asn_info(asn_problem p, double* dt, int64_t* steps_done, int64_t* ste
 
 /* Arithmetic of one contraction Y = K Psi: dense_flops = 2 Q^2 C; tile_flops =
  * 2 C times the number of K entries in the blocks the kernel multiplies (banded
- * step: the runs it multiplies, see asn_contraction_nonzero; in BF16 / FP16 every
- * coupled pair's whole n_azim x n_azim block, not counting the zero operands that fill a
- * level's pair slots up to 2 reach + 1).  K is
+ * step: the runs of its pairs, see asn_contraction_nonzero; in BF16 / FP16 every coupled
+ * pair's whole n_azim x n_azim block, though the step multiplies the runs only).  K is
  * forward peaked (paper Section 3.5: the discrete artificial in-scattering is a
  * sparse matrix), so blocks whose entries are all zero in the stored operand type
  * are skipped: 128-row x 32-column tiles for BF16/FP16, and for FP32 the 16-row x
@@ -316,7 +314,7 @@ asn_status asn_contraction_work(asn_problem p, double* dense_flops, double* tile
  * entries of K in the stored operand type (FP32, or the BF16/FP16 copy), the products
  * the method needs (paper Section 3.5: S_as^+ is sparse).  The banded step
  * (ASN_FORM_BANDED) is counted in asn_contraction_work's tile_flops by every stored nonzero
- * of a pair's run plus the zeros that pad wide runs to a multiple of four; in FP32 it adds
+ * of a pair's run plus the zeros that pad wide runs to a multiple of four; the step adds
  * the two ordinates at offsets +-d first, so it multiplies about half as often.
  * Errors: ASN_E_INVALID (NULL problem or pointer). */
 asn_status asn_contraction_nonzero(asn_problem p, double* nonzero_flops);

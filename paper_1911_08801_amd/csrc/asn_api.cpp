@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <map>
 #include <memory>
@@ -48,17 +49,17 @@ struct Layout {
     bool banded = false; // banded step: one kernel per step for a product ordinate set
     int ktab_len = 0;
     size_t off_psi0, off_psi1, off_Y, off_Kt, off_Klp, off_rdef, off_ktab, off_qi, off_coef, off_iso,
-        off_band, off_bcoef5, off_bcoef7, off_bcxy, off_bfrag,
+        off_band, off_bcoef[3], off_bcxy,
         off_phi64, off_phipart, off_blk, off_fin, off_ypart, off_fix, off_delta, off_bmax0, off_bmax1, off_rec,
         off_tab, off_off, off_base, off_left, off_imp,
         total;
 };
 
-// Coefficients either table of band_scatter_tables can need at most for `levels` polar
-// levels of `azim` azimuths: offsets 0 .. azim / 2 (a multiple of 4), 7 columns each; and 16
-// more (the kernel reads whole scalar loads).
-static size_t band_coef_capacity(int levels, int azim) {
-    return (size_t)levels * 7 * (size_t)(1 + round_up(azim / 2, 4)) + 16;
+// Coefficients a table of band_scatter_tables can need at most for `levels` polar levels of
+// `azim` azimuths: offsets 0 .. azim / 2 (a multiple of 4) of n outputs; and 16 more (the
+// kernel reads whole scalar loads).
+static size_t band_coef_capacity(int levels, int azim, int n) {
+    return (size_t)levels * n * (size_t)(1 + round_up(azim / 2, 4)) + 16;
 }
 
 // log2 of an accepted operand scale block (0 selects the default), else -1.
@@ -95,10 +96,9 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
     }
     int tiles = L.tiles_x * L.tiles_y;
     if (L.banded) {
-        // one block per kBandCells (kBandLpCells) cells, every ordinate: each cell's Phi
+        // one block per kBandCells cells, every ordinate: each cell's Phi
         // complete
-        const int cells = L.lowp ? asn::kBandLpCells : asn::kBandCells;
-        L.tiles_x = (int)((L.C + cells - 1) / cells);
+        L.tiles_x = (int)((L.C + asn::kBandCells - 1) / asn::kBandCells);
         L.tiles_y = 1;
         tiles = L.tiles_x;
         L.qchunk = Q;
@@ -141,31 +141,23 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
         L.ktab_len = mt + 1 + 2 * mt * (L.Qp / bk);   // offsets, k-steps, sub-block masks
         L.off_ktab = take((size_t)L.ktab_len * 4);
     }
-    // level descriptors, 8 words (reduced precision: one more)
-    L.off_band = take(L.banded ? (size_t)(band_levels + 1) * 32 : 0);
-    L.off_bcoef5 = take(L.banded && !L.lowp ? band_coef_capacity(band_levels, band_azim) * 4 : 0);
-    L.off_bcoef7 = take(L.banded && !L.lowp ? band_coef_capacity(band_levels, band_azim) * 4 : 0);
-    L.off_bcxy = take(L.banded && !L.lowp ? (size_t)Q * 8 : 0);
-    // reduced-precision banded step: per level and one more, 2 kBandLpMaxReach + 1 pair
-    // slots of n_az / 16 A operands of 1 KiB and a (cx, cy) table of n_az float pairs, and
-    // 1 KiB after them
-    L.off_bfrag = take(L.banded && L.lowp
-                           ? (size_t)(band_levels + 1) *
-                                     ((2 * asn::kBandLpMaxReach + 1) * (band_azim / 16) * 1024 + band_azim * 8) +
-                                 1024
-                           : 0);
+    // level descriptors, 8 words; the coefficient tables of each reach; (cx, cy)
+    L.off_band = take(L.banded ? (size_t)band_levels * 32 : 0);
+    for (int r = 0; r < 3; ++r)
+        L.off_bcoef[r] = take(L.banded ? band_coef_capacity(band_levels, band_azim, 2 * r + 3) * 4 : 0);
+    L.off_bcxy = take(L.banded ? (size_t)Q * 8 : 0);
     L.off_qi = take((size_t)Q * sizeof(QInfo));
     L.off_coef = take(plane * 16);
     L.off_iso = take(plane * 4);
     L.off_phi64 = take(plane * 8);
     L.off_phipart = take((size_t)L.G * plane * 8);
-    // banded FP32: the partials of a step are read in the next one, so once per state buffer
-    const size_t sets = L.banded && !L.lowp ? 2 : 1;
+    // banded: the partials of a step are read in the next one, so once per state buffer
+    const size_t sets = L.banded ? 2 : 1;
     L.off_blk = take(sets * tiles * L.G * 2 * 8);
     L.off_fin = take(sets * std::max<size_t>(L.fin_blocks, L.banded ? tiles : 0) * 4 * 8);
-    L.off_ypart = take(L.lowp ? (size_t)(L.Qp / asn::kGemmBM) * plane * 8 : 0);
+    L.off_ypart = take(L.lowp && !L.banded ? (size_t)(L.Qp / asn::kGemmBM) * plane * 8 : 0);
     L.off_fix = take(L.lowp && !fused ? plane * 4 : 0);
-    L.off_delta = take(L.lowp && fused ? plane * 4 : 0);
+    L.off_delta = take(L.lowp && fused ? sets * plane * 4 : 0);   // banded: follows the state buffer
     // block maxima for the smallest scale block (any block size a problem takes fits)
     L.off_bmax0 = take((size_t)asn::scale_blocks(L.P, scale_block_log(asn::kScaleBlockMin)) * 4);
     L.off_bmax1 = take((size_t)asn::scale_blocks(L.P, scale_block_log(asn::kScaleBlockMin)) * 4);
@@ -215,8 +207,7 @@ struct asn_problem_s {
     std::unique_ptr<asn::ImplicitSolver> imp;   // the implicit scheme's solver (else null)
     int band_levels = 0, band_azim = 0, band_reach = 0;   // banded step (else 0)
     size_t band_lds() const {
-        return dtype == ASN_GEMM_F32 ? asn::band_lds_bytes(band_azim)
-                                     : asn::band_lp_lds_bytes(band_azim, band_reach, dtype);
+        return asn::band_lds_bytes(band_azim, dtype);
     }
 };
 
@@ -282,16 +273,20 @@ StepArgs make_args(asn_problem p, int cur) {
     a.bmax_cur = cur == 0 ? bm0 : bm1;
     a.bmax_next = cur == 0 ? bm1 : bm0;
     a.rec = reinterpret_cast<double*>(b + L.off_rec);
-    if (L.banded && !L.lowp && cur) {
+    if (L.banded && L.lowp) {
+        a.delta_next = a.delta + (cur ? 0 : L.P);
+        a.delta += cur ? L.P : 0;
+    }
+    if (L.banded && cur) {
         a.blk_part += 2 * (size_t)L.tiles_x;
         a.fin_part += 4 * (size_t)L.tiles_x;
     }
     if (L.banded) {
         a.band = reinterpret_cast<const uint4*>(b + L.off_band);   // two per level
-        a.bcoef5 = reinterpret_cast<const float*>(b + L.off_bcoef5);
-        a.bcoef7 = reinterpret_cast<const float*>(b + L.off_bcoef7);
+        a.bcoef3 = reinterpret_cast<const float*>(b + L.off_bcoef[0]);
+        a.bcoef5 = reinterpret_cast<const float*>(b + L.off_bcoef[1]);
+        a.bcoef7 = reinterpret_cast<const float*>(b + L.off_bcoef[2]);
         a.bcxy = reinterpret_cast<const float2*>(b + L.off_bcxy);
-        a.bfrag = reinterpret_cast<const uint4*>(b + L.off_bfrag);
         a.n_lev = p->band_levels;
         a.n_az = p->band_azim;
         a.reach = p->band_reach;
@@ -443,8 +438,7 @@ bool band_candidate(int dtype, int scheme, int form, const asn_quadrature* q, in
     // the kernel addresses one polar level of planes (n_azim * P floats) with byte
     // offsets below 2^31
     const int64_t P = round_up(C, asn::kScaleBlock);
-    const bool az_ok = dtype == ASN_GEMM_F32 ? asn::band_azimuths_supported(q->n_azim)
-                                             : asn::band_lp_azimuths_supported(q->n_azim);
+    const bool az_ok = asn::band_azimuths_supported(q->n_azim, dtype);
     return az_ok && scheme == ASN_SCHEME_EULER &&
            (int64_t)std::max(q->n_azim, 1) * P * 4 < ((int64_t)1 << 31) &&
            (form == ASN_FORM_AUTO || form == ASN_FORM_BANDED) && q->q_custom == 0 &&
@@ -594,8 +588,8 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
     // banded step when K has that form (ASN_FORM_AUTO) or on request (ASN_FORM_BANDED)
     asn::BandForm bf;
     bool banded = false;
-    std::vector<uint32_t> sdesc;   // FP32 kernel: level descriptors and coefficients
-    std::vector<float> coef5, coef7;
+    std::vector<uint32_t> ddesc;   // its level descriptors and coefficients
+    std::array<std::vector<float>, 3> bcoef;
     if (band_candidate(p->dtype, p->scheme, opt.step_form, quad, C)) {
         // the values the kernel multiplies: FP32 K, or its BF16 / FP16 rounding
         std::vector<float> K32((size_t)Q * Q);
@@ -610,12 +604,11 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         }
         banded = asn::band_form(quad->n_polar, quad->n_azim, K32.data(), asn::kBandMaxReach,
                                 asn::kBandNarrow, bf);
-        if (banded && p->dtype == ASN_GEMM_F32) banded = asn::band_scatter_tables(bf, sdesc, coef5, coef7);
+        banded = banded && asn::band_supported(bf.azim, p->dtype, bf.reach) &&
+                 asn::band_scatter_tables(bf, p->dtype, ddesc, bcoef);
         if (banded && p->dtype != ASN_GEMM_F32) {
-            // the reduced-precision kernel takes one row defect per level (the rows of a
-            // level hold the same values, so their FP64 sums agree; checked) and must fit
-            // its LDS
-            if (asn::band_lp_lds_bytes(bf.azim, bf.reach, p->dtype) > asn::kMaxBlockLds) banded = false;
+            // the kernel takes one row defect per level (the rows of a level hold the same
+            // values, so their FP64 sums agree; checked)
             std::vector<uint16_t> kq((size_t)Q * Q);
             std::vector<float> rd((size_t)Q);
             quantise_kernel(Q, K.data(), p->dtype, Q, kq.data(), rd.data());
@@ -762,50 +755,13 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         coef[c].w = source ? (float)(p->dt * (double)source[c]) : 0.f;
     }
 
-    std::vector<uint32_t> ddesc;
-    std::vector<float> dcxy;   // FP32 banded kernel: (cx, cy) per ordinate
-    std::vector<uint16_t> bfrag;
-    if (banded && !L.lowp) {
-        ddesc = sdesc;   // and the FP64 weight of the level's ordinates
-        for (int i = 0; i < bf.levels; ++i)
+    std::vector<float> dcxy;   // banded kernel: (cx, cy) per ordinate
+    if (banded) {
+        for (int i = 0; i < bf.levels; ++i)   // the FP64 weight of a level's ordinates
             std::memcpy(&ddesc[8 * (size_t)i + 4], &qi[(size_t)i * bf.azim].w, 8);
         for (const QInfo& v : qi) {
             dcxy.push_back(v.cx);
             dcxy.push_back(v.cy);
-        }
-    } else if (banded) {
-        // per level and one more {pairs, first uint4 of its block, the level offsets k of its
-        // pair slots (4 bits each), 0}.  Block l: 2 kBandLpMaxReach + 1 pair slots of
-        // n_az / 16 A operands of MFMA 16x16x32 (band_lp_fragments), the coupled pairs of
-        // level l first, then zero operands whose partner is the level itself (the kernel
-        // runs the first 2 reach + 1 slots of its launch's largest reach, with no count);
-        // then (cx, cy) of level l - 1's ordinates as FP32 pairs (its update runs a level
-        // behind); block n_lev holds only the last level's table
-        constexpr int slots = 2 * asn::kBandLpMaxReach + 1;
-        const int per_slot = bf.azim / 16;
-        const size_t block = (size_t)slots * per_slot * 512 + (size_t)bf.azim * 4;   // 16-bit words
-        ddesc.assign((size_t)(bf.levels + 1) * 8, 0u);
-        for (int i = 0; i <= bf.levels; ++i) {
-            const int n = i < bf.levels ? (int)bf.desc[(size_t)i * 8] : 0;
-            uint32_t kc = 0;
-            for (int t = 0; t < slots; ++t)
-                kc |= (t < n ? ((bf.desc[(size_t)i * 8 + 1 + t] >> 8) & 7u) : (uint32_t)bf.reach)
-                      << (4 * t);
-            ddesc[(size_t)i * 8] = (uint32_t)n;
-            ddesc[(size_t)i * 8 + 1] = (uint32_t)(i * block / 8);
-            ddesc[(size_t)i * 8 + 2] = kc;
-            for (int t = 0; t < n; ++t) asn::band_lp_fragments(bf, i, t, p->dtype, bfrag);
-            bfrag.resize((size_t)i * block + (size_t)slots * per_slot * 512, 0);
-            for (int az = 0; az < bf.azim; ++az) {
-                float c[2] = {0.f, 0.f};
-                if (i > 0) {
-                    c[0] = qi[(size_t)(i - 1) * bf.azim + az].cx;
-                    c[1] = qi[(size_t)(i - 1) * bf.azim + az].cy;
-                }
-                uint16_t w[4];
-                std::memcpy(w, c, sizeof(c));
-                bfrag.insert(bfrag.end(), w, w + 4);
-            }
         }
     }
     auto bail = [&](asn_status st) {
@@ -814,6 +770,14 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         return st;
     };
     char* b = p->base;
+    auto copy_tables = [&] {
+        hipError_t e = hipSuccess;
+        for (int r = 0; r < 3 && e == hipSuccess; ++r)
+            if (!bcoef[r].empty())
+                e = hipMemcpyAsync(b + L.off_bcoef[r], bcoef[r].data(), bcoef[r].size() * 4, hipMemcpyHostToDevice,
+                                   p->stream);
+        return e;
+    };
     if (hipMemsetAsync(b, 0, L.total, p->stream) != hipSuccess ||
         hipMemcpyAsync(b + L.off_Kt, Kt.data(), Kt.size() * 4, hipMemcpyHostToDevice, p->stream) !=
             hipSuccess ||
@@ -823,21 +787,13 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
                        p->stream) != hipSuccess ||
         hipMemcpyAsync(b + L.off_ktab, ktab.data(), ktab.size() * 4, hipMemcpyHostToDevice,
                        p->stream) != hipSuccess ||
-        (banded && !L.lowp &&
+        (banded &&
          (hipMemcpyAsync(b + L.off_band, ddesc.data(), ddesc.size() * 4, hipMemcpyHostToDevice,
-                         p->stream) != hipSuccess ||
-          (!coef5.empty() && hipMemcpyAsync(b + L.off_bcoef5, coef5.data(), coef5.size() * 4,
-                                            hipMemcpyHostToDevice, p->stream) != hipSuccess) ||
-          hipMemcpyAsync(b + L.off_bcoef7, coef7.data(), coef7.size() * 4, hipMemcpyHostToDevice,
                          p->stream) != hipSuccess ||
           hipMemcpyAsync(b + L.off_bcxy, dcxy.data(), dcxy.size() * 4, hipMemcpyHostToDevice,
-                         p->stream) != hipSuccess)) ||
-        (banded && L.lowp &&
-         (hipMemcpyAsync(b + L.off_band, ddesc.data(), ddesc.size() * 4, hipMemcpyHostToDevice,
                          p->stream) != hipSuccess ||
-          hipMemcpyAsync(b + L.off_bfrag, bfrag.data(), bfrag.size() * 2, hipMemcpyHostToDevice,
-                         p->stream) != hipSuccess ||
-          asn::prepare_banded_lp(bf.azim, p->dtype, bf.reach, p->band_lds()) != hipSuccess)) ||
+          copy_tables() != hipSuccess ||
+          asn::prepare_banded(bf.azim, p->dtype, bf.reach, p->band_lds()) != hipSuccess)) ||
         (L.lowp && hipMemcpyAsync(b + L.off_Klp, Klp.data(), Klp.size() * 2,
                                   hipMemcpyHostToDevice, p->stream) != hipSuccess) ||
         hipMemcpyAsync(b + L.off_coef, coef.data(), coef.size() * 16, hipMemcpyHostToDevice,
@@ -981,7 +937,7 @@ asn_status asn_step(asn_problem p, int64_t n_steps) {
         HIP_TRY(asn::launch_step(b, p->blocks, p->dtype, launch_scheme(p), p->stream, nullptr,
                                  p->band_azim, lds, p->band_reach));
     }
-    HIP_TRY(asn::launch_last_budget(b, (int)n_steps, p->dtype, launch_scheme(p), p->stream));
+    HIP_TRY(asn::launch_last_budget(b, (int)n_steps, launch_scheme(p), p->stream));
     p->cur ^= state_flip(p->scheme, n_steps);
     p->steps_done += n_steps;
     return ASN_OK;
@@ -1030,7 +986,7 @@ asn_status asn_step_timed(asn_problem p, int64_t n_steps, double kernel_ms[5]) {
             break;
         }
     }
-    if (st == ASN_OK && asn::launch_last_budget(bt, (int)n_steps, p->dtype, launch_scheme(p), p->stream) != hipSuccess)
+    if (st == ASN_OK && asn::launch_last_budget(bt, (int)n_steps, launch_scheme(p), p->stream) != hipSuccess)
         st = fail(ASN_E_HIP, "budget launch failed");
     if (st == ASN_OK) {
         p->cur ^= state_flip(p->scheme, n_steps);
@@ -1177,7 +1133,7 @@ asn_status asn_batch_step(asn_batch b, int64_t n_steps, const int64_t* limit) {
                                      b->band_az, b->band_lds, b->band_reach);
             }
             if (e == hipSuccess)
-                e = asn::launch_last_budget(args, (int)n_steps, b->dtype, b->launch_scheme, b->stream);
+                e = asn::launch_last_budget(args, (int)n_steps, b->launch_scheme, b->stream);
             const hipError_t e2 = hipStreamEndCapture(b->stream, &g);
             if (e != hipSuccess || e2 != hipSuccess) {
                 if (g) (void)hipGraphDestroy(g);
@@ -1198,7 +1154,7 @@ asn_status asn_batch_step(asn_batch b, int64_t n_steps, const int64_t* limit) {
             HIP_TRY(asn::launch_step(args, b->grid, b->dtype, b->launch_scheme, b->stream, nullptr,
                                      b->band_az, b->band_lds, b->band_reach));
         }
-        HIP_TRY(asn::launch_last_budget(args, (int)n_steps, b->dtype, b->launch_scheme, b->stream));
+        HIP_TRY(asn::launch_last_budget(args, (int)n_steps, b->launch_scheme, b->stream));
     }
     for (int i = 0; i < b->n; ++i) {
         b->probs[i]->cur ^= state_flip(b->scheme, take[i]);
@@ -1302,7 +1258,7 @@ asn_status asn_step_batch_noalloc(asn_problem* probs, int32_t n, int64_t n_steps
         HIP_TRY(asn::launch_step(args, grid, probs[0]->dtype, scheme, stream, nullptr,
                                  probs[0]->band_azim, band_lds, band_reach));
     }
-    HIP_TRY(asn::launch_last_budget(args, (int)n_steps, probs[0]->dtype, scheme, stream));
+    HIP_TRY(asn::launch_last_budget(args, (int)n_steps, scheme, stream));
     for (int i = 0; i < n; ++i) {
         probs[i]->cur ^= state_flip(probs[i]->scheme, n_steps);
         probs[i]->steps_done += n_steps;

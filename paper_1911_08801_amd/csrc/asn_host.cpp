@@ -400,12 +400,14 @@ bool band_form(int levels, int azim, const float* K32, int max_reach, int narrow
     return true;
 }
 
-bool band_scatter_tables(const BandForm& bf, std::vector<uint32_t>& desc, std::vector<float>& coef5,
-                         std::vector<float>& coef7) {
+bool band_scatter_tables(const BandForm& bf, int dtype, std::vector<uint32_t>& desc,
+                         std::array<std::vector<float>, 3>& coef) {
     const int azim = bf.azim, half = azim / 2;
     desc.assign((size_t)bf.levels * 8, 0u);
-    coef5.clear();
-    coef7.clear();
+    for (auto& c : coef) c.clear();
+    // neighbouring values of the stored type: relative, and where it is subnormal
+    const float rel = dtype == 0 ? 0x1p-23f : dtype == 1 ? 0x1p-7f : 0x1p-10f;
+    const float sub = dtype == 0 ? 0x1p-149f : dtype == 1 ? 0x1p-133f : 0x1p-24f;
     for (int j = 0; j < bf.levels; ++j) {
         std::array<std::vector<float>, 7> col;   // c_ij(d), d = 0 .. s, of output i = j + m - 3
         for (int m = 0; m < 7; ++m) {
@@ -420,7 +422,7 @@ bool band_scatter_tables(const BandForm& bf, std::vector<uint32_t>& desc, std::v
                 const float* run = &bf.coef[(size_t)bf.range[2 * (size_t)i] + 4 * ((code >> 11) & 127u)];
                 for (int d = 0; d < lo + len; ++d) {
                     const float plus = run[d - lo], minus = -d >= lo ? run[-d - lo] : plus;
-                    if (plus != minus && std::nextafter(plus, minus) != minus) return false;
+                    if (std::fabs(plus - minus) > std::fmax(rel * std::fmax(plus, minus), sub)) return false;
                     col[(size_t)m].push_back(2 * d == azim ? 0.5f * plus : plus);
                 }
             }
@@ -434,43 +436,28 @@ bool band_scatter_tables(const BandForm& bf, std::vector<uint32_t>& desc, std::v
         }
         if (D > half) return false;
         uint32_t* d8 = &desc[(size_t)j * 8];
-        d8[0] = (uint32_t)coef5.size();
-        d8[1] = (uint32_t)coef7.size();
+        d8[0] = (uint32_t)coef[1].size();
+        d8[1] = (uint32_t)coef[2].size();
+        d8[7] = (uint32_t)coef[0].size();
         d8[2] = (uint32_t)((D + 3) / 4) | (D > 2 ? kBandBeyond2 : 0u) | (outer > 1 ? kBandOuter2 : 0u) |
                 (outer > 2 ? kBandOuter3 : 0u);
         const int rows = D <= 2 ? 3 : 1 + (D + 3) / 4 * 4;
-        for (int N = 7; N >= (bf.reach <= 2 ? 5 : 7); N -= 2) {
-            std::vector<float>& out = N == 7 ? coef7 : coef5;
+        for (int R = std::max(1, bf.reach); R <= 3; ++R) {
+            const int N = 2 * R + 1;
+            std::vector<float>& out = coef[(size_t)R - 1];
             const size_t base = out.size();
             out.resize(base + (size_t)rows * N, 0.f);
-            for (int m = (7 - N) / 2; m < 7 - (7 - N) / 2; ++m) {
-                const std::vector<float>& c = col[(size_t)m];
+            for (int r = 0; r < N; ++r) {
+                const std::vector<float>& c = col[(size_t)(r + 3 - R)];
                 if (c.empty()) continue;
-                const int r = m - (7 - N) / 2;
                 for (size_t d = 0; d < c.size(); ++d) out[base + d * N + r] = c[d];
-                d8[N == 7 ? 6 : 3] |= (uint32_t)((c.size() + 2) / 4) << (4 * r);
+                if (R > 1) d8[R == 3 ? 6 : 3] |= (uint32_t)((c.size() + 2) / 4) << (4 * r);
             }
         }
+        // (the steps of reach 1 are read as those of reach 2 less the first output)
+        if (bf.reach > 2) d8[3] = 0u;
     }
     return true;
-}
-
-void band_lp_fragments(const BandForm& bf, int level, int pair, int dtype,
-                       std::vector<uint16_t>& out) {
-    const int azim = bf.azim;
-    const uint32_t code = bf.desc[(size_t)level * 8 + 1 + pair];
-    int lo = 0, len = 0;
-    band_run(code, azim, lo, len);
-    const int start = 4 * (int)((code >> 11) & 127u) + bf.range[2 * (size_t)level];
-    std::vector<float> c((size_t)azim, 0.f);   // c(delta), delta = 0 .. azim - 1
-    for (int t = 0; t < len; ++t) c[(size_t)(((lo + t) % azim + azim) % azim)] = bf.coef[(size_t)start + t];
-    for (int f = 0; f < azim / 16; ++f)
-        for (int l = 0; l < 64; ++l)
-            for (int t = 0; t < 8; ++t) {
-                const int m = l % 16, k = 8 * (l / 16) + t;
-                const float v = c[(size_t)(((16 * f + k - m) % azim + azim) % azim)];
-                out.push_back(dtype == 1 ? float_to_bf16_rne(v) : float_to_half_rne(v));
-            }
 }
 
 }  // namespace asn

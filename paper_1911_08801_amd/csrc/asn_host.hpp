@@ -2,6 +2,7 @@
 // and operand rounding.  Plain C++ (no HIP), FP64 throughout.
 #pragma once
 
+#include <array>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -57,32 +58,24 @@ struct BandForm {
 // Even azim up to 126.
 bool band_form(int levels, int azim, const float* K32, int max_reach, int narrow_max,
                BandForm& out);
-// The tables the FP32 banded kernel reads, by source level: level j adds to the outputs of
+// The tables the banded kernel reads, by source level: level j adds to the outputs of
 // level i = j + m - 3, column m = 0 .. 6, the products c_ij(d) (psi[k + d] + psi[k - d]),
 // d = 0 .. D (d = 0: the value itself once; d = azim / 2, where both are one ordinate: half
 // the coefficient).  The set is symmetric under phi -> -phi, so c_ij(d) = c_ij(-d); where
-// the two stored values round to neighbouring floats the one at +d serves both (either is
+// the two stored values round to neighbouring numbers the one at +d serves both (either is
 // within half an ulp, plus the FP64 evaluation's error, of the exact entry).
 // Per level rows d of N = 2 R + 1 floats, output levels j - R .. j + R (zero where nothing
-// couples), for R = 2 in coef5 (empty when the set's reach is 3) and R = 3 in coef7; padded
-// with zeros to D = 2 or a multiple of 4.  desc, 8 words a level: its first float in coef5 and
-// coef7; its form (kBand flags below); ceil(D / 4) of each output, 4 bits each, in coef5's
-// order; two free words; the same in coef7's order; 0.  False on asymmetry beyond that.
+// couples), in coef[R - 1] for every R from the set's reach (at least 1) to 3, padded with
+// zeros to D = 2 or a multiple of 4.  desc, 8 words a level: its first float in coef[1] and
+// coef[2]; its form (kBand flags below); ceil(D / 4) of each output, 4 bits each, for R = 2;
+// two free words; the same for R = 3; its first float in coef[0].  dtype: the operand type the
+// values were rounded to.  False on asymmetry beyond that.
 constexpr uint32_t kBandSteps = 15;          // ceil(D / 4)
 constexpr uint32_t kBandBeyond2 = 16;        // D > 2
 constexpr uint32_t kBandOuter2 = 32;         // an output other than j - 1 .. j + 1 couples at d >= 2
 constexpr uint32_t kBandOuter3 = 64;         // ... at d >= 3
-bool band_scatter_tables(const BandForm& bf, std::vector<uint32_t>& desc, std::vector<float>& coef5,
-                         std::vector<float>& coef7);
-// The A operands of MFMA 16x16x32 for pair `pair` of level `level` of a banded form of
-// the BF16 (dtype 1) or FP16 (dtype 2) K: the pair's circulant block C[a][a'] =
-// c((a' - a) mod azim) sliced as 16 output x 32 input azimuths at the offsets 16 f,
-// f = 0 .. azim / 16 - 1 (slice f: rows m, columns k hold c((16 f + k - m) mod azim)),
-// each as 64 lanes x 8 values (lane l: row l % 16, columns 8 (l / 16) .. + 7), appended
-// to `out` as operand bits.  azim 32, 48 or 64 (48: columns past the last azimuth meet
-// zero operands in the kernel).
-void band_lp_fragments(const BandForm& bf, int level, int pair, int dtype,
-                       std::vector<uint16_t>& out);
+bool band_scatter_tables(const BandForm& bf, int dtype, std::vector<uint32_t>& desc,
+                         std::array<std::vector<float>, 3>& coef);
 // The run of a pair code: first offset and length.
 inline void band_run(uint32_t code, int azim, int& lo, int& len) {
     const int s = (int)(code & 63u);

@@ -1893,7 +1893,7 @@ __global__ __launch_bounds__(256) void moments_kernel(StepArgs a) {
         mx = fmaxf(mx, fabsf(v));
     }
     a.phi_part[c] = phi;
-    atomicMax(&a.bmax_cur[c >> a.sb_log], __float_as_uint(mx));
+    atomicMax(&a.bmax_cur[c >> (a.band ? 6 : a.sb_log)], __float_as_uint(mx));
 }
 
 __global__ void fill_u32_kernel(unsigned* p, int64_t n, unsigned v) {
@@ -1908,7 +1908,7 @@ __global__ void broadcast_kernel(float* psi, const float* cell, int Q, int64_t C
 }
 
 // ---------------------------------------------------------------------------
-// 5. Banded forward-Euler step for product ordinate sets (FP32).
+// 5. Banded forward-Euler step for product ordinate sets.
 //    The set is invariant under rotations by 2 pi / n_az about the polar axis and under
 //    reflection of the azimuth, so Y_(i,k) = sum_j sum_d c_ij(d) (psi_(j, k + d) + psi_(j, k - d)):
 //    per pair of levels a short symmetric circular convolution along the azimuth.  The
@@ -1935,6 +1935,13 @@ __global__ void broadcast_kernel(float* psi, const float* cell, int Q, int64_t C
 //    2.23 ms.  Two levels of loads in flight, flags between neighbouring waves instead of
 //    the barrier, and loads issued at the start of a pass instead of its end were all
 //    slower: what they add in registers and instructions costs more than they hide.
+//    BF16 / FP16 operands: the recipe of the fused reduced-precision form (the state is
+//    stored without its pending per-cell correction delta, only the anisotropic part is
+//    rounded: x = T((psi^ - iso^) 2^(E - e_b)), Y^ - iso^ = 2^(e_b - E) sum T(K) x + r_q
+//    (psi^ - iso^)), its products in FP32: a rounded operand, both BF16 terms together, is an
+//    FP32 number.  K is 2 % dense, so the vector units, which skip its zeros, finish before
+//    the matrix cores did with each level pair's whole circulant block: 400^2 x 512 BF16
+//    0.242 -> 0.196 ms, 700^2 x 1152 FP16 1.63 -> 1.34 ms.
 // ---------------------------------------------------------------------------
 // The band tables are written by the host before any step and only read by the
 // kernels: reached through the constant address space, their uniform loads are scalar
@@ -2080,18 +2087,33 @@ struct BandLevel {
 template <int RT>
 __device__ __forceinline__ BandLevel band_level(const uint4* band, int l) {
     const ASN_K uint4* p = kp(band) + 2 * l;
-    return {RT == 2 ? p[0].x : p[0].y, p[0].z, RT == 2 ? p[0].w : p[1].z};
+    return {RT == 1 ? p[1].w : RT == 2 ? p[0].x : p[0].y, p[0].z, RT == 1 ? p[0].w >> 4 : RT == 2 ? p[0].w : p[1].z};
 }
 // ... and the weight of its ordinates.
 __device__ __forceinline__ double band_weight(const uint4* band, int l) {
     return *reinterpret_cast<const ASN_K double*>(kp(band) + 2 * l + 1);
 }
 
+// The rounded operand of the reduced-precision contraction, x = T(s) for s = dev 2^(E - e_b)
+// (BF16: hi + lo), as the FP32 number it is: a lo term ends within s's 24 bits.
+template <int DT>
+__device__ __forceinline__ void round_pair(float s0, float s1, float& x0, float& x1) {
+    if constexpr (DT == 1) {
+        const uint32_t p = pack2<1>(s0, s1), r = bf16_residual2(p, s0, s1);
+        x0 = __uint_as_float(p << 16) + __uint_as_float(r << 16);
+        x1 = __uint_as_float(p & 0xFFFF0000u) + __uint_as_float(r & 0xFFFF0000u);
+    } else {
+        x0 = (float)(_Float16)s0;
+        x1 = (float)(_Float16)s1;
+    }
+}
+
 // T: the largest block (512 threads up to 32 azimuths: the reach-3 instance then keeps its
-// queue in registers).
-template <int RT, int T>
+// queue in registers).  DT: operand type of the contraction.
+template <int RT, int T, int DT>
 __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     constexpr int O = kBandO;
+    constexpr bool LP = DT != 0;
     extern __shared__ float slots[];
     int pi, local;
     if ((int)blockIdx.x < B.n) {   // the last step's budget, one block per problem
@@ -2111,7 +2133,7 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     const int nx = a.nx, ny = a.ny, L = a.n_lev, C = (int)a.C;
     const int c0 = local * kBandCells, cell = c0 + lane;
     const bool in = cell < C;
-    const ASN_K float* bcoef = kp(RT == 2 ? a.bcoef5 : a.bcoef7);
+    const ASN_K float* bcoef = kp(RT == 1 ? a.bcoef3 : RT == 2 ? a.bcoef5 : a.bcoef7);
     const ASN_K float2* bcxy = kp(a.bcxy) + a0;
 
     float4 cf = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -2119,6 +2141,20 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     if (in) {
         cf = gp(a.coef)[cell];
         isov = gp(a.iso)[cell];
+    }
+    // reduced precision: the pending correction of the cell, and E - e_b of its operand scale,
+    // from the maxima of the 64-cell blocks of its scale block
+    float dv = 0.f;
+    int sc = 0;
+    if constexpr (LP) {
+        if (in) dv = gp(a.delta)[cell];
+        const int first = (c0 >> a.sb_log) << (a.sb_log - 6), b = first + lane;
+        unsigned bits = 0u;
+        if (lane < 1 << (a.sb_log - 6) && b < a.tiles_x) bits = gp(a.bmax_cur)[b];
+        const float bm = __uint_as_float(wave_max_u32(bits));
+        int e = 0;
+        if (bm > 0.f) (void)frexpf(bm, &e);
+        sc = __builtin_amdgcn_readfirstlane(kScaleExp - max(e, -100));
     }
     // boundary of the lane's cell: 1 / 2 first / last column, 4 / 8 first / last row; 16 a
     // padding cell
@@ -2132,13 +2168,21 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     const size_t lvl_floats = (size_t)A * (size_t)a.P;
     const uint32_t voff = 4u * (uint32_t)cell;
     // n_az / 4 is even, so the flow direction is the same for azimuths 0, 1 and for 2, 3 of the
-    // wave (index o / 2)
-    uint32_t dir[2], yoff[2];
+    // wave (reduced precision: n_az / 16 is whole, it is the same for all four): index o / G.
+    // yd, xd: the pending corrections of the upwind cells (0 for a ghost)
+    constexpr int G = LP ? 4 : 2, NG = O / G;
+    uint32_t dir[NG], yoff[NG];
+    float yd = 0.f, xd = 0.f;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        dir[h] = (uint32_t)kp(a.qi)[a0 + 2 * h].dir;
+    for (int h = 0; h < NG; ++h) {
+        dir[h] = (uint32_t)kp(a.qi)[a0 + G * h].dir;
         const int yc = (dir[h] & 4) ? cell - nx : cell + nx;
-        yoff[h] = (in && yc >= 0 && yc < C) ? 4u * (uint32_t)yc : kOOB;
+        const bool yv = in && yc >= 0 && yc < C;
+        yoff[h] = yv ? 4u * (uint32_t)yc : kOOB;
+        if constexpr (LP) {
+            if (yv) yd = gp(a.delta)[yc];
+            if (!(at & ((dir[h] & 1) ? 17 : 18))) xd = gp(a.delta)[(dir[h] & 1) ? cell - 1 : cell + 1];
+        }
     }
     // lane l also fetches azimuth a0 + l % 4's upwind cell beyond the block's end, and keeps it
     // in the column before / after the cells of that row (every lane: no branch on lanes, so
@@ -2151,7 +2195,11 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     const int own = a0 * kBandRow + 1 + lane;
     const int lo = (a0 == 0 ? A - O : a0 - O) * kBandRow + 1 + lane;
     const int hi = (a0 + O == A ? 0 : a0 + O) * kBandRow + 1 + lane;
-    const int xup[2] = {own + ((dir[0] & 1) ? -1 : 1), own + ((dir[1] & 1) ? -1 : 1)};
+    int xup[NG];
+#pragma unroll
+    for (int h = 0; h < NG; ++h) xup[h] = own + ((dir[h] & 1) ? -1 : 1);
+    // (reduced precision: the rounded operands of a level follow its values)
+    const int XO = LP ? SF : 0, SS = SF + XO;
 
     struct Entry {
         float v[O], t[O];     // value, terms but the in-scattering
@@ -2172,15 +2220,23 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
         preh = load(r, hoff, s0);
     };
     auto put = [&](int slot) {
-        float* s = slots + slot * SF;
+        float* s = slots + slot * SS;
 #pragma unroll
         for (int o = 0; o < O; ++o) s[own + o * kBandRow] = pre[o];
         s[hrow] = preh;
+        if constexpr (LP) {
+            float x[O];
+#pragma unroll
+            for (int o = 0; o < O; o += 2)
+                round_pair<DT>(ldexpf(pre[o] - isov, sc), ldexpf(pre[o + 1] - isov, sc), x[o], x[o + 1]);
+#pragma unroll
+            for (int o = 0; o < O; ++o) s[XO + own + o * kBandRow] = x[o];
+        }
     };
     auto fetch_y = [&](const float* base) {
         const __amdgpu_buffer_rsrc_t r = level_rsrc(base);
 #pragma unroll
-        for (int o = 0; o < O; ++o) uy[o] = load(r, yoff[o / 2], s0 + (uint32_t)o * pb);
+        for (int o = 0; o < O; ++o) uy[o] = load(r, yoff[o / G], s0 + (uint32_t)o * pb);
     };
 
     // (level j's at j mod N, of which RT + 1 are in use at a time)
@@ -2191,7 +2247,8 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     for (int m = 0; m < N; ++m)
 #pragma unroll
         for (int o = 0; o < O; ++o) acc[m][o] = 0.f;
-    double phacc = 0.0, defect = 0.0, outflow = 0.0;
+    double phacc = 0.0, defect = 0.0, outflow = 0.0, ypacc = 0.0;
+    float mx = 0.f;
     const float* pf = a.psi;   // planes of the level fetched next
     const float* py = a.psi;   // and of the one whose y-upwind values are
     float* po = a.psi_new;     // planes of the level finished next
@@ -2210,16 +2267,20 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
         Entry& e = q[PJ];                   // level j
         Entry& n = q[(PJ + N - RT) % N];    // level j - RT
         BandLevel dn = d;
-        // the weight of the level finished here
+        // the weight of the level finished here, and its row defect
         const double w = band_weight(a.band, max(j - RT, 0));
+        const float rq = LP ? kp(a.rdef)[max(j - RT, 0) * A] : 0.f;
         if (j < L) {
-            const float* s = slots + (j & 1) * SF;
-            float ux[O];
+            const float* s = slots + (j & 1) * SS;
+            float ux[O], xv[O];
 #pragma unroll
             for (int o = 0; o < O; ++o) {
                 e.v[o] = s[own + o * kBandRow];
-                ux[o] = s[xup[o / 2] + o * kBandRow];
+                ux[o] = s[xup[o / G] + o * kBandRow];
             }
+            s += XO;
+#pragma unroll
+            for (int o = 0; o < O; ++o) xv[o] = LP ? s[own + o * kBandRow] : e.v[o];
             const float near[4] = {s[lo + 2 * kBandRow], s[lo + 3 * kBandRow], s[hi], s[hi + kBandRow]};
             // the level's uniform values, in one round trip with the LDS rows
             const ASN_K float* kc = bcoef + d.coef;
@@ -2232,31 +2293,35 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
             dn = band_level<RT>(a.band, min(j + 1, L - 1));
             await(k0);
             await(cc);
-            asm volatile("" ::"s"(w));
-            scatter<RT, PJ>(acc, e.v, near, k0, s + lo, s + hi, s + 1 + lane, a0, A, d.form, d.steps, kc);
+            asm volatile("" ::"s"(w), "s"(rq));
+            scatter<RT, PJ>(acc, xv, near, k0, s + lo, s + hi, s + 1 + lane, a0, A, d.form, d.steps, kc);
             // stream + collide without the in-scattering, one chain of FMAs:
             //   psi' = psi + [bs (iso - psi) + ss - aa psi + cy (uy - psi) + cx (ux - psi) + gs (Y - psi)]
             // (aa = dt sigma_a, bs = dt sigma_s, gs = dt sigma_as, ss = dt q); no coefficient
             // of psi is folded into a per-cell constant, whose rounding would bias every
             // ordinate of the cell alike.  A padding cell (not in) has psi = 0, zero
-            // coefficients and zero upwind values, so it stays zero.
+            // coefficients and zero upwind values, so it stays zero.  Reduced precision: psi is
+            // the stored value plus the pending correction in the streaming and absorption
+            // terms, the stored one in the collision (the correction is isotropic).
             if (edge) {   // ghosts along x, outflow through the faces on the boundary
                 asm volatile("" : "+v"(at));   // (evaluated here, not kept in masks)
                 float ob = 0.f;
 #pragma unroll
                 for (int o = 0; o < O; ++o) {
-                    const int dx = (dir[o / 2] & 1) ? 1 : 2, dy = (dir[o / 2] & 4) ? 8 : 4;
+                    const int dx = (dir[o / G] & 1) ? 1 : 2, dy = (dir[o / G] & 4) ? 8 : 4;
+                    const float v = e.v[o] + dv;
                     if (at & (dx | 16)) ux[o] = 0.f;
-                    ob += (at & (3 - dx) ? cc[2 * o] * e.v[o] : 0.f) + (at & dy ? cc[2 * o + 1] * e.v[o] : 0.f);
+                    ob += (at & (3 - dx) ? cc[2 * o] * v : 0.f) + (at & dy ? cc[2 * o + 1] * v : 0.f);
                 }
                 outflow += band_weight(a.band, j) * (double)ob;
             }
 #pragma unroll
             for (int o = 0; o < O; ++o) {
                 float t = fmaf(cf.y, isov - e.v[o], cf.w);
-                t = fmaf(-cf.x, e.v[o], t);
-                t = fmaf(cc[2 * o + 1], uy[o] - e.v[o], t);
-                e.t[o] = fmaf(cc[2 * o], ux[o] - e.v[o], t);
+                const float v = LP ? e.v[o] + dv : e.v[o];
+                t = fmaf(-cf.x, v, t);
+                t = fmaf(cc[2 * o + 1], (LP ? uy[o] + yd : uy[o]) - v, t);
+                e.t[o] = fmaf(cc[2 * o], (LP ? ux[o] + xd : ux[o]) - v, t);
             }
             if (j + 1 < L) put((j + 1) & 1);   // this slot's readers passed the last barrier
         }
@@ -2266,17 +2331,28 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
             // (small terms) and added once per level
             const __amdgpu_buffer_rsrc_t r = level_rsrc(po);
             po += lvl_floats;
-            float sd = 0.f;
+            float sd = 0.f, ys = 0.f;
 #pragma unroll
             for (int o = 0; o < O; ++o) {
-                const float dy = acc[(PJ + N - RT) % N][o] - n.v[o];
-                const float nv = n.v[o] + fmaf(cf.z, dy, n.t[o]);
+                const float sum = acc[(PJ + N - RT) % N][o];
+                float dy, v = n.v[o];
+                if constexpr (LP) {   // Y^ - iso^ = 2^(e_b - E) sum + r_q dev, dev = psi^ - iso^
+                    const float dev = v - isov, ya = fmaf(rq, dev, ldexpf(sum, -sc));
+                    ys += ya;
+                    dy = ya - dev;
+                    v += dv;
+                } else {
+                    dy = sum - v;
+                }
+                const float nv = v + fmaf(cf.z, dy, n.t[o]);
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(nv), r, voff, s0 + (uint32_t)o * pb,
                                                       kCachePolicyNT);   // read next step, not from L2
                 phacc += w * (double)nv;
                 sd += dy;
+                if constexpr (LP) mx = fmaxf(mx, fabsf(nv));
             }
             defect += w * (double)(cf.z * sd);
+            if constexpr (LP) ypacc += w * (double)ys;
         }
         if (j + 1 < L) {
             py += lvl_floats;
@@ -2295,501 +2371,75 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
         pass(j + 1, std::integral_constant<int, 1>{});
         if (j + 2 >= L + RT) break;
         pass(j + 2, std::integral_constant<int, 2>{});
-        if (j + 3 >= L + RT) break;
-        pass(j + 3, std::integral_constant<int, 3>{});
-        if (j + 4 >= L + RT) break;
-        pass(j + 4, std::integral_constant<int, 4>{});
-        if constexpr (RT == 3) {
+        if constexpr (N > 3) {
+            if (j + 3 >= L + RT) break;
+            pass(j + 3, std::integral_constant<int, 3>{});
+            if (j + 4 >= L + RT) break;
+            pass(j + 4, std::integral_constant<int, 4>{});
+        }
+        if constexpr (N > 5) {
             if (j + 5 >= L + RT) break;
-            pass(j + 5, std::integral_constant<int, 5 % N>{});
+            pass(j + 5, std::integral_constant<int, 5>{});
             if (j + 6 >= L + RT) break;
-            pass(j + 6, std::integral_constant<int, 6 % N>{});
+            pass(j + 6, std::integral_constant<int, 6>{});
         }
     }
 
     // Phi^{n+1} of each cell: the waves' partials in a fixed order.  Wave 0 holds the block's
     // cells, so it takes over what finalize_kernel does for the other forms: Phi, Phi / W and
     // the mass partials.
+    // Reduced precision also sums Y and turns its particle defect into the new state's pending
+    // correction (the neighbours read the old one, so there are two buffers), and takes the
+    // block's maximum for the next operand scale.
     double* red = reinterpret_cast<double*>(slots);
+    double* redy = red + NW * kBandCells;
     red[wave * kBandCells + lane] = phacc;
+    if constexpr (LP) {
+        redy[wave * kBandCells + lane] = ypacc;
+        const unsigned m = wave_max_u32(__float_as_uint(mx));
+        if (lane == 0) reinterpret_cast<unsigned*>(redy + NW * kBandCells)[wave] = m;
+    }
     lds_barrier();
     if (wave == 0) {
         double fin[4] = {0.0, 0.0, 0.0, 0.0};
         if (in) {
             double phi = red[lane];
             for (int g = 1; g < NW; ++g) phi += red[g * kBandCells + lane];
+            // Phi of psi^n, in FP64; and of its stored values
+            const double old = gp(a.phi64)[cell], stored = LP ? old - a.W * (double)dv : old;
             // the physical scattering's part of the collision defect, sum_q w_q bs (iso -
-            // psi_q) = bs (W iso - Phi), once per cell (Phi of psi^n in FP64)
-            defect += (double)cf.y * (a.W * (double)isov - gp(a.phi64)[cell]);
+            // psi_q) = bs (W iso - Phi), once per cell
+            defect += (double)cf.y * (a.W * (double)isov - stored);
             gp(a.iso)[cell] = (float)(phi / a.W);
+            if constexpr (LP) {
+                double ys = redy[lane];
+                for (int g = 1; g < NW; ++g) ys += redy[g * kBandCells + lane];
+                ys += a.W * (double)(isov + dv);   // sum_q w_q Y, Y = iso^ + delta + (Y^ - iso^)
+                const float d = (float)(-(double)cf.z * (ys - old) / a.W);
+                gp(a.delta_next)[cell] = d;
+                fin[3] = a.W * (double)d;
+                phi += fin[3];
+            }
             gp(a.phi64)[cell] = phi;
             fin[0] = phi;
             fin[1] = (double)cf.x * phi;
             fin[2] = (double)cf.w;
         }
 #pragma unroll
-        for (int k = 0; k < 3; ++k) fin[k] = wave_sum(fin[k]);
-        if (lane == 0)
+        for (int k = 0; k < 4; ++k) fin[k] = wave_sum(fin[k]);
+        if (lane == 0) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) gp(a.fin_part)[4 * (size_t)local + k] = fin[k];
+            if constexpr (LP) {
+                const unsigned* m = reinterpret_cast<const unsigned*>(redy + NW * kBandCells);
+                unsigned t = m[0];
+                for (int g = 1; g < NW; ++g) t = max(t, m[g]);
+                gp(a.bmax_next)[local] = t;
+            }
+        }
     }
     double sums[2] = {defect, outflow};
     block_sum_n<16, 2>(sums, NW, gp(a.blk_part) + 2 * (size_t)local);
-}
-
-// ---------------------------------------------------------------------------
-// 6. Banded reduced-precision step (BF16 / FP16 operands, FP32 accumulate) on product
-//    sets of 32, 48 or 64 azimuths.  As in the fused reduced-precision form the state is
-//    stored without its pending per-cell particle correction delta (isotropic, so it
-//    drops out of the rounded deviation), and only the anisotropic part is rounded:
-//      x = T((psi^ - iso^) 2^(E - e_b))  (BF16: hi + lo),
-//      Y^ - iso^ = 2^(e_b - E) sum_j T(C_ij) x_j + r_q (psi^ - iso^),
-//    T(C_ij) the circulant block of level pair (i, j) of the stored K.  Block =
-//    kBandLpCells cells x every ordinate; wave (m-tile mt, n-tile nt) owns azimuths
-//    16 mt .. + 15 of cells 16 nt .. + 15, lane l the four azimuths 16 mt + 4 (l / 16) ..
-//    of cell 16 nt + l % 16, which is where MFMA 16x16x32 leaves them.  Per level pair
-//    and k-step of 32 azimuths one MFMA per operand term: A is the block's 16 x 32 slice
-//    at the wave's azimuth offset (host-built, staged in LDS a level ahead), B eight
-//    consecutive azimuths of one cell of the partner level from a ring of quantised
-//    levels ([8-azimuth chunk][cell], 16-byte reads).  The ring is filled from registers
-//    loaded a level before; the unrounded values of the lane's own cell wait in registers
-//    (reach + 1 levels) for the level's update, which runs one level behind the products
-//    and is interleaved with them; x neighbours come from the adjacent lanes (DPP) or, at
-//    the edges of a 16-cell tile, from a small ring the neighbouring waves (or the block's
-//    halo loads) fill at the same time.  Outputs as the fused form:
-//    psi^{n+1} without its correction, per cell Phi^ and sum_q w_q Y^, budget partials,
-//    block maxima of the next operand scale.
-// ---------------------------------------------------------------------------
-// (lanes at the row's edge get 0; the kernel takes their value from the edge ring)
-__device__ __forceinline__ float dpp_from_left(float v) {   // lane l gets lane l - 1 (row of 16)
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x111, 0xF, 0xF, true));
-}
-__device__ __forceinline__ float dpp_from_right(float v) {  // lane l gets lane l + 1 (row of 16)
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x101, 0xF, 0xF, true));
-}
-
-template <int A, int DT, int R>
-__global__ __launch_bounds__(band_lp_threads(A)) void banded_lp_kernel(BatchArgs B) {
-    constexpr int MT = A / 16, NT = kBandLpCells / 16, KS = band_lp_ksteps(A), TERMS = DT == 1 ? 2 : 1;
-    constexpr int NW = MT * NT, T = NW * 64;
-    constexpr int KC = 4 * KS;                // 16-byte chunks of 8 azimuths a cell holds
-    constexpr int NS = 2 * R + 2, NE = R + 3, NP = 2 * R + 1;
-    constexpr int XSLOT = band_lp_slot(A);    // elements per ring slot and term:
-                                              // [chunk][cell][8 azimuths]
-    constexpr int FR = NP * MT * 64;          // uint4 of A operands (NP pair slots)
-    constexpr int FRX = FR + A / 2;           // and the (cx, cy) table: uint4 per buffer
-    constexpr int FSL = (2 * kBandLpMaxReach + 1) * MT * 64;   // uint4 of a level's slots
-    constexpr int CPT = (FRX + T - 1) / T;    // uint4 staged per thread
-    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    uint16_t* xr = reinterpret_cast<uint16_t*>(lds_raw);
-    uint4* fr = reinterpret_cast<uint4*>(lds_raw + (size_t)NS * TERMS * XSLOT * 2);
-    float* edge = reinterpret_cast<float*>(lds_raw + (size_t)NS * TERMS * XSLOT * 2 + (size_t)2 * FRX * 16);
-    int pi, local;
-    if (!locate(B, KT_SC, xcd_remap(blockIdx.x, gridDim.x), pi, local)) return;
-    const StepArgs a = args_of(B, pi);   // by value: no reloads after stores
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int mt = wave % MT, nt = wave / MT;
-    const int g = lane >> 4, cl = lane & 15;
-    const int a0 = 16 * mt + 4 * g;      // the lane's first azimuth
-    const int cc = 16 * nt + cl;         // its cell within the block
-    const int nx = a.nx, ny = a.ny, L = a.n_lev, RE = a.reach;
-    const int C = (int)a.C;
-    const int64_t P = a.P;
-    const int cell = local * kBandLpCells + cc;
-    const bool in = cell < C;
-    const ASN_G QInfo* __restrict__ qtab = gp(a.qi);
-    const ASN_K QInfo* qk = kp(a.qi);
-    const ASN_K uint4* ldesc = kp(a.band);
-    const ASN_G uint4* __restrict__ frag = gp(a.bfrag);
-    const ASN_K float* rdk = kp(a.rdef);   // r_q, the same for every ordinate of a level
-
-    float4 cf = make_float4(0.f, 0.f, 0.f, 0.f);
-    float ihv = 0.f, dv = 0.f;   // iso^ = Phi^ / W and the pending correction of the cell
-    if (in) {
-        cf = gp(a.coef)[cell];
-        ihv = gp(a.iso)[cell];
-        dv = gp(a.delta)[cell];
-    }
-    float s_in, s_out;   // the cell's operand scale 2^(E - e_b) and its inverse
-    {
-        const float bm = in ? __uint_as_float(gp(a.bmax_cur)[cell >> a.sb_log]) : 0.f;
-        int e = 0;
-        if (bm > 0.f) (void)frexpf(bm, &e);
-        e = max(e, -100);
-        s_in = ldexpf(1.f, kScaleExp - e);
-        s_out = ldexpf(1.f, e - kScaleExp);
-    }
-    const float ivs = ihv * s_in;
-    const int y = cell / nx, x = cell - y * nx;
-    const int e = in ? ((x == 0 ? 1 : 0) | (x == nx - 1 ? 2 : 0) | (y == 0 ? 4 : 0) |
-                        (y == ny - 1 ? 8 : 0))
-                     : 0;
-    const bool wedge = __ballot(e != 0) != 0;
-    const uint32_t lvl_bytes = (uint32_t)(A * P * 4), pb = (uint32_t)(P * 4);
-    const uint32_t off0 = 4u * (uint32_t)(a0 * P) + 4u * (uint32_t)cell;
-    // the lane's four azimuths lie in one quadrant (n_az / 4 is a multiple of 4): one
-    // y-upwind cell; its offsets yoff + o pb (from kOOB they stay past every plane: a
-    // level holds under 2^31 bytes, and 3 pb more stays below 2^32)
-    uint32_t yoff;
-    float ydl;   // pending correction of the y-upwind cell
-    bool tl[4], tr[4], ox[4], oy[4];
-    {
-        const int d = qtab[a0].dir;
-        const int yc = (d & 4) ? cell - nx : cell + nx;
-        const bool yv = in && yc >= 0 && yc < C;
-        ydl = yv ? gp(a.delta)[yc] : 0.f;
-        yoff = yv ? off0 + 4u * (uint32_t)(yc - cell) : kOOB;
-    }
-#pragma unroll
-    for (int o = 0; o < 4; ++o) {
-        const int d = qtab[a0 + o].dir;
-        const bool gx = !in || (d & e & 3) != 0;
-        tl[o] = !gx && (d & 1);
-        tr[o] = !gx && !(d & 1);
-        const int go = (((d & 5) << 1) | ((d & 10) >> 1)) & e;   // outflow faces of d
-        ox[o] = in && (go & 3);
-        oy[o] = in && (go & 12);
-    }
-    // the block's halo cells, one value a lane: in tile 0 lanes 0 .. 3 of each row of 16
-    // read azimuth a0 + cl of the cell before the block, in the last tile lanes 12 .. 15
-    // azimuth a0 + cl - 12 of the cell after it (the other lanes' halo offsets read 0)
-    const bool hlo = nt == 0 && cl < 4, hhi = nt == NT - 1 && cl >= 12;
-    const int hcell = hlo ? local * kBandLpCells - 1 : local * kBandLpCells + kBandLpCells;
-    const int haz = a0 + (hlo ? cl : cl - 12);
-    const bool hvalid = (hlo || hhi) && hcell >= 0 && hcell < (int)P;
-    const float hdl = (hvalid && hcell < C) ? gp(a.delta)[hcell] : 0.f;
-    const uint32_t hoff = hvalid ? 4u * (uint32_t)(haz * P) + 4u * (uint32_t)hcell : kOOB;
-    const int hslot = hlo ? haz : (NT + NT - 1) * A + haz;   // its place in an edge slot
-    const size_t lvl_floats = (size_t)A * (size_t)P;
-    auto level_rsrc = [&](const float* base) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)lvl_bytes, kRsrcWord3);
-    };
-
-    struct Fill {
-        float v[4], h;
-    };
-    auto fetch = [&](int l, Fill& f) {
-        const __amdgpu_buffer_rsrc_t r = level_rsrc(a.psi + (size_t)l * lvl_floats);
-#pragma unroll
-        for (int o = 0; o < 4; ++o) f.v[o] = load_plane(r, off0 + (uint32_t)o * pb);
-        f.h = load_plane(r, hoff);
-    };
-    // the lane's four azimuths of level l into the ring (rounded operand terms) and the
-    // tile-edge values (true state psi^ + delta) its neighbours need
-    auto put = [&](int l, const Fill& f) {
-        uint16_t* xs = xr + (size_t)(l % NS) * TERMS * XSLOT + ((a0 >> 3) * kBandLpCells + cc) * 8 + (a0 & 7);
-        float xv[4];
-#pragma unroll
-        for (int o = 0; o < 4; ++o) xv[o] = __builtin_fmaf(f.v[o], s_in, -ivs);
-        uint2 pk;
-        pk.x = pack2<DT>(xv[0], xv[1]);
-        pk.y = pack2<DT>(xv[2], xv[3]);
-        *reinterpret_cast<uint2*>(xs) = pk;
-        if constexpr (DT == 1) {
-            uint2 pl;
-            pl.x = bf16_residual2(pk.x, xv[0], xv[1]);
-            pl.y = bf16_residual2(pk.y, xv[2], xv[3]);
-            *reinterpret_cast<uint2*>(xs + XSLOT) = pl;
-        }
-        float* es = edge + (size_t)(l % NE) * 2 * NT * A;
-        if (cl == 15 && nt < NT - 1) {   // the left neighbour of the next tile
-            float* d = es + (nt + 1) * A + a0;
-#pragma unroll
-            for (int o = 0; o < 4; ++o) d[o] = f.v[o] + dv;
-        }
-        if (cl == 0 && nt > 0) {         // the right neighbour of the previous tile
-            float* d = es + (NT + nt - 1) * A + a0;
-#pragma unroll
-            for (int o = 0; o < 4; ++o) d[o] = f.v[o] + dv;
-        }
-        if (hlo || hhi) es[hslot] = f.h + hdl;   // the block's halo
-    };
-    // block l of the operand table into buffer l & 1 (thread t moves uint4 t and t + T):
-    // level l's A operands (2 kBandLpMaxReach + 1 pair slots, the coupled pairs first; the
-    // kernel runs the first NP, those past a problem's pairs hold zero operands), then the
-    // (cx, cy) of level l - 1's ordinates, read by the update that runs one level behind.
-    // Block n_lev holds the last level's (cx, cy).
-    static_assert(CPT <= 2, "at most two staged uint4 per thread");
-    auto src_of = [&](int x) { return x < FR ? x : FSL + (x - FR); };
-    auto fetch_frag = [&](int l, uint4& f0, uint4& f1) {
-        const ASN_G uint4* src = frag + ldesc[2 * l].y;
-        f0 = src[src_of(FRX >= T ? tid : min(tid, FRX - 1))];
-        if constexpr (CPT > 1) f1 = src[src_of(min(tid + T, FRX - 1))];
-    };
-    auto put_frag = [&](int l, const uint4& f0, const uint4& f1) {
-        uint4* dst = fr + (size_t)(l & 1) * FRX;
-        if (FRX >= T || tid < FRX) dst[tid] = f0;
-        if constexpr (CPT > 1) if (tid + T < FRX) dst[tid + T] = f1;
-    };
-    // the next update's inputs: the lane's own four values (from the register queue), the
-    // y-upwind values and the level's r_q and weight (its (cx, cy) come from LDS)
-    struct Ahead {
-        float v[4], y[4];
-        float rq;
-        double w;
-    };
-    auto fetch_ahead = [&](int l, Ahead& ah) {
-        const __amdgpu_buffer_rsrc_t r = level_rsrc(a.psi + (size_t)l * lvl_floats);
-        const int q0 = l * A;
-#pragma unroll
-        for (int o = 0; o < 4; ++o) {
-            ah.y[o] = load_plane(r, yoff + (uint32_t)o * pb);
-        }
-        ah.rq = rdk[q0];
-        ah.w = qk[q0].w;
-    };
-
-    // n_az not a multiple of 32: the last k-step reads azimuths past n_az, which the ring
-    // holds at zero (the A operands' wrapped values there multiply zeros)
-    if constexpr (A % 32 != 0) {
-        uint4* z = reinterpret_cast<uint4*>(xr);
-        constexpr int NZ = NS * TERMS * XSLOT * 2 / 16;
-        for (int t = tid; t < NZ; t += T) z[t] = make_uint4(0u, 0u, 0u, 0u);
-        lds_barrier();
-    }
-    // The level loop runs one level behind in its update: pass i contracts level i and
-    // updates level i - 1 with the products of the pass before, two independent streams
-    // (LDS reads and MFMA; VALU, DPP and stores) interleaved in one schedule.  The edge
-    // ring is reach + 3 levels deep: a level's edges stay until its lagging update has
-    // read them.
-    // the lane's own unrounded values of the levels in the ring ahead of the update
-    // (levels i + 1 .. i + R + 1 at the end of pass i)
-    float fifo[R + 1][4];
-    {   // prologue: levels 0 .. R into the ring and the queue, level 0's operands
-        Fill f;
-#pragma unroll
-        for (int l = 0; l <= R; ++l) {
-            fetch(min(l, L - 1), f);
-            if (l < L) put(l, f);
-#pragma unroll
-            for (int o = 0; o < 4; ++o) fifo[l][o] = f.v[o];
-        }
-        uint4 g0, g1;
-        fetch_frag(0, g0, g1);
-        put_frag(0, g0, g1);
-    }
-    Fill pre;
-    fetch(min(R + 1, L - 1), pre);
-    uint4 fp0, fp1;
-    fetch_frag(1, fp0, fp1);
-    Ahead ah;
-    lds_barrier();
-
-    double phacc = 0.0, ypacc = 0.0, defect = 0.0, outflow = 0.0;
-    float mx = 0.f;
-    const int mtk0 = ((0 - mt) % MT + MT) % MT;   // fragment of k-step 0: offset (32 kt - 16 mt) mod A
-    // B operand of k-step kt: chunk g + 4 kt of the lane's cell (16 lanes of a row read
-    // 256 contiguous bytes)
-    const uint16_t* xl = xr + (g * kBandLpCells + cc) * 8;
-    static_assert(KC * kBandLpCells * 8 == XSLOT, "ring slot layout");
-    static_assert(A * 256 <= NS * TERMS * XSLOT * 2, "the final partials fit in the ring");
-    // level i's products: every pair slot, k-steps of 32 azimuths, operand terms
-    struct Ops {
-        uint4 a[KS], b[KS];
-        const uint16_t* xs;
-    };
-    struct Pass {
-        uint32_t kcodes;
-        int sb;
-        const uint4* fl;
-    };
-    auto pass_of = [&](int i) {
-        Pass ps;
-        ps.kcodes = ldesc[2 * i].z;
-        ps.fl = fr + (size_t)(i & 1) * FRX + lane;
-        // ring slot of level i - RE (k = 0); a pair's partner i - RE + k sits k slots on
-        ps.sb = ((i - RE) % NS + NS) % NS;
-        return ps;
-    };
-    // a pair's A operands and its first operand term; the second term (BF16) is read
-    // into the same registers after the first term's products
-    auto load_pair = [&](const Pass& ps, int p, Ops& op) {
-        int sl = ps.sb + (int)((ps.kcodes >> (4 * p)) & 15u);
-        sl = sl >= NS ? sl - NS : sl;
-        op.xs = xl + (size_t)sl * TERMS * XSLOT;
-#pragma unroll
-        for (int kt = 0; kt < KS; ++kt) op.a[kt] = ps.fl[(p * MT + (mtk0 + 2 * kt) % MT) * 64];
-#pragma unroll
-        for (int kt = 0; kt < KS; ++kt)
-            op.b[kt] = *reinterpret_cast<const uint4*>(op.xs + 4 * kBandLpCells * 8 * kt);
-    };
-    auto load_term = [&](int t, Ops& op) {
-#pragma unroll
-        for (int kt = 0; kt < KS; ++kt)
-            op.b[kt] = *reinterpret_cast<const uint4*>(op.xs + t * XSLOT + 4 * kBandLpCells * 8 * kt);
-    };
-    auto mul_term = [&](const Ops& op, f32x4& acc) {
-#pragma unroll
-        for (int kt = 0; kt < KS; ++kt) acc = mfma_lp<DT>(op.a[kt], op.b[kt], acc);
-    };
-    auto mul_pair = [&](Ops& op, f32x4& acc) {   // (no overlap with other work)
-        mul_term(op, acc);
-#pragma unroll
-        for (int t = 1; t < TERMS; ++t) {
-            load_term(t, op);
-            mul_term(op, acc);
-        }
-    };
-    // the update of the lane's four outputs of level j (as the fused reduced-precision form):
-    //   v = psi^ + delta, dev = psi^ - iso^, Y^ - iso^ = s_out acc + r_q dev
-    //   col = gs ((iso^ + Y^ - iso^) - psi^) + bs (iso^ - psi^)
-    //   new = v - cx (v - ux) - cy (v - uy) - aa v + col + ss
-    // (the look-ahead values hold level j)
-    struct Upd {
-        __amdgpu_buffer_rsrc_t ro;
-        const float* es;   // the level's edge slot at the lane's tile and azimuths
-        const float2* cxy;   // the level's (cx, cy) at the lane's azimuths
-        float colsum, yas;
-        double ph;
-    };
-    auto upd_begin = [&](int j, Upd& u) {
-        u.es = edge + (size_t)(j % NE) * 2 * NT * A + nt * A + a0;
-        u.cxy = reinterpret_cast<const float2*>(fr + (size_t)((j + 1) & 1) * FRX + FR) + a0;
-        u.ro = level_rsrc(a.psi_new + (size_t)j * lvl_floats);
-        u.colsum = 0.f;
-        u.yas = 0.f;
-        u.ph = 0.0;
-    };
-    auto upd_out = [&](int o, const f32x4& acc, Upd& u) {
-        const float vh = ah.v[o];
-        const float v = vh + dv;
-        // the row shifts run in every lane (a lane whose neighbour is inactive would read
-        // 0), then the row's edge lanes (0 and 15) take the edge ring's value
-        const float dl = dpp_from_left(v), dr = dpp_from_right(v);
-        const float left = cl == 0 ? u.es[o] : dl;
-        const float right = cl == 15 ? u.es[NT * A + o] : dr;
-        const float ux = tl[o] ? left : (tr[o] ? right : 0.f);
-        const float uy = ah.y[o] + ydl;
-        const float dev = vh - ihv;
-        const float ya = s_out * acc[o] + ah.rq * dev;
-        const float col = cf.z * ((ihv + ya) - vh) + cf.y * (ihv - vh);
-        // a padding cell (not in) has psi^ = delta = iso^ = 0, zero coefficients, zero
-        // operands and ghosts: its update is 0 without a select
-        const float2 c = u.cxy[o];
-        const float nv = v - c.x * (v - ux) - c.y * (v - uy) - cf.x * v + col + cf.w;
-        // a wave writes half of each 128-byte line, a sibling wave the other half: the L2
-        // joins them (non-temporal stores wrote 1.4x the bytes)
-        store_plane(nv, u.ro, off0 + (uint32_t)o * pb);
-        u.ph += (double)nv;
-        u.yas += ya;
-        u.colsum += col;
-        mx = fmaxf(mx, fabsf(nv));
-    };
-    auto upd_end = [&](const Upd& u) {
-        phacc += ah.w * u.ph;
-        // sum over the four outputs of Y^ = iso^ + delta + (Y^ - iso^); the deviations,
-        // small against iso^, summed in FP32
-        ypacc += ah.w * ((in ? 4.0 * (double)(ihv + dv) : 0.0) + (double)u.yas);
-        defect += ah.w * (double)u.colsum;
-    };
-    // the outflow of the level just updated (the look-ahead values still hold it)
-    auto outflow_of = [&](const Upd& u) {
-        if (wedge) {
-            float ob = 0.f;
-#pragma unroll
-            for (int o = 0; o < 4; ++o) {
-                const float v = ah.v[o] + dv;
-                const float2 c = u.cxy[o];
-                ob += (ox[o] ? c.x * v : 0.f) + (oy[o] ? c.y * v : 0.f);
-            }
-            outflow += ah.w * (double)ob;
-        }
-    };
-    // the end of pass i: level i + R + 1 goes into the ring slot level i - R - 1 held and
-    // the queue, level i leaves the queue for the next pass's update, loads for the next
-    // passes
-    auto advance = [&](int i) {
-        if (i + R + 1 < L) put(i + R + 1, pre);
-        fetch_ahead(i, ah);
-#pragma unroll
-        for (int o = 0; o < 4; ++o) ah.v[o] = fifo[0][o];
-#pragma unroll
-        for (int q = 0; q < R; ++q)
-#pragma unroll
-            for (int o = 0; o < 4; ++o) fifo[q][o] = fifo[q + 1][o];
-#pragma unroll
-        for (int o = 0; o < 4; ++o) fifo[R][o] = pre.v[o];
-        fetch(min(i + R + 2, L - 1), pre);
-        lds_barrier();
-    };
-
-    f32x4 accp = {0.f, 0.f, 0.f, 0.f};
-    {   // pass 0: products only
-        put_frag(1, fp0, fp1);
-        fetch_frag(min(2, L), fp0, fp1);
-        const Pass ps = pass_of(0);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            Ops op;
-            load_pair(ps, p, op);
-            mul_pair(op, accp);
-        }
-        advance(0);
-    }
-    for (int i = 1; i < L; ++i) {
-        // block i + 1 of the operand table (its buffer's last readers passed the barrier)
-        put_frag(i + 1, fp0, fp1);
-        fetch_frag(min(i + 2, L), fp0, fp1);
-        // pass i in chunks the scheduler may not merge: chunk p reads pair p's operands,
-        // updates output p of level i - 1 while they arrive, then multiplies pair p (the
-        // MFMAs run on while the next chunk issues)
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        const Pass ps = pass_of(i);
-        Upd u;
-        upd_begin(i - 1, u);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            __builtin_amdgcn_sched_barrier(0);
-            Ops op;
-            load_pair(ps, p, op);
-            if (p < 4) upd_out(p, accp, u);
-            mul_term(op, acc);
-#pragma unroll
-            for (int t = 1; t < TERMS; ++t) {
-                load_term(t, op);
-                mul_term(op, acc);
-            }
-        }
-#pragma unroll
-        for (int o = NP; o < 4; ++o) upd_out(o, accp, u);
-        __builtin_amdgcn_sched_barrier(0);
-        upd_end(u);
-        accp = acc;
-        outflow_of(u);
-        advance(i);
-    }
-    {
-        Upd u;
-        upd_begin(L - 1, u);
-#pragma unroll
-        for (int o = 0; o < 4; ++o) upd_out(o, accp, u);
-        upd_end(u);
-        outflow_of(u);
-    }
-
-    // per cell Phi^ and sum_q w_q Y^: the (n_az / 4) lane groups' partials in a fixed order
-    double* red = reinterpret_cast<double*>(lds_raw);
-    red[(4 * mt + g) * kBandLpCells + cc] = phacc;
-    red[(A / 4 + 4 * mt + g) * kBandLpCells + cc] = ypacc;
-    lds_barrier();
-    if (tid < kBandLpCells) {
-        const int c = local * kBandLpCells + tid;
-        if (c < C) {
-            double s = red[tid], sy = red[(A / 4) * kBandLpCells + tid];
-#pragma unroll
-            for (int k = 1; k < A / 4; ++k) {
-                s += red[k * kBandLpCells + tid];
-                sy += red[(A / 4 + k) * kBandLpCells + tid];
-            }
-            gp(a.phi_part)[c] = s;
-            gp(a.ypart)[c] = sy;
-        }
-    }
-    // block max |psi^{n+1}| of the next operand scale: the block's cells lie in one block
-    const unsigned mbits = wave_max_u32(__float_as_uint(mx));
-    if (lane == 0 && mbits) atomicMax(&a.bmax_next[(local * kBandLpCells) >> a.sb_log], mbits);
-    double sums[2] = {defect, outflow};
-    block_sum_waves<NW, 2>(sums, gp(a.blk_part) + 2 * (size_t)local);
 }
 
 // ---------------------------------------------------------------------------
@@ -2805,74 +2455,42 @@ void blocks_per_kind(const StepArgs& a, int out[KT_COUNT]) {
     out[KT_FIN] = a.fin_blocks;
 }
 
-// The instance for reach 2 also serves smaller reaches (zero coefficients), the one for
-// reach 3 any.
 // One launch per step: each block finishes its cells' moments, and the fold of a step's budget
 // partials, which nothing in the next step waits for, runs in n more blocks of that step's
 // launch (the partials alternate with the state buffers; the call's last fold is a launch of
 // its own, launch_last_budget).  With finalize_kernel and budget_kernel after every step
 // 24 steps of 50^2 x 128, set-up and results included, took 726 us instead of 516, 40 steps of
 // 311 x 173 x 288 3.13 ms instead of 2.76, a step of 400^2 x 512 187 us instead of 175.
-static hipError_t launch_banded(const BatchArgs& b, int blocks, int az, size_t lds, hipStream_t s,
-                                int reach) {
-    if (!band_azimuths_supported(az) || reach < 0 || reach > kBandMaxReach) return hipErrorInvalidValue;
-    const int threads = az / kBandO * 64;
-    blocks += b.n;   // and the last step's budget
-    if (reach <= 2) banded_euler_kernel<2, 1024><<<blocks, threads, lds, s>>>(b);
-    else if (threads <= 512) banded_euler_kernel<3, 512><<<blocks, threads, lds, s>>>(b);
-    else banded_euler_kernel<3, 1024><<<blocks, threads, lds, s>>>(b);
-    return hipSuccess;
+template <typename F>
+static hipError_t with_banded(int az, int dtype, int reach, F&& f) {
+    const bool small = az <= 32;   // at most 512 threads
+    if (reach < 0 || reach > kBandMaxReach || !band_supported(az, dtype, reach)) return hipErrorInvalidValue;
+    // FP32: the instance for reach 2 also serves smaller reaches (zero coefficients)
+    if (dtype == 0) {
+        if (reach <= 2) return f(banded_euler_kernel<2, 1024, 0>);
+        return small ? f(banded_euler_kernel<3, 512, 0>) : f(banded_euler_kernel<3, 1024, 0>);
+    }
+    if (dtype == 1) {
+        if (reach <= 1) return f(banded_euler_kernel<1, 1024, 1>);
+        return reach == 2 ? f(banded_euler_kernel<2, 1024, 1>) : f(banded_euler_kernel<3, 512, 1>);
+    }
+    if (reach <= 1) return f(banded_euler_kernel<1, 1024, 2>);
+    if (reach == 2) return f(banded_euler_kernel<2, 1024, 2>);
+    return small ? f(banded_euler_kernel<3, 512, 2>) : f(banded_euler_kernel<3, 1024, 2>);
 }
 
-template <int A, int DT, int R>
-static void launch_banded_lp_r(const BatchArgs& b, int blocks, size_t lds, hipStream_t s) {
-    banded_lp_kernel<A, DT, R><<<blocks, band_lp_threads(A), lds, s>>>(b);
+static hipError_t launch_banded(const BatchArgs& b, int blocks, int az, int dtype, size_t lds, hipStream_t s,
+                                int reach) {
+    return with_banded(az, dtype, reach, [&](auto kernel) {
+        kernel<<<blocks + b.n, az / kBandO * 64, lds, s>>>(b);
+        return hipSuccess;
+    });
 }
-template <int A, int DT>
-static hipError_t launch_banded_lp_a(const BatchArgs& b, int blocks, size_t lds, hipStream_t s,
-                                     int reach) {
-    switch (reach) {
-        case 0: launch_banded_lp_r<A, DT, 0>(b, blocks, lds, s); break;
-        case 1: launch_banded_lp_r<A, DT, 1>(b, blocks, lds, s); break;
-        case 2: launch_banded_lp_r<A, DT, 2>(b, blocks, lds, s); break;
-        case 3: launch_banded_lp_r<A, DT, 3>(b, blocks, lds, s); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipSuccess;
-}
-static hipError_t launch_banded_lp(const BatchArgs& b, int blocks, int az, int dtype, size_t lds,
-                                   hipStream_t s, int reach) {
-    if (az == 32 && dtype == 1) return launch_banded_lp_a<32, 1>(b, blocks, lds, s, reach);
-    if (az == 32 && dtype == 2) return launch_banded_lp_a<32, 2>(b, blocks, lds, s, reach);
-    if (az == 48 && dtype == 1) return launch_banded_lp_a<48, 1>(b, blocks, lds, s, reach);
-    if (az == 48 && dtype == 2) return launch_banded_lp_a<48, 2>(b, blocks, lds, s, reach);
-    if (az == 64 && dtype == 1) return launch_banded_lp_a<64, 1>(b, blocks, lds, s, reach);
-    if (az == 64 && dtype == 2) return launch_banded_lp_a<64, 2>(b, blocks, lds, s, reach);
-    return hipErrorInvalidValue;
-}
-template <int A, int DT, int R>
-static hipError_t prepare_banded_lp_r(size_t lds) {
-    return hipFuncSetAttribute((const void*)banded_lp_kernel<A, DT, R>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-template <int A, int DT>
-static hipError_t prepare_banded_lp_a(int reach, size_t lds) {
-    switch (reach) {
-        case 0: return prepare_banded_lp_r<A, DT, 0>(lds);
-        case 1: return prepare_banded_lp_r<A, DT, 1>(lds);
-        case 2: return prepare_banded_lp_r<A, DT, 2>(lds);
-        case 3: return prepare_banded_lp_r<A, DT, 3>(lds);
-        default: return hipErrorInvalidValue;
-    }
-}
-hipError_t prepare_banded_lp(int band_az, int dtype, int reach, size_t band_lds) {
-    if (band_az == 32 && dtype == 1) return prepare_banded_lp_a<32, 1>(reach, band_lds);
-    if (band_az == 32 && dtype == 2) return prepare_banded_lp_a<32, 2>(reach, band_lds);
-    if (band_az == 48 && dtype == 1) return prepare_banded_lp_a<48, 1>(reach, band_lds);
-    if (band_az == 48 && dtype == 2) return prepare_banded_lp_a<48, 2>(reach, band_lds);
-    if (band_az == 64 && dtype == 1) return prepare_banded_lp_a<64, 1>(reach, band_lds);
-    if (band_az == 64 && dtype == 2) return prepare_banded_lp_a<64, 2>(reach, band_lds);
-    return hipErrorInvalidValue;
+
+hipError_t prepare_banded(int az, int dtype, int reach, size_t lds) {
+    return with_banded(az, dtype, reach, [&](auto kernel) {
+        return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    });
 }
 
 // Stencil kinds of a pass: 0 donor-cell strips, 1 / 2 Heun stages (strips), 3 donor-cell
@@ -2890,14 +2508,8 @@ static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, in
     };
     if (stencil == kStencilBanded) {   // contraction and stencil in one kernel
         mark(0);
-        e = dtype == 0 ? launch_banded(b, grid[KT_SC], band_az, band_lds, s, band_reach)
-                       : launch_banded_lp(b, grid[KT_SC], band_az, dtype, band_lds, s, band_reach);
-        mark(1);
-        mark(2);
-        if (e == hipSuccess && dtype != 0) finalize_kernel<<<grid[KT_FIN], 256, 0, s>>>(b, 0);
-        mark(3);
-        if (e == hipSuccess && dtype != 0) budget_kernel<<<b.n, kBudgetThreads, 0, s>>>(b, BUD_STEP);
-        mark(4);
+        e = launch_banded(b, grid[KT_SC], band_az, dtype, band_lds, s, band_reach);
+        for (int k = 1; k < 5; ++k) mark(k);
         if (e != hipSuccess) return e;
         return hipGetLastError();
     }
@@ -2963,8 +2575,8 @@ hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int schem
     return launch_pass(b1, grid, dtype, st + 1, BUD_STAGE2, s, ev ? ev + 5 : nullptr);
 }
 
-hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int dtype, int scheme, hipStream_t s) {
-    if (scheme != SCHEME_EULER_BANDED || dtype != 0 || n_steps < 1) return hipSuccess;
+hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int scheme, hipStream_t s) {
+    if (scheme != SCHEME_EULER_BANDED || n_steps < 1) return hipSuccess;
     BatchArgs l = b;
     l.step = n_steps;
     l.s_par = (n_steps - 1) & 1;
@@ -2987,7 +2599,7 @@ hipError_t launch_arm(int* limit, int* base, int n, const ArmArgs& v, hipStream_
 }
 
 hipError_t launch_init(const StepArgs& a, const BatchArgs& one, hipStream_t s) {
-    const int64_t nb = scale_blocks(a.P, a.sb_log);
+    const int64_t nb = scale_blocks(a.P, a.band ? 6 : a.sb_log);
     fill_u32_kernel<<<div_up(nb, 256), 256, 0, s>>>(a.bmax_cur, nb, 0u);
     fill_u32_kernel<<<div_up(nb, 256), 256, 0, s>>>(a.bmax_next, nb, 0u);
     moments_kernel<<<div_up(a.C, 256), 256, 0, s>>>(a);

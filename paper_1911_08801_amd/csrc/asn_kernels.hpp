@@ -55,12 +55,13 @@ constexpr int SCHEME_HEUN_FLAT = 4;
 constexpr int kFlatResident = 512;
 constexpr int kFlatMaxNxM = (kFlatRounds * kFlatCells - kFlatCells - 8) / 3;
 
-// Banded forward-Euler step (product ordinate sets, FP32): one kernel per step does
-// the contraction, the stream + collide update, the moments and the budget partials.
+// Banded forward-Euler step (product ordinate sets): one kernel per step does the
+// contraction, the stream + collide update, the moments and the budget partials.
 // A block owns kBandCells consecutive cells (flat index) and every ordinate and walks
 // the polar levels in order; a wave owns kBandO consecutive azimuths of every level, a
 // lane one cell, so a block has n_az / kBandO waves.  LDS holds two levels: n_az rows of
-// kBandRow floats (the cells, with the neighbour on either side at the ends).
+// kBandRow floats (the cells, with the neighbour on either side at the ends), for BF16 /
+// FP16 operands followed by as many rows of the rounded operands.
 constexpr int SCHEME_EULER_BANDED = 5;
 constexpr int kBandCells = 64;
 constexpr int kBandO = 4;
@@ -68,39 +69,16 @@ constexpr int kBandRow = kBandCells + 2;
 constexpr int kBandMaxReach = 3;
 // Largest half-width of the pair codes marked narrow by band_form (asn_host.hpp).
 constexpr int kBandNarrow = 8;
-// Azimuth counts the kernel takes.
-inline bool band_azimuths_supported(int az) { return az >= 8 && az <= 64 && az % 8 == 0; }
-// Dynamic LDS of a banded block (the final sums reuse them).
-inline size_t band_lds_bytes(int az) { return (size_t)2 * az * kBandRow * 4; }
-
-// Banded reduced-precision step (BF16 / FP16 operands on MFMA 16x16x32, FP32 accumulate)
-// for product sets of 32, 48 or 64 azimuths: a block owns kBandLpCells consecutive cells and
-// every ordinate; wave (m, n) produces azimuths 16 m .. 16 m + 15 of cells 16 n .. 16 n + 15.
-// Per level pair (i, j) the circulant block of the stored K is multiplied as A operands
-// of 16 x 32 (one per 16-azimuth offset, built on the host: band_lp_fragments) with the
-// quantised partner level as B operand.
-constexpr int kBandLpCells = 64;
-constexpr int kBandLpMaxReach = 3;
-inline bool band_lp_azimuths_supported(int az) { return az == 32 || az == 48 || az == 64; }
-// k-steps of 32 azimuths a level pair takes (48 azimuths: two, the second half-padded)
-__host__ __device__ constexpr int band_lp_ksteps(int az) { return (az + 31) / 32; }
-__host__ __device__ constexpr int band_lp_threads(int az) { return (az / 16) * (kBandLpCells / 16) * 64; }
-// 16-bit elements of a slot of the quantised-level ring (one level, one operand term): the
-// 8-azimuth chunks of every k-step (the padding past n_az held at zero), each chunk the
-// block's cells in a row ([chunk][cell][8]: 16 lanes reading one chunk of 16 cells read
-// 256 contiguous bytes)
-__host__ __device__ constexpr int band_lp_slot(int az) { return 4 * band_lp_ksteps(az) * kBandLpCells * 8; }
-// Dynamic LDS of a banded reduced-precision block: the ring of 2 reach + 2 quantised
-// levels (two operand terms for BF16), two buffers of a level's A operands (at most
-// 2 reach + 1 pairs, n_az / 16 fragments of 1 KiB each, and the previous level's
-// (cx, cy)), the ring of tile-edge values (reach + 3 levels).
-inline size_t band_lp_lds_bytes(int az, int reach, int dtype) {
-    const int terms = dtype == 1 ? 2 : 1, mt = az / 16, nt = kBandLpCells / 16;
-    return (size_t)(2 * reach + 2) * terms * band_lp_slot(az) * 2 +
-           (size_t)2 * ((2 * reach + 1) * mt * 1024 + az * 8) + (size_t)(reach + 3) * 2 * nt * az * 4;
+// Azimuth counts the step takes: FP32 8 .. 64 in steps of 8, BF16 / FP16 32, 48 or 64; BF16
+// at 48 or 64 azimuths couples levels at most 2 apart.
+inline bool band_azimuths_supported(int az, int dtype) {
+    return dtype == 0 ? az >= 8 && az <= 64 && az % 8 == 0 : az == 32 || az == 48 || az == 64;
 }
-// Largest dynamic LDS a block may take.
-constexpr size_t kMaxBlockLds = 160 * 1024 - 1024;
+inline bool band_supported(int az, int dtype, int reach) {
+    return band_azimuths_supported(az, dtype) && reach <= (dtype == 1 && az > 32 ? 2 : kBandMaxReach);
+}
+// Dynamic LDS of a banded block (the final sums reuse it).
+inline size_t band_lds_bytes(int az, int dtype) { return (size_t)(dtype == 0 ? 2 : 4) * az * kBandRow * 4; }
 
 // Modes of the budget kernel.
 enum { BUD_STEP = 0, BUD_INIT = 1, BUD_STAGE1 = 2, BUD_STAGE2 = 3, BUD_BANDED = 4 };
@@ -164,29 +142,28 @@ struct StepArgs {
     double* phi64;          // Phi (FP64)
     double* phi_part;       // [G][P]
     double* blk_part;       // stencil block partials [G * tiles][2]
-    double* fin_part;       // finalize block partials [fin_blocks][4] (banded FP32: [tiles][4], and
-                            // both kinds once per state buffer)
+    double* fin_part;       // finalize block partials [fin_blocks][4] (banded: [tiles][4], and both
+                            // kinds once per state buffer)
     double* ypart;          // [Qp / kGemmBM][P] weighted row sums of Y (reduced precision)
     float* fix;             // [P] per-cell particle correction of the reduced-precision Y
     float* delta;           // [P] fused reduced precision: pending isotropic correction of the
                             // stored state (true state = psi + delta); iso then holds Phi^ / W
                             // of the stored state and phi64 the true Phi
-    unsigned* bmax_cur;     // block max |psi^n| (read by the GEMM), follows the psi buffer
+    float* delta_next;      // [P] banded: that of the new state (delta follows the psi buffer)
+    unsigned* bmax_cur;     // block max |psi^n| (read by the GEMM), follows the psi buffer; per
+                            // scale block, banded: per 64 cells
     unsigned* bmax_next;    // block max |psi^{n+1}| (written by the stencil)
     double* rec;
     // banded step (product ordinate sets): n_lev levels of n_az azimuths, coupling
     // levels up to `reach` apart; per level a descriptor (band, two uint4) and its coefficients for
-    // the kernel's instances of reach 2 and 3 (bcoef5, bcoef7) as built by
+    // the kernel's instances of reach 1, 2 and 3 (bcoef3, bcoef5, bcoef7) as built by
     // band_scatter_tables (asn_host.hpp), and per ordinate (cx, cy) (bcxy)
     const uint4* band;
+    const float* bcoef3;
     const float* bcoef5;
     const float* bcoef7;
     const float2* bcxy;
     int n_lev, n_az, reach;
-    // banded reduced-precision step: per level pair and 16-azimuth offset the A operand
-    // of MFMA 16x16x32 as 64 lanes x 8 16-bit values (band_lp_fragments); band then holds
-    // per level {pairs, first fragment, level offsets k of the pairs (4 bits each), 0}
-    const uint4* bfrag;
 };
 
 // Kernel kinds of one step, each with its own block decomposition.
@@ -226,17 +203,16 @@ inline bool can_fuse(int dtype, int scheme) { (void)dtype; return scheme == SCHE
 hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int scheme, hipStream_t s,
                        hipEvent_t* ev = nullptr, int band_az = 0, size_t band_lds = 0,
                        int band_reach = 0);
-// Raise the dynamic LDS limit of the banded reduced-precision kernel of an azimuth count,
-// operand type
+// Raise the dynamic LDS limit of the banded kernel that serves an azimuth count, operand type
 // and reach.
-hipError_t prepare_banded_lp(int band_az, int dtype, int reach, size_t band_lds);
+hipError_t prepare_banded(int band_az, int dtype, int reach, size_t band_lds);
 // Passes per step of a scheme.
 inline int passes_per_step(int scheme) {
     return scheme == SCHEME_HEUN || scheme == SCHEME_HEUN_FLAT ? 2 : 1;
 }
 // After the last of a call's n_steps steps: what the next step's launch would do for it (the
 // banded step's budget).
-hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int dtype, int scheme, hipStream_t s);
+hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int scheme, hipStream_t s);
 // Arm a batch: limit[i] and base[i] = cur[i], i < n <= kMaxArm.
 constexpr int kMaxArm = 64;
 struct ArmArgs {

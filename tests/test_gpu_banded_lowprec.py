@@ -53,6 +53,19 @@ def test_one_step_matches_emulation(dtype, nx, ny, n_polar, n_azim, beta):
     assert np.max(np.abs(phi - phi_f)) <= 1e-6 * np.abs(phi_f).max()
 
 
+@pytest.mark.parametrize("nx,ny", [(63, 2), (64, 3), (65, 4)])
+@pytest.mark.parametrize("dtype,n_polar,n_azim,beta", [("f16", 12, 48, 45.0), ("f16", 16, 64, 45.0),
+                                                       ("bf16", 32, 64, 4.5), ("f16", 32, 64, 4.5)])
+def test_one_step_around_one_block(nx, ny, dtype, n_polar, n_azim, beta):
+    # around one 64-cell block: the FP16 instance for reach 3 with more than 8 waves, and the
+    # set of the largest configured workload
+    spec = wl.random_problem(nx + ny + n_azim, nx, ny, n_polar=n_polar, n_azim=n_azim, beta=beta)
+    psi0 = wl.random_state(nx + n_polar, spec.q, ny, nx)
+    state, _, _, _ = gpu_run(asn, spec, 1, psi0=psi0, dtype=dtype, form="banded")
+    ref, _ = _emulated(spec, 1, psi0, dtype)
+    assert np.max(np.abs(state - ref)) <= 2e-6 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("n_polar,n_azim", [(8, 32), (4, 64)])
 def test_multi_step_budget_and_exact_oracle(dtype, n_polar, n_azim):
