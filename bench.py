@@ -229,7 +229,9 @@ def roofline(res, spec, dtype):
     ach = bytes_ / t / 1e9
     nz = res["work"]["nonzero_flops"]
     executed = res["work"]["tile_flops"]
-    compute_peak = (PEAK_FP32_VALU_TFLOPS if res["form"] == "banded" else
+    # (BF16 / FP16: the peak the operand type offers; the banded step's few products run on the
+    # vector units)
+    compute_peak = (PEAK_FP32_VALU_TFLOPS if res["form"] == "banded" and dtype == "f32" else
                     PEAK_FP32_MFMA_TFLOPS if dtype == "f32" else PEAK_LP_MFMA_TFLOPS)
     traffic = measured_traffic(name, spec)
     return {"bound": "hbm", "kernel": name, "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
