@@ -71,6 +71,20 @@ int scale_block_log(int32_t n) {
     return l;
 }
 
+// Pitch of an ordinate's plane in cells: the cells rounded up to a scale block of 256 (1 KiB).
+// The banded step streams n_azim planes at once, and at a pitch of a multiple of 16 KiB (of 64
+// KiB above all) their cells meet in fewer memory channels, so there the pitch is 6 KiB more:
+// kernel at 256^2 x 2048 339 -> 314 us, 512^2 x 1152 777 -> 743, 640^2 x 512 453 -> 422, 768^2 x
+// 512 631 -> 599, 1024^2 x 2048 5.26 -> 4.95 ms (pads of 2 to 37 KiB do as well but for a few:
+// 1 KiB at 256^2 380 us, 9 at 768^2 643).  Not below 64 KiB, where the pad would cost memory
+// for nothing.  azim: the planes the banded kernel reaches with one 31-bit byte offset (0:
+// another form).
+int64_t plane_pitch(int64_t C, int azim) {
+    const int64_t u = round_up(C, asn::kScaleBlock) / asn::kScaleBlock, v = u + 6;
+    const bool pad = azim > 0 && u >= 64 && u % 16 == 0 && azim * v * asn::kScaleBlock * 4 < (int64_t)1 << 31;
+    return (pad ? v : u) * asn::kScaleBlock;
+}
+
 Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int band_levels = 0,
                    int band_azim = 0) {
     Layout L;
@@ -81,7 +95,7 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
     L.Q = Q;
     L.Qp = (int)round_up(Q, asn::kGemmBM);
     L.C = (int64_t)nx * ny;
-    L.P = round_up(L.C, asn::kScaleBlock);
+    L.P = plane_pitch(L.C, band_azim);
     L.lowp = dtype != ASN_GEMM_F32;
     const int strip = scheme == ASN_SCHEME_HEUN ? asn::kStripXM : asn::kStripX;
     L.tiles_x = (nx + strip - 1) / strip;
