@@ -90,7 +90,7 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
     Layout L;
     L.banded = band_levels > 0;
     // the banded reduced-precision step keeps the fused form's pending correction
-    if (L.banded) fused = dtype != ASN_GEMM_F32;
+    if (L.banded) fused = dtype != ASN_GEMM_F32 && scheme == ASN_SCHEME_EULER;
     L.fused = fused;
     L.Q = Q;
     L.Qp = (int)round_up(Q, asn::kGemmBM);
@@ -221,23 +221,34 @@ struct asn_problem_s {
     std::unique_ptr<asn::ImplicitSolver> imp;   // the implicit scheme's solver (else null)
     int band_levels = 0, band_azim = 0, band_reach = 0;   // banded step (else 0)
     size_t band_lds() const {
-        return asn::band_lds_bytes(band_azim, dtype);
+        return asn::band_lds_bytes(band_azim, dtype, scheme == ASN_SCHEME_HEUN);
     }
 };
 
-struct asn_batch_s {
-    std::vector<asn_problem> probs;
-    int n = 0, dtype = 0, scheme = 0;
-    int launch_scheme = 0;   // scheme, or its flat-chunk stencil form
-    int band_az = 0;         // banded batches: the azimuth count and LDS bytes per block
+// Problems that share their launches: a batch is one such group, a Heun batch up to two (the
+// problems whose passes are banded and those on separate kernels).
+struct Group {
+    int first = 0, n = 0;    // of the batch's problems in launch order
+    int scheme = 0;          // launch scheme (the flat-chunk, strip or banded form)
+    int band_az = 0;         // banded: the largest azimuth count, LDS bytes per block and reach
     size_t band_lds = 0;
-    int band_reach = 0;      // the largest reach of a banded batch
-    hipStream_t stream = nullptr;
-    std::vector<StepArgs> tab;
-    std::vector<int> off;
-    char* dev = nullptr;
-    asn::BatchArgs args{};
+    int band_reach = 0;
     int grid[asn::KT_COUNT] = {};
+    asn::BatchArgs args{};
+};
+constexpr int kMaxGroups = 2;
+struct Plan {
+    int n = 0, n_groups = 0;
+    asn_problem order[asn::kMaxArm];
+    Group groups[kMaxGroups];
+};
+
+struct asn_batch_s {
+    Plan plan;
+    int dtype = 0, scheme = 0;
+    int index[asn::kMaxArm];   // problem order[i] is the caller's problem index[i]
+    hipStream_t stream = nullptr;
+    char* dev = nullptr;
     std::map<int64_t, std::pair<hipGraph_t, hipGraphExec_t>> graphs;
 };
 
@@ -444,7 +455,8 @@ bool use_fused(int dtype, int scheme, int form, int nx, int ny, int Q) {
     return !(nx <= asn::kFlatMaxNx && (double)nx * ny * Q >= 33554432.0);
 }
 
-// Whether a problem may take the banded step: forward Euler on a product set whose
+// Whether a problem may take the banded step: forward Euler, or Heun in FP32 unless separate
+// kernels were asked for (its form is reported as separate either way), on a product set whose
 // azimuth count has a kernel instance (FP32: 8 .. 64 in steps of 8; BF16 / FP16: 32 or
 // 64) (ASN_FORM_AUTO or ASN_FORM_BANDED); the stored K must then also have the banded
 // form (band_form).
@@ -453,10 +465,12 @@ bool band_candidate(int dtype, int scheme, int form, const asn_quadrature* q, in
     // offsets below 2^31
     const int64_t P = round_up(C, asn::kScaleBlock);
     const bool az_ok = asn::band_azimuths_supported(q->n_azim, dtype);
-    return az_ok && scheme == ASN_SCHEME_EULER &&
-           (int64_t)std::max(q->n_azim, 1) * P * 4 < ((int64_t)1 << 31) &&
-           (form == ASN_FORM_AUTO || form == ASN_FORM_BANDED) && q->q_custom == 0 &&
-           q->icosahedron_order == 0 && q->n_polar >= 1;
+    const bool scheme_ok = scheme == ASN_SCHEME_EULER
+                               ? form == ASN_FORM_AUTO || form == ASN_FORM_BANDED
+                               : scheme == ASN_SCHEME_HEUN && dtype == ASN_GEMM_F32 &&
+                                     (form == ASN_FORM_AUTO || form == ASN_FORM_FUSED);
+    return az_ok && scheme_ok && (int64_t)std::max(q->n_azim, 1) * P * 4 < ((int64_t)1 << 31) &&
+           q->q_custom == 0 && q->icosahedron_order == 0 && q->n_polar >= 1;
 }
 
 }  // namespace
@@ -618,7 +632,7 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         }
         banded = asn::band_form(quad->n_polar, quad->n_azim, K32.data(), asn::kBandMaxReach,
                                 asn::kBandNarrow, bf);
-        banded = banded && asn::band_supported(bf.azim, p->dtype, bf.reach) &&
+        banded = banded && asn::band_supported(bf.azim, p->dtype, bf.reach, p->scheme == ASN_SCHEME_HEUN) &&
                  asn::band_scatter_tables(bf, p->dtype, ddesc, bcoef);
         if (banded && p->dtype != ASN_GEMM_F32) {
             // the kernel takes one row defect per level (the rows of a level hold the same
@@ -807,7 +821,8 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
           hipMemcpyAsync(b + L.off_bcxy, dcxy.data(), dcxy.size() * 4, hipMemcpyHostToDevice,
                          p->stream) != hipSuccess ||
           copy_tables() != hipSuccess ||
-          asn::prepare_banded(bf.azim, p->dtype, bf.reach, p->band_lds()) != hipSuccess)) ||
+          asn::prepare_banded(bf.azim, p->dtype, bf.reach, p->scheme == ASN_SCHEME_HEUN, p->band_lds()) !=
+              hipSuccess)) ||
         (L.lowp && hipMemcpyAsync(b + L.off_Klp, Klp.data(), Klp.size() * 2,
                                   hipMemcpyHostToDevice, p->stream) != hipSuccess) ||
         hipMemcpyAsync(b + L.off_coef, coef.data(), coef.size() * 16, hipMemcpyHostToDevice,
@@ -921,7 +936,7 @@ asn_status asn_get_state(asn_problem p, float* psi, int32_t on_device) {
 // The scheme the kernels are launched with: a separate-kernel step whose stencil
 // runs over flat cell chunks (Euler or Heun) has a launch form of its own.
 static int launch_scheme(asn_problem p) {
-    if (p->L.banded) return asn::SCHEME_EULER_BANDED;
+    if (p->L.banded) return p->scheme == ASN_SCHEME_HEUN ? asn::SCHEME_HEUN_BANDED : asn::SCHEME_EULER_BANDED;
     if (!p->L.flat) return p->scheme;
     return p->scheme == ASN_SCHEME_HEUN ? asn::SCHEME_HEUN_FLAT : asn::SCHEME_EULER_FLAT;
 }
@@ -1045,11 +1060,14 @@ static asn_status check_batch(asn_problem* probs, int32_t n) {
             return fail(ASN_E_INVALID, "problems of a batch must share the kernel form "
                                        "(asn_step_form; ask for ASN_FORM_FUSED or ASN_FORM_SEPARATE "
                                        "when their sizes differ)");
-        if (probs[i]->L.banded != probs[0]->L.banded ||
-            probs[i]->band_azim != probs[0]->band_azim)
+        if (probs[0]->scheme == ASN_SCHEME_EULER && (probs[i]->L.banded != probs[0]->L.banded ||
+                                                     probs[i]->band_azim != probs[0]->band_azim))
             return fail(ASN_E_INVALID, "problems of a banded batch must share the azimuth count "
                                        "(and a batch is banded for all its problems or none)");
-        if (probs[i]->L.flat != probs[0]->L.flat)
+        // (Heun: by the grid's width, also where the banded passes run)
+        if (probs[0]->scheme == ASN_SCHEME_HEUN
+                ? (probs[i]->nx <= asn::kFlatMaxNxM) != (probs[0]->nx <= asn::kFlatMaxNxM)
+                : probs[i]->L.flat != probs[0]->L.flat)
             return fail(ASN_E_INVALID, std::string("problems of a batch must share the stencil form: ") +
                                        "separate-kernel steps use flat cell chunks up to nx = " +
                                        std::to_string(asn::kFlatMaxNx) + " (Euler) or " +
@@ -1062,56 +1080,102 @@ static asn_status check_batch(asn_problem* probs, int32_t n) {
     return ASN_OK;
 }
 
+// The groups of a checked batch, and the device tables behind them as one block: step arguments
+// of both buffers, block offsets per kernel kind and group, buffer bases, limits.
+static size_t plan_bytes(int n) {
+    return 2 * (size_t)n * sizeof(StepArgs) + (size_t)asn::KT_COUNT * (n + kMaxGroups) * sizeof(int) +
+           2 * (size_t)asn::kMaxArm * sizeof(int);
+}
+static void make_plan(asn_problem* probs, int32_t n, char* dev, Plan& p, int* index, StepArgs* tab, int* off) {
+    p.n = n;
+    int at = 0;
+    for (int banded = 1; banded >= 0; --banded) {
+        const int first = at;
+        for (int32_t i = 0; i < n; ++i)
+            if ((int)probs[i]->L.banded == banded) {
+                if (index) index[at] = i;
+                p.order[at++] = probs[i];
+            }
+        if (at == first) continue;
+        Group& g = p.groups[p.n_groups++];
+        g.first = first;
+        g.n = at - first;
+        g.scheme = launch_scheme(p.order[first]);
+    }
+    int* o = off;
+    const size_t tab_b = 2 * (size_t)n * sizeof(StepArgs);
+    for (int k = 0; k < p.n_groups; ++k) {
+        Group& g = p.groups[k];
+        g.args.tab = reinterpret_cast<const StepArgs*>(dev) + 2 * g.first;
+        g.args.off = reinterpret_cast<const int*>(dev + tab_b) + (o - off);
+        int* tail = reinterpret_cast<int*>(dev + tab_b) + asn::KT_COUNT * (n + kMaxGroups);
+        g.args.base = tail + g.first;
+        g.args.limit = tail + asn::kMaxArm + g.first;
+        g.args.n = g.n;
+        for (int i = 0; i < g.n; ++i) {
+            asn_problem q = p.order[g.first + i];
+            tab[2 * (g.first + i)] = q->tab[0];
+            tab[2 * (g.first + i) + 1] = q->tab[1];
+            for (int kind = 0; kind < asn::KT_COUNT; ++kind) {
+                int* row = o + kind * (g.n + 1);
+                if (i == 0) row[0] = 0;
+                row[i + 1] = row[i] + q->blocks[kind];
+            }
+            if (q->L.banded) g.band_lds = std::max(g.band_lds, q->band_lds());
+            g.band_az = std::max(g.band_az, q->band_azim);
+            g.band_reach = std::max(g.band_reach, q->band_reach);
+        }
+        for (int kind = 0; kind < asn::KT_COUNT; ++kind) g.grid[kind] = o[kind * (g.n + 1) + g.n];
+        o += asn::KT_COUNT * (g.n + 1);
+    }
+}
+static hipError_t arm_plan(const Plan& p, const asn::ArmArgs& v, hipStream_t s) {
+    return asn::launch_arm(const_cast<int*>(p.groups[0].args.limit), const_cast<int*>(p.groups[0].args.base), p.n, v,
+                           s);
+}
+// n_steps steps of every group, and what follows the last.
+static hipError_t launch_plan(const Plan& p, int64_t n_steps, int dtype, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < p.n_groups && e == hipSuccess; ++k) {
+        const Group& g = p.groups[k];
+        asn::BatchArgs args = g.args;
+        for (int64_t j = 0; j < n_steps && e == hipSuccess; ++j) {
+            args.step = (int)j;
+            args.s_par = (int)(j & 1);
+            e = asn::launch_step(args, g.grid, dtype, g.scheme, s, nullptr, g.band_az, g.band_lds, g.band_reach);
+        }
+        if (e == hipSuccess) e = asn::launch_last_budget(args, (int)n_steps, g.scheme, s);
+    }
+    return e;
+}
+
 asn_status asn_batch_create(asn_problem* probs, int32_t n, asn_batch* out) {
     if (!out) return fail(ASN_E_INVALID, "out is NULL");
     *out = nullptr;
     const asn_status cs = check_batch(probs, n);
     if (cs != ASN_OK) return cs;
     auto* b = new asn_batch_s();
-    b->probs.assign(probs, probs + n);
-    b->n = n;
     b->dtype = probs[0]->dtype;
     b->scheme = probs[0]->scheme;
-    b->launch_scheme = launch_scheme(probs[0]);
-    b->band_az = probs[0]->band_azim;
-    for (int32_t i = 0; i < n; ++i) {
-        if (probs[i]->L.banded)
-            b->band_lds = std::max(b->band_lds, probs[i]->band_lds());
-        b->band_reach = std::max(b->band_reach, probs[i]->band_reach);
-    }
     b->stream = probs[0]->stream;
-    b->tab.resize(2 * (size_t)n);
-    b->off.assign((size_t)asn::KT_COUNT * (n + 1), 0);
-    for (int32_t i = 0; i < n; ++i) {
-        b->tab[2 * i] = probs[i]->tab[0];
-        b->tab[2 * i + 1] = probs[i]->tab[1];
-        for (int k = 0; k < asn::KT_COUNT; ++k)
-            b->off[(size_t)k * (n + 1) + i + 1] = b->off[(size_t)k * (n + 1) + i] + probs[i]->blocks[k];
-    }
-    for (int k = 0; k < asn::KT_COUNT; ++k) b->grid[k] = b->off[(size_t)k * (n + 1) + n];
-    const size_t tab_b = b->tab.size() * sizeof(StepArgs);
-    const size_t off_b = b->off.size() * sizeof(int);
-    const size_t bytes = tab_b + off_b + 2 * asn::kMaxArm * sizeof(int);
+    std::vector<StepArgs> tab(2 * (size_t)n);
+    std::vector<int> off((size_t)asn::KT_COUNT * (n + kMaxGroups), 0);
     void* m = nullptr;
-    if (hipMalloc(&m, bytes) != hipSuccess) {
+    if (hipMalloc(&m, plan_bytes(n)) != hipSuccess) {
         delete b;
         return fail(ASN_E_OOM, "hipMalloc of the batch tables failed");
     }
     b->dev = static_cast<char*>(m);
-    if (hipMemcpyAsync(b->dev, b->tab.data(), tab_b, hipMemcpyHostToDevice, b->stream) != hipSuccess ||
-        hipMemcpyAsync(b->dev + tab_b, b->off.data(), off_b, hipMemcpyHostToDevice, b->stream) !=
+    make_plan(probs, n, b->dev, b->plan, b->index, tab.data(), off.data());
+    const size_t tab_b = tab.size() * sizeof(StepArgs);
+    if (hipMemcpyAsync(b->dev, tab.data(), tab_b, hipMemcpyHostToDevice, b->stream) != hipSuccess ||
+        hipMemcpyAsync(b->dev + tab_b, off.data(), off.size() * sizeof(int), hipMemcpyHostToDevice, b->stream) !=
             hipSuccess ||
         hipStreamSynchronize(b->stream) != hipSuccess) {
         (void)hipFree(b->dev);
         delete b;
         return fail(ASN_E_HIP, "copying the batch tables failed");
     }
-    b->args.tab = reinterpret_cast<const StepArgs*>(b->dev);
-    b->args.off = reinterpret_cast<const int*>(b->dev + tab_b);
-    b->args.base = reinterpret_cast<const int*>(b->dev + tab_b + off_b);
-    b->args.limit = reinterpret_cast<const int*>(b->dev + tab_b + off_b + asn::kMaxArm * sizeof(int));
-    b->args.n = n;
-    b->args.s_par = 0;
     *out = b;
     return ASN_OK;
 }
@@ -1120,18 +1184,16 @@ asn_status asn_batch_step(asn_batch b, int64_t n_steps, const int64_t* limit) {
     if (!b) return fail(ASN_E_INVALID, "batch is NULL");
     if (n_steps < 0 || n_steps > (1 << 20)) return fail(ASN_E_INVALID, "n_steps must be in [0, 2^20]");
     asn::ArmArgs v{};
-    std::vector<int64_t> take(b->n);
+    int64_t take[asn::kMaxArm];
     bool any = false;
-    for (int i = 0; i < b->n; ++i) {
-        take[i] = limit ? std::max<int64_t>(0, std::min<int64_t>(limit[i], n_steps)) : n_steps;
+    for (int i = 0; i < b->plan.n; ++i) {
+        take[i] = limit ? std::max<int64_t>(0, std::min<int64_t>(limit[b->index[i]], n_steps)) : n_steps;
         v.limit[i] = (int)take[i];
-        v.cur[i] = b->probs[i]->cur;
+        v.cur[i] = b->plan.order[i]->cur;
         any = any || take[i] > 0;
     }
     if (!any) return ASN_OK;
-    HIP_TRY(asn::launch_arm(const_cast<int*>(b->args.limit), const_cast<int*>(b->args.base), b->n, v,
-                            b->stream));
-    asn::BatchArgs args = b->args;
+    HIP_TRY(arm_plan(b->plan, v, b->stream));
     if (b->stream != nullptr && n_steps >= 2) {
         // Capture the step sequence once per length; later calls replay it.
         auto it = b->graphs.find(n_steps);
@@ -1139,15 +1201,7 @@ asn_status asn_batch_step(asn_batch b, int64_t n_steps, const int64_t* limit) {
             hipGraph_t g = nullptr;
             hipGraphExec_t ge = nullptr;
             HIP_TRY(hipStreamBeginCapture(b->stream, hipStreamCaptureModeRelaxed));
-            hipError_t e = hipSuccess;
-            for (int64_t j = 0; j < n_steps && e == hipSuccess; ++j) {
-                args.step = (int)j;
-                args.s_par = (int)(j & 1);
-                e = asn::launch_step(args, b->grid, b->dtype, b->launch_scheme, b->stream, nullptr,
-                                     b->band_az, b->band_lds, b->band_reach);
-            }
-            if (e == hipSuccess)
-                e = asn::launch_last_budget(args, (int)n_steps, b->launch_scheme, b->stream);
+            const hipError_t e = launch_plan(b->plan, n_steps, b->dtype, b->stream);
             const hipError_t e2 = hipStreamEndCapture(b->stream, &g);
             if (e != hipSuccess || e2 != hipSuccess) {
                 if (g) (void)hipGraphDestroy(g);
@@ -1162,17 +1216,11 @@ asn_status asn_batch_step(asn_batch b, int64_t n_steps, const int64_t* limit) {
         }
         HIP_TRY(hipGraphLaunch(it->second.second, b->stream));
     } else {
-        for (int64_t j = 0; j < n_steps; ++j) {
-            args.step = (int)j;
-            args.s_par = (int)(j & 1);
-            HIP_TRY(asn::launch_step(args, b->grid, b->dtype, b->launch_scheme, b->stream, nullptr,
-                                     b->band_az, b->band_lds, b->band_reach));
-        }
-        HIP_TRY(asn::launch_last_budget(args, (int)n_steps, b->launch_scheme, b->stream));
+        HIP_TRY(launch_plan(b->plan, n_steps, b->dtype, b->stream));
     }
-    for (int i = 0; i < b->n; ++i) {
-        b->probs[i]->cur ^= state_flip(b->scheme, take[i]);
-        b->probs[i]->steps_done += take[i];
+    for (int i = 0; i < b->plan.n; ++i) {
+        b->plan.order[i]->cur ^= state_flip(b->scheme, take[i]);
+        b->plan.order[i]->steps_done += take[i];
     }
     return ASN_OK;
 }
@@ -1223,56 +1271,31 @@ asn_status asn_step_batch_noalloc(asn_problem* probs, int32_t n, int64_t n_steps
     // the tables, laid out as in asn_batch_create, in host arrays of fixed size
     constexpr int kN = asn::kMaxArm;
     StepArgs tab[2 * kN];
-    int off[asn::KT_COUNT * (kN + 1)];
-    const size_t tab_b = 2 * (size_t)n * sizeof(StepArgs);
-    const size_t off_b = (size_t)asn::KT_COUNT * (n + 1) * sizeof(int);
-    const size_t bytes = tab_b + off_b + 2 * (size_t)kN * sizeof(int);
-    if (bytes > kNoAllocBytes)
+    int off[asn::KT_COUNT * (kN + kMaxGroups)];
+    if (plan_bytes(n) > kNoAllocBytes)
         return fail(ASN_E_INVALID, "batch tables exceed the no-allocation scratch (" +
                                        std::to_string(kNoAllocBytes) + " bytes)");
-    int grid[asn::KT_COUNT];
-    for (int k = 0; k < asn::KT_COUNT; ++k) off[k * (n + 1)] = 0;
-    size_t band_lds = 0;
-    int band_reach = 0;
-    for (int32_t i = 0; i < n; ++i) {
-        tab[2 * i] = probs[i]->tab[0];
-        tab[2 * i + 1] = probs[i]->tab[1];
-        for (int k = 0; k < asn::KT_COUNT; ++k)
-            off[k * (n + 1) + i + 1] = off[k * (n + 1) + i] + probs[i]->blocks[k];
-        if (probs[i]->L.banded) band_lds = std::max(band_lds, probs[i]->band_lds());
-        band_reach = std::max(band_reach, probs[i]->band_reach);
-    }
-    for (int k = 0; k < asn::KT_COUNT; ++k) grid[k] = off[k * (n + 1) + n];
     if (n_steps == 0) return ASN_OK;
     char* dev = nullptr;
     const asn_status ss = scratch_on_device(&dev);
     if (ss != ASN_OK) return ss;
+    Plan plan;
+    make_plan(probs, n, dev, plan, nullptr, tab, off);
     hipStream_t stream = probs[0]->stream;
     // stream order: earlier work on this stream that read the tables has finished
     // before the copies land; the host arrays must outlive the copies, hence the wait
+    const size_t tab_b = 2 * (size_t)n * sizeof(StepArgs);
     HIP_TRY(hipMemcpyAsync(dev, tab, tab_b, hipMemcpyHostToDevice, stream));
-    HIP_TRY(hipMemcpyAsync(dev + tab_b, off, off_b, hipMemcpyHostToDevice, stream));
+    HIP_TRY(hipMemcpyAsync(dev + tab_b, off, (size_t)asn::KT_COUNT * (n + kMaxGroups) * sizeof(int),
+                           hipMemcpyHostToDevice, stream));
     HIP_TRY(hipStreamSynchronize(stream));
-    asn::BatchArgs args{};
-    args.tab = reinterpret_cast<const StepArgs*>(dev);
-    args.off = reinterpret_cast<const int*>(dev + tab_b);
-    args.base = reinterpret_cast<const int*>(dev + tab_b + off_b);
-    args.limit = reinterpret_cast<const int*>(dev + tab_b + off_b + kN * sizeof(int));
-    args.n = n;
     asn::ArmArgs v{};
     for (int i = 0; i < n; ++i) {
         v.limit[i] = (int)n_steps;
-        v.cur[i] = probs[i]->cur;
+        v.cur[i] = plan.order[i]->cur;
     }
-    HIP_TRY(asn::launch_arm(const_cast<int*>(args.limit), const_cast<int*>(args.base), n, v, stream));
-    const int scheme = launch_scheme(probs[0]);
-    for (int64_t j = 0; j < n_steps; ++j) {
-        args.step = (int)j;
-        args.s_par = (int)(j & 1);
-        HIP_TRY(asn::launch_step(args, grid, probs[0]->dtype, scheme, stream, nullptr,
-                                 probs[0]->band_azim, band_lds, band_reach));
-    }
-    HIP_TRY(asn::launch_last_budget(args, (int)n_steps, scheme, stream));
+    HIP_TRY(arm_plan(plan, v, stream));
+    HIP_TRY(launch_plan(plan, n_steps, probs[0]->dtype, stream));
     for (int i = 0; i < n; ++i) {
         probs[i]->cur ^= state_flip(probs[i]->scheme, n_steps);
         probs[i]->steps_done += n_steps;
@@ -1334,7 +1357,7 @@ asn_status asn_info(asn_problem p, double* dt, int64_t* steps_done, int64_t* ste
 
 asn_status asn_step_form(asn_problem p, int32_t* form) {
     if (!p || !form) return fail(ASN_E_INVALID, "NULL argument");
-    *form = p->L.banded ? ASN_FORM_BANDED : p->L.fused ? ASN_FORM_FUSED : ASN_FORM_SEPARATE;
+    *form = p->L.banded && p->scheme == ASN_SCHEME_EULER ? ASN_FORM_BANDED : p->L.fused ? ASN_FORM_FUSED : ASN_FORM_SEPARATE;
     return ASN_OK;
 }
 

@@ -350,9 +350,9 @@ bool band_form(int levels, int azim, const float* K32, int max_reach, int narrow
         for (int k = 1; k < azim; ++k) {
             const float* r0 = K32 + (size_t)(i * azim) * Q;
             const float* rk = K32 + (size_t)(i * azim + k) * Q;
-            for (int j = 0; j < levels; ++j)
-                for (int kp = 0; kp < azim; ++kp)
-                    if (rk[j * azim + kp] != r0[j * azim + wrap(kp - k)]) return false;
+            for (int j = 0; j < levels; ++j, r0 += azim, rk += azim)
+                if (!std::equal(r0, r0 + azim - k, rk + k) || !std::equal(r0 + azim - k, r0 + azim, rk))
+                    return false;
         }
     int reach = 0;
     for (int i = 0; i < levels; ++i)

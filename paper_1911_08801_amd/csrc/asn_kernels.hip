@@ -1867,15 +1867,18 @@ __device__ __forceinline__ void budget_fold(const StepArgs& a, int n_fin, int n_
     store();
 }
 
-// One block per problem.  A banded step's partials are one of either kind per block of the
-// step, written by step B.step - 1 (the fold of the call's last step).
-__global__ __launch_bounds__(kBudgetThreads) void budget_kernel(BatchArgs B, int mode) {
+// One block per problem.  A banded pass's partials are one of either kind per block of the
+// pass; its fold takes band_fold_threads(n_az) threads here and in the next pass's launch, so
+// that a record does not depend on which of the two did it.
+__device__ __forceinline__ int band_fold_threads(int n_az) { return n_az / kBandO * 64; }
+__global__ __launch_bounds__(kBudgetThreads) void budget_kernel(BatchArgs B, int mode, bool banded) {
     const int pi = blockIdx.x;
-    if (gp(B.limit)[pi] <= (mode == BUD_BANDED ? B.step - 1 : B.step)) return;
+    if (gp(B.limit)[pi] <= B.step) return;
     const StepArgs a = args_of(B, pi);   // by value: no reloads after stores
-    if (mode == BUD_BANDED)
-        budget_fold(a, a.tiles_x, a.tiles_x, kBudgetThreads, BUD_STEP);
-    else
+    if (banded) {
+        if ((int)threadIdx.x >= band_fold_threads(a.n_az)) return;
+        budget_fold(a, a.tiles_x, a.tiles_x, band_fold_threads(a.n_az), mode);
+    } else
         budget_fold(a, a.fin_blocks, mode == BUD_INIT ? 0 : a.tiles_x * a.tiles_y * a.G, kBudgetThreads, mode);
 }
 
@@ -1908,7 +1911,7 @@ __global__ void broadcast_kernel(float* psi, const float* cell, int Q, int64_t C
 }
 
 // ---------------------------------------------------------------------------
-// 5. Banded forward-Euler step for product ordinate sets.
+// 5. Banded step for product ordinate sets (forward Euler; FP32 Heun).
 //    The set is invariant under rotations by 2 pi / n_az about the polar axis and under
 //    reflection of the azimuth, so Y_(i,k) = sum_j sum_d c_ij(d) (psi_(j, k + d) + psi_(j, k - d)):
 //    per pair of levels a short symmetric circular convolution along the azimuth.  The
@@ -1942,6 +1945,12 @@ __global__ void broadcast_kernel(float* psi, const float* cell, int Q, int64_t C
 //    FP32 number.  K is 2 % dense, so the vector units, which skip its zeros, finish before
 //    the matrix cores did with each level pair's whole circulant block: 400^2 x 512 BF16
 //    0.242 -> 0.196 ms, 700^2 x 1152 FP16 1.63 -> 1.34 ms.
+//    Heun + minmod, FP32: both passes in this form, instead of a contraction, stencil, finalize
+//    and budget kernel each.  A pass without its contraction's round trip through Y reads psi
+//    (its three y neighbours from L2) and writes it, the second also reads psi^n, where its
+//    result goes.  400^2 x 512 981 -> 531 us a step, 700^2 x 1152 6.78 -> 4.32 ms, 50^2 x 128
+//    70 -> 33 us, 2000 x 1000 x 32 0.81 -> 0.41 ms.  Its bounds are VALU issue (the limiters are
+//    half the pass) and registers, 128 a lane: one block of 16 waves in a CU at 64 azimuths.
 // ---------------------------------------------------------------------------
 // The band tables are written by the host before any step and only read by the
 // kernels: reached through the constant address space, their uniform loads are scalar
@@ -1970,7 +1979,7 @@ __device__ __forceinline__ void await(const float (&k)[M]) {
 // and the others to at most 1: those products always; the rest by the level's flags, offsets
 // beyond 4 in steps of four, each output as many as it needs (steps: 4 bits each).  lo / hi:
 // the lane's column in the four rows before / after its wave's; col: in row 0.
-template <int RT, int P>
+template <int RT, int P, int ROW>
 __device__ __forceinline__ void scatter(float (&acc)[2 * RT + 1][kBandO], const float (&v)[kBandO],
                                         const float (&near)[4], const float (&k0)[3 * (2 * RT + 1)],
                                         const float* lo, const float* hi, const float* col, int a0,
@@ -2012,9 +2021,9 @@ __device__ __forceinline__ void scatter(float (&acc)[2 * RT + 1][kBandO], const 
         float k[2 * N], s4[O];
 #pragma unroll
         for (int i = 0; i < 2 * N; ++i) k[i] = kc[3 * N + i];
-        up[O + 2] = hi[2 * kBandRow];
-        up[O + 3] = hi[3 * kBandRow];
-        dn[1] = lo[kBandRow];
+        up[O + 2] = hi[2 * ROW];
+        up[O + 3] = hi[3 * ROW];
+        dn[1] = lo[ROW];
         dn[0] = lo[0];
         await(k);
         sum(3, s);
@@ -2044,15 +2053,15 @@ __device__ __forceinline__ void scatter(float (&acc)[2 * RT + 1][kBandO], const 
             ah = ah >= A - O ? ah + O - A : ah + O;
             al = al < O ? al - O + A : al - O;
             kc += 4 * N;
-            const float* ph = col + ah * kBandRow;
-            const float* pl = col + al * kBandRow;
+            const float* ph = col + ah * ROW;
+            const float* pl = col + al * ROW;
             float kw[4 * N];
 #pragma unroll
             for (int i = 0; i < 4 * N; ++i) kw[i] = kc[N + i];
 #pragma unroll
             for (int o = 0; o < O; ++o) {
-                u1[o] = ph[o * kBandRow];
-                d1[o] = pl[o * kBandRow];
+                u1[o] = ph[o * ROW];
+                d1[o] = pl[o * ROW];
             }
             await(kw);
 #pragma unroll
@@ -2109,20 +2118,25 @@ __device__ __forceinline__ void round_pair(float s0, float s1, float& x0, float&
 }
 
 // T: the largest block (512 threads up to 32 azimuths: the reach-3 instance then keeps its
-// queue in registers).  DT: operand type of the contraction.
-template <int RT, int T, int DT>
+// queue in registers).  DT: operand type of the contraction.  HS: 0 forward Euler, 1 / 2 the
+// first / second pass of the Heun + minmod scheme (FP32; muscl_kernel's fluxes, so the rows hold
+// two cells beyond each end and three y neighbours are loaded).
+template <int RT, int T, int DT, int HS>
 __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
-    constexpr int O = kBandO;
+    constexpr int O = kBandO, ROW = band_row(HS != 0), LEFT = HS ? 2 : 1;   // LEFT: the first cell's column
     constexpr bool LP = DT != 0;
     extern __shared__ float slots[];
     int pi, local;
-    if ((int)blockIdx.x < B.n) {   // the last step's budget, one block per problem
+    if ((int)blockIdx.x < B.n) {   // the last pass's budget, one block per problem
         pi = blockIdx.x;
-        if (B.step == 0 || gp(B.limit)[pi] < B.step) return;
+        const int last = HS == 2 ? B.step : B.step - 1;   // its step
+        if (last < 0 || gp(B.limit)[pi] <= last) return;
         BatchArgs P = B;
         P.s_par ^= 1;
         const StepArgs a = args_of(P, pi);
-        budget_fold(a, a.tiles_x, a.tiles_x, (int)blockDim.x, BUD_STEP);
+        if ((int)threadIdx.x >= band_fold_threads(a.n_az)) return;
+        budget_fold(a, a.tiles_x, a.tiles_x, band_fold_threads(a.n_az),
+                    HS == 0 ? BUD_STEP : HS == 1 ? BUD_STAGE2 : BUD_STAGE1);
         return;
     }
     if (!locate(B, KT_SC, xcd_remap(blockIdx.x - B.n, gridDim.x - B.n), pi, local)) return;
@@ -2130,6 +2144,7 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int A = a.n_az, NW = A / O, a0 = wave * O;
+    if (wave >= NW) return;   // a Heun batch's problems may have different azimuth counts
     const int nx = a.nx, ny = a.ny, L = a.n_lev, C = (int)a.C;
     const int c0 = local * kBandCells, cell = c0 + lane;
     const bool in = cell < C;
@@ -2160,6 +2175,8 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     // padding cell
     const int y = cell / nx, x = cell - y * nx;
     int at = in ? (x == 0 ? 1 : 0) | (x == nx - 1 ? 2 : 0) | (y == 0 ? 4 : 0) | (y == ny - 1 ? 8 : 0) : 16;
+    // (Heun: 32 / 64 also where the second cell that way is a ghost)
+    if (HS) at |= in ? (x <= 1 ? 32 : 0) | (x >= nx - 2 ? 64 : 0) : 0;
     const bool edge = __ballot(at != 0) != 0;
     // Memory is reached through one buffer descriptor per level, a lane's byte offset in a
     // plane and the (uniform) offset of the plane; kOOB reads 0 (the vacuum ghost).
@@ -2171,7 +2188,8 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     // wave (reduced precision: n_az / 16 is whole, it is the same for all four): index o / G.
     // yd, xd: the pending corrections of the upwind cells (0 for a ghost)
     constexpr int G = LP ? 4 : 2, NG = O / G;
-    uint32_t dir[NG], yoff[NG];
+    uint32_t dir[NG], yoff[NG], yoff2[HS ? NG : 1], ydn[HS ? NG : 1];   // Heun: also the cell
+                                                                      // beyond, the downwind one
     float yd = 0.f, xd = 0.f;
 #pragma unroll
     for (int h = 0; h < NG; ++h) {
@@ -2179,6 +2197,11 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
         const int yc = (dir[h] & 4) ? cell - nx : cell + nx;
         const bool yv = in && yc >= 0 && yc < C;
         yoff[h] = yv ? 4u * (uint32_t)yc : kOOB;
+        if constexpr (HS != 0) {
+            const int y2 = (dir[h] & 4) ? cell - 2 * nx : cell + 2 * nx, y1 = 2 * cell - yc;
+            yoff2[h] = (in && y2 >= 0 && y2 < C) ? 4u * (uint32_t)y2 : kOOB;
+            ydn[h] = (in && y1 >= 0 && y1 < C) ? 4u * (uint32_t)y1 : kOOB;
+        }
         if constexpr (LP) {
             if (yv) yd = gp(a.delta)[yc];
             if (!(at & ((dir[h] & 1) ? 17 : 18))) xd = gp(a.delta)[(dir[h] & 1) ? cell - 1 : cell + 1];
@@ -2186,15 +2209,19 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     }
     // lane l also fetches azimuth a0 + l % 4's upwind cell beyond the block's end, and keeps it
     // in the column before / after the cells of that row (every lane: no branch on lanes, so
-    // the kernel's branches all stay scalar)
+    // the kernel's branches all stay scalar).  Heun: lanes of l / 4 % 4 = 1 the second cell
+    // upwind, 2 the one downwind.
     const int hd = gp(a.qi)[a0 + (lane & 3)].dir;
-    const int hc = (hd & 1) ? c0 - 1 : c0 + kBandCells;
+    const int hk = HS ? (lane >> 2) & 3 : 0;
+    const bool hleft = (hd & 1) ? hk != 2 : hk == 2;
+    const int hcol = hleft ? (hk == 1 ? -2 : -1) : kBandCells + (hk == 1 ? 1 : 0);   // from the first cell
+    const int hc = c0 + hcol;
     const uint32_t hoff = hc >= 0 ? (uint32_t)(lane & 3) * pb + 4u * (uint32_t)hc : kOOB;
-    const int hrow = (a0 + (lane & 3)) * kBandRow + ((hd & 1) ? 0 : kBandCells + 1);
-    const int SF = A * kBandRow;
-    const int own = a0 * kBandRow + 1 + lane;
-    const int lo = (a0 == 0 ? A - O : a0 - O) * kBandRow + 1 + lane;
-    const int hi = (a0 + O == A ? 0 : a0 + O) * kBandRow + 1 + lane;
+    const int hrow = (a0 + (lane & 3)) * ROW + LEFT + hcol;
+    const int SF = A * ROW;
+    const int own = a0 * ROW + LEFT + lane;
+    const int lo = (a0 == 0 ? A - O : a0 - O) * ROW + LEFT + lane;
+    const int hi = (a0 + O == A ? 0 : a0 + O) * ROW + LEFT + lane;
     int xup[NG];
 #pragma unroll
     for (int h = 0; h < NG; ++h) xup[h] = own + ((dir[h] & 1) ? -1 : 1);
@@ -2206,6 +2233,7 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     };
     float pre[O], preh;   // the next level, on its way into LDS (lanes 0 .. 3: a halo value)
     float uy[O];          // its y-upwind values
+    float uy2[HS ? O : 1], dy1[HS ? O : 1], old[HS == 2 ? O : 1];   // Heun: the other two; psi^n
     auto level_rsrc = [&](const float* base) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)lvl_bytes,
                                                  kRsrcWord3);
@@ -2222,7 +2250,7 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
     auto put = [&](int slot) {
         float* s = slots + slot * SS;
 #pragma unroll
-        for (int o = 0; o < O; ++o) s[own + o * kBandRow] = pre[o];
+        for (int o = 0; o < O; ++o) s[own + o * ROW] = pre[o];
         s[hrow] = preh;
         if constexpr (LP) {
             float x[O];
@@ -2230,13 +2258,24 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
             for (int o = 0; o < O; o += 2)
                 round_pair<DT>(ldexpf(pre[o] - isov, sc), ldexpf(pre[o + 1] - isov, sc), x[o], x[o + 1]);
 #pragma unroll
-            for (int o = 0; o < O; ++o) s[XO + own + o * kBandRow] = x[o];
+            for (int o = 0; o < O; ++o) s[XO + own + o * ROW] = x[o];
         }
     };
     auto fetch_y = [&](const float* base) {
         const __amdgpu_buffer_rsrc_t r = level_rsrc(base);
 #pragma unroll
-        for (int o = 0; o < O; ++o) uy[o] = load(r, yoff[o / G], s0 + (uint32_t)o * pb);
+        for (int o = 0; o < O; ++o) {
+            uy[o] = load(r, yoff[o / G], s0 + (uint32_t)o * pb);
+            if constexpr (HS != 0) {
+                uy2[o] = load(r, yoff2[o / G], s0 + (uint32_t)o * pb);
+                dy1[o] = load(r, ydn[o / G], s0 + (uint32_t)o * pb);
+            }
+        }
+    };
+    auto fetch_old = [&](const float* base) {   // psi^n, where the result goes
+        const __amdgpu_buffer_rsrc_t r = level_rsrc(base);
+#pragma unroll
+        for (int o = 0; o < O; ++o) old[o] = load(r, voff, s0 + (uint32_t)o * pb);
     };
 
     // (level j's at j mod N, of which RT + 1 are in use at a time)
@@ -2272,16 +2311,16 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
         const float rq = LP ? kp(a.rdef)[max(j - RT, 0) * A] : 0.f;
         if (j < L) {
             const float* s = slots + (j & 1) * SS;
-            float ux[O], xv[O];
+            float ux[O], xv[O], ux2[HS ? O : 1], dx1[HS ? O : 1];
 #pragma unroll
             for (int o = 0; o < O; ++o) {
-                e.v[o] = s[own + o * kBandRow];
-                ux[o] = s[xup[o / G] + o * kBandRow];
+                e.v[o] = s[own + o * ROW];
+                if constexpr (HS == 0) ux[o] = s[xup[o / G] + o * ROW];
             }
             s += XO;
 #pragma unroll
-            for (int o = 0; o < O; ++o) xv[o] = LP ? s[own + o * kBandRow] : e.v[o];
-            const float near[4] = {s[lo + 2 * kBandRow], s[lo + 3 * kBandRow], s[hi], s[hi + kBandRow]};
+            for (int o = 0; o < O; ++o) xv[o] = LP ? s[own + o * ROW] : e.v[o];
+            const float near[4] = {s[lo + 2 * ROW], s[lo + 3 * ROW], s[hi], s[hi + ROW]};
             // the level's uniform values, in one round trip with the LDS rows
             const ASN_K float* kc = bcoef + d.coef;
             const ASN_K float* kcc = reinterpret_cast<const ASN_K float*>(bcxy + j * A);
@@ -2294,7 +2333,15 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
             await(k0);
             await(cc);
             asm volatile("" ::"s"(w), "s"(rq));
-            scatter<RT, PJ>(acc, xv, near, k0, s + lo, s + hi, s + 1 + lane, a0, A, d.form, d.steps, kc);
+            scatter<RT, PJ, ROW>(acc, xv, near, k0, s + lo, s + hi, s + LEFT + lane, a0, A, d.form, d.steps, kc);
+            if constexpr (HS != 0) {   // (after the convolution: registers)
+#pragma unroll
+                for (int o = 0; o < O; ++o) {   // xup = own -+ 1: the second cell upwind, the downwind one
+                    ux[o] = s[xup[o / G] + o * ROW];
+                    ux2[o] = s[2 * xup[o / G] - own + o * ROW];
+                    dx1[o] = s[2 * own - xup[o / G] + o * ROW];
+                }
+            }
             // stream + collide without the in-scattering, one chain of FMAs:
             //   psi' = psi + [bs (iso - psi) + ss - aa psi + cy (uy - psi) + cx (ux - psi) + gs (Y - psi)]
             // (aa = dt sigma_a, bs = dt sigma_s, gs = dt sigma_as, ss = dt q); no coefficient
@@ -2309,9 +2356,15 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
 #pragma unroll
                 for (int o = 0; o < O; ++o) {
                     const int dx = (dir[o / G] & 1) ? 1 : 2, dy = (dir[o / G] & 4) ? 8 : 4;
-                    const float v = e.v[o] + dv;
                     if (at & (dx | 16)) ux[o] = 0.f;
-                    ob += (at & (3 - dx) ? cc[2 * o] * v : 0.f) + (at & dy ? cc[2 * o + 1] * v : 0.f);
+                    float vx = e.v[o] + dv, vy = vx;   // the value on an outflow face
+                    if constexpr (HS != 0) {
+                        if (at & (32 * dx | 16)) ux2[o] = 0.f;
+                        if (at & ((3 - dx) | 16)) dx1[o] = 0.f;
+                        vx += 0.5f * minmod(vx - ux[o], dx1[o] - vx);
+                        vy += 0.5f * minmod(vy - uy[o], dy1[o] - vy);
+                    }
+                    ob += (at & (3 - dx) ? cc[2 * o] * vx : 0.f) + (at & dy ? cc[2 * o + 1] * vy : 0.f);
                 }
                 outflow += band_weight(a.band, j) * (double)ob;
             }
@@ -2320,6 +2373,17 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
                 float t = fmaf(cf.y, isov - e.v[o], cf.w);
                 const float v = LP ? e.v[o] + dv : e.v[o];
                 t = fmaf(-cf.x, v, t);
+                if constexpr (HS != 0) {
+                    // upwind flux differences with minmod-limited slopes, (v + s/2) - (u + s_u/2)
+                    // with s = minmod(v - u, d - v), s_u = minmod(u - u2, v - u)
+                    auto flux = [&](float u, float u2, float d1) {
+                        const float g = v - u;
+                        return fmaf(0.5f, minmod(g, d1 - v) - minmod(u - u2, g), g);
+                    };
+                    t = fmaf(-cc[2 * o + 1], flux(uy[o], uy2[o], dy1[o]), t);
+                    e.t[o] = fmaf(-cc[2 * o], flux(ux[o], ux2[o], dx1[o]), t);
+                    continue;
+                }
                 t = fmaf(cc[2 * o + 1], (LP ? uy[o] + yd : uy[o]) - v, t);
                 e.t[o] = fmaf(cc[2 * o], (LP ? ux[o] + xd : ux[o]) - v, t);
             }
@@ -2344,7 +2408,8 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
                 } else {
                     dy = sum - v;
                 }
-                const float nv = v + fmaf(cf.z, dy, n.t[o]);
+                float nv = v + fmaf(cf.z, dy, n.t[o]);
+                if constexpr (HS == 2) nv = 0.5f * (old[o] + nv);
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(nv), r, voff, s0 + (uint32_t)o * pb,
                                                       kCachePolicyNT);   // read next step, not from L2
                 phacc += w * (double)nv;
@@ -2354,6 +2419,8 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
             defect += w * (double)(cf.z * sd);
             if constexpr (LP) ypacc += w * (double)ys;
         }
+        if constexpr (HS == 2)
+            if (j + 1 >= RT && j + 1 < L + RT) fetch_old(po);
         if (j + 1 < L) {
             py += lvl_floats;
             fetch_y(py);
@@ -2462,40 +2529,46 @@ void blocks_per_kind(const StepArgs& a, int out[KT_COUNT]) {
 // 24 steps of 50^2 x 128, set-up and results included, took 726 us instead of 516, 40 steps of
 // 311 x 173 x 288 3.13 ms instead of 2.76, a step of 400^2 x 512 187 us instead of 175.
 template <typename F>
-static hipError_t with_banded(int az, int dtype, int reach, F&& f) {
+static hipError_t with_banded(int az, int dtype, int reach, int heun, F&& f) {
     const bool small = az <= 32;   // at most 512 threads
-    if (reach < 0 || reach > kBandMaxReach || !band_supported(az, dtype, reach)) return hipErrorInvalidValue;
+    if (reach < 0 || !band_supported(az, dtype, reach, heun != 0)) return hipErrorInvalidValue;
     // FP32: the instance for reach 2 also serves smaller reaches (zero coefficients)
+    if (heun == 1) return f(banded_euler_kernel<2, 1024, 0, 1>);
+    if (heun == 2) return f(banded_euler_kernel<2, 1024, 0, 2>);
     if (dtype == 0) {
-        if (reach <= 2) return f(banded_euler_kernel<2, 1024, 0>);
-        return small ? f(banded_euler_kernel<3, 512, 0>) : f(banded_euler_kernel<3, 1024, 0>);
+        if (reach <= 2) return f(banded_euler_kernel<2, 1024, 0, 0>);
+        return small ? f(banded_euler_kernel<3, 512, 0, 0>) : f(banded_euler_kernel<3, 1024, 0, 0>);
     }
     if (dtype == 1) {
-        if (reach <= 1) return f(banded_euler_kernel<1, 1024, 1>);
-        return reach == 2 ? f(banded_euler_kernel<2, 1024, 1>) : f(banded_euler_kernel<3, 512, 1>);
+        if (reach <= 1) return f(banded_euler_kernel<1, 1024, 1, 0>);
+        return reach == 2 ? f(banded_euler_kernel<2, 1024, 1, 0>) : f(banded_euler_kernel<3, 512, 1, 0>);
     }
-    if (reach <= 1) return f(banded_euler_kernel<1, 1024, 2>);
-    if (reach == 2) return f(banded_euler_kernel<2, 1024, 2>);
-    return small ? f(banded_euler_kernel<3, 512, 2>) : f(banded_euler_kernel<3, 1024, 2>);
+    if (reach <= 1) return f(banded_euler_kernel<1, 1024, 2, 0>);
+    if (reach == 2) return f(banded_euler_kernel<2, 1024, 2, 0>);
+    return small ? f(banded_euler_kernel<3, 512, 2, 0>) : f(banded_euler_kernel<3, 1024, 2, 0>);
 }
 
+// heun: 0, or the pass.
 static hipError_t launch_banded(const BatchArgs& b, int blocks, int az, int dtype, size_t lds, hipStream_t s,
-                                int reach) {
-    return with_banded(az, dtype, reach, [&](auto kernel) {
+                                int reach, int heun) {
+    return with_banded(az, dtype, reach, heun, [&](auto kernel) {
         kernel<<<blocks + b.n, az / kBandO * 64, lds, s>>>(b);
         return hipSuccess;
     });
 }
 
-hipError_t prepare_banded(int az, int dtype, int reach, size_t lds) {
-    return with_banded(az, dtype, reach, [&](auto kernel) {
-        return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    });
+hipError_t prepare_banded(int az, int dtype, int reach, bool heun, size_t lds) {
+    hipError_t e = hipSuccess;
+    for (int pass = heun ? 1 : 0; pass <= (heun ? 2 : 0) && e == hipSuccess; ++pass)
+        e = with_banded(az, dtype, reach, pass, [&](auto kernel) {
+            return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        });
+    return e;
 }
 
 // Stencil kinds of a pass: 0 donor-cell strips, 1 / 2 Heun stages (strips), 3 donor-cell
-// flat chunks, 4 / 5 Heun stages (flat chunks), kStencilBanded the banded step (its
-// contraction and stencil are one kernel).
+// flat chunks, 4 / 5 Heun stages (flat chunks), kStencilBanded the banded Euler step and + 1,
+// + 2 the banded Heun passes (contraction and stencil in one kernel).
 constexpr int kStencilBanded = 16;
 
 // One pass: contraction, stencil, finalize, budget.
@@ -2506,9 +2579,9 @@ static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, in
     auto mark = [&](int k) {
         if (ev && e == hipSuccess) e = hipEventRecord(ev[k], s);
     };
-    if (stencil == kStencilBanded) {   // contraction and stencil in one kernel
+    if (stencil >= kStencilBanded) {   // contraction and stencil in one kernel
         mark(0);
-        e = launch_banded(b, grid[KT_SC], band_az, dtype, band_lds, s, band_reach);
+        e = launch_banded(b, grid[KT_SC], band_az, dtype, band_lds, s, band_reach, stencil - kStencilBanded);
         for (int k = 1; k < 5; ++k) mark(k);
         if (e != hipSuccess) return e;
         return hipGetLastError();
@@ -2553,7 +2626,7 @@ static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, in
     mark(2);
     finalize_kernel<<<grid[KT_FIN], 256, 0, s>>>(b, 0);
     mark(3);
-    budget_kernel<<<b.n, kBudgetThreads, 0, s>>>(b, bud);
+    budget_kernel<<<b.n, kBudgetThreads, 0, s>>>(b, bud, false);
     mark(4);
     if (e != hipSuccess) return e;
     return hipGetLastError();
@@ -2564,23 +2637,25 @@ hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int schem
     if (scheme == SCHEME_EULER_BANDED)
         return launch_pass(b, grid, dtype, kStencilBanded, BUD_STEP, s, ev, band_az, band_lds,
                            band_reach);
-    if (scheme != SCHEME_HEUN && scheme != SCHEME_HEUN_FLAT)
+    if (scheme != SCHEME_HEUN && scheme != SCHEME_HEUN_FLAT && scheme != SCHEME_HEUN_BANDED)
         return launch_pass(b, grid, dtype, scheme == SCHEME_EULER_FLAT ? 3 : 0, BUD_STEP, s, ev);
-    const int st = scheme == SCHEME_HEUN_FLAT ? 4 : 1;   // stencil of the first pass
+    // stencil of the first pass
+    const int st = scheme == SCHEME_HEUN_BANDED ? kStencilBanded + 1 : scheme == SCHEME_HEUN_FLAT ? 4 : 1;
     BatchArgs b1 = b;
     b1.s_par = 0;
-    hipError_t e = launch_pass(b1, grid, dtype, st, BUD_STAGE1, s, ev);
+    hipError_t e = launch_pass(b1, grid, dtype, st, BUD_STAGE1, s, ev, band_az, band_lds, band_reach);
     if (e != hipSuccess) return e;
     b1.s_par = 1;
-    return launch_pass(b1, grid, dtype, st + 1, BUD_STAGE2, s, ev ? ev + 5 : nullptr);
+    return launch_pass(b1, grid, dtype, st + 1, BUD_STAGE2, s, ev ? ev + 5 : nullptr, band_az, band_lds, band_reach);
 }
 
 hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int scheme, hipStream_t s) {
-    if (scheme != SCHEME_EULER_BANDED || n_steps < 1) return hipSuccess;
+    const bool heun = scheme == SCHEME_HEUN_BANDED;
+    if ((scheme != SCHEME_EULER_BANDED && !heun) || n_steps < 1) return hipSuccess;
     BatchArgs l = b;
-    l.step = n_steps;
-    l.s_par = (n_steps - 1) & 1;
-    budget_kernel<<<l.n, kBudgetThreads, 0, s>>>(l, BUD_BANDED);
+    l.step = n_steps - 1;
+    l.s_par = heun ? 1 : l.step & 1;
+    budget_kernel<<<l.n, kBudgetThreads, 0, s>>>(l, heun ? BUD_STAGE2 : BUD_STEP, true);
     return hipGetLastError();
 }
 
@@ -2604,7 +2679,7 @@ hipError_t launch_init(const StepArgs& a, const BatchArgs& one, hipStream_t s) {
     fill_u32_kernel<<<div_up(nb, 256), 256, 0, s>>>(a.bmax_next, nb, 0u);
     moments_kernel<<<div_up(a.C, 256), 256, 0, s>>>(a);
     finalize_kernel<<<a.fin_blocks, 256, 0, s>>>(one, 1);
-    budget_kernel<<<1, kBudgetThreads, 0, s>>>(one, BUD_INIT);
+    budget_kernel<<<1, kBudgetThreads, 0, s>>>(one, BUD_INIT, false);
     return hipGetLastError();
 }
 

@@ -60,12 +60,15 @@ constexpr int kFlatMaxNxM = (kFlatRounds * kFlatCells - kFlatCells - 8) / 3;
 // A block owns kBandCells consecutive cells (flat index) and every ordinate and walks
 // the polar levels in order; a wave owns kBandO consecutive azimuths of every level, a
 // lane one cell, so a block has n_az / kBandO waves.  LDS holds two levels: n_az rows of
-// kBandRow floats (the cells, with the neighbour on either side at the ends), for BF16 /
+// band_row floats (the cells, with the neighbour on either side at the ends), for BF16 /
 // FP16 operands followed by as many rows of the rounded operands.
 constexpr int SCHEME_EULER_BANDED = 5;
+// Both passes of the FP32 Heun + minmod scheme in the same form.
+constexpr int SCHEME_HEUN_BANDED = 6;
 constexpr int kBandCells = 64;
 constexpr int kBandO = 4;
-constexpr int kBandRow = kBandCells + 2;
+// (Heun passes: two neighbours on either side)
+__host__ __device__ constexpr int band_row(bool heun) { return kBandCells + (heun ? 4 : 2); }
 constexpr int kBandMaxReach = 3;
 // Largest half-width of the pair codes marked narrow by band_form (asn_host.hpp).
 constexpr int kBandNarrow = 8;
@@ -74,14 +77,18 @@ constexpr int kBandNarrow = 8;
 inline bool band_azimuths_supported(int az, int dtype) {
     return dtype == 0 ? az >= 8 && az <= 64 && az % 8 == 0 : az == 32 || az == 48 || az == 64;
 }
-inline bool band_supported(int az, int dtype, int reach) {
-    return band_azimuths_supported(az, dtype) && reach <= (dtype == 1 && az > 32 ? 2 : kBandMaxReach);
+// The Heun passes are FP32, reach 2 at most.
+inline bool band_supported(int az, int dtype, int reach, bool heun) {
+    return band_azimuths_supported(az, dtype) && (!heun || dtype == 0) &&
+           reach <= (heun || (dtype == 1 && az > 32) ? 2 : kBandMaxReach);
 }
 // Dynamic LDS of a banded block (the final sums reuse it).
-inline size_t band_lds_bytes(int az, int dtype) { return (size_t)(dtype == 0 ? 2 : 4) * az * kBandRow * 4; }
+inline size_t band_lds_bytes(int az, int dtype, bool heun) {
+    return (size_t)(dtype == 0 ? 2 : 4) * az * band_row(heun) * 4;
+}
 
 // Modes of the budget kernel.
-enum { BUD_STEP = 0, BUD_INIT = 1, BUD_STAGE1 = 2, BUD_STAGE2 = 3, BUD_BANDED = 4 };
+enum { BUD_STEP = 0, BUD_INIT = 1, BUD_STAGE1 = 2, BUD_STAGE2 = 3 };
 
 // Cells per block of the reduced-precision operand scale: the default, and the range
 // of powers of two a problem may choose (StepArgs::sb_log).  A block holds at least 64
@@ -197,18 +204,18 @@ inline bool can_fuse(int dtype, int scheme) { (void)dtype; return scheme == SCHE
 // Heun: two such passes (s_par 0, then 1), so the state returns to its buffer.
 // If ev is given, ev[5 k .. 5 k + 4] are recorded before, between and after
 // the four kernels of pass k.
-// band_az / band_lds: the banded step's azimuth count and dynamic LDS bytes (every
-// problem of a banded batch has that azimuth count); band_reach: the reach the banded
+// band_az / band_lds: the banded step's azimuth count and dynamic LDS bytes (the largest of
+// the batch); band_reach: the reach the banded
 // kernel is instantiated for (at least every problem's).
 hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int scheme, hipStream_t s,
                        hipEvent_t* ev = nullptr, int band_az = 0, size_t band_lds = 0,
                        int band_reach = 0);
 // Raise the dynamic LDS limit of the banded kernel that serves an azimuth count, operand type
 // and reach.
-hipError_t prepare_banded(int band_az, int dtype, int reach, size_t band_lds);
+hipError_t prepare_banded(int band_az, int dtype, int reach, bool heun, size_t band_lds);
 // Passes per step of a scheme.
 inline int passes_per_step(int scheme) {
-    return scheme == SCHEME_HEUN || scheme == SCHEME_HEUN_FLAT ? 2 : 1;
+    return scheme == SCHEME_HEUN || scheme == SCHEME_HEUN_FLAT || scheme == SCHEME_HEUN_BANDED ? 2 : 1;
 }
 // After the last of a call's n_steps steps: what the next step's launch would do for it (the
 // banded step's budget).

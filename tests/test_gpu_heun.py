@@ -54,6 +54,21 @@ def test_flat_chunk_and_strip_forms_match_oracle(nx, ny, dtype):
         assert rel_l2(phi, phi_ref) <= 2e-3
 
 
+@pytest.mark.parametrize("nx,ny", [(1, 3), (63, 2), (64, 3), (65, 4), (1363, 2)])
+@pytest.mark.parametrize("n_polar,n_azim,beta", [(32, 64, 4.5), (6, 24, 4.5), (20, 40, 6.0), (3, 56, 2.0), (1, 8, 4.5)])
+def test_passes_by_level_around_one_block(nx, ny, n_polar, n_azim, beta):
+    # product sets run both passes in 64-cell blocks (two halo columns each way, in the next row
+    # at a block's end), one launch a pass; the budget of step 1 is folded beside step 2
+    spec = wl.random_problem(nx + ny + n_azim, nx, ny, n_polar=n_polar, n_azim=n_azim, beta=beta)
+    psi0 = wl.random_state(nx + n_polar, spec.q, ny, nx)
+    state, phi, bud, _ = gpu_run(asn, spec, 2, psi0=psi0, scheme="heun")
+    ref, phi_ref, st = oracle_run(spec, 2, psi0=psi0, scheme="heun")
+    assert np.max(np.abs(state - ref)) <= 8e-6 * np.abs(ref).max()
+    assert np.max(np.abs(phi - phi_ref)) <= 8e-6 * np.abs(phi_ref).max()
+    assert bud["steps"] == 2
+    assert bud["max_residual"] <= max(1e-10, 64 * fp32_budget_floor(state, st.w))
+
+
 @pytest.mark.parametrize("norm", ["sym", "row"])
 def test_multi_step_random_fields(norm):
     spec = wl.random_problem(15, 70, 33, n_polar=4, n_azim=8, beta=4.5, t_final=0.3)
