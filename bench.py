@@ -197,7 +197,8 @@ def measured_traffic(kernel, spec):
 
 # the dominant kernel of each kernel form (its event slot in asn_step_timed).  The banded step is
 # one kernel, instantiated by reach and operand type; here it goes by its workload's azimuth count
-# and row width (FP32) or operand type.
+# and row width (FP32) or operand type.  The step that multiplies the nonzeros of a small
+# set's K, also one kernel, goes by the form it replaces.
 def dominant_kernel(res, spec, dtype):
     form = res["form"]
     lp = {"f32": 0, "bf16": 1, "f16": 2}[dtype]

@@ -114,7 +114,11 @@ enum { ASN_DT_STREAMING = 0, ASN_DT_STIFF = 1 };
  * ASN_FORM_AUTO:     the banded form where it applies; else BF16/FP16 fuse, and FP32
  *                    runs separate kernels from 2^25 cell-ordinates (nx <= 4088) and
  *                    fuses smaller problems, the faster forms on MI355X at the sizes
- *                    measured.  asn_workspace_size covers every form AUTO may take. */
+ *                    measured.  asn_workspace_size covers every form AUTO may take.
+ * AUTO and FUSED: where one block holds every ordinate (up to 640) and K is sparse (or there
+ * are few ordinates), one kernel that multiplies K's nonzeros takes the place of the fused or
+ * separate kernels, whose form it reports; FP32 Heun passes likewise, and banded on product
+ * sets with an azimuth count above. */
 enum { ASN_FORM_AUTO = 0, ASN_FORM_SEPARATE = 1, ASN_FORM_FUSED = 2, ASN_FORM_BANDED = 3 };
 
 #define ASN_BUDGET_LEN 8
@@ -302,7 +306,8 @@ asn_status asn_info(asn_problem p, double* dt, int64_t* steps_done, int64_t* ste
 /* Arithmetic of one contraction Y = K Psi: dense_flops = 2 Q^2 C; tile_flops =
  * 2 C times the number of K entries in the blocks the kernel multiplies (banded
  * step: the runs of its pairs, see asn_contraction_nonzero; in BF16 / FP16 every coupled
- * pair's whole n_azim x n_azim block, though the step multiplies the runs only).  K is
+ * pair's whole n_azim x n_azim block, though the step multiplies the runs only; where K's
+ * nonzeros are multiplied instead, the blocks of the form it reports).  K is
  * forward peaked (paper Section 3.5: the discrete artificial in-scattering is a
  * sparse matrix), so blocks whose entries are all zero in the stored operand type
  * are skipped: 128-row x 32-column tiles for BF16/FP16, and for FP32 the 16-row x

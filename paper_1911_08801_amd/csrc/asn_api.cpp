@@ -46,10 +46,12 @@ struct Layout {
     int64_t C = 0, P = 0;
     bool lowp = false, fused = false;
     bool flat = false;   // separate-kernel stencil over flat cell chunks (not column strips)
-    bool banded = false; // banded step: one kernel per step for a product ordinate set
+    bool banded = false; // banded step: one kernel per pass for a product ordinate set
+    bool sparse = false; // sparse step: one kernel per pass for any set with a sparse K
+    bool by_cells() const { return banded || sparse; }   // 64-cell blocks of every ordinate
     int ktab_len = 0;
     size_t off_psi0, off_psi1, off_Y, off_Kt, off_Klp, off_rdef, off_ktab, off_qi, off_coef, off_iso,
-        off_band, off_bcoef[3], off_bcxy,
+        off_band, off_bcoef[3], off_bcxy, off_sgroup, off_sord, off_srow, off_scoef,
         off_phi64, off_phipart, off_blk, off_fin, off_ypart, off_fix, off_delta, off_bmax0, off_bmax1, off_rec,
         off_tab, off_off, off_base, off_left, off_imp,
         total;
@@ -85,12 +87,25 @@ int64_t plane_pitch(int64_t C, int azim) {
     return (pad ? v : u) * asn::kScaleBlock;
 }
 
+// Mean sources of a group of the sparse step at most.  Its time goes with their number, the tiled
+// contraction's with its nonzero blocks: 200^2 x 492, us a step, 33 sources 96 (tiled 155; BF16 96 and
+// 137), 78 sources 144 (196; BF16 150 and 149), 177 sources 251 (235).  Up to 170 ordinates it is the
+// faster one at a dense K too (200^2 x 162 70 and 86, BF16 73 and 77; x 92 28 and 45).
+int sparse_sources(int Q) { return Q <= 170 ? Q : 64; }
+// Groups of the sparse step, and the chunks of sources it takes at most (the larger its K's
+// unions, the less it is worth), with the one that the kernel loads beyond the last.
+size_t sparse_groups(int Q) { return ((size_t)Q + asn::kBandO - 1) / asn::kBandO; }
+size_t sparse_chunks(int Q) {
+    return sparse_groups(Q) * ((sparse_sources(Q) + asn::kSparseChunk - 1) / asn::kSparseChunk) + 1;
+}
+
 Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int band_levels = 0,
-                   int band_azim = 0) {
+                   int band_azim = 0, bool sparse = false) {
     Layout L;
     L.banded = band_levels > 0;
-    // the banded reduced-precision step keeps the fused form's pending correction
-    if (L.banded) fused = dtype != ASN_GEMM_F32 && scheme == ASN_SCHEME_EULER;
+    L.sparse = sparse;
+    // the reduced-precision step of these forms keeps the fused form's pending correction
+    if (L.by_cells()) fused = dtype != ASN_GEMM_F32 && scheme == ASN_SCHEME_EULER;
     L.fused = fused;
     L.Q = Q;
     L.Qp = (int)round_up(Q, asn::kGemmBM);
@@ -102,14 +117,14 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
     L.tiles_y = (ny + asn::kTileY - 1) / asn::kTileY;
     // Separate stencils up to a width run over flat cell chunks, wider grids over
     // column strips; the ordinates are split into chunks sized to the grid below.
-    L.flat = !fused && !L.banded && ((scheme == ASN_SCHEME_EULER && nx <= asn::kFlatMaxNx) ||
+    L.flat = !fused && !L.by_cells() && ((scheme == ASN_SCHEME_EULER && nx <= asn::kFlatMaxNx) ||
                                      (scheme == ASN_SCHEME_HEUN && nx <= asn::kFlatMaxNxM));
     if (L.flat) {
         L.tiles_x = (int)((L.P + asn::kFlatCells - 1) / asn::kFlatCells);
         L.tiles_y = 1;
     }
     int tiles = L.tiles_x * L.tiles_y;
-    if (L.banded) {
+    if (L.by_cells()) {
         // one block per kBandCells cells, every ordinate: each cell's Phi
         // complete
         L.tiles_x = (int)((L.C + asn::kBandCells - 1) / asn::kBandCells);
@@ -144,8 +159,8 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
     const size_t plane = (size_t)L.P;
     L.off_psi0 = take((size_t)Q * plane * 4);
     L.off_psi1 = take((size_t)Q * plane * 4);
-    // the fused and banded steps keep Y in registers
-    L.off_Y = take(fused || L.banded ? 0 : (size_t)Q * plane * 4);
+    // the fused, banded and sparse steps keep Y in registers
+    L.off_Y = take(fused || L.by_cells() ? 0 : (size_t)Q * plane * 4);
     L.off_Kt = take((size_t)L.Qp * L.Qp * 4);
     L.off_Klp = take(L.lowp ? (size_t)L.Qp * L.Qp * 2 : 0);
     L.off_rdef = take((size_t)L.Qp * 4);
@@ -160,18 +175,23 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
     for (int r = 0; r < 3; ++r)
         L.off_bcoef[r] = take(L.banded ? band_coef_capacity(band_levels, band_azim, 2 * r + 3) * 4 : 0);
     L.off_bcxy = take(L.banded ? (size_t)Q * 8 : 0);
+    const size_t groups = sparse ? sparse_groups(Q) : 0, chunks = sparse ? sparse_chunks(Q) : 0;
+    L.off_sgroup = take(groups * sizeof(asn::SparseGroup));
+    L.off_sord = take(groups * asn::kBandO * sizeof(asn::SparseOrdinate));
+    L.off_srow = take(chunks * asn::kSparseChunk * 4);
+    L.off_scoef = take(chunks * asn::kSparseChunk * asn::kBandO * 4);
     L.off_qi = take((size_t)Q * sizeof(QInfo));
     L.off_coef = take(plane * 16);
     L.off_iso = take(plane * 4);
     L.off_phi64 = take(plane * 8);
     L.off_phipart = take((size_t)L.G * plane * 8);
-    // banded: the partials of a step are read in the next one, so once per state buffer
-    const size_t sets = L.banded ? 2 : 1;
+    // (these forms) the partials of a step are read in the next one, so once per state buffer
+    const size_t sets = L.by_cells() ? 2 : 1;
     L.off_blk = take(sets * tiles * L.G * 2 * 8);
-    L.off_fin = take(sets * std::max<size_t>(L.fin_blocks, L.banded ? tiles : 0) * 4 * 8);
-    L.off_ypart = take(L.lowp && !L.banded ? (size_t)(L.Qp / asn::kGemmBM) * plane * 8 : 0);
+    L.off_fin = take(sets * std::max<size_t>(L.fin_blocks, L.by_cells() ? tiles : 0) * 4 * 8);
+    L.off_ypart = take(L.lowp && !L.by_cells() ? (size_t)(L.Qp / asn::kGemmBM) * plane * 8 : 0);
     L.off_fix = take(L.lowp && !fused ? plane * 4 : 0);
-    L.off_delta = take(L.lowp && fused ? sets * plane * 4 : 0);   // banded: follows the state buffer
+    L.off_delta = take(L.lowp && fused ? sets * plane * 4 : 0);   // (sets: follows the state buffer)
     // block maxima for the smallest scale block (any block size a problem takes fits)
     L.off_bmax0 = take((size_t)asn::scale_blocks(L.P, scale_block_log(asn::kScaleBlockMin)) * 4);
     L.off_bmax1 = take((size_t)asn::scale_blocks(L.P, scale_block_log(asn::kScaleBlockMin)) * 4);
@@ -220,13 +240,18 @@ struct asn_problem_s {
     int blocks[asn::KT_COUNT];
     std::unique_ptr<asn::ImplicitSolver> imp;   // the implicit scheme's solver (else null)
     int band_levels = 0, band_azim = 0, band_reach = 0;   // banded step (else 0)
+    bool fuses = false;   // what asn_step_form reports of a sparse step: the form it replaces
+    bool flat = false;    // whether that form's stencil runs over flat cell chunks
+    // a step's block as if of a product set with so many azimuths, kBandO a wave
+    int block_az() const { return L.sparse ? asn::sparse_waves(L.Q) * asn::kBandO : band_azim; }
     size_t band_lds() const {
+        if (L.sparse) return asn::sparse_lds_bytes(L.Q);
         return asn::band_lds_bytes(band_azim, dtype, scheme == ASN_SCHEME_HEUN);
     }
 };
 
-// Problems that share their launches: a batch is one such group, a Heun batch up to two (the
-// problems whose passes are banded and those on separate kernels).
+// Problems that share their launches: a batch is up to four such groups (the problems whose steps
+// are banded, sparse with blocks of 8 or of 16 waves, and the others).
 struct Group {
     int first = 0, n = 0;    // of the batch's problems in launch order
     int scheme = 0;          // launch scheme (the flat-chunk, strip or banded form)
@@ -236,7 +261,7 @@ struct Group {
     int grid[asn::KT_COUNT] = {};
     asn::BatchArgs args{};
 };
-constexpr int kMaxGroups = 2;
+constexpr int kMaxGroups = 4;
 struct Plan {
     int n = 0, n_groups = 0;
     asn_problem order[asn::kMaxArm];
@@ -298,11 +323,11 @@ StepArgs make_args(asn_problem p, int cur) {
     a.bmax_cur = cur == 0 ? bm0 : bm1;
     a.bmax_next = cur == 0 ? bm1 : bm0;
     a.rec = reinterpret_cast<double*>(b + L.off_rec);
-    if (L.banded && L.lowp) {
+    if (L.by_cells() && L.lowp) {
         a.delta_next = a.delta + (cur ? 0 : L.P);
         a.delta += cur ? L.P : 0;
     }
-    if (L.banded && cur) {
+    if (L.by_cells() && cur) {
         a.blk_part += 2 * (size_t)L.tiles_x;
         a.fin_part += 4 * (size_t)L.tiles_x;
     }
@@ -315,6 +340,14 @@ StepArgs make_args(asn_problem p, int cur) {
         a.n_lev = p->band_levels;
         a.n_az = p->band_azim;
         a.reach = p->band_reach;
+    }
+    if (L.sparse) {
+        a.sp_group = reinterpret_cast<const asn::SparseGroup*>(b + L.off_sgroup);
+        a.sp_ord = reinterpret_cast<const asn::SparseOrdinate*>(b + L.off_sord);
+        a.sp_row = reinterpret_cast<const uint32_t*>(b + L.off_srow);
+        a.sp_coef = reinterpret_cast<const float*>(b + L.off_scoef);
+        a.band = reinterpret_cast<const uint4*>(a.sp_group);
+        a.n_az = p->block_az();
     }
     return a;
 }
@@ -473,6 +506,17 @@ bool band_candidate(int dtype, int scheme, int form, const asn_quadrature* q, in
            q->q_custom == 0 && q->icosahedron_order == 0 && q->n_polar >= 1;
 }
 
+// Whether a problem that does not take the banded step may take the sparse one (unless separate
+// kernels were asked for; it reports the form it replaces): its LDS rows fit a block, and a
+// plane's bytes 31 bits.  K must then also be sparse enough (sparse_form).
+bool sparse_candidate(int dtype, int scheme, int form, int Q, int64_t C) {
+    const bool heun = scheme == ASN_SCHEME_HEUN;
+    const bool ok = (form == ASN_FORM_AUTO || form == ASN_FORM_FUSED) &&
+                    (heun ? dtype == ASN_GEMM_F32 : scheme == ASN_SCHEME_EULER);
+    return ok && asn::sparse_lds_bytes(Q) <= 160 * 1024 &&
+           round_up(C, asn::kScaleBlock) * 4 < ((int64_t)1 << 31);
+}
+
 }  // namespace
 
 extern "C" {
@@ -518,6 +562,8 @@ asn_status asn_workspace_size(const asn_grid* grid, const asn_quadrature* quad,
     if (band_candidate(dtype, scheme, form, quad, (int64_t)grid->nx * grid->ny))
         total = std::max(total, make_layout(grid->nx, grid->ny, Q, dtype, scheme, false, quad->n_polar,
                                             quad->n_azim).total);
+    if (sparse_candidate(dtype, scheme, form, Q, (int64_t)grid->nx * grid->ny))
+        total = std::max(total, make_layout(grid->nx, grid->ny, Q, dtype, scheme, false, 0, 0, true).total);
     *bytes = total;
     return ASN_OK;
 }
@@ -618,31 +664,36 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
     bool banded = false;
     std::vector<uint32_t> ddesc;   // its level descriptors and coefficients
     std::array<std::vector<float>, 3> bcoef;
-    if (band_candidate(p->dtype, p->scheme, opt.step_form, quad, C)) {
-        // the values the kernel multiplies: FP32 K, or its BF16 / FP16 rounding
+    asn::SparseForm sf;
+    bool sparse = sparse_candidate(p->dtype, p->scheme, opt.step_form, Q, C);
+    const bool may_band = band_candidate(p->dtype, p->scheme, opt.step_form, quad, C);
+    const int Qp = (int)round_up(Q, asn::kGemmBM);
+    std::vector<uint16_t> Klp;   // BF16 / FP16 K and its row defects
+    std::vector<float> rdef((size_t)Qp, 0.f);
+    if (p->dtype != ASN_GEMM_F32) {
+        Klp.assign((size_t)Qp * Qp, 0);
+        quantise_kernel(Q, K.data(), p->dtype, Qp, Klp.data(), rdef.data());
+    }
+    if (may_band || sparse) {
+        // the values the kernels multiply: FP32 K, or its BF16 / FP16 rounding
         std::vector<float> K32((size_t)Q * Q);
-        if (p->dtype == ASN_GEMM_F32) {
-            for (size_t i = 0; i < K32.size(); ++i) K32[i] = (float)K[i];
-        } else {
-            std::vector<uint16_t> kq((size_t)Q * Q);
-            std::vector<float> rd((size_t)Q);
-            quantise_kernel(Q, K.data(), p->dtype, Q, kq.data(), rd.data());
-            for (size_t i = 0; i < K32.size(); ++i)
-                K32[i] = p->dtype == ASN_GEMM_BF16 ? asn::bf16_to_float(kq[i]) : asn::half_to_float(kq[i]);
-        }
-        banded = asn::band_form(quad->n_polar, quad->n_azim, K32.data(), asn::kBandMaxReach,
-                                asn::kBandNarrow, bf);
+        for (int q = 0; q < Q; ++q)
+            for (int k = 0; k < Q; ++k) {
+                const size_t i = (size_t)q * Q + k, j = (size_t)q * Qp + k;
+                K32[i] = p->dtype == ASN_GEMM_F32    ? (float)K[i]
+                         : p->dtype == ASN_GEMM_BF16 ? asn::bf16_to_float(Klp[j])
+                                                     : asn::half_to_float(Klp[j]);
+            }
+        banded = may_band &&
+                 asn::band_form(quad->n_polar, quad->n_azim, K32.data(), asn::kBandMaxReach, asn::kBandNarrow, bf);
         banded = banded && asn::band_supported(bf.azim, p->dtype, bf.reach, p->scheme == ASN_SCHEME_HEUN) &&
                  asn::band_scatter_tables(bf, p->dtype, ddesc, bcoef);
-        if (banded && p->dtype != ASN_GEMM_F32) {
-            // the kernel takes one row defect per level (the rows of a level hold the same
-            // values, so their FP64 sums agree; checked)
-            std::vector<uint16_t> kq((size_t)Q * Q);
-            std::vector<float> rd((size_t)Q);
-            quantise_kernel(Q, K.data(), p->dtype, Q, kq.data(), rd.data());
-            for (int q = 0; banded && q < Q; ++q)
-                if (rd[(size_t)q] != rd[(size_t)(q / quad->n_azim) * quad->n_azim]) banded = false;
-        }
+        // the kernel takes one row defect per level (the rows of a level hold the same values, so
+        // their FP64 sums agree; checked)
+        for (int q = 0; banded && p->dtype != ASN_GEMM_F32 && q < Q; ++q)
+            if (rdef[(size_t)q] != rdef[(size_t)(q / quad->n_azim) * quad->n_azim]) banded = false;
+        sparse = sparse && !banded &&
+                 asn::sparse_form(Q, K32.data(), asn::kBandO, asn::kSparseChunk, sparse_chunks(Q) - 1, sf);
     }
     if (opt.step_form == ASN_FORM_BANDED && !banded) {
         delete p;
@@ -660,6 +711,9 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
     } else {
         p->L = make_layout(p->nx, p->ny, Q, p->dtype, p->scheme,
                            use_fused(p->dtype, p->scheme, opt.step_form, p->nx, p->ny, Q));
+        p->fuses = p->L.fused;
+        p->flat = p->L.flat;
+        if (sparse) p->L = make_layout(p->nx, p->ny, Q, p->dtype, p->scheme, false, 0, 0, true);
     }
     const Layout& L = p->L;
     if (workspace) {
@@ -684,12 +738,6 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
     std::vector<float> Kt((size_t)L.Qp * L.Qp, 0.f);
     for (int q = 0; q < Q; ++q)
         for (int k = 0; k < Q; ++k) Kt[(size_t)k * L.Qp + q] = (float)K[(size_t)q * Q + k];
-    std::vector<uint16_t> Klp;
-    std::vector<float> rdef((size_t)L.Qp, 0.f);
-    if (L.lowp) {
-        Klp.assign((size_t)L.Qp * L.Qp, 0);
-        quantise_kernel(Q, K.data(), p->dtype, L.Qp, Klp.data(), rdef.data());
-    }
     // k-steps per M-tile whose tile of the stored K (FP32 or 16-bit) has a nonzero entry.
     // Steps inside the tile's own ordinate range come last: the fused epilogue then
     // reads rows that the block (and its neighbours) has just streamed through L2.
@@ -792,6 +840,24 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
             dcxy.push_back(v.cy);
         }
     }
+    std::vector<asn::SparseGroup> sgroup;   // sparse kernel
+    std::vector<asn::SparseOrdinate> sord;
+    std::vector<uint32_t> srow;
+    if (sparse) {
+        for (size_t g = 0; g + 1 < sf.first.size(); ++g) {
+            asn::SparseGroup v{};
+            for (int o = 0; o < asn::kBandO; ++o) {
+                const int q = sf.order[g * asn::kBandO + o];
+                v.ord[o] = (uint32_t)q << 4 | (uint32_t)qi[q].dir;
+                const bool again = (int)g * asn::kBandO + o >= Q;
+                sord.push_back({qi[q].cx, qi[q].cy, rdef[q], 0.f, again ? 0.0 : qi[q].w, 0.0});
+            }
+            v.first = sf.first[g];
+            v.chunks = sf.first[g + 1] - sf.first[g];
+            sgroup.push_back(v);
+        }
+        for (int k : sf.src) srow.push_back(4u * (uint32_t)(k * asn::kBandCells));
+    }
     auto bail = [&](asn_status st) {
         if (p->owns) (void)hipFree(p->base);
         delete p;
@@ -823,6 +889,16 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
           copy_tables() != hipSuccess ||
           asn::prepare_banded(bf.azim, p->dtype, bf.reach, p->scheme == ASN_SCHEME_HEUN, p->band_lds()) !=
               hipSuccess)) ||
+        (sparse &&
+         (hipMemcpyAsync(b + L.off_sgroup, sgroup.data(), sgroup.size() * sizeof(sgroup[0]), hipMemcpyHostToDevice,
+                         p->stream) != hipSuccess ||
+          hipMemcpyAsync(b + L.off_sord, sord.data(), sord.size() * sizeof(sord[0]), hipMemcpyHostToDevice,
+                         p->stream) != hipSuccess ||
+          hipMemcpyAsync(b + L.off_srow, srow.data(), srow.size() * 4, hipMemcpyHostToDevice, p->stream) !=
+              hipSuccess ||
+          hipMemcpyAsync(b + L.off_scoef, sf.coef.data(), sf.coef.size() * 4, hipMemcpyHostToDevice, p->stream) !=
+              hipSuccess ||
+          asn::prepare_sparse(asn::sparse_waves(Q), p->dtype, p->scheme == ASN_SCHEME_HEUN, p->band_lds()) != hipSuccess)) ||
         (L.lowp && hipMemcpyAsync(b + L.off_Klp, Klp.data(), Klp.size() * 2,
                                   hipMemcpyHostToDevice, p->stream) != hipSuccess) ||
         hipMemcpyAsync(b + L.off_coef, coef.data(), coef.size() * 16, hipMemcpyHostToDevice,
@@ -936,6 +1012,7 @@ asn_status asn_get_state(asn_problem p, float* psi, int32_t on_device) {
 // The scheme the kernels are launched with: a separate-kernel step whose stencil
 // runs over flat cell chunks (Euler or Heun) has a launch form of its own.
 static int launch_scheme(asn_problem p) {
+    if (p->L.sparse) return p->scheme == ASN_SCHEME_HEUN ? asn::SCHEME_HEUN_SPARSE : asn::SCHEME_EULER_SPARSE;
     if (p->L.banded) return p->scheme == ASN_SCHEME_HEUN ? asn::SCHEME_HEUN_BANDED : asn::SCHEME_EULER_BANDED;
     if (!p->L.flat) return p->scheme;
     return p->scheme == ASN_SCHEME_HEUN ? asn::SCHEME_HEUN_FLAT : asn::SCHEME_EULER_FLAT;
@@ -959,12 +1036,12 @@ asn_status asn_step(asn_problem p, int64_t n_steps) {
     }
     HIP_TRY(arm_single(p, n_steps));
     asn::BatchArgs b = single_batch(p);
-    const size_t lds = p->L.banded ? p->band_lds() : 0;
+    const size_t lds = p->L.by_cells() ? p->band_lds() : 0;
     for (int64_t i = 0; i < n_steps; ++i) {
         b.step = (int)i;
         b.s_par = (int)(i & 1);
         HIP_TRY(asn::launch_step(b, p->blocks, p->dtype, launch_scheme(p), p->stream, nullptr,
-                                 p->band_azim, lds, p->band_reach));
+                                 p->block_az(), lds, p->band_reach));
     }
     HIP_TRY(asn::launch_last_budget(b, (int)n_steps, launch_scheme(p), p->stream));
     p->cur ^= state_flip(p->scheme, n_steps);
@@ -1008,8 +1085,8 @@ asn_status asn_step_timed(asn_problem p, int64_t n_steps, double kernel_ms[5]) {
         bt.step = (int)i;
         bt.s_par = (int)(i & 1);
         const hipError_t e = asn::launch_step(
-            bt, p->blocks, p->dtype, launch_scheme(p), p->stream, &ev[(size_t)i * per], p->band_azim,
-            p->L.banded ? p->band_lds() : 0, p->band_reach);
+            bt, p->blocks, p->dtype, launch_scheme(p), p->stream, &ev[(size_t)i * per], p->block_az(),
+            p->L.by_cells() ? p->band_lds() : 0, p->band_reach);
         if (e != hipSuccess) {
             st = fail(ASN_E_HIP, std::string("step launch failed: ") + hipGetErrorString(e));
             break;
@@ -1056,7 +1133,8 @@ static asn_status check_batch(asn_problem* probs, int32_t n) {
             return fail(ASN_E_INVALID, "problems of a batch must share the time scheme");
         if (probs[i]->imp)
             return fail(ASN_E_UNSUPPORTED, "implicit problems step alone (asn_step)");
-        if (probs[i]->L.fused != probs[0]->L.fused)
+        auto fused = [&](int32_t k) { return probs[k]->L.sparse ? probs[k]->fuses : probs[k]->L.fused; };
+        if (fused(i) != fused(0))
             return fail(ASN_E_INVALID, "problems of a batch must share the kernel form "
                                        "(asn_step_form; ask for ASN_FORM_FUSED or ASN_FORM_SEPARATE "
                                        "when their sizes differ)");
@@ -1067,7 +1145,7 @@ static asn_status check_batch(asn_problem* probs, int32_t n) {
         // (Heun: by the grid's width, also where the banded passes run)
         if (probs[0]->scheme == ASN_SCHEME_HEUN
                 ? (probs[i]->nx <= asn::kFlatMaxNxM) != (probs[0]->nx <= asn::kFlatMaxNxM)
-                : probs[i]->L.flat != probs[0]->L.flat)
+                : probs[i]->flat != probs[0]->flat)
             return fail(ASN_E_INVALID, std::string("problems of a batch must share the stencil form: ") +
                                        "separate-kernel steps use flat cell chunks up to nx = " +
                                        std::to_string(asn::kFlatMaxNx) + " (Euler) or " +
@@ -1086,13 +1164,16 @@ static size_t plan_bytes(int n) {
     return 2 * (size_t)n * sizeof(StepArgs) + (size_t)asn::KT_COUNT * (n + kMaxGroups) * sizeof(int) +
            2 * (size_t)asn::kMaxArm * sizeof(int);
 }
+static int group_kind(asn_problem p) {
+    return p->L.banded ? 0 : p->L.sparse ? (asn::sparse_waves(p->L.Q) == 8 ? 1 : 2) : 3;
+}
 static void make_plan(asn_problem* probs, int32_t n, char* dev, Plan& p, int* index, StepArgs* tab, int* off) {
     p.n = n;
     int at = 0;
-    for (int banded = 1; banded >= 0; --banded) {
+    for (int kind = 0; kind < kMaxGroups; ++kind) {
         const int first = at;
         for (int32_t i = 0; i < n; ++i)
-            if ((int)probs[i]->L.banded == banded) {
+            if (group_kind(probs[i]) == kind) {
                 if (index) index[at] = i;
                 p.order[at++] = probs[i];
             }
@@ -1121,8 +1202,8 @@ static void make_plan(asn_problem* probs, int32_t n, char* dev, Plan& p, int* in
                 if (i == 0) row[0] = 0;
                 row[i + 1] = row[i] + q->blocks[kind];
             }
-            if (q->L.banded) g.band_lds = std::max(g.band_lds, q->band_lds());
-            g.band_az = std::max(g.band_az, q->band_azim);
+            if (q->L.by_cells()) g.band_lds = std::max(g.band_lds, q->band_lds());
+            g.band_az = std::max(g.band_az, q->block_az());
             g.band_reach = std::max(g.band_reach, q->band_reach);
         }
         for (int kind = 0; kind < asn::KT_COUNT; ++kind) g.grid[kind] = o[kind * (g.n + 1) + g.n];
@@ -1357,7 +1438,9 @@ asn_status asn_info(asn_problem p, double* dt, int64_t* steps_done, int64_t* ste
 
 asn_status asn_step_form(asn_problem p, int32_t* form) {
     if (!p || !form) return fail(ASN_E_INVALID, "NULL argument");
-    *form = p->L.banded && p->scheme == ASN_SCHEME_EULER ? ASN_FORM_BANDED : p->L.fused ? ASN_FORM_FUSED : ASN_FORM_SEPARATE;
+    *form = p->L.banded && p->scheme == ASN_SCHEME_EULER       ? ASN_FORM_BANDED
+            : (p->L.sparse ? p->fuses : p->L.fused) ? ASN_FORM_FUSED
+                                                    : ASN_FORM_SEPARATE;
     return ASN_OK;
 }
 

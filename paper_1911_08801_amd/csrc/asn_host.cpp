@@ -400,6 +400,69 @@ bool band_form(int levels, int azim, const float* K32, int max_reach, int narrow
     return true;
 }
 
+bool sparse_form(int Q, const float* K32, int width, int chunk, size_t max_chunks, SparseForm& out) {
+    const size_t words = ((size_t)Q + 63) / 64;
+    std::vector<uint64_t> bits(words * Q, 0);   // sources of each ordinate
+    size_t nz = 0;
+    for (int q = 0; q < Q; ++q)
+        for (int k = 0; k < Q; ++k)
+            if (K32[(size_t)q * Q + k] != 0.f) {
+                bits[q * words + k / 64] |= 1ull << (k % 64);
+                ++nz;
+            }
+    if (nz > max_chunks * chunk * width) return false;
+    out = SparseForm();
+    out.first.push_back(0);
+    std::vector<char> taken(Q, 0);
+    std::vector<uint64_t> have(words);
+    int next = 0, left = Q;
+    while (left > 0) {
+        std::fill(have.begin(), have.end(), 0);
+        const size_t at = out.order.size();
+        while (taken[next]) ++next;
+        for (int n = 0; n < width && left > 0; ++n) {
+            int best = -1, cost = 0;
+            auto consider = [&](int q) {
+                if (taken[q]) return;
+                int c = 0;
+                for (size_t w = 0; w < words; ++w)
+                    c += __builtin_popcountll(bits[q * words + w] & ~have[w]);
+                if (best < 0 || c < cost) {
+                    best = q;
+                    cost = c;
+                }
+            };
+            if (n == 0) best = next;
+            else {
+                const float* row = K32 + (size_t)out.order[at] * Q;
+                for (int q = 0; q < Q; ++q)
+                    if (row[q] != 0.f) consider(q);
+                for (int q = next; best < 0 && q < Q; ++q)
+                    if (!taken[q]) best = q;
+            }
+            out.order.push_back(best);
+            taken[best] = 1;
+            --left;
+            for (size_t w = 0; w < words; ++w) have[w] |= bits[best * words + w];
+        }
+        while ((int)(out.order.size() - at) < width) out.order.push_back(out.order[at]);
+        const size_t base = out.src.size();
+        for (int k = 0; k < Q; ++k)
+            if (have[k / 64] >> (k % 64) & 1) out.src.push_back(k);
+        while ((out.src.size() - base) % chunk) out.src.push_back(out.src[base]);
+        out.first.push_back((int)(out.src.size() / chunk));
+        if (out.src.size() > max_chunks * chunk) return false;
+        int seen = -1;
+        for (size_t i = base; i < out.src.size(); ++i) {
+            const bool fill = out.src[i] <= seen;
+            seen = std::max(seen, out.src[i]);
+            for (int n = 0; n < width; ++n)
+                out.coef.push_back(fill ? 0.f : K32[(size_t)out.order[at + n] * Q + out.src[i]]);
+        }
+    }
+    return true;
+}
+
 bool band_scatter_tables(const BandForm& bf, int dtype, std::vector<uint32_t>& desc,
                          std::array<std::vector<float>, 3>& coef) {
     const int azim = bf.azim, half = azim / 2;

@@ -76,6 +76,17 @@ constexpr uint32_t kBandOuter2 = 32;         // an output other than j - 1 .. j 
 constexpr uint32_t kBandOuter3 = 64;         // ... at d >= 3
 bool band_scatter_tables(const BandForm& bf, int dtype, std::vector<uint32_t>& desc,
                          std::array<std::vector<float>, 3>& coef);
+// The tables of the sparse step: the ordinates in groups of `width` that share sources, in order
+// (order; the last group filled up with its first ordinate), and per group the ordinates that any
+// of its rows of K32[Q][Q] has a nonzero at, in `chunk`s, as rows of K in that order: src, and
+// coef, width a source (zeros fill the last chunk up, at its first source).  first: the chunks
+// before each group, and in all.  A group is an ordinate not taken yet and those of its sources
+// that add the fewest sources of their own.  False when there would be more than max_chunks.
+struct SparseForm {
+    std::vector<int> order, src, first;
+    std::vector<float> coef;
+};
+bool sparse_form(int Q, const float* K32, int width, int chunk, size_t max_chunks, SparseForm& out);
 // The run of a pair code: first offset and length.
 inline void band_run(uint32_t code, int azim, int& lo, int& len) {
     const int s = (int)(code & 63u);

@@ -1770,18 +1770,22 @@ __global__ void materialize_done_kernel(StepArgs a) {
 // threads in a fixed order.  Thread 0 reads the record while the partials arrive and
 // writes it back whole.
 constexpr int kBudgetThreads = 1024;
-// T: threads of the block (at most kBudgetThreads); n_fin, n_blk: partials of either kind.
+// T: threads of the block (at most kBudgetThreads); n_fin, n_blk: partials of either kind; U: of
+// each in flight a thread (1: and the record loaded after them, for the fewest registers).
+template <int U = 4>
 __device__ __forceinline__ void budget_fold(const StepArgs& a, int n_fin, int n_blk, int T, int mode) {
+#pragma clang fp contract(off)   // (the same bits from each kernel it is part of)
     const bool init = mode == BUD_INIT;
     ASN_G double* rec = gp(a.rec);
     double r[REC_LEN];
-    if (threadIdx.x == 0)
+    auto record = [&] {
 #pragma unroll
         for (int k = 0; k < REC_LEN; ++k) r[k] = rec[k];
+    };
+    if (U > 1 && threadIdx.x == 0) record();
     double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const ASN_G double4* fp = reinterpret_cast<const ASN_G double4*>(gp(a.fin_part));
     const ASN_G double2* bp = reinterpret_cast<const ASN_G double2*>(gp(a.blk_part));
-    constexpr int U = 4;
     for (int i0 = threadIdx.x; i0 < max(n_fin, n_blk); i0 += T * U) {
         double4 v[U];
         double2 w[U];
@@ -1811,6 +1815,7 @@ __device__ __forceinline__ void budget_fold(const StepArgs& a, int n_fin, int n_
     block_sum_n<kBudgetThreads / 64, 6>(s, T / 64, tot);
     __syncthreads();
     if (threadIdx.x != 0) return;
+    if (U == 1) record();
     const double m_next = a.area * tot[0];
     const double abs_next = a.area * tot[1];
     auto store = [&]() {
@@ -1949,8 +1954,8 @@ __global__ void broadcast_kernel(float* psi, const float* cell, int Q, int64_t C
 //    and budget kernel each.  A pass without its contraction's round trip through Y reads psi
 //    (its three y neighbours from L2) and writes it, the second also reads psi^n, where its
 //    result goes.  400^2 x 512 981 -> 531 us a step, 700^2 x 1152 6.78 -> 4.32 ms, 50^2 x 128
-//    70 -> 33 us, 2000 x 1000 x 32 0.81 -> 0.41 ms.  Its bounds are VALU issue (the limiters are
-//    half the pass) and registers, 128 a lane: one block of 16 waves in a CU at 64 azimuths.
+//    70 -> 33 us, 2000 x 1000 x 32 0.81 -> 0.41 ms.  Registers bound it, 128 a lane: 16 waves in
+//    a CU, with about 120 vector instructions more a wave and level than forward Euler.
 // ---------------------------------------------------------------------------
 // The band tables are written by the host before any step and only read by the
 // kernels: reached through the constant address space, their uniform loads are scalar
@@ -2117,6 +2122,83 @@ __device__ __forceinline__ void round_pair(float s0, float s1, float& x0, float&
     }
 }
 
+// E - e_b of the operand scale of the 64 cells from c0, from the maxima of the 64-cell blocks of
+// their scale block.
+__device__ __forceinline__ int operand_scale(const StepArgs& a, int c0, int lane) {
+    const int first = (c0 >> a.sb_log) << (a.sb_log - 6), b = first + lane;
+    unsigned bits = 0u;
+    if (lane < 1 << (a.sb_log - 6) && b < a.tiles_x) bits = gp(a.bmax_cur)[b];
+    const float bm = __uint_as_float(wave_max_u32(bits));
+    int e = 0;
+    if (bm > 0.f) (void)frexpf(bm, &e);
+    return __builtin_amdgcn_readfirstlane(kScaleExp - max(e, -100));
+}
+
+// The end of a 64-cell block of NW waves, each with some of the ordinates of every cell (slots:
+// LDS that is free again).
+template <bool LP>
+__device__ __forceinline__ void finish_cells(const StepArgs& a, float* slots, int NW, int wave, int lane,
+                                             int local, const float4& cf, float isov, float dv, double phacc,
+                                             double ypacc, float mx, double defect, double outflow) {
+    const int cell = local * kBandCells + lane;
+    const bool in = cell < (int)a.C;
+    // Phi^{n+1} of each cell: the waves' partials in a fixed order.  Wave 0 holds the block's
+    // cells, so it takes over what finalize_kernel does for the other forms: Phi, Phi / W and
+    // the mass partials.
+    // Reduced precision also sums Y and turns its particle defect into the new state's pending
+    // correction (the neighbours read the old one, so there are two buffers), and takes the
+    // block's maximum for the next operand scale.
+    double* red = reinterpret_cast<double*>(slots);
+    double* redy = red + NW * kBandCells;
+    red[wave * kBandCells + lane] = phacc;
+    if constexpr (LP) {
+        redy[wave * kBandCells + lane] = ypacc;
+        const unsigned m = wave_max_u32(__float_as_uint(mx));
+        if (lane == 0) reinterpret_cast<unsigned*>(redy + NW * kBandCells)[wave] = m;
+    }
+    lds_barrier();
+    if (wave == 0) {
+        double fin[4] = {0.0, 0.0, 0.0, 0.0};
+        if (in) {
+            double phi = red[lane];
+            for (int g = 1; g < NW; ++g) phi += red[g * kBandCells + lane];
+            // Phi of psi^n, in FP64; and of its stored values
+            const double old = gp(a.phi64)[cell], stored = LP ? old - a.W * (double)dv : old;
+            // the physical scattering's part of the collision defect, sum_q w_q bs (iso -
+            // psi_q) = bs (W iso - Phi), once per cell
+            defect += (double)cf.y * (a.W * (double)isov - stored);
+            gp(a.iso)[cell] = (float)(phi / a.W);
+            if constexpr (LP) {
+                double ys = redy[lane];
+                for (int g = 1; g < NW; ++g) ys += redy[g * kBandCells + lane];
+                ys += a.W * (double)(isov + dv);   // sum_q w_q Y, Y = iso^ + delta + (Y^ - iso^)
+                const float d = (float)(-(double)cf.z * (ys - old) / a.W);
+                gp(a.delta_next)[cell] = d;
+                fin[3] = a.W * (double)d;
+                phi += fin[3];
+            }
+            gp(a.phi64)[cell] = phi;
+            fin[0] = phi;
+            fin[1] = (double)cf.x * phi;
+            fin[2] = (double)cf.w;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) fin[k] = wave_sum(fin[k]);
+        if (lane == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) gp(a.fin_part)[4 * (size_t)local + k] = fin[k];
+            if constexpr (LP) {
+                const unsigned* m = reinterpret_cast<const unsigned*>(redy + NW * kBandCells);
+                unsigned t = m[0];
+                for (int g = 1; g < NW; ++g) t = max(t, m[g]);
+                gp(a.bmax_next)[local] = t;
+            }
+        }
+    }
+    double sums[2] = {defect, outflow};
+    block_sum_n<16, 2>(sums, NW, gp(a.blk_part) + 2 * (size_t)local);
+}
+
 // T: the largest block (512 threads up to 32 azimuths: the reach-3 instance then keeps its
 // queue in registers).  DT: operand type of the contraction.  HS: 0 forward Euler, 1 / 2 the
 // first / second pass of the Heun + minmod scheme (FP32; muscl_kernel's fluxes, so the rows hold
@@ -2157,19 +2239,12 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
         cf = gp(a.coef)[cell];
         isov = gp(a.iso)[cell];
     }
-    // reduced precision: the pending correction of the cell, and E - e_b of its operand scale,
-    // from the maxima of the 64-cell blocks of its scale block
+    // reduced precision: the pending correction of the cell, and E - e_b of its operand scale
     float dv = 0.f;
     int sc = 0;
     if constexpr (LP) {
         if (in) dv = gp(a.delta)[cell];
-        const int first = (c0 >> a.sb_log) << (a.sb_log - 6), b = first + lane;
-        unsigned bits = 0u;
-        if (lane < 1 << (a.sb_log - 6) && b < a.tiles_x) bits = gp(a.bmax_cur)[b];
-        const float bm = __uint_as_float(wave_max_u32(bits));
-        int e = 0;
-        if (bm > 0.f) (void)frexpf(bm, &e);
-        sc = __builtin_amdgcn_readfirstlane(kScaleExp - max(e, -100));
+        sc = operand_scale(a, c0, lane);
     }
     // boundary of the lane's cell: 1 / 2 first / last column, 4 / 8 first / last row; 16 a
     // padding cell
@@ -2452,61 +2527,239 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
         }
     }
 
-    // Phi^{n+1} of each cell: the waves' partials in a fixed order.  Wave 0 holds the block's
-    // cells, so it takes over what finalize_kernel does for the other forms: Phi, Phi / W and
-    // the mass partials.
-    // Reduced precision also sums Y and turns its particle defect into the new state's pending
-    // correction (the neighbours read the old one, so there are two buffers), and takes the
-    // block's maximum for the next operand scale.
-    double* red = reinterpret_cast<double*>(slots);
-    double* redy = red + NW * kBandCells;
-    red[wave * kBandCells + lane] = phacc;
+    finish_cells<LP>(a, slots, NW, wave, lane, local, cf, isov, dv, phacc, ypacc, mx, defect, outflow);
+}
+
+// ---------------------------------------------------------------------------
+// 6. Step for any ordinate set whose K is sparse and whose values at 64 cells fit LDS
+//    (forward Euler; FP32 Heun).
+//    A K with 13 % nonzeros (162 ordinates of the icosahedron: 21 a row) leaves the matrix cores
+//    nearly all zeros whatever the tile, and few ordinates leave most of a 128-row tile empty.
+//    Block = kBandCells consecutive cells x every ordinate, all their values (reduced precision:
+//    rounded operands) in LDS; a wave takes groups of kBandO ordinates that share most of their
+//    sources (sparse_form: 32 for those four) and multiplies the union of their rows' nonzeros:
+//    an LDS value serves four outputs, coefficients are scalar.  The neighbours' values are loaded
+//    beside the products, from L2.  The rest of the step as in the banded kernel.
+//    What bounds it: 280^2 x 162 takes 43 us (2.4 TB/s on 8 B per update); without the products
+//    26 us, without scalar misses the products alone would be 21 us of VALU issue.  The two
+//    overlap only between a CU's blocks (three at 162 ordinates), which start together.  A chunk
+//    of eight sources a trip to the scalar tables instead of four: 55 -> 47 us; ten waves a block
+//    59 (the tables' 35 KB outrun the scalar cache sooner); neighbours or a group's constants
+//    fetched a group ahead: no gain; halo columns in LDS instead of loads: 58, and reduced
+//    precision 42 -> 33 us with the LDS that saves.  Against a contraction over 128 x 128 tiles
+//    with the step in its epilogue, us a step: 280^2 x 162 FP32 117 -> 46, BF16 108 -> 50;
+//    50^2 x 12 25 -> 4.5; 400^2 x 492 505 -> 322, BF16 442 -> 329; 200^2 x 128 (16 azimuths) BF16
+//    52 -> 27; Heun 280^2 x 162 217 -> 95.
+// ---------------------------------------------------------------------------
+template <int DT, int HS, int T>
+__global__ __launch_bounds__(T, T == 512 ? 6 : 4) void sparse_step_kernel(BatchArgs B) {
+    constexpr int O = kBandO, ROW = kBandCells, NW = T / 64;
+    constexpr bool LP = DT != 0;
+    extern __shared__ float slots[];
+    int pi, local;
+    if ((int)blockIdx.x < B.n) {   // the last pass's budget, one block per problem
+        pi = blockIdx.x;
+        const int last = HS == 2 ? B.step : B.step - 1;   // its step
+        if (last < 0 || gp(B.limit)[pi] <= last) return;
+        BatchArgs P = B;
+        P.s_par ^= 1;
+        const StepArgs a = args_of(P, pi);
+        budget_fold<1>(a, a.tiles_x, a.tiles_x, T,
+                       HS == 0 ? BUD_STEP : HS == 1 ? BUD_STAGE2 : BUD_STAGE1);
+        return;
+    }
+    if (!locate(B, KT_SC, xcd_remap(blockIdx.x - B.n, gridDim.x - B.n), pi, local)) return;
+    const StepArgs a = args_of(B, pi);   // by value: no reloads after stores
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nx = a.nx, ny = a.ny, Q = a.Q, C = (int)a.C;
+    const int c0 = local * kBandCells, cell = c0 + lane;
+    const bool in = cell < C;
+
+    float4 cf = make_float4(0.f, 0.f, 0.f, 0.f);
+    float isov = 0.f;
+    if (in) {
+        cf = gp(a.coef)[cell];
+        isov = gp(a.iso)[cell];
+    }
+    // 1 / 2 first / last column, 4 / 8 first / last row; 16 a padding cell
+    const int y = cell / nx, x = cell - y * nx;
+    int at = in ? (x == 0 ? 1 : 0) | (x == nx - 1 ? 2 : 0) | (y == 0 ? 4 : 0) | (y == ny - 1 ? 8 : 0) : 16;
+    const bool edge = __ballot(at != 0) != 0;
+    // reduced precision: the pending corrections of the cell and its four neighbours (0 for a
+    // ghost), the operand scale
+    float dv = 0.f, dl = 0.f, dr = 0.f, dd = 0.f, du = 0.f;
+    int sc = 0;
     if constexpr (LP) {
-        redy[wave * kBandCells + lane] = ypacc;
-        const unsigned m = wave_max_u32(__float_as_uint(mx));
-        if (lane == 0) reinterpret_cast<unsigned*>(redy + NW * kBandCells)[wave] = m;
+        if (in) {
+            const float* dp = a.delta + cell;
+            dv = gp(dp)[0];
+            if (!(at & 1)) dl = gp(dp)[-1];
+            if (!(at & 2)) dr = gp(dp)[1];
+            if (!(at & 4)) dd = gp(dp)[-nx];
+            if (!(at & 8)) du = gp(dp)[nx];
+        }
+        sc = operand_scale(a, c0, lane);
+    }
+    // one buffer descriptor per plane; kOOB reads 0 (the vacuum ghost)
+    const uint32_t voff = 4u * (uint32_t)cell;
+    auto plane = [&](const float* base, int q) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base + (size_t)q * (size_t)a.P), 0,
+                                                 (int)(uint32_t)(a.P * 4), kRsrcWord3);
+    };
+    auto load = [&](__amdgpu_buffer_rsrc_t r, uint32_t off) {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    };
+    // byte offsets in a plane of the cells 1 (and for Heun 2) columns and rows away
+    auto x_off = [&](int d) { return in && x + d >= 0 && x + d < nx ? voff + 4u * (uint32_t)d : kOOB; };
+    auto y_off = [&](int d) {
+        return in && y + d >= 0 && y + d < ny ? voff + 4u * (uint32_t)(d * nx) : kOOB;
+    };
+    const uint32_t x_m = x_off(-1), x_p = x_off(1), x_mm = HS ? x_off(-2) : 0u, x_pp = HS ? x_off(2) : 0u;
+    const uint32_t y_m = y_off(-1), y_p = y_off(1), y_mm = HS ? y_off(-2) : 0u, y_pp = HS ? y_off(2) : 0u;
+
+    // the block's values, straight into LDS, all in flight; reduced precision: through registers,
+    // the rounded operands
+    if constexpr (LP) {
+        constexpr int U = 16;
+        for (int q0 = wave; q0 < Q; q0 += U * NW) {
+            float v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = load(plane(a.psi, min(q0 + u * NW, Q - 1)), voff);
+#pragma unroll
+            for (int u = 0; u < U; u += 2) {
+                float x0, x1;
+                round_pair<DT>(ldexpf(v[u] - isov, sc), ldexpf(v[u + 1] - isov, sc), x0, x1);
+                const int q = q0 + u * NW;
+                if (q < Q) slots[q * ROW + lane] = x0;
+                if (q + NW < Q) slots[(q + NW) * ROW + lane] = x1;
+            }
+        }
+    } else {
+        using Lds = __attribute__((address_space(3))) void;
+        for (int q = wave; q < Q; q += NW)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(plane(a.psi, q), (Lds*)(slots + q * ROW), 4, voff, 0, 0, 0);
+        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
     }
     lds_barrier();
-    if (wave == 0) {
-        double fin[4] = {0.0, 0.0, 0.0, 0.0};
-        if (in) {
-            double phi = red[lane];
-            for (int g = 1; g < NW; ++g) phi += red[g * kBandCells + lane];
-            // Phi of psi^n, in FP64; and of its stored values
-            const double old = gp(a.phi64)[cell], stored = LP ? old - a.W * (double)dv : old;
-            // the physical scattering's part of the collision defect, sum_q w_q bs (iso -
-            // psi_q) = bs (W iso - Phi), once per cell
-            defect += (double)cf.y * (a.W * (double)isov - stored);
-            gp(a.iso)[cell] = (float)(phi / a.W);
-            if constexpr (LP) {
-                double ys = redy[lane];
-                for (int g = 1; g < NW; ++g) ys += redy[g * kBandCells + lane];
-                ys += a.W * (double)(isov + dv);   // sum_q w_q Y, Y = iso^ + delta + (Y^ - iso^)
-                const float d = (float)(-(double)cf.z * (ys - old) / a.W);
-                gp(a.delta_next)[cell] = d;
-                fin[3] = a.W * (double)d;
-                phi += fin[3];
+
+    double phacc = 0.0, defect = 0.0, outflow = 0.0, ypacc = 0.0;
+    float mx = 0.f;
+    const int groups = (Q + O - 1) / O;
+    for (int g = wave; g < groups; g += NW) {
+        const ASN_K SparseGroup* d = kp(a.sp_group) + g;
+        uint32_t od[O];
+#pragma unroll
+        for (int o = 0; o < O; ++o) od[o] = d->ord[o];   // ordinate << 4 | its direction bits
+        // its own value (FP32: in LDS) and its neighbours' (Heun: the second ones upwind, the ones
+        // downwind; psi^n)
+        float v0[O], ux[O], uy[O], ux2[HS ? O : 1], uy2[HS ? O : 1], dx1[HS ? O : 1], dy1[HS ? O : 1],
+            old[HS == 2 ? O : 1];
+#pragma unroll
+        for (int o = 0; o < O; ++o) {
+            const int q = (int)(od[o] >> 4);
+            const __amdgpu_buffer_rsrc_t r = plane(a.psi, q);
+            if constexpr (LP) v0[o] = load(r, voff);
+            ux[o] = load(r, od[o] & 1 ? x_m : x_p);
+            uy[o] = load(r, od[o] & 4 ? y_m : y_p);
+            if constexpr (HS != 0) {
+                ux2[o] = load(r, od[o] & 1 ? x_mm : x_pp);
+                dx1[o] = load(r, od[o] & 1 ? x_p : x_m);
+                uy2[o] = load(r, od[o] & 4 ? y_mm : y_pp);
+                dy1[o] = load(r, od[o] & 4 ? y_p : y_m);
             }
-            gp(a.phi64)[cell] = phi;
-            fin[0] = phi;
-            fin[1] = (double)cf.x * phi;
-            fin[2] = (double)cf.w;
+            if constexpr (HS == 2) old[o] = load(plane(a.psi_new, q), voff);
+            if constexpr (!LP) v0[o] = slots[q * ROW + lane];
+        }
+        float acc[O];
+#pragma unroll
+        for (int o = 0; o < O; ++o) acc[o] = 0.f;
+        constexpr int S = kSparseChunk;
+        const char* lds = reinterpret_cast<const char*>(slots + lane);
+        // The coefficients of all groups are more than the scalar cache holds, and scalar loads return
+        // in no order, so each chunk waits for one trip to L2: chunks of as many coefficients as
+        // there are registers, and the next chunk's row offsets with them.
+        const ASN_K uint32_t* rp = kp(a.sp_row) + S * d->first;
+        const ASN_K float* kc = kp(a.sp_coef) + S * O * d->first;
+        uint32_t row[S];
+#pragma unroll
+        for (int i = 0; i < S; ++i) row[i] = rp[i];
+        for (int c = d->chunks; c > 0; --c) {
+            float v[S], k[S * O];
+#pragma unroll
+            for (int i = 0; i < S * O; ++i) k[i] = kc[i];
+#pragma unroll
+            for (int i = 0; i < S; ++i) v[i] = *reinterpret_cast<const float*>(lds + row[i]);
+            kc += S * O;
+            rp += S;
+#pragma unroll
+            for (int i = 0; i < S; ++i) row[i] = rp[i];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < S; ++i)
+#pragma unroll
+                for (int o = 0; o < O; ++o) acc[o] = fmaf(k[i * O + o], v[i], acc[o]);
+            asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
+#pragma unroll
+            for (int i = 0; i < S; ++i) asm volatile("" : "+s"(row[i]));   // (a value, not a load to move)
+        }
+        float cx[O], cy[O], rq[O];
+        double w[O];   // (0 where the last group repeats an ordinate)
+#pragma unroll
+        for (int o = 0; o < O; ++o) {
+            const ASN_K SparseOrdinate* t = kp(a.sp_ord) + (O * g + o);
+            cx[o] = t->cx;
+            cy[o] = t->cy;
+            rq[o] = t->rdef;
+            w[o] = t->w;
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) fin[k] = wave_sum(fin[k]);
-        if (lane == 0) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) gp(a.fin_part)[4 * (size_t)local + k] = fin[k];
-            if constexpr (LP) {
-                const unsigned* m = reinterpret_cast<const unsigned*>(redy + NW * kBandCells);
-                unsigned t = m[0];
-                for (int g = 1; g < NW; ++g) t = max(t, m[g]);
-                gp(a.bmax_next)[local] = t;
+        for (int o = 0; o < O; ++o) {
+            const int q = (int)(od[o] >> 4), right = od[o] & 1, up = od[o] & 4;
+            const float v = v0[o] + dv;
+            if (edge) {   // outflow through the faces on the boundary
+                float vx = v, vy = v;   // the value there
+                if constexpr (HS != 0) {
+                    vx += 0.5f * minmod(v - ux[o], dx1[o] - v);
+                    vy += 0.5f * minmod(v - uy[o], dy1[o] - v);
+                }
+                outflow += w[o] * (double)((at & (right ? 2 : 1) ? cx[o] * vx : 0.f) + (at & (up ? 8 : 4) ? cy[o] * vy : 0.f));
             }
+            // the banded kernel's chain
+            float t1 = fmaf(cf.y, isov - v0[o], cf.w);
+            t1 = fmaf(-cf.x, v, t1);
+            if constexpr (HS != 0) {
+                auto flux = [&](float u, float u2, float d1) {
+                    const float gr = v - u;
+                    return fmaf(0.5f, minmod(gr, d1 - v) - minmod(u - u2, gr), gr);
+                };
+                t1 = fmaf(-cy[o], flux(uy[o], uy2[o], dy1[o]), t1);
+                t1 = fmaf(-cx[o], flux(ux[o], ux2[o], dx1[o]), t1);
+            } else if constexpr (LP) {
+                t1 = fmaf(cy[o], uy[o] + (up ? dd : du) - v, t1);
+                t1 = fmaf(cx[o], ux[o] + (right ? dl : dr) - v, t1);
+            } else {
+                t1 = fmaf(cy[o], uy[o] - v, t1);
+                t1 = fmaf(cx[o], ux[o] - v, t1);
+            }
+            float dy;
+            if constexpr (LP) {   // Y^ - iso^ = 2^(e_b - E) sum + r_q dev, dev = psi^ - iso^
+                const float dev = v0[o] - isov, ya = fmaf(rq[o], dev, ldexpf(acc[o], -sc));
+                ypacc += w[o] * (double)ya;
+                dy = ya - dev;
+            } else {
+                dy = acc[o] - v0[o];
+            }
+            float nv = v + fmaf(cf.z, dy, t1);
+            if constexpr (HS == 2) nv = 0.5f * (old[o] + nv);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(nv), plane(a.psi_new, q), voff, 0, 0);
+            phacc += w[o] * (double)nv;
+            defect += w[o] * (double)(cf.z * dy);
+            if constexpr (LP) mx = fmaxf(mx, fabsf(nv));
         }
     }
-    double sums[2] = {defect, outflow};
-    block_sum_n<16, 2>(sums, NW, gp(a.blk_part) + 2 * (size_t)local);
+    lds_barrier();
+    finish_cells<LP>(a, slots, NW, wave, lane, local, cf, isov, dv, phacc, ypacc, mx, defect, outflow);
 }
 
 // ---------------------------------------------------------------------------
@@ -2566,10 +2819,37 @@ hipError_t prepare_banded(int az, int dtype, int reach, bool heun, size_t lds) {
     return e;
 }
 
+template <int T, typename F>
+static hipError_t with_sparse(int dtype, int heun, F&& f) {
+    if (heun == 1) return f(sparse_step_kernel<0, 1, T>);
+    if (heun == 2) return f(sparse_step_kernel<0, 2, T>);
+    if (dtype == 0) return f(sparse_step_kernel<0, 0, T>);
+    return dtype == 1 ? f(sparse_step_kernel<1, 0, T>) : f(sparse_step_kernel<2, 0, T>);
+}
+
+static hipError_t launch_sparse(const BatchArgs& b, int blocks, int waves, int dtype, size_t lds, hipStream_t s,
+                                int heun) {
+    auto launch = [&](auto kernel) {
+        kernel<<<blocks + b.n, waves * 64, lds, s>>>(b);
+        return hipSuccess;
+    };
+    return waves == 8 ? with_sparse<512>(dtype, heun, launch) : with_sparse<1024>(dtype, heun, launch);
+}
+
+hipError_t prepare_sparse(int waves, int dtype, bool heun, size_t lds) {
+    hipError_t e = hipSuccess;
+    auto prepare = [&](auto kernel) {
+        return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    };
+    for (int pass = heun ? 1 : 0; pass <= (heun ? 2 : 0) && e == hipSuccess; ++pass)
+        e = waves == 8 ? with_sparse<512>(dtype, pass, prepare) : with_sparse<1024>(dtype, pass, prepare);
+    return e;
+}
+
 // Stencil kinds of a pass: 0 donor-cell strips, 1 / 2 Heun stages (strips), 3 donor-cell
 // flat chunks, 4 / 5 Heun stages (flat chunks), kStencilBanded the banded Euler step and + 1,
-// + 2 the banded Heun passes (contraction and stencil in one kernel).
-constexpr int kStencilBanded = 16;
+// + 2 the banded Heun passes (contraction and stencil in one kernel), kStencilSparse likewise.
+constexpr int kStencilBanded = 16, kStencilSparse = 32;
 
 // One pass: contraction, stencil, finalize, budget.
 static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, int stencil,
@@ -2581,7 +2861,9 @@ static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, in
     };
     if (stencil >= kStencilBanded) {   // contraction and stencil in one kernel
         mark(0);
-        e = launch_banded(b, grid[KT_SC], band_az, dtype, band_lds, s, band_reach, stencil - kStencilBanded);
+        e = stencil >= kStencilSparse
+                ? launch_sparse(b, grid[KT_SC], band_az / kBandO, dtype, band_lds, s, stencil - kStencilSparse)
+                : launch_banded(b, grid[KT_SC], band_az, dtype, band_lds, s, band_reach, stencil - kStencilBanded);
         for (int k = 1; k < 5; ++k) mark(k);
         if (e != hipSuccess) return e;
         return hipGetLastError();
@@ -2634,13 +2916,16 @@ static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, in
 
 hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int scheme, hipStream_t s,
                        hipEvent_t* ev, int band_az, size_t band_lds, int band_reach) {
-    if (scheme == SCHEME_EULER_BANDED)
-        return launch_pass(b, grid, dtype, kStencilBanded, BUD_STEP, s, ev, band_az, band_lds,
-                           band_reach);
-    if (scheme != SCHEME_HEUN && scheme != SCHEME_HEUN_FLAT && scheme != SCHEME_HEUN_BANDED)
+    if (scheme == SCHEME_EULER_BANDED || scheme == SCHEME_EULER_SPARSE)
+        return launch_pass(b, grid, dtype, scheme == SCHEME_EULER_SPARSE ? kStencilSparse : kStencilBanded,
+                           BUD_STEP, s, ev, band_az, band_lds, band_reach);
+    if (passes_per_step(scheme) == 1)
         return launch_pass(b, grid, dtype, scheme == SCHEME_EULER_FLAT ? 3 : 0, BUD_STEP, s, ev);
     // stencil of the first pass
-    const int st = scheme == SCHEME_HEUN_BANDED ? kStencilBanded + 1 : scheme == SCHEME_HEUN_FLAT ? 4 : 1;
+    const int st = scheme == SCHEME_HEUN_BANDED   ? kStencilBanded + 1
+                   : scheme == SCHEME_HEUN_SPARSE ? kStencilSparse + 1
+                   : scheme == SCHEME_HEUN_FLAT   ? 4
+                                                  : 1;
     BatchArgs b1 = b;
     b1.s_par = 0;
     hipError_t e = launch_pass(b1, grid, dtype, st, BUD_STAGE1, s, ev, band_az, band_lds, band_reach);
@@ -2650,8 +2935,8 @@ hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int schem
 }
 
 hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int scheme, hipStream_t s) {
-    const bool heun = scheme == SCHEME_HEUN_BANDED;
-    if ((scheme != SCHEME_EULER_BANDED && !heun) || n_steps < 1) return hipSuccess;
+    if (scheme < SCHEME_EULER_BANDED || n_steps < 1) return hipSuccess;
+    const bool heun = passes_per_step(scheme) == 2;
     BatchArgs l = b;
     l.step = n_steps - 1;
     l.s_par = heun ? 1 : l.step & 1;

@@ -87,6 +87,31 @@ inline size_t band_lds_bytes(int az, int dtype, bool heun) {
     return (size_t)(dtype == 0 ? 2 : 4) * az * band_row(heun) * 4;
 }
 
+// A step's form for any ordinate set with a sparse K, also one kernel a pass (Heun: FP32).  A block
+// owns kBandCells cells and every ordinate, whose values (BF16 / FP16: rounded operands) are all in
+// LDS, a row each, so their number is bounded by it.  Tables: sparse_form (asn_host.hpp).
+constexpr int SCHEME_EULER_SPARSE = 7;
+constexpr int SCHEME_HEUN_SPARSE = 8;
+constexpr int kSparseChunk = 8;   // sources multiplied at a time
+// Waves of a block: 8, and 16 where LDS has room for one block a CU (200^2 x 492: 142 -> 96 us; at
+// 252 ordinates, two blocks a CU, 54.7 and 54.8; at 288 in BF16 70 and 74).
+inline int sparse_waves(int Q) { return 2 * Q * kBandCells * 4 > 160 * 1024 ? 16 : 8; }
+inline size_t sparse_lds_bytes(int Q) {
+    const size_t rows = (size_t)Q * kBandCells * 4;
+    const size_t sums = (size_t)sparse_waves(Q) * (kBandCells * 16 + 4);   // finish_cells
+    return rows > sums ? rows : sums;
+}
+struct SparseGroup {
+    uint32_t ord[kBandO];     // ordinate << 4 | its direction bits (the last group: repeated)
+    int first, chunks;        // its chunks of sources
+    int pad[2];
+};
+struct SparseOrdinate {
+    float cx, cy, rdef, pad;
+    double w;
+    double pad2;
+};
+
 // Modes of the budget kernel.
 enum { BUD_STEP = 0, BUD_INIT = 1, BUD_STAGE1 = 2, BUD_STAGE2 = 3 };
 
@@ -171,6 +196,13 @@ struct StepArgs {
     const float* bcoef7;
     const float2* bcxy;
     int n_lev, n_az, reach;
+    // sparse step (then also `band` is set and n_az such that the budget's fold has its threads):
+    // groups of ordinates, per position in them what the step takes of an ordinate, LDS byte
+    // offsets of the sources' rows and their coefficients, kBandO a source
+    const SparseGroup* sp_group;
+    const SparseOrdinate* sp_ord;
+    const uint32_t* sp_row;
+    const float* sp_coef;
 };
 
 // Kernel kinds of one step, each with its own block decomposition.
@@ -213,9 +245,14 @@ hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int schem
 // Raise the dynamic LDS limit of the banded kernel that serves an azimuth count, operand type
 // and reach.
 hipError_t prepare_banded(int band_az, int dtype, int reach, bool heun, size_t band_lds);
+// The same of the sparse kernel of so many waves.
+hipError_t prepare_sparse(int waves, int dtype, bool heun, size_t lds);
 // Passes per step of a scheme.
 inline int passes_per_step(int scheme) {
-    return scheme == SCHEME_HEUN || scheme == SCHEME_HEUN_FLAT || scheme == SCHEME_HEUN_BANDED ? 2 : 1;
+    return scheme == SCHEME_HEUN || scheme == SCHEME_HEUN_FLAT || scheme == SCHEME_HEUN_BANDED ||
+                   scheme == SCHEME_HEUN_SPARSE
+               ? 2
+               : 1;
 }
 // After the last of a call's n_steps steps: what the next step's launch would do for it (the
 // banded step's budget).

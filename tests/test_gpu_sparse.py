@@ -1,0 +1,91 @@
+"""GPU parity of the step that keeps every ordinate of 64 cells in LDS and multiplies the
+nonzeros of any K (icosahedron sets, product sets without a banded kernel), against the
+oracle on the same seeded inputs, and of what lies beyond its limits (a dense K of many
+ordinates, more ordinates than LDS holds)."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from gpu_util import fp32_budget_floor, gpu_run, oracle_run, rel_l2
+from test_gpu_banded_lowprec import _emulated
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+from paper_1911_08801_amd import asn  # noqa: E402
+
+# (n_polar, n_azim, icosahedron order, beta): one ordinate group and a part of one, groups filled
+# up (42, 162 ordinates), 16 waves (362), dense K of 162 and (too dense) 252 ordinates, more than
+# LDS holds (812); product sets
+SETS = [(1, 2, 0, 4.5), (3, 2, 0, 4.5), (1, 4, 2, 4.5), (1, 4, 3, 4.5), (1, 4, 5, 4.5), (1, 4, 7, 4.5),
+        (1, 4, 5, 80.0), (1, 4, 6, 80.0), (1, 4, 10, 4.5), (5, 10, 0, 4.5), (8, 16, 0, 6.0)]
+GRIDS = [(1, 1), (3, 70), (63, 2), (64, 3), (65, 4)]
+
+
+def _spec(nx, ny, n_polar, n_azim, ico, beta):
+    spec = wl.random_problem(nx + ny + n_azim + ico, nx, ny, n_polar=n_polar, n_azim=n_azim, beta=beta)
+    spec.ico_order = ico
+    return spec, wl.random_state(nx + n_polar, spec.q, ny, nx)
+
+
+@pytest.mark.parametrize("nx,ny", GRIDS)
+@pytest.mark.parametrize("n_polar,n_azim,ico,beta", SETS)
+@pytest.mark.parametrize("scheme", ["euler", "heun"])
+def test_two_steps_match_oracle(nx, ny, n_polar, n_azim, ico, beta, scheme):
+    spec, psi0 = _spec(nx, ny, n_polar, n_azim, ico, beta)
+    state, phi, bud, _ = gpu_run(asn, spec, 2, psi0=psi0, scheme=scheme)
+    ref, phi_ref, st = oracle_run(spec, 2, psi0=psi0, scheme=scheme)
+    assert np.max(np.abs(state - ref)) <= 8e-6 * np.abs(ref).max()
+    assert np.max(np.abs(phi - phi_ref)) <= 8e-6 * np.abs(phi_ref).max()
+    assert bud["steps"] == 2
+    assert bud["max_residual"] <= max(1e-10, 64 * fp32_budget_floor(state, st.w))
+
+
+@pytest.mark.parametrize("nx,ny,block", [(1, 1, 256), (63, 2, 64), (65, 4, 256), (130, 40, 4096)])
+@pytest.mark.parametrize("n_polar,n_azim,ico,beta", [(1, 2, 0, 4.5), (1, 4, 3, 4.5), (1, 4, 7, 4.5), (1, 4, 6, 80.0),
+                                                     (8, 16, 0, 4.5)])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_reduced_precision_step_matches_emulation(nx, ny, block, n_polar, n_azim, ico, beta, dtype):
+    spec, psi0 = _spec(nx, ny, n_polar, n_azim, ico, beta)
+    state, _, _, _ = gpu_run(asn, spec, 1, psi0=psi0, dtype=dtype, scale_block=block)
+    ref, _ = _emulated(spec, 1, psi0, dtype, block)
+    assert np.max(np.abs(state - ref)) <= 2e-6 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("scheme,dtype", [("euler", "f32"), ("euler", "bf16"), ("heun", "f32")])
+def test_batch_of_all_kinds_equals_alone_bitwise(scheme, dtype):
+    # 8 and 16 waves, beyond the limits, and (Heun) a banded one, in an order that interleaves them
+    sets = [(1, 4, 10, 4.5), (1, 4, 5, 4.5), (1, 4, 7, 4.5), (1, 4, 6, 80.0), (5, 10, 0, 4.5), (4, 8, 0, 4.5)]
+    specs = [_spec(20 + 13 * i, 9 + i, *s)[0] for i, s in enumerate(sets)]
+    kw = dict(dtype=dtype, scheme=scheme, form="fused")
+    limits = [5, 2, 7, 4, 3, 6]
+    alone = []
+    for spec, n in zip(specs, limits):
+        p = asn.from_spec(spec, **kw)
+        asn.asn_step(p, n)
+        alone.append((asn.asn_get_state(p), asn.asn_scalar_flux(p), asn.asn_mass_budget(p)))
+        p.close()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        probs = [asn.from_spec(s, **kw) for s in specs]
+        b = asn.asn_batch_create(probs)
+        for k in range(2):
+            asn.asn_batch_step(b, 4, limits=[max(0, n - 4 * k) for n in limits])
+        for p, (state, phi, bud), n in zip(probs, alone, limits):
+            assert asn.asn_info(p)["steps_done"] == n
+            assert np.array_equal(asn.asn_get_state(p), state)
+            assert np.array_equal(asn.asn_scalar_flux(p), phi)
+            assert asn.asn_mass_budget(p) == bud
+        b.close()
+        for p in probs:
+            p.close()
+    torch.cuda.synchronize()
+
+
+def test_automatic_form_equals_separate_kernels():
+    # 350^2 x 362 cell-ordinates: reported as separate kernels
+    spec, _ = _spec(350, 350, 1, 4, 7, 4.5)
+    state, phi, _, _ = gpu_run(asn, spec, 2, form="auto")
+    sep, phi_s, _, _ = gpu_run(asn, spec, 2, form="separate")
+    assert rel_l2(state, sep) <= 1e-6 and rel_l2(phi, phi_s) <= 1e-6
