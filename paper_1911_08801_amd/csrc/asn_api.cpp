@@ -953,10 +953,11 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
     return ASN_OK;
 }
 
-static asn_status finish_set_state(asn_problem p) {
+// cell: as launch_init.
+static asn_status finish_set_state(asn_problem p, const float* cell = nullptr) {
     p->steps_done = 0;
     HIP_TRY(arm_single(p, 1));
-    HIP_TRY(asn::launch_init(p->tab[p->cur], single_batch(p), p->stream));
+    HIP_TRY(asn::launch_init(p->tab[p->cur], single_batch(p), p->stream, cell));
     if (p->imp) {
         const Layout& L = p->L;
         std::string ierr;
@@ -988,7 +989,7 @@ asn_status asn_set_state_isotropic(asn_problem p, const float* cell, int32_t on_
                            on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, p->stream));
     HIP_TRY(asn::launch_broadcast(dst, stage, L.Q, L.C, L.P, p->stream));
     if (!on_device) HIP_TRY(hipStreamSynchronize(p->stream));
-    return finish_set_state(p);
+    return finish_set_state(p, stage);
 }
 
 asn_status asn_get_state(asn_problem p, float* psi, int32_t on_device) {

@@ -1887,18 +1887,48 @@ __global__ __launch_bounds__(kBudgetThreads) void budget_kernel(BatchArgs B, int
         budget_fold(a, a.fin_blocks, mode == BUD_INIT ? 0 : a.tiles_x * a.tiles_y * a.G, kBudgetThreads, mode);
 }
 
+// Tables that the host writes before any step and the kernels only read: reached through the
+// constant address space, their uniform loads are scalar (SMEM) loads, which do not wait behind
+// the vector memory counter.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define ASN_K __attribute__((address_space(4)))
+#else
+#define ASN_K
+#endif
+template <typename T>
+__device__ __forceinline__ const ASN_K T* kp(const T* p) {
+    return (const ASN_K T*)p;
+}
+
 // ---------------------------------------------------------------------------
-// Moments of a freshly set state: Phi partial (G = 1) and block max |psi|.
+// Moments of a freshly set state: Phi partial (G = 1) and block max |psi|.  `cell`: the value
+// of every ordinate of a cell where the state is isotropic (the same sum, without reading the
+// state), or NULL.  A call that sets an isotropic state, with four cells and eight planes a thread
+// in broadcast_kernel: 1024^2 x 2048 4.97 -> 2.53 ms (3.4 TB/s of writes), 700^2 x 1152 1.35 ->
+// 0.79 ms, 50^2 x 128 93 -> 70 us; one that sets any, 311 x 173 x 288 154 -> 118 us.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void moments_kernel(StepArgs a) {
+__global__ __launch_bounds__(256) void moments_kernel(StepArgs a, const float* cell) {
     const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (c >= a.C) return;
     double phi = 0.0;
     float mx = 0.f;
-    for (int q = 0; q < a.Q; ++q) {
-        const float v = a.psi[(size_t)q * a.P + c];
-        phi += a.qi[q].w * (double)v;
-        mx = fmaxf(mx, fabsf(v));
+    const ASN_K QInfo* qi = kp(a.qi);
+    if (cell) {
+        const float v = gp(cell)[c];
+        for (int q = 0; q < a.Q; ++q) phi += qi[q].w * (double)v;
+        mx = fabsf(v);
+    } else {
+        constexpr int U = 16;   // planes in flight: a thread's reads are a chain otherwise
+        for (int q0 = 0; q0 < a.Q; q0 += U) {
+            float v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = q0 + u < a.Q ? gp(a.psi)[(size_t)(q0 + u) * a.P + c] : 0.f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (q0 + u < a.Q) phi += qi[q0 + u].w * (double)v[u];
+                mx = fmaxf(mx, fabsf(v[u]));
+            }
+        }
     }
     a.phi_part[c] = phi;
     atomicMax(&a.bmax_cur[c >> (a.band ? 6 : a.sb_log)], __float_as_uint(mx));
@@ -1909,10 +1939,16 @@ __global__ void fill_u32_kernel(unsigned* p, int64_t n, unsigned v) {
     if (i < n) p[i] = v;
 }
 
-__global__ void broadcast_kernel(float* psi, const float* cell, int Q, int64_t C, int64_t P) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int q = blockIdx.y;
-    if (c < P && q < Q) psi[(size_t)q * P + c] = (c < C) ? cell[c] : 0.f;
+// Four cells and kBroadcast planes a thread (P is a multiple of four).
+constexpr int kBroadcast = 8;
+__global__ __launch_bounds__(256) void broadcast_kernel(float* psi, const float* cell, int Q, int64_t C, int64_t P) {
+    const int64_t c = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
+    if (c >= P) return;
+    f32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = c + i < C ? cell[c + i] : 0.f;
+    for (int q = blockIdx.y * kBroadcast; q < min(Q, ((int)blockIdx.y + 1) * kBroadcast); ++q)
+        *reinterpret_cast<f32x4*>(psi + (size_t)q * P + c) = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -1957,19 +1993,6 @@ __global__ void broadcast_kernel(float* psi, const float* cell, int Q, int64_t C
 //    70 -> 33 us, 2000 x 1000 x 32 0.81 -> 0.41 ms.  Registers bound it, 128 a lane: 16 waves in
 //    a CU, with about 120 vector instructions more a wave and level than forward Euler.
 // ---------------------------------------------------------------------------
-// The band tables are written by the host before any step and only read by the
-// kernels: reached through the constant address space, their uniform loads are scalar
-// (SMEM) loads, which do not wait behind the vector memory counter.
-#if defined(__HIP_DEVICE_COMPILE__)
-#define ASN_K __attribute__((address_space(4)))
-#else
-#define ASN_K
-#endif
-template <typename T>
-__device__ __forceinline__ const ASN_K T* kp(const T* p) {
-    return (const ASN_K T*)p;
-}
-
 // Awaits scalar loads here (and what is in flight in LDS), so that they are issued together
 // and not one by one where each is used.
 template <int M>
@@ -2958,11 +2981,11 @@ hipError_t launch_arm(int* limit, int* base, int n, const ArmArgs& v, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_init(const StepArgs& a, const BatchArgs& one, hipStream_t s) {
+hipError_t launch_init(const StepArgs& a, const BatchArgs& one, hipStream_t s, const float* cell) {
     const int64_t nb = scale_blocks(a.P, a.band ? 6 : a.sb_log);
     fill_u32_kernel<<<div_up(nb, 256), 256, 0, s>>>(a.bmax_cur, nb, 0u);
     fill_u32_kernel<<<div_up(nb, 256), 256, 0, s>>>(a.bmax_next, nb, 0u);
-    moments_kernel<<<div_up(a.C, 256), 256, 0, s>>>(a);
+    moments_kernel<<<div_up(a.C, 256), 256, 0, s>>>(a, cell);
     finalize_kernel<<<a.fin_blocks, 256, 0, s>>>(one, 1);
     budget_kernel<<<1, kBudgetThreads, 0, s>>>(one, BUD_INIT, false);
     return hipGetLastError();
@@ -2977,7 +3000,7 @@ hipError_t launch_materialize(const StepArgs& a, hipStream_t s) {
 
 hipError_t launch_broadcast(float* psi, const float* cell, int Q, int64_t C, int64_t P,
                             hipStream_t s) {
-    dim3 g(div_up(P, 256), Q);
+    dim3 g(div_up(P, 1024), div_up(Q, kBroadcast));
     broadcast_kernel<<<g, 256, 0, s>>>(psi, cell, Q, C, P);
     return hipGetLastError();
 }

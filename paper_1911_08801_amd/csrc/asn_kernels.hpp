@@ -265,7 +265,7 @@ struct ArmArgs {
 };
 hipError_t launch_arm(int* limit, int* base, int n, const ArmArgs& v, hipStream_t s);
 // Moments of the current state (after set_state): phi64, iso, bmax, budget record.
-hipError_t launch_init(const StepArgs& a, const BatchArgs& one, hipStream_t s);
+hipError_t launch_init(const StepArgs& a, const BatchArgs& one, hipStream_t s, const float* cell = nullptr);
 // Fused reduced precision: fold the pending correction into the stored state.
 hipError_t launch_materialize(const StepArgs& a, hipStream_t s);
 // psi[q][c] = cell[c] for all q (pitch P), zero padding.
