@@ -115,7 +115,7 @@ enum { ASN_DT_STREAMING = 0, ASN_DT_STIFF = 1 };
  *                    runs separate kernels from 2^25 cell-ordinates (nx <= 4088) and
  *                    fuses smaller problems, the faster forms on MI355X at the sizes
  *                    measured.  asn_workspace_size covers every form AUTO may take.
- * AUTO and FUSED: where one block holds every ordinate (up to 640) and K is sparse (or there
+ * AUTO and FUSED: where one block holds every ordinate (up to 632) and K is sparse (or there
  * are few ordinates), one kernel that multiplies K's nonzeros takes the place of the fused or
  * separate kernels, whose form it reports; FP32 Heun passes likewise, and banded on product
  * sets with an azimuth count above. */

@@ -513,7 +513,7 @@ bool sparse_candidate(int dtype, int scheme, int form, int Q, int64_t C) {
     const bool heun = scheme == ASN_SCHEME_HEUN;
     const bool ok = (form == ASN_FORM_AUTO || form == ASN_FORM_FUSED) &&
                     (heun ? dtype == ASN_GEMM_F32 : scheme == ASN_SCHEME_EULER);
-    return ok && asn::sparse_lds_bytes(Q) <= 160 * 1024 &&
+    return ok && asn::sparse_lds_bytes(Q) + asn::kSparseSums <= asn::kLds &&
            round_up(C, asn::kScaleBlock) * 4 < ((int64_t)1 << 31);
 }
 

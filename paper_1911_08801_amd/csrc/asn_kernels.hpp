@@ -93,9 +93,11 @@ inline size_t band_lds_bytes(int az, int dtype, bool heun) {
 constexpr int SCHEME_EULER_SPARSE = 7;
 constexpr int SCHEME_HEUN_SPARSE = 8;
 constexpr int kSparseChunk = 8;   // sources multiplied at a time
+// LDS of a CU, and what a sparse block takes beside its rows (1072 bytes of sums).
+constexpr size_t kLds = 160 * 1024, kSparseSums = 2048;
 // Waves of a block: 8, and 16 where LDS has room for one block a CU (200^2 x 492: 142 -> 96 us; at
 // 252 ordinates, two blocks a CU, 54.7 and 54.8; at 288 in BF16 70 and 74).
-inline int sparse_waves(int Q) { return 2 * Q * kBandCells * 4 > 160 * 1024 ? 16 : 8; }
+inline int sparse_waves(int Q) { return 2 * ((size_t)Q * kBandCells * 4 + kSparseSums) > kLds ? 16 : 8; }
 inline size_t sparse_lds_bytes(int Q) {
     const size_t rows = (size_t)Q * kBandCells * 4;
     const size_t sums = (size_t)sparse_waves(Q) * (kBandCells * 16 + 4);   // finish_cells

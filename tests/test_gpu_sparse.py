@@ -17,10 +17,10 @@ if not torch.cuda.is_available():
 from paper_1911_08801_amd import asn  # noqa: E402
 
 # (n_polar, n_azim, icosahedron order, beta): one ordinate group and a part of one, groups filled
-# up (42, 162 ordinates), 16 waves (362), dense K of 162 and (too dense) 252 ordinates, more than
-# LDS holds (812); product sets
+# up (42, 162 ordinates), 16 waves (362), dense K of 162 and (too dense) 252 ordinates, as many
+# as LDS holds (632) and more (640, 812); product sets
 SETS = [(1, 2, 0, 4.5), (3, 2, 0, 4.5), (1, 4, 2, 4.5), (1, 4, 3, 4.5), (1, 4, 5, 4.5), (1, 4, 7, 4.5),
-        (1, 4, 5, 80.0), (1, 4, 6, 80.0), (1, 4, 10, 4.5), (5, 10, 0, 4.5), (8, 16, 0, 6.0)]
+        (1, 4, 5, 80.0), (1, 4, 6, 80.0), (1, 4, 10, 4.5), (5, 10, 0, 4.5), (8, 16, 0, 6.0), (4, 158, 0, 4.5), (4, 160, 0, 4.5)]
 GRIDS = [(1, 1), (3, 70), (63, 2), (64, 3), (65, 4)]
 
 
@@ -45,7 +45,7 @@ def test_two_steps_match_oracle(nx, ny, n_polar, n_azim, ico, beta, scheme):
 
 @pytest.mark.parametrize("nx,ny,block", [(1, 1, 256), (63, 2, 64), (65, 4, 256), (130, 40, 4096)])
 @pytest.mark.parametrize("n_polar,n_azim,ico,beta", [(1, 2, 0, 4.5), (1, 4, 3, 4.5), (1, 4, 7, 4.5), (1, 4, 6, 80.0),
-                                                     (8, 16, 0, 4.5)])
+                                                     (8, 16, 0, 4.5), (4, 158, 0, 4.5), (4, 160, 0, 4.5)])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_reduced_precision_step_matches_emulation(nx, ny, block, n_polar, n_azim, ico, beta, dtype):
     spec, psi0 = _spec(nx, ny, n_polar, n_azim, ico, beta)
