@@ -1740,11 +1740,21 @@ __global__ __launch_bounds__(256) void finalize_kernel(BatchArgs B, int init) {
 
 // The stored state of a fused reduced-precision problem plus its pending per-cell
 // correction becomes the plain state: psi[q][c] += delta[c], delta = 0, iso = Phi / W.
-__global__ void materialize_kernel(StepArgs a, float* psi) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int q = blockIdx.y;
-    if (c >= a.C || q >= a.Q) return;
-    psi[(size_t)q * a.P + c] += a.delta[c];
+// Four cells (P is a multiple; delta is 0 beyond C) and eight planes a thread: 700^2 x 1152 1.27 ->
+// 0.90 ms (5.0 TB/s).
+constexpr int kMaterialize = 8;
+__global__ __launch_bounds__(256) void materialize_kernel(StepArgs a, float* psi) {
+    const int64_t c = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
+    if (c >= a.P) return;
+    const f32x4 d = *reinterpret_cast<const ASN_G f32x4*>(gp(a.delta) + c);
+    const int q0 = blockIdx.y * kMaterialize;
+    f32x4 v[kMaterialize];
+#pragma unroll
+    for (int u = 0; u < kMaterialize; ++u)
+        v[u] = *reinterpret_cast<const ASN_G f32x4*>(gp(psi) + (size_t)min(q0 + u, a.Q - 1) * a.P + c);
+#pragma unroll
+    for (int u = 0; u < kMaterialize; ++u)
+        if (q0 + u < a.Q) *reinterpret_cast<ASN_G f32x4*>(gp(psi) + (size_t)(q0 + u) * a.P + c) = v[u] + d;
 }
 
 __global__ void materialize_done_kernel(StepArgs a) {
@@ -2992,7 +3002,7 @@ hipError_t launch_init(const StepArgs& a, const BatchArgs& one, hipStream_t s, c
 }
 
 hipError_t launch_materialize(const StepArgs& a, hipStream_t s) {
-    dim3 g(div_up(a.C, 256), a.Q);
+    dim3 g(div_up(a.P, 1024), div_up(a.Q, kMaterialize));
     materialize_kernel<<<g, 256, 0, s>>>(a, const_cast<float*>(a.psi));
     materialize_done_kernel<<<div_up(a.C, 256), 256, 0, s>>>(a);
     return hipGetLastError();
