@@ -664,6 +664,7 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
     bool banded = false;
     std::vector<uint32_t> ddesc;   // its level descriptors and coefficients
     std::array<std::vector<float>, 3> bcoef;
+    std::vector<double> gain;
     asn::SparseForm sf;
     bool sparse = sparse_candidate(p->dtype, p->scheme, opt.step_form, Q, C);
     const bool may_band = band_candidate(p->dtype, p->scheme, opt.step_form, quad, C);
@@ -687,11 +688,14 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         banded = may_band &&
                  asn::band_form(quad->n_polar, quad->n_azim, K32.data(), asn::kBandMaxReach, asn::kBandNarrow, bf);
         banded = banded && asn::band_supported(bf.azim, p->dtype, bf.reach, p->scheme == ASN_SCHEME_HEUN) &&
-                 asn::band_scatter_tables(bf, p->dtype, ddesc, bcoef);
+                 asn::band_scatter_tables(bf, p->dtype, ddesc, bcoef, gain);
         // the kernel takes one row defect per level (the rows of a level hold the same values, so
         // their FP64 sums agree; checked)
         for (int q = 0; banded && p->dtype != ASN_GEMM_F32 && q < Q; ++q)
             if (rdef[(size_t)q] != rdef[(size_t)(q / quad->n_azim) * quad->n_azim]) banded = false;
+        // ... of the coefficients it multiplies
+        for (int q = 0; banded && p->dtype != ASN_GEMM_F32 && q < Q; ++q)
+            rdef[(size_t)q] = (float)((double)rdef[(size_t)q] - gain[(size_t)(q / quad->n_azim)]);
         sparse = sparse && !banded &&
                  asn::sparse_form(Q, K32.data(), asn::kBandO, asn::kSparseChunk, sparse_chunks(Q) - 1, sf);
     }

@@ -464,9 +464,10 @@ bool sparse_form(int Q, const float* K32, int width, int chunk, size_t max_chunk
 }
 
 bool band_scatter_tables(const BandForm& bf, int dtype, std::vector<uint32_t>& desc,
-                         std::array<std::vector<float>, 3>& coef) {
+                         std::array<std::vector<float>, 3>& coef, std::vector<double>& gain) {
     const int azim = bf.azim, half = azim / 2;
     desc.assign((size_t)bf.levels * 8, 0u);
+    gain.assign((size_t)bf.levels, 0.0);
     for (auto& c : coef) c.clear();
     // neighbouring values of the stored type: relative, and where it is subnormal
     const float rel = dtype == 0 ? 0x1p-23f : dtype == 1 ? 0x1p-7f : 0x1p-10f;
@@ -486,6 +487,7 @@ bool band_scatter_tables(const BandForm& bf, int dtype, std::vector<uint32_t>& d
                 for (int d = 0; d < lo + len; ++d) {
                     const float plus = run[d - lo], minus = -d >= lo ? run[-d - lo] : plus;
                     if (std::fabs(plus - minus) > std::fmax(rel * std::fmax(plus, minus), sub)) return false;
+                    gain[(size_t)i] += (double)plus - (double)minus;
                     col[(size_t)m].push_back(2 * d == azim ? 0.5f * plus : plus);
                 }
             }

@@ -63,7 +63,9 @@ bool band_form(int levels, int azim, const float* K32, int max_reach, int narrow
 // d = 0 .. D (d = 0: the value itself once; d = azim / 2, where both are one ordinate: half
 // the coefficient).  The set is symmetric under phi -> -phi, so c_ij(d) = c_ij(-d); where
 // the two stored values round to neighbouring numbers the one at +d serves both (either is
-// within half an ulp, plus the FP64 evaluation's error, of the exact entry).
+// within half an ulp, plus the FP64 evaluation's error, of the exact entry), and gain[i] is what
+// the sum of a row of level i so grows by (0 without such a pair): the row defect of a
+// reduced-precision K is less by it.
 // Per level rows d of N = 2 R + 1 floats, output levels j - R .. j + R (zero where nothing
 // couples), in coef[R - 1] for every R from the set's reach (at least 1) to 3, padded with
 // zeros to D = 2 or a multiple of 4.  desc, 8 words a level: its first float in coef[1] and
@@ -75,7 +77,7 @@ constexpr uint32_t kBandBeyond2 = 16;        // D > 2
 constexpr uint32_t kBandOuter2 = 32;         // an output other than j - 1 .. j + 1 couples at d >= 2
 constexpr uint32_t kBandOuter3 = 64;         // ... at d >= 3
 bool band_scatter_tables(const BandForm& bf, int dtype, std::vector<uint32_t>& desc,
-                         std::array<std::vector<float>, 3>& coef);
+                         std::array<std::vector<float>, 3>& coef, std::vector<double>& gain);
 // The tables of the sparse step: the ordinates in groups of `width` that share sources, in order
 // (order; the last group filled up with its first ordinate), and per group the ordinates that any
 // of its rows of K32[Q][Q] has a nonzero at, in `chunk`s, as rows of K in that order: src, and
