@@ -891,8 +891,7 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
           hipMemcpyAsync(b + L.off_bcxy, dcxy.data(), dcxy.size() * 4, hipMemcpyHostToDevice,
                          p->stream) != hipSuccess ||
           copy_tables() != hipSuccess ||
-          asn::prepare_banded(bf.azim, p->dtype, bf.reach, p->scheme == ASN_SCHEME_HEUN, p->band_lds()) !=
-              hipSuccess)) ||
+          asn::prepare_banded(bf.azim, p->dtype, bf.reach, p->scheme == ASN_SCHEME_HEUN) != hipSuccess)) ||
         (sparse &&
          (hipMemcpyAsync(b + L.off_sgroup, sgroup.data(), sgroup.size() * sizeof(sgroup[0]), hipMemcpyHostToDevice,
                          p->stream) != hipSuccess ||
@@ -902,7 +901,7 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
               hipSuccess ||
           hipMemcpyAsync(b + L.off_scoef, sf.coef.data(), sf.coef.size() * 4, hipMemcpyHostToDevice, p->stream) !=
               hipSuccess ||
-          asn::prepare_sparse(asn::sparse_waves(Q), p->dtype, p->scheme == ASN_SCHEME_HEUN, p->band_lds()) != hipSuccess)) ||
+          asn::prepare_sparse(asn::sparse_waves(Q), p->dtype, p->scheme == ASN_SCHEME_HEUN) != hipSuccess)) ||
         (L.lowp && hipMemcpyAsync(b + L.off_Klp, Klp.data(), Klp.size() * 2,
                                   hipMemcpyHostToDevice, p->stream) != hipSuccess) ||
         hipMemcpyAsync(b + L.off_coef, coef.data(), coef.size() * 16, hipMemcpyHostToDevice,

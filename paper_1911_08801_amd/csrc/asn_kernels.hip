@@ -2843,7 +2843,8 @@ static hipError_t launch_banded(const BatchArgs& b, int blocks, int az, int dtyp
     });
 }
 
-hipError_t prepare_banded(int az, int dtype, int reach, bool heun, size_t lds) {
+hipError_t prepare_banded(int az, int dtype, int reach, bool heun) {
+    const size_t lds = band_lds_bytes(kBandMaxAzim, dtype, heun);
     hipError_t e = hipSuccess;
     for (int pass = heun ? 1 : 0; pass <= (heun ? 2 : 0) && e == hipSuccess; ++pass)
         e = with_banded(az, dtype, reach, pass, [&](auto kernel) {
@@ -2869,10 +2870,11 @@ static hipError_t launch_sparse(const BatchArgs& b, int blocks, int waves, int d
     return waves == 8 ? with_sparse<512>(dtype, heun, launch) : with_sparse<1024>(dtype, heun, launch);
 }
 
-hipError_t prepare_sparse(int waves, int dtype, bool heun, size_t lds) {
+hipError_t prepare_sparse(int waves, int dtype, bool heun) {
     hipError_t e = hipSuccess;
     auto prepare = [&](auto kernel) {
-        return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)(kLds - kSparseSums));
     };
     for (int pass = heun ? 1 : 0; pass <= (heun ? 2 : 0) && e == hipSuccess; ++pass)
         e = waves == 8 ? with_sparse<512>(dtype, pass, prepare) : with_sparse<1024>(dtype, pass, prepare);

@@ -74,8 +74,9 @@ constexpr int kBandMaxReach = 3;
 constexpr int kBandNarrow = 8;
 // Azimuth counts the step takes: FP32 8 .. 64 in steps of 8, BF16 / FP16 32, 48 or 64; BF16
 // at 48 or 64 azimuths couples levels at most 2 apart.
+constexpr int kBandMaxAzim = 64;
 inline bool band_azimuths_supported(int az, int dtype) {
-    return dtype == 0 ? az >= 8 && az <= 64 && az % 8 == 0 : az == 32 || az == 48 || az == 64;
+    return dtype == 0 ? az >= 8 && az <= kBandMaxAzim && az % 8 == 0 : az == 32 || az == 48 || az == 64;
 }
 // The Heun passes are FP32, reach 2 at most.
 inline bool band_supported(int az, int dtype, int reach, bool heun) {
@@ -245,10 +246,11 @@ hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int schem
                        hipEvent_t* ev = nullptr, int band_az = 0, size_t band_lds = 0,
                        int band_reach = 0);
 // Raise the dynamic LDS limit of the banded kernel that serves an azimuth count, operand type
-// and reach.
-hipError_t prepare_banded(int band_az, int dtype, int reach, bool heun, size_t band_lds);
+// and reach, to the most that any problem of that instance takes (a limit set for one problem
+// would hold for a larger one that is still alive).
+hipError_t prepare_banded(int band_az, int dtype, int reach, bool heun);
 // The same of the sparse kernel of so many waves.
-hipError_t prepare_sparse(int waves, int dtype, bool heun, size_t lds);
+hipError_t prepare_sparse(int waves, int dtype, bool heun);
 // Passes per step of a scheme.
 inline int passes_per_step(int scheme) {
     return scheme == SCHEME_HEUN || scheme == SCHEME_HEUN_FLAT || scheme == SCHEME_HEUN_BANDED ||

@@ -89,3 +89,22 @@ def test_automatic_form_equals_separate_kernels():
     state, phi, _, _ = gpu_run(asn, spec, 2, form="auto")
     sep, phi_s, _, _ = gpu_run(asn, spec, 2, form="separate")
     assert rel_l2(state, sep) <= 1e-6 and rel_l2(phi, phi_s) <= 1e-6
+
+
+@pytest.mark.parametrize("large,small,dtype", [((4, 158, 0, 4.5), (1, 4, 7, 4.5), "f32"),
+                                               ((4, 158, 0, 4.5), (1, 4, 7, 4.5), "bf16"),
+                                               ((1, 4, 6, 4.5), (1, 4, 2, 4.5), "f32"),
+                                               ((2, 64, 0, 4.5), (2, 32, 0, 4.5), "f16")])
+def test_larger_problem_steps_after_a_smaller_one_is_created(large, small, dtype):
+    # one kernel instance serves both (sparse of 16 waves: 158 and 91 KiB of LDS, of 8 waves: 63 and
+    # 10; banded: 66 and 33), whose limit for LDS a problem's creation must not lower
+    spec, psi0 = _spec(65, 4, *large)
+    state, _, _, _ = gpu_run(asn, spec, 2, psi0=psi0, dtype=dtype, form="auto")
+    p = asn.from_spec(spec, dtype=dtype, set_initial_state=False)
+    asn.asn_set_state(p, psi0)
+    q = asn.from_spec(_spec(9, 5, *small)[0], dtype=dtype)
+    asn.asn_step(q, 1)
+    asn.asn_step(p, 2)
+    assert np.array_equal(asn.asn_get_state(p), state)
+    p.close()
+    q.close()
