@@ -33,7 +33,7 @@ PEAK_FP32_MFMA_TFLOPS = 157.3
 PEAK_FP32_VALU_TFLOPS = 78.6     # FMA on 16 lanes per SIMD, no packed FP32 (not used here)
 PEAK_LP_MFMA_TFLOPS = 2500.0     # dense BF16 / FP16 MFMA
 BYTES_PER_UPDATE = 8.0           # read psi^n and write psi^{n+1} once, FP32
-BAND_WIDE_ROW_CELLS = 1024       # rows from this width on are labelled wide
+BAND_WIDE_ROW_CELLS = 1024       # rows from this width on are labelled wide (records without a kernel's name)
 
 
 def parse():
@@ -126,6 +126,7 @@ def measure(asn, spec, dtype, steps, warmup, reps, scheme="euler", form=None, gr
         info = asn.asn_info(p)
         work = asn.asn_contraction_work(p)
         step_form = asn.asn_step_form(p)
+        step_kernel = asn.asn_step_kernel(p)
         asn.asn_step(p, warmup)
         chunk = max(1, steps // reps)
         sizes = [chunk] * (reps - 1) + [steps - chunk * (reps - 1)]
@@ -158,7 +159,7 @@ def measure(asn, spec, dtype, steps, warmup, reps, scheme="euler", form=None, gr
         p.close()
     torch.cuda.synchronize()
     return {"wall": wall, "kms": kms, "info": info, "work": work, "budget": bud,
-            "scheme": scheme, "form": step_form, "eager_chunk_rates": eager,
+            "scheme": scheme, "form": step_form, "kernel": step_kernel, "eager_chunk_rates": eager,
             "graph_chunk_rates": graph_rates, "chunk": chunk, "steps": steps}
 
 
@@ -180,8 +181,7 @@ def kernel_source_hash(path=KERNEL_SOURCE):
 
 def measured_traffic(kernel, spec):
     """HBM bytes per dispatch (read + write) from the committed counter summary, or None
-    if the kernels changed since it was taken or the workload is not the one measured.
-    A name ending in ", R>" stands for the instance of any reach R."""
+    if the kernels changed since it was taken or the workload is not the one measured."""
     try:
         rec = json.load(open(TRAFFIC_FILE))
     except (OSError, ValueError):
@@ -190,18 +190,17 @@ def measured_traffic(kernel, spec):
             [spec.nx, spec.ny, spec.q] != rec.get("workload_nx_ny_q"):
         return None
     k = rec["kernels"].get(kernel)
-    if k is None and kernel.endswith(", R>"):
-        k = next((v for n, v in rec["kernels"].items() if n.startswith(kernel[:-2])), None)
     return None if k is None else k["fetch_bytes"] + k["write_bytes"]
 
 
-# the dominant kernel of each kernel form (its event slot in asn_step_timed).  The banded step is
-# one kernel, instantiated by reach and operand type; here it goes by its workload's azimuth count
-# and row width (FP32) or operand type.  The step that multiplies the nonzeros of a small
-# set's K, also one kernel, goes by the form it replaces.
+# The dominant kernel of a step and its event slot in asn_step_timed: the kernel that multiplies by
+# K, as the library names it, or a separate stencil where that takes longer.  A record without the
+# kernel's name is labelled by its form.
 def dominant_kernel(res, spec, dtype):
     form = res["form"]
     lp = {"f32": 0, "bf16": 1, "f16": 2}[dtype]
+    if res.get("kernel") and form != "separate" or on_vector_units(res):
+        return res["kernel"], "contraction"
     if form == "banded" and lp:
         return f"banded_lp_kernel<{spec.n_azim}, {lp}, R>", "contraction"
     if form == "banded":
@@ -217,6 +216,11 @@ def dominant_kernel(res, spec, dtype):
             "stream_collide_flat_kernel<true>"), "stream_collide"
 
 
+def on_vector_units(res):
+    """Whether the step is one kernel that multiplies nonzeros of K on the vector units."""
+    return res.get("kernel", "").startswith(("banded_euler_kernel", "sparse_step_kernel"))
+
+
 def roofline(res, spec, dtype):
     """Roofline of the step's dominant kernel on the method's own work.  Bytes: each
     update reads psi^n and writes psi^{n+1} once (8 B in FP32) -- the binding roof, since
@@ -230,9 +234,8 @@ def roofline(res, spec, dtype):
     ach = bytes_ / t / 1e9
     nz = res["work"]["nonzero_flops"]
     executed = res["work"]["tile_flops"]
-    # (BF16 / FP16: the peak the operand type offers; the banded step's few products run on the
-    # vector units)
-    compute_peak = (PEAK_FP32_VALU_TFLOPS if res["form"] == "banded" and dtype == "f32" else
+    compute_peak = (PEAK_FP32_VALU_TFLOPS if on_vector_units(res) or
+                    (res["form"] == "banded" and dtype == "f32") else
                     PEAK_FP32_MFMA_TFLOPS if dtype == "f32" else PEAK_LP_MFMA_TFLOPS)
     traffic = measured_traffic(name, spec)
     return {"bound": "hbm", "kernel": name, "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
@@ -247,7 +250,8 @@ def roofline(res, spec, dtype):
             "method_compute_frac": nz / t / 1e12 / compute_peak,
             "intensity_flop_per_byte": nz / bytes_,
             "ridge_flop_per_byte": compute_peak * 1e12 / (PEAK_HBM_GBS * 1e9),
-            "executed_over_nonzero": executed / nz,
+            # (the blocks that asn_contraction_work counts are multiplied on the matrix cores only)
+            "executed_over_nonzero": None if on_vector_units(res) else executed / nz,
             "dense_equivalent_TFLOPs": res["work"]["dense_flops"] / t / 1e12,
             "traffic_over_algorithmic": None if traffic is None else traffic / bytes_,
             "kernels": per_kernel_rooflines(res, spec, dtype)}
@@ -256,11 +260,13 @@ def roofline(res, spec, dtype):
 def per_kernel_rooflines(res, spec, dtype):
     """Each kernel of the step against its own roof: a separate stencil against HBM on
     its algorithmic bytes (psi^n and Y read, psi^{n+1} written: 12 B per update in FP32),
-    a contraction against its MFMA peak on the products it executes (the multiplied
-    blocks) and on the nonzeros of K."""
+    a contraction on the matrix cores against their peak on the products it executes (the
+    multiplied blocks) and on the nonzeros of K."""
     kms = res["kms"]
     cq = spec.cells * spec.q
     out = {}
+    if on_vector_units(res):
+        return out
     if res["form"] == "separate" and kms.get("stream_collide", 0) > 0:
         t = kms["stream_collide"] * 1e-3
         out["stream_collide"] = {"bound": "hbm", "algorithmic_bytes": 12.0 * cq,
@@ -281,7 +287,7 @@ def summary(res, spec, dtype="f32"):
     cq = spec.cells * spec.q
     steps = res["steps"]
     out = {"value": cq * steps / res["wall"], "ms_per_step": 1e3 * res["wall"] / steps,
-           "form": res["form"], "dtype": dtype,
+           "form": res["form"], "kernel": res.get("kernel"), "dtype": dtype,
            "eager_chunk_median_updates_per_s": statistics.median(res["eager_chunk_rates"]),
            "eager_chunk_rates": res["eager_chunk_rates"],
            "chunk_steps": res["chunk"],

@@ -272,8 +272,8 @@ asn_status asn_iteration_counts(asn_problem p, int64_t* sweeps, int64_t* matvecs
  * stream between its kernels; synchronises.  kernel_ms[k] receives the average
  * duration per step of kernel k: 0 the ordinate contraction Y = K Psi, 1 stream
  * + collide, 2 moment finalize, 3 budget fold (for ASN_SCHEME_HEUN, the sum over
- * its two passes; the ASN_FORM_BANDED step does all of it in kernel 0, but for the
- * last step's fold); kernel_ms[4] the average span of a whole step.  Measurement
+ * its two passes; the steps of banded_euler_kernel and sparse_step_kernel, see
+ * asn_step_kernel, do all of it in kernel 0, but for the last step's fold); kernel_ms[4] the average span of a whole step.  Measurement
  * support for benchmarks; results equal asn_step.
  * Errors: ASN_E_INVALID (n_steps < 1), ASN_E_HIP. */
 asn_status asn_step_timed(asn_problem p, int64_t n_steps, double kernel_ms[5]);
@@ -297,6 +297,14 @@ asn_status asn_mass_budget(asn_problem p, double out[ASN_BUDGET_LEN]);
  * report ASN_FORM_SEPARATE).  Problems of one batch must share it.  Errors: ASN_E_INVALID
  * for a NULL argument. */
 asn_status asn_step_form(asn_problem p, int32_t* form);
+
+/* The kernel that multiplies by K in the problem's steps (Heun: in the first pass), as a profiler
+ * names it, cut to len characters with its closing 0: banded_euler_kernel<...> and
+ * sparse_step_kernel<...> do a whole pass in one launch and multiply nonzeros of K on the vector
+ * units, gemm_f32_kernel<F> and gemm_lp_kernel<T, F> multiply the blocks that asn_contraction_work
+ * counts on the matrix cores (F: the update in their epilogue).  Empty for the implicit scheme.
+ * asn_step_form goes by the form, which more than one kernel may serve.  Errors: ASN_E_INVALID. */
+asn_status asn_step_kernel(asn_problem p, char* name, int32_t len);
 
 /* Problem facts: time step, steps taken, steps to t_final, ordinate count.
  * Any output pointer may be NULL. */

@@ -103,6 +103,7 @@ _SIG = {
     "asn_mass_budget": [_P, _D],
     "asn_info": [_P, _D, _I64, _I64, ctypes.POINTER(ctypes.c_int32)],
     "asn_step_form": [_P, ctypes.POINTER(ctypes.c_int32)],
+    "asn_step_kernel": [_P, ctypes.c_char_p, ctypes.c_int32],
     "asn_destroy": [_P],
     "asn_contraction_work": [_P, _D, _D],
     "asn_contraction_nonzero": [_P, _D],
@@ -459,6 +460,13 @@ def asn_step_form(p: AsnProblem) -> str:
     f = ctypes.c_int32()
     _check(_lib.asn_step_form(p.handle, ctypes.byref(f)), "asn_step_form")
     return {ASN_FORM_FUSED: "fused", ASN_FORM_BANDED: "banded"}.get(f.value, "separate")
+
+
+def asn_step_kernel(p: AsnProblem) -> str:
+    """Name of the kernel that multiplies by K in the problem's steps (implicit: "")."""
+    name = ctypes.create_string_buffer(96)
+    _check(_lib.asn_step_kernel(p.handle, name, len(name)), "asn_step_kernel")
+    return name.value.decode()
 
 
 def asn_iteration_counts(p: AsnProblem) -> dict:

@@ -1448,6 +1448,13 @@ asn_status asn_step_form(asn_problem p, int32_t* form) {
     return ASN_OK;
 }
 
+asn_status asn_step_kernel(asn_problem p, char* name, int32_t len) {
+    if (!p || !name || len < 1) return fail(ASN_E_INVALID, "NULL argument");
+    if (p->imp) name[0] = 0;
+    else asn::contraction_kernel(p->dtype, launch_scheme(p), p->L.fused, p->block_az(), p->band_reach, name, (size_t)len);
+    return ASN_OK;
+}
+
 asn_status asn_iteration_counts(asn_problem p, int64_t* sweeps, int64_t* matvecs) {
     if (!p) return fail(ASN_E_INVALID, "problem is NULL");
     if (sweeps) *sweeps = p->imp ? p->imp->sweeps : 0;

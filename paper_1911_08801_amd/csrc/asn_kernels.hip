@@ -11,6 +11,7 @@
 // bitwise reproducible.
 #include "asn_kernels.hpp"
 
+#include <cstdio>
 #include <type_traits>
 
 #include "asn_host.hpp"
@@ -2814,31 +2815,37 @@ void blocks_per_kind(const StepArgs& a, int out[KT_COUNT]) {
 // its own, launch_last_budget).  With finalize_kernel and budget_kernel after every step
 // 24 steps of 50^2 x 128, set-up and results included, took 726 us instead of 516, 40 steps of
 // 311 x 173 x 288 3.13 ms instead of 2.76, a step of 400^2 x 512 187 us instead of 175.
+// (f takes the instance: its kernel, and its name as a profiler prints it)
+template <int RT, int T, int DT, int HS>
+struct BandedInstance {
+    static constexpr auto kernel = banded_euler_kernel<RT, T, DT, HS>;
+    static void name(char* out, size_t n) { std::snprintf(out, n, "banded_euler_kernel<%d, %d, %d, %d>", RT, T, DT, HS); }
+};
 template <typename F>
 static hipError_t with_banded(int az, int dtype, int reach, int heun, F&& f) {
     const bool small = az <= 32;   // at most 512 threads
     if (reach < 0 || !band_supported(az, dtype, reach, heun != 0)) return hipErrorInvalidValue;
     // FP32: the instance for reach 2 also serves smaller reaches (zero coefficients)
-    if (heun == 1) return f(banded_euler_kernel<2, 1024, 0, 1>);
-    if (heun == 2) return f(banded_euler_kernel<2, 1024, 0, 2>);
+    if (heun == 1) return f(BandedInstance<2, 1024, 0, 1>{});
+    if (heun == 2) return f(BandedInstance<2, 1024, 0, 2>{});
     if (dtype == 0) {
-        if (reach <= 2) return f(banded_euler_kernel<2, 1024, 0, 0>);
-        return small ? f(banded_euler_kernel<3, 512, 0, 0>) : f(banded_euler_kernel<3, 1024, 0, 0>);
+        if (reach <= 2) return f(BandedInstance<2, 1024, 0, 0>{});
+        return small ? f(BandedInstance<3, 512, 0, 0>{}) : f(BandedInstance<3, 1024, 0, 0>{});
     }
     if (dtype == 1) {
-        if (reach <= 1) return f(banded_euler_kernel<1, 1024, 1, 0>);
-        return reach == 2 ? f(banded_euler_kernel<2, 1024, 1, 0>) : f(banded_euler_kernel<3, 512, 1, 0>);
+        if (reach <= 1) return f(BandedInstance<1, 1024, 1, 0>{});
+        return reach == 2 ? f(BandedInstance<2, 1024, 1, 0>{}) : f(BandedInstance<3, 512, 1, 0>{});
     }
-    if (reach <= 1) return f(banded_euler_kernel<1, 1024, 2, 0>);
-    if (reach == 2) return f(banded_euler_kernel<2, 1024, 2, 0>);
-    return small ? f(banded_euler_kernel<3, 512, 2, 0>) : f(banded_euler_kernel<3, 1024, 2, 0>);
+    if (reach <= 1) return f(BandedInstance<1, 1024, 2, 0>{});
+    if (reach == 2) return f(BandedInstance<2, 1024, 2, 0>{});
+    return small ? f(BandedInstance<3, 512, 2, 0>{}) : f(BandedInstance<3, 1024, 2, 0>{});
 }
 
 // heun: 0, or the pass.
 static hipError_t launch_banded(const BatchArgs& b, int blocks, int az, int dtype, size_t lds, hipStream_t s,
                                 int reach, int heun) {
-    return with_banded(az, dtype, reach, heun, [&](auto kernel) {
-        kernel<<<blocks + b.n, az / kBandO * 64, lds, s>>>(b);
+    return with_banded(az, dtype, reach, heun, [&](auto i) {
+        i.kernel<<<blocks + b.n, az / kBandO * 64, lds, s>>>(b);
         return hipSuccess;
     });
 }
@@ -2847,37 +2854,44 @@ hipError_t prepare_banded(int az, int dtype, int reach, bool heun) {
     const size_t lds = band_lds_bytes(kBandMaxAzim, dtype, heun);
     hipError_t e = hipSuccess;
     for (int pass = heun ? 1 : 0; pass <= (heun ? 2 : 0) && e == hipSuccess; ++pass)
-        e = with_banded(az, dtype, reach, pass, [&](auto kernel) {
-            return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        e = with_banded(az, dtype, reach, pass, [&](auto i) {
+            return hipFuncSetAttribute((const void*)i.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         });
     return e;
 }
 
+template <int DT, int HS, int T>
+struct SparseInstance {
+    static constexpr auto kernel = sparse_step_kernel<DT, HS, T>;
+    static void name(char* out, size_t n) { std::snprintf(out, n, "sparse_step_kernel<%d, %d, %d>", DT, HS, T); }
+};
 template <int T, typename F>
-static hipError_t with_sparse(int dtype, int heun, F&& f) {
-    if (heun == 1) return f(sparse_step_kernel<0, 1, T>);
-    if (heun == 2) return f(sparse_step_kernel<0, 2, T>);
-    if (dtype == 0) return f(sparse_step_kernel<0, 0, T>);
-    return dtype == 1 ? f(sparse_step_kernel<1, 0, T>) : f(sparse_step_kernel<2, 0, T>);
+static hipError_t with_sparse_t(int dtype, int heun, F&& f) {
+    if (heun == 1) return f(SparseInstance<0, 1, T>{});
+    if (heun == 2) return f(SparseInstance<0, 2, T>{});
+    if (dtype == 0) return f(SparseInstance<0, 0, T>{});
+    return dtype == 1 ? f(SparseInstance<1, 0, T>{}) : f(SparseInstance<2, 0, T>{});
+}
+template <typename F>
+static hipError_t with_sparse(int waves, int dtype, int heun, F&& f) {
+    return waves == 8 ? with_sparse_t<512>(dtype, heun, f) : with_sparse_t<1024>(dtype, heun, f);
 }
 
 static hipError_t launch_sparse(const BatchArgs& b, int blocks, int waves, int dtype, size_t lds, hipStream_t s,
                                 int heun) {
-    auto launch = [&](auto kernel) {
-        kernel<<<blocks + b.n, waves * 64, lds, s>>>(b);
+    return with_sparse(waves, dtype, heun, [&](auto i) {
+        i.kernel<<<blocks + b.n, waves * 64, lds, s>>>(b);
         return hipSuccess;
-    };
-    return waves == 8 ? with_sparse<512>(dtype, heun, launch) : with_sparse<1024>(dtype, heun, launch);
+    });
 }
 
 hipError_t prepare_sparse(int waves, int dtype, bool heun) {
     hipError_t e = hipSuccess;
-    auto prepare = [&](auto kernel) {
-        return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)(kLds - kSparseSums));
-    };
     for (int pass = heun ? 1 : 0; pass <= (heun ? 2 : 0) && e == hipSuccess; ++pass)
-        e = waves == 8 ? with_sparse<512>(dtype, pass, prepare) : with_sparse<1024>(dtype, pass, prepare);
+        e = with_sparse(waves, dtype, pass, [&](auto i) {
+            return hipFuncSetAttribute((const void*)i.kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)(kLds - kSparseSums));
+        });
     return e;
 }
 
@@ -2967,6 +2981,22 @@ hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int schem
     if (e != hipSuccess) return e;
     b1.s_par = 1;
     return launch_pass(b1, grid, dtype, st + 1, BUD_STAGE2, s, ev ? ev + 5 : nullptr, band_az, band_lds, band_reach);
+}
+
+void contraction_kernel(int dtype, int scheme, bool fused, int band_az, int band_reach, char* out, size_t n) {
+    const int heun = passes_per_step(scheme) == 2 ? 1 : 0;
+    auto name = [&](auto i) {
+        i.name(out, n);
+        return hipSuccess;
+    };
+    if (scheme == SCHEME_EULER_BANDED || scheme == SCHEME_HEUN_BANDED)
+        (void)with_banded(band_az, dtype, band_reach, heun, name);
+    else if (scheme == SCHEME_EULER_SPARSE || scheme == SCHEME_HEUN_SPARSE)
+        (void)with_sparse(band_az / kBandO, dtype, heun, name);
+    else if (dtype == 0)
+        std::snprintf(out, n, "gemm_f32_kernel<%s>", fused ? "true" : "false");
+    else
+        std::snprintf(out, n, "gemm_lp_kernel<%d, %s>", dtype, fused ? "true" : "false");
 }
 
 hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int scheme, hipStream_t s) {

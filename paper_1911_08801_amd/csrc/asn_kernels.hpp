@@ -258,6 +258,8 @@ inline int passes_per_step(int scheme) {
                ? 2
                : 1;
 }
+// The name of the kernel that launch_step contracts with (Heun: in the first pass).
+void contraction_kernel(int dtype, int scheme, bool fused, int band_az, int band_reach, char* out, size_t n);
 // After the last of a call's n_steps steps: what the next step's launch would do for it (the
 // banded step's budget).
 hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int scheme, hipStream_t s);
