@@ -108,7 +108,8 @@ enum { ASN_DT_STREAMING = 0, ASN_DT_STIFF = 1 };
  *                    and the update, reading psi^n once.  FP32: n_azim in {8, 16, ..., 64}.
  *                    BF16 / FP16: the rounded operands and the rounded K (the same rounding
  *                    recipe and pending per-cell correction as ASN_FORM_FUSED), n_azim 32,
- *                    48 or 64.  Needs levels at most 3 apart coupled (BF16 at 48 or 64
+ *                    48 or 64; where K is wide, each coupled pair's circulant block on the
+ *                    matrix cores instead, whichever is faster at the grid's size.  Needs levels at most 3 apart coupled (BF16 at 48 or 64
  *                    azimuths: 2) and the stored K exactly circulant (checked at asn_create;
  *                    ASN_E_UNSUPPORTED otherwise).
  * ASN_FORM_AUTO:     the banded form where it applies; else BF16/FP16 fuse, and FP32
@@ -314,7 +315,7 @@ asn_status asn_info(asn_problem p, double* dt, int64_t* steps_done, int64_t* ste
 /* Arithmetic of one contraction Y = K Psi: dense_flops = 2 Q^2 C; tile_flops =
  * 2 C times the number of K entries in the blocks the kernel multiplies (banded
  * step: the runs of its pairs, see asn_contraction_nonzero; in BF16 / FP16 every coupled
- * pair's whole n_azim x n_azim block, though the step multiplies the runs only; where K's
+ * pair's whole n_azim x n_azim block, which the matrix cores multiply; where K's runs or
  * nonzeros are multiplied instead, the blocks of the form it reports).  K is
  * forward peaked (paper Section 3.5: the discrete artificial in-scattering is a
  * sparse matrix), so blocks whose entries are all zero in the stored operand type

@@ -48,10 +48,12 @@ struct Layout {
     bool flat = false;   // separate-kernel stencil over flat cell chunks (not column strips)
     bool banded = false; // banded step: one kernel per pass for a product ordinate set
     bool sparse = false; // sparse step: one kernel per pass for any set with a sparse K
-    bool by_cells() const { return banded || sparse; }   // 64-cell blocks of every ordinate
+    bool matrix = false; // the banded step, on the matrix cores
+    // one launch a pass: 64-cell blocks of every ordinate that finish their cells' moments
+    bool by_cells() const { return (banded && !matrix) || sparse; }
     int ktab_len = 0;
     size_t off_psi0, off_psi1, off_Y, off_Kt, off_Klp, off_rdef, off_ktab, off_qi, off_coef, off_iso,
-        off_band, off_bcoef[3], off_bcxy, off_sgroup, off_sord, off_srow, off_scoef,
+        off_band, off_bcoef[3], off_bcxy, off_bfrag, off_sgroup, off_sord, off_srow, off_scoef,
         off_phi64, off_phipart, off_blk, off_fin, off_ypart, off_fix, off_delta, off_bmax0, off_bmax1, off_rec,
         off_tab, off_off, off_base, off_left, off_imp,
         total;
@@ -100,12 +102,13 @@ size_t sparse_chunks(int Q) {
 }
 
 Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int band_levels = 0,
-                   int band_azim = 0, bool sparse = false) {
+                   int band_azim = 0, bool sparse = false, bool matrix = false) {
     Layout L;
     L.banded = band_levels > 0;
     L.sparse = sparse;
+    L.matrix = matrix;
     // the reduced-precision step of these forms keeps the fused form's pending correction
-    if (L.by_cells()) fused = dtype != ASN_GEMM_F32 && scheme == ASN_SCHEME_EULER;
+    if (L.banded || sparse) fused = dtype != ASN_GEMM_F32 && scheme == ASN_SCHEME_EULER;
     L.fused = fused;
     L.Q = Q;
     L.Qp = (int)round_up(Q, asn::kGemmBM);
@@ -117,14 +120,14 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
     L.tiles_y = (ny + asn::kTileY - 1) / asn::kTileY;
     // Separate stencils up to a width run over flat cell chunks, wider grids over
     // column strips; the ordinates are split into chunks sized to the grid below.
-    L.flat = !fused && !L.by_cells() && ((scheme == ASN_SCHEME_EULER && nx <= asn::kFlatMaxNx) ||
+    L.flat = !fused && !L.banded && !sparse && ((scheme == ASN_SCHEME_EULER && nx <= asn::kFlatMaxNx) ||
                                      (scheme == ASN_SCHEME_HEUN && nx <= asn::kFlatMaxNxM));
     if (L.flat) {
         L.tiles_x = (int)((L.P + asn::kFlatCells - 1) / asn::kFlatCells);
         L.tiles_y = 1;
     }
     int tiles = L.tiles_x * L.tiles_y;
-    if (L.by_cells()) {
+    if (L.banded || sparse) {
         // one block per kBandCells cells, every ordinate: each cell's Phi
         // complete
         L.tiles_x = (int)((L.C + asn::kBandCells - 1) / asn::kBandCells);
@@ -160,7 +163,7 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
     L.off_psi0 = take((size_t)Q * plane * 4);
     L.off_psi1 = take((size_t)Q * plane * 4);
     // the fused, banded and sparse steps keep Y in registers
-    L.off_Y = take(fused || L.by_cells() ? 0 : (size_t)Q * plane * 4);
+    L.off_Y = take(fused || L.banded || sparse ? 0 : (size_t)Q * plane * 4);
     L.off_Kt = take((size_t)L.Qp * L.Qp * 4);
     L.off_Klp = take(L.lowp ? (size_t)L.Qp * L.Qp * 2 : 0);
     L.off_rdef = take((size_t)L.Qp * 4);
@@ -171,10 +174,12 @@ Layout make_layout(int nx, int ny, int Q, int dtype, int scheme, bool fused, int
         L.off_ktab = take((size_t)L.ktab_len * 4);
     }
     // level descriptors, 8 words; the coefficient tables of each reach; (cx, cy)
-    L.off_band = take(L.banded ? (size_t)band_levels * 32 : 0);
+    // (on the matrix cores: one level more, the operand table and 1 KiB after it)
+    L.off_band = take(L.banded ? (size_t)(band_levels + (matrix ? 1 : 0)) * 32 : 0);
     for (int r = 0; r < 3; ++r)
-        L.off_bcoef[r] = take(L.banded ? band_coef_capacity(band_levels, band_azim, 2 * r + 3) * 4 : 0);
-    L.off_bcxy = take(L.banded ? (size_t)Q * 8 : 0);
+        L.off_bcoef[r] = take(L.banded && !matrix ? band_coef_capacity(band_levels, band_azim, 2 * r + 3) * 4 : 0);
+    L.off_bcxy = take(L.banded && !matrix ? (size_t)Q * 8 : 0);
+    L.off_bfrag = take(matrix ? (size_t)(band_levels + 1) * asn::band_lp_block(band_azim) * 16 + 1024 : 0);
     const size_t groups = sparse ? sparse_groups(Q) : 0, chunks = sparse ? sparse_chunks(Q) : 0;
     L.off_sgroup = take(groups * sizeof(asn::SparseGroup));
     L.off_sord = take(groups * asn::kBandO * sizeof(asn::SparseOrdinate));
@@ -243,6 +248,7 @@ struct asn_problem_s {
     bool fuses = false;   // what asn_step_form reports of a sparse step: the form it replaces
     bool flat = false;    // whether that form's stencil runs over flat cell chunks
     // a step's block as if of a product set with so many azimuths, kBandO a wave
+    // (with matrix cores: its azimuth count)
     int block_az() const { return L.sparse ? asn::sparse_waves(L.Q) * asn::kBandO : band_azim; }
     size_t band_lds() const {
         if (L.sparse) return asn::sparse_lds_bytes(L.Q);
@@ -250,8 +256,8 @@ struct asn_problem_s {
     }
 };
 
-// Problems that share their launches: a batch is up to four such groups (the problems whose steps
-// are banded, sparse with blocks of 8 or of 16 waves, and the others).
+// Problems that share their launches: a batch is up to five such groups (the problems whose steps
+// are banded, banded on the matrix cores, sparse with blocks of 8 or of 16 waves, and the others).
 struct Group {
     int first = 0, n = 0;    // of the batch's problems in launch order
     int scheme = 0;          // launch scheme (the flat-chunk, strip or banded form)
@@ -261,7 +267,7 @@ struct Group {
     int grid[asn::KT_COUNT] = {};
     asn::BatchArgs args{};
 };
-constexpr int kMaxGroups = 4;
+constexpr int kMaxGroups = 5;
 struct Plan {
     int n = 0, n_groups = 0;
     asn_problem order[asn::kMaxArm];
@@ -332,7 +338,8 @@ StepArgs make_args(asn_problem p, int cur) {
         a.fin_part += 4 * (size_t)L.tiles_x;
     }
     if (L.banded) {
-        a.band = reinterpret_cast<const uint4*>(b + L.off_band);   // two per level
+        (L.matrix ? a.bpairs : a.band) = reinterpret_cast<const uint4*>(b + L.off_band);   // two per level
+        a.bfrag = L.matrix ? reinterpret_cast<const uint4*>(b + L.off_bfrag) : nullptr;
         a.bcoef3 = reinterpret_cast<const float*>(b + L.off_bcoef[0]);
         a.bcoef5 = reinterpret_cast<const float*>(b + L.off_bcoef[1]);
         a.bcoef7 = reinterpret_cast<const float*>(b + L.off_bcoef[2]);
@@ -506,6 +513,14 @@ bool band_candidate(int dtype, int scheme, int form, const asn_quadrature* q, in
            q->q_custom == 0 && q->icosahedron_order == 0 && q->n_polar >= 1;
 }
 
+// Bytes that either layout of the banded step needs.
+size_t band_layouts(const asn_grid& g, const asn_quadrature& q, int Q, int dtype, int scheme) {
+    size_t bytes = make_layout(g.nx, g.ny, Q, dtype, scheme, false, q.n_polar, q.n_azim).total;
+    if (dtype != ASN_GEMM_F32)
+        bytes = std::max(bytes, make_layout(g.nx, g.ny, Q, dtype, scheme, false, q.n_polar, q.n_azim, false, true).total);
+    return bytes;
+}
+
 // Whether a problem that does not take the banded step may take the sparse one (unless separate
 // kernels were asked for; it reports the form it replaces): its LDS rows fit a block, and a
 // plane's bytes 31 bits.  K must then also be sparse enough (sparse_form).
@@ -552,16 +567,14 @@ asn_status asn_workspace_size(const asn_grid* grid, const asn_quadrature* quad,
             return fail(ASN_E_UNSUPPORTED, "ASN_FORM_BANDED needs forward Euler on a product set "
                                            "with n_azim in {8, 16, ..., 64} (FP32) or {32, 48, 64} "
                                            "(BF16, FP16)");
-        *bytes = make_layout(grid->nx, grid->ny, Q, dtype, scheme, false, quad->n_polar,
-                             quad->n_azim).total;
+        *bytes = band_layouts(*grid, *quad, Q, dtype, scheme);
         return ASN_OK;
     }
     const bool fused = use_fused(dtype, scheme, form, grid->nx, grid->ny, Q);
     size_t total = make_layout(grid->nx, grid->ny, Q, dtype, scheme, fused).total;
-    // whether K has the banded form is known only once K is built: cover both layouts
+    // which of the forms a K has is known only once it is built: cover every layout
     if (band_candidate(dtype, scheme, form, quad, (int64_t)grid->nx * grid->ny))
-        total = std::max(total, make_layout(grid->nx, grid->ny, Q, dtype, scheme, false, quad->n_polar,
-                                            quad->n_azim).total);
+        total = std::max(total, band_layouts(*grid, *quad, Q, dtype, scheme));
     if (sparse_candidate(dtype, scheme, form, Q, (int64_t)grid->nx * grid->ny))
         total = std::max(total, make_layout(grid->nx, grid->ny, Q, dtype, scheme, false, 0, 0, true).total);
     *bytes = total;
@@ -661,7 +674,7 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
 
     // banded step when K has that form (ASN_FORM_AUTO) or on request (ASN_FORM_BANDED)
     asn::BandForm bf;
-    bool banded = false;
+    bool banded = false, matrix = false;
     std::vector<uint32_t> ddesc;   // its level descriptors and coefficients
     std::array<std::vector<float>, 3> bcoef;
     std::vector<double> gain;
@@ -693,8 +706,9 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         // their FP64 sums agree; checked)
         for (int q = 0; banded && p->dtype != ASN_GEMM_F32 && q < Q; ++q)
             if (rdef[(size_t)q] != rdef[(size_t)(q / quad->n_azim) * quad->n_azim]) banded = false;
+        matrix = banded && p->dtype != ASN_GEMM_F32 && asn::band_on_matrix_cores(bf, ddesc, C);
         // ... of the coefficients it multiplies
-        for (int q = 0; banded && p->dtype != ASN_GEMM_F32 && q < Q; ++q)
+        for (int q = 0; banded && !matrix && p->dtype != ASN_GEMM_F32 && q < Q; ++q)
             rdef[(size_t)q] = (float)((double)rdef[(size_t)q] - gain[(size_t)(q / quad->n_azim)]);
         sparse = sparse && !banded &&
                  asn::sparse_form(Q, K32.data(), asn::kBandO, asn::kSparseChunk, sparse_chunks(Q) - 1, sf);
@@ -711,7 +725,7 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         p->band_levels = bf.levels;
         p->band_azim = bf.azim;
         p->band_reach = bf.reach;
-        p->L = make_layout(p->nx, p->ny, Q, p->dtype, p->scheme, false, bf.levels, bf.azim);
+        p->L = make_layout(p->nx, p->ny, Q, p->dtype, p->scheme, false, bf.levels, bf.azim, false, matrix);
     } else {
         p->L = make_layout(p->nx, p->ny, Q, p->dtype, p->scheme,
                            use_fused(p->dtype, p->scheme, opt.step_form, p->nx, p->ny, Q));
@@ -836,7 +850,37 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
     }
 
     std::vector<float> dcxy;   // banded kernel: (cx, cy) per ordinate
-    if (banded) {
+    std::vector<uint16_t> bfrag;   // (on the matrix cores) its operand table
+    if (matrix) {
+        // Per level the coupled pairs of level l first, then zero operands whose partner is the level
+        // itself (the kernel runs the first 2 reach + 1 slots of its launch's largest reach, with no
+        // count); then (cx, cy) of level l - 1's ordinates (its update runs a level behind); the last
+        // block holds only the last level's.
+        constexpr int slots = 2 * asn::kBandMaxReach + 1;
+        const size_t block = asn::band_lp_block(bf.azim), pairs = block - (size_t)bf.azim / 2;   // uint4
+        ddesc.assign((size_t)(bf.levels + 1) * 8, 0u);
+        for (int i = 0; i <= bf.levels; ++i) {
+            const int n = i < bf.levels ? (int)bf.desc[(size_t)i * 8] : 0;
+            uint32_t kc = 0;
+            for (int t = 0; t < slots; ++t)
+                kc |= (t < n ? ((bf.desc[(size_t)i * 8 + 1 + t] >> 8) & 7u) : (uint32_t)bf.reach) << (4 * t);
+            ddesc[(size_t)i * 8] = (uint32_t)n;
+            ddesc[(size_t)i * 8 + 1] = (uint32_t)(i * block);
+            ddesc[(size_t)i * 8 + 2] = kc;
+            for (int t = 0; t < n; ++t) asn::band_lp_fragments(bf, i, t, p->dtype, bfrag);
+            bfrag.resize((i * block + pairs) * 8, 0);
+            for (int az = 0; az < bf.azim; ++az) {
+                float c[2] = {0.f, 0.f};
+                if (i > 0) {
+                    c[0] = qi[(size_t)(i - 1) * bf.azim + az].cx;
+                    c[1] = qi[(size_t)(i - 1) * bf.azim + az].cy;
+                }
+                uint16_t w[4];
+                std::memcpy(w, c, sizeof(c));
+                bfrag.insert(bfrag.end(), w, w + 4);
+            }
+        }
+    } else if (banded) {
         for (int i = 0; i < bf.levels; ++i)   // the FP64 weight of a level's ordinates
             std::memcpy(&ddesc[8 * (size_t)i + 4], &qi[(size_t)i * bf.azim].w, 8);
         for (const QInfo& v : qi) {
@@ -869,12 +913,18 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
     };
     char* b = p->base;
     auto copy_tables = [&] {
-        hipError_t e = hipSuccess;
+        auto copy = [&](size_t off, const void* from, size_t bytes) {
+            return hipMemcpyAsync(b + off, from, bytes, hipMemcpyHostToDevice, p->stream);
+        };
+        hipError_t e = copy(L.off_band, ddesc.data(), ddesc.size() * 4);
+        if (matrix) {
+            if (e == hipSuccess) e = copy(L.off_bfrag, bfrag.data(), bfrag.size() * 2);
+            return e == hipSuccess ? asn::prepare_banded_lp(bf.azim, p->dtype, bf.reach) : e;
+        }
         for (int r = 0; r < 3 && e == hipSuccess; ++r)
-            if (!bcoef[r].empty())
-                e = hipMemcpyAsync(b + L.off_bcoef[r], bcoef[r].data(), bcoef[r].size() * 4, hipMemcpyHostToDevice,
-                                   p->stream);
-        return e;
+            if (!bcoef[r].empty()) e = copy(L.off_bcoef[r], bcoef[r].data(), bcoef[r].size() * 4);
+        if (e == hipSuccess) e = copy(L.off_bcxy, dcxy.data(), dcxy.size() * 4);
+        return e == hipSuccess ? asn::prepare_banded(bf.azim, p->dtype, bf.reach, p->scheme == ASN_SCHEME_HEUN) : e;
     };
     if (hipMemsetAsync(b, 0, L.total, p->stream) != hipSuccess ||
         hipMemcpyAsync(b + L.off_Kt, Kt.data(), Kt.size() * 4, hipMemcpyHostToDevice, p->stream) !=
@@ -885,13 +935,7 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
                        p->stream) != hipSuccess ||
         hipMemcpyAsync(b + L.off_ktab, ktab.data(), ktab.size() * 4, hipMemcpyHostToDevice,
                        p->stream) != hipSuccess ||
-        (banded &&
-         (hipMemcpyAsync(b + L.off_band, ddesc.data(), ddesc.size() * 4, hipMemcpyHostToDevice,
-                         p->stream) != hipSuccess ||
-          hipMemcpyAsync(b + L.off_bcxy, dcxy.data(), dcxy.size() * 4, hipMemcpyHostToDevice,
-                         p->stream) != hipSuccess ||
-          copy_tables() != hipSuccess ||
-          asn::prepare_banded(bf.azim, p->dtype, bf.reach, p->scheme == ASN_SCHEME_HEUN) != hipSuccess)) ||
+        (banded && copy_tables() != hipSuccess) ||
         (sparse &&
          (hipMemcpyAsync(b + L.off_sgroup, sgroup.data(), sgroup.size() * sizeof(sgroup[0]), hipMemcpyHostToDevice,
                          p->stream) != hipSuccess ||
@@ -1017,6 +1061,7 @@ asn_status asn_get_state(asn_problem p, float* psi, int32_t on_device) {
 // runs over flat cell chunks (Euler or Heun) has a launch form of its own.
 static int launch_scheme(asn_problem p) {
     if (p->L.sparse) return p->scheme == ASN_SCHEME_HEUN ? asn::SCHEME_HEUN_SPARSE : asn::SCHEME_EULER_SPARSE;
+    if (p->L.matrix) return asn::SCHEME_EULER_BANDED_LP;
     if (p->L.banded) return p->scheme == ASN_SCHEME_HEUN ? asn::SCHEME_HEUN_BANDED : asn::SCHEME_EULER_BANDED;
     if (!p->L.flat) return p->scheme;
     return p->scheme == ASN_SCHEME_HEUN ? asn::SCHEME_HEUN_FLAT : asn::SCHEME_EULER_FLAT;
@@ -1169,7 +1214,7 @@ static size_t plan_bytes(int n) {
            2 * (size_t)asn::kMaxArm * sizeof(int);
 }
 static int group_kind(asn_problem p) {
-    return p->L.banded ? 0 : p->L.sparse ? (asn::sparse_waves(p->L.Q) == 8 ? 1 : 2) : 3;
+    return p->L.matrix ? 4 : p->L.banded ? 0 : p->L.sparse ? (asn::sparse_waves(p->L.Q) == 8 ? 1 : 2) : 3;
 }
 static void make_plan(asn_problem* probs, int32_t n, char* dev, Plan& p, int* index, StepArgs* tab, int* off) {
     p.n = n;

@@ -525,4 +525,39 @@ bool band_scatter_tables(const BandForm& bf, int dtype, std::vector<uint32_t>& d
     return true;
 }
 
+bool band_on_matrix_cores(const BandForm& bf, const std::vector<uint32_t>& desc, int64_t cells) {
+    const int N = 2 * std::max(1, bf.reach) + 1;
+    int64_t products = 0;
+    for (int j = 0; j < bf.levels; ++j) {
+        const uint32_t form = desc[8 * (size_t)j + 2];
+        const uint32_t steps = N == 3 ? desc[8 * (size_t)j + 3] >> 4 : desc[8 * (size_t)j + (N == 5 ? 3 : 6)];
+        products += 2 * N + 3 + ((form & kBandOuter2) ? N - 3 : 0);
+        if (!(form & kBandBeyond2)) continue;
+        products += 6 + ((form & kBandOuter3) ? 2 * (N - 3) : 0);
+        for (int m = 0; m < N; ++m) products += 4 * std::max((int)((steps >> (4 * m)) & 15u) - 1, 0);
+    }
+    const double az = bf.azim / 16.0, m = 1e-6 * (double)cells * bf.levels * bf.azim;
+    const double cached = m <= 32.0 ? 28.0 - 6.0 * az : 0.0;
+    const double line = 24.0 - 5.0 * az + 8.0 * std::log2((double)bf.levels) - cached;
+    return (double)products / bf.levels > line + std::min(4000.0 / (m * m), 400.0 / bf.levels);
+}
+
+void band_lp_fragments(const BandForm& bf, int level, int pair, int dtype,
+                       std::vector<uint16_t>& out) {
+    const int azim = bf.azim;
+    const uint32_t code = bf.desc[(size_t)level * 8 + 1 + pair];
+    int lo = 0, len = 0;
+    band_run(code, azim, lo, len);
+    const int start = 4 * (int)((code >> 11) & 127u) + bf.range[2 * (size_t)level];
+    std::vector<float> c((size_t)azim, 0.f);   // c(delta), delta = 0 .. azim - 1
+    for (int t = 0; t < len; ++t) c[(size_t)(((lo + t) % azim + azim) % azim)] = bf.coef[(size_t)start + t];
+    for (int f = 0; f < azim / 16; ++f)
+        for (int l = 0; l < 64; ++l)
+            for (int t = 0; t < 8; ++t) {
+                const int m = l % 16, k = 8 * (l / 16) + t;
+                const float v = c[(size_t)(((16 * f + k - m) % azim + azim) % azim)];
+                out.push_back(dtype == 1 ? float_to_bf16_rne(v) : float_to_half_rne(v));
+            }
+}
+
 }  // namespace asn

@@ -78,6 +78,27 @@ constexpr uint32_t kBandOuter2 = 32;         // an output other than j - 1 .. j 
 constexpr uint32_t kBandOuter3 = 64;         // ... at d >= 3
 bool band_scatter_tables(const BandForm& bf, int dtype, std::vector<uint32_t>& desc,
                          std::array<std::vector<float>, 3>& coef, std::vector<double>& gain);
+// Whether the BF16 / FP16 banded step of this K is faster on the matrix cores, which multiply every
+// coupled pair's whole circulant block, than by the tables above, whose time grows with K's width
+// (desc: their descriptors).  The line, in products of the tables a level and ordinate, is fitted to
+// 1039 timings of both (1 to 32 levels, 32 to 64 azimuths, 50^2 to 800^2 cells, K of one level to
+// dense; 0.3 % above the faster of the two on average, 14 % at most): higher with more levels, whose
+// operands wait in LDS, and with fewer azimuths, of which the tables sum fewer; lower up to 32 M
+// cell-ordinates, where both states stay in the 256 MB cache, which the tables' kernel writes past;
+// higher below about 15 M, where the matrix form's two further launches and its start count.  Us a
+// step, tables and matrix: BF16 4 x 64 azimuths, 400^2 cells, 21 products 161 and 154, 33: 172 and
+// 164, 51: 206 and 168, 101: 294 and 195; 8 x 64, 200^2, 19: 73 and 87, 66: 120 and 99; 16 x 32,
+// 400^2, 22: 207 and 250, 50: 384 and 377; FP16 4 x 64, 400^2, 147 (reach 3): 385 and 191.
+bool band_on_matrix_cores(const BandForm& bf, const std::vector<uint32_t>& desc, int64_t cells);
+// The A operands of MFMA 16x16x32 for pair `pair` of level `level` of a banded form of
+// the BF16 (dtype 1) or FP16 (dtype 2) K: the pair's circulant block C[a][a'] =
+// c((a' - a) mod azim) sliced as 16 output x 32 input azimuths at the offsets 16 f,
+// f = 0 .. azim / 16 - 1 (slice f: rows m, columns k hold c((16 f + k - m) mod azim)),
+// each as 64 lanes x 8 values (lane l: row l % 16, columns 8 (l / 16) .. + 7), appended
+// to `out` as operand bits.  azim 32, 48 or 64 (48: columns past the last azimuth meet
+// zero operands in the kernel).
+void band_lp_fragments(const BandForm& bf, int level, int pair, int dtype,
+                       std::vector<uint16_t>& out);
 // The tables of the sparse step: the ordinates in groups of `width` that share sources, in order
 // (order; the last group filled up with its first ordinate), and per group the ordinates that any
 // of its rows of K32[Q][Q] has a nonzero at, in `chunk`s, as rows of K in that order: src, and

@@ -1994,9 +1994,9 @@ __global__ __launch_bounds__(256) void broadcast_kernel(float* psi, const float*
 //    stored without its pending per-cell correction delta, only the anisotropic part is
 //    rounded: x = T((psi^ - iso^) 2^(E - e_b)), Y^ - iso^ = 2^(e_b - E) sum T(K) x + r_q
 //    (psi^ - iso^)), its products in FP32: a rounded operand, both BF16 terms together, is an
-//    FP32 number.  K is 2 % dense, so the vector units, which skip its zeros, finish before
-//    the matrix cores did with each level pair's whole circulant block: 400^2 x 512 BF16
-//    0.242 -> 0.196 ms, 700^2 x 1152 FP16 1.63 -> 1.34 ms.
+//    FP32 number.  Where K is narrow the vector units, which skip its zeros, finish before the
+//    matrix cores do with each level pair's whole circulant block (the kernel below, for wide K):
+//    400^2 x 512 BF16 0.242 -> 0.196 ms, 700^2 x 1152 FP16 1.63 -> 1.34 ms.
 //    Heun + minmod, FP32: both passes in this form, instead of a contraction, stencil, finalize
 //    and budget kernel each.  A pass without its contraction's round trip through Y reads psi
 //    (its three y neighbours from L2) and writes it, the second also reads psi^n, where its
@@ -2565,7 +2565,466 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
 }
 
 // ---------------------------------------------------------------------------
-// 6. Step for any ordinate set whose K is sparse and whose values at 64 cells fit LDS
+// 6. The banded BF16 / FP16 step on the matrix cores (FP32 accumulate), for product sets of 32,
+//    48 or 64 azimuths whose K is wide (band_on_matrix_cores, asn_host.hpp).  As in the fused reduced-precision form the state is
+//    stored without its pending per-cell particle correction delta (isotropic, so it
+//    drops out of the rounded deviation), and only the anisotropic part is rounded:
+//      x = T((psi^ - iso^) 2^(E - e_b))  (BF16: hi + lo),
+//      Y^ - iso^ = 2^(e_b - E) sum_j T(C_ij) x_j + r_q (psi^ - iso^),
+//    T(C_ij) the circulant block of level pair (i, j) of the stored K.  Block =
+//    kBandCells cells x every ordinate; wave (m-tile mt, n-tile nt) owns azimuths
+//    16 mt .. + 15 of cells 16 nt .. + 15, lane l the four azimuths 16 mt + 4 (l / 16) ..
+//    of cell 16 nt + l % 16, which is where MFMA 16x16x32 leaves them.  Per level pair
+//    and k-step of 32 azimuths one MFMA per operand term: A is the block's 16 x 32 slice
+//    at the wave's azimuth offset (host-built, staged in LDS a level ahead), B eight
+//    consecutive azimuths of one cell of the partner level from a ring of quantised
+//    levels ([8-azimuth chunk][cell], 16-byte reads).  The ring is filled from registers
+//    loaded a level before; the unrounded values of the lane's own cell wait in registers
+//    (reach + 1 levels) for the level's update, which runs one level behind the products
+//    and is interleaved with them; x neighbours come from the adjacent lanes (DPP) or, at
+//    the edges of a 16-cell tile, from a small ring the neighbouring waves (or the block's
+//    halo loads) fill at the same time.  Outputs as the fused form:
+//    psi^{n+1} without its correction, per cell Phi^ and sum_q w_q Y^, budget partials,
+//    block maxima of the next operand scale; finalize and budget kernels follow.
+//    Its time hardly depends on K's width: BF16 4 x 64, 400^2, 151 us with one level coupled and
+//    195 with a whole ring of five (294 by the tables of the kernel above), 2 x 64, dense 114 (152),
+//    4 x 32, dense 123 (174), 8 x 64, 200^2, a fifth of K 99 (120); FP16 4 x 64, 400^2, dense 191
+//    (385).  What bounds it: each B operand is read from LDS by n_az / 16 waves.
+// ---------------------------------------------------------------------------
+// (lanes at the row's edge get 0; the kernel takes their value from the edge ring)
+__device__ __forceinline__ float dpp_from_left(float v) {   // lane l gets lane l - 1 (row of 16)
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x111, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float dpp_from_right(float v) {  // lane l gets lane l + 1 (row of 16)
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x101, 0xF, 0xF, true));
+}
+
+template <int A, int DT, int R>
+__global__ __launch_bounds__(band_lp_threads(A)) void banded_lp_kernel(BatchArgs B) {
+    constexpr int MT = A / 16, NT = kBandCells / 16, KS = band_lp_ksteps(A), TERMS = DT == 1 ? 2 : 1;
+    constexpr int NW = MT * NT, T = NW * 64;
+    constexpr int KC = 4 * KS;                // 16-byte chunks of 8 azimuths a cell holds
+    constexpr int NS = 2 * R + 2, NE = R + 3, NP = 2 * R + 1;
+    constexpr int XSLOT = band_lp_slot(A);    // elements per ring slot and term:
+                                              // [chunk][cell][8 azimuths]
+    constexpr int FR = NP * MT * 64;          // uint4 of A operands (NP pair slots)
+    constexpr int FRX = FR + A / 2;           // and the (cx, cy) table: uint4 per buffer
+    constexpr int FSL = (2 * kBandMaxReach + 1) * MT * 64;   // uint4 of a level's slots
+    constexpr int CPT = (FRX + T - 1) / T;    // uint4 staged per thread
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    uint16_t* xr = reinterpret_cast<uint16_t*>(lds_raw);
+    uint4* fr = reinterpret_cast<uint4*>(lds_raw + (size_t)NS * TERMS * XSLOT * 2);
+    float* edge = reinterpret_cast<float*>(lds_raw + (size_t)NS * TERMS * XSLOT * 2 + (size_t)2 * FRX * 16);
+    int pi, local;
+    if (!locate(B, KT_SC, xcd_remap(blockIdx.x, gridDim.x), pi, local)) return;
+    const StepArgs a = args_of(B, pi);   // by value: no reloads after stores
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int mt = wave % MT, nt = wave / MT;
+    const int g = lane >> 4, cl = lane & 15;
+    const int a0 = 16 * mt + 4 * g;      // the lane's first azimuth
+    const int cc = 16 * nt + cl;         // its cell within the block
+    const int nx = a.nx, ny = a.ny, L = a.n_lev, RE = a.reach;
+    const int C = (int)a.C;
+    const int64_t P = a.P;
+    const int cell = local * kBandCells + cc;
+    const bool in = cell < C;
+    const ASN_G QInfo* __restrict__ qtab = gp(a.qi);
+    const ASN_K QInfo* qk = kp(a.qi);
+    const ASN_K uint4* ldesc = kp(a.bpairs);
+    const ASN_G uint4* __restrict__ frag = gp(a.bfrag);
+    const ASN_K float* rdk = kp(a.rdef);   // r_q, the same for every ordinate of a level
+
+    float4 cf = make_float4(0.f, 0.f, 0.f, 0.f);
+    float ihv = 0.f, dv = 0.f;   // iso^ = Phi^ / W and the pending correction of the cell
+    if (in) {
+        cf = gp(a.coef)[cell];
+        ihv = gp(a.iso)[cell];
+        dv = gp(a.delta)[cell];
+    }
+    float s_in, s_out;   // the cell's operand scale 2^(E - e_b) and its inverse
+    {
+        const float bm = in ? __uint_as_float(gp(a.bmax_cur)[cell >> a.sb_log]) : 0.f;
+        int e = 0;
+        if (bm > 0.f) (void)frexpf(bm, &e);
+        e = max(e, -100);
+        s_in = ldexpf(1.f, kScaleExp - e);
+        s_out = ldexpf(1.f, e - kScaleExp);
+    }
+    const float ivs = ihv * s_in;
+    const int y = cell / nx, x = cell - y * nx;
+    const int e = in ? ((x == 0 ? 1 : 0) | (x == nx - 1 ? 2 : 0) | (y == 0 ? 4 : 0) |
+                        (y == ny - 1 ? 8 : 0))
+                     : 0;
+    const bool wedge = __ballot(e != 0) != 0;
+    const uint32_t lvl_bytes = (uint32_t)(A * P * 4), pb = (uint32_t)(P * 4);
+    const uint32_t off0 = 4u * (uint32_t)(a0 * P) + 4u * (uint32_t)cell;
+    // the lane's four azimuths lie in one quadrant (n_az / 4 is a multiple of 4): one
+    // y-upwind cell; its offsets yoff + o pb (from kOOB they stay past every plane: a
+    // level holds under 2^31 bytes, and 3 pb more stays below 2^32)
+    uint32_t yoff;
+    float ydl;   // pending correction of the y-upwind cell
+    bool tl[4], tr[4], ox[4], oy[4];
+    {
+        const int d = qtab[a0].dir;
+        const int yc = (d & 4) ? cell - nx : cell + nx;
+        const bool yv = in && yc >= 0 && yc < C;
+        ydl = yv ? gp(a.delta)[yc] : 0.f;
+        yoff = yv ? off0 + 4u * (uint32_t)(yc - cell) : kOOB;
+    }
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+        const int d = qtab[a0 + o].dir;
+        const bool gx = !in || (d & e & 3) != 0;
+        tl[o] = !gx && (d & 1);
+        tr[o] = !gx && !(d & 1);
+        const int go = (((d & 5) << 1) | ((d & 10) >> 1)) & e;   // outflow faces of d
+        ox[o] = in && (go & 3);
+        oy[o] = in && (go & 12);
+    }
+    // the block's halo cells, one value a lane: in tile 0 lanes 0 .. 3 of each row of 16
+    // read azimuth a0 + cl of the cell before the block, in the last tile lanes 12 .. 15
+    // azimuth a0 + cl - 12 of the cell after it (the other lanes' halo offsets read 0)
+    const bool hlo = nt == 0 && cl < 4, hhi = nt == NT - 1 && cl >= 12;
+    const int hcell = hlo ? local * kBandCells - 1 : local * kBandCells + kBandCells;
+    const int haz = a0 + (hlo ? cl : cl - 12);
+    const bool hvalid = (hlo || hhi) && hcell >= 0 && hcell < (int)P;
+    const float hdl = (hvalid && hcell < C) ? gp(a.delta)[hcell] : 0.f;
+    const uint32_t hoff = hvalid ? 4u * (uint32_t)(haz * P) + 4u * (uint32_t)hcell : kOOB;
+    const int hslot = hlo ? haz : (NT + NT - 1) * A + haz;   // its place in an edge slot
+    const size_t lvl_floats = (size_t)A * (size_t)P;
+    auto level_rsrc = [&](const float* base) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)lvl_bytes, kRsrcWord3);
+    };
+
+    struct Fill {
+        float v[4], h;
+    };
+    auto fetch = [&](int l, Fill& f) {
+        const __amdgpu_buffer_rsrc_t r = level_rsrc(a.psi + (size_t)l * lvl_floats);
+#pragma unroll
+        for (int o = 0; o < 4; ++o) f.v[o] = load_plane(r, off0 + (uint32_t)o * pb);
+        f.h = load_plane(r, hoff);
+    };
+    // the lane's four azimuths of level l into the ring (rounded operand terms) and the
+    // tile-edge values (true state psi^ + delta) its neighbours need
+    auto put = [&](int l, const Fill& f) {
+        uint16_t* xs = xr + (size_t)(l % NS) * TERMS * XSLOT + ((a0 >> 3) * kBandCells + cc) * 8 + (a0 & 7);
+        float xv[4];
+#pragma unroll
+        for (int o = 0; o < 4; ++o) xv[o] = __builtin_fmaf(f.v[o], s_in, -ivs);
+        uint2 pk;
+        pk.x = pack2<DT>(xv[0], xv[1]);
+        pk.y = pack2<DT>(xv[2], xv[3]);
+        *reinterpret_cast<uint2*>(xs) = pk;
+        if constexpr (DT == 1) {
+            uint2 pl;
+            pl.x = bf16_residual2(pk.x, xv[0], xv[1]);
+            pl.y = bf16_residual2(pk.y, xv[2], xv[3]);
+            *reinterpret_cast<uint2*>(xs + XSLOT) = pl;
+        }
+        float* es = edge + (size_t)(l % NE) * 2 * NT * A;
+        if (cl == 15 && nt < NT - 1) {   // the left neighbour of the next tile
+            float* d = es + (nt + 1) * A + a0;
+#pragma unroll
+            for (int o = 0; o < 4; ++o) d[o] = f.v[o] + dv;
+        }
+        if (cl == 0 && nt > 0) {         // the right neighbour of the previous tile
+            float* d = es + (NT + nt - 1) * A + a0;
+#pragma unroll
+            for (int o = 0; o < 4; ++o) d[o] = f.v[o] + dv;
+        }
+        if (hlo || hhi) es[hslot] = f.h + hdl;   // the block's halo
+    };
+    // block l of the operand table into buffer l & 1 (thread t moves uint4 t and t + T):
+    // level l's A operands (2 kBandMaxReach + 1 pair slots, the coupled pairs first; the
+    // kernel runs the first NP, those past a problem's pairs hold zero operands), then the
+    // (cx, cy) of level l - 1's ordinates, read by the update that runs one level behind.
+    // Block n_lev holds the last level's (cx, cy).
+    static_assert(CPT <= 2, "at most two staged uint4 per thread");
+    auto src_of = [&](int x) { return x < FR ? x : FSL + (x - FR); };
+    auto fetch_frag = [&](int l, uint4& f0, uint4& f1) {
+        const ASN_G uint4* src = frag + ldesc[2 * l].y;
+        f0 = src[src_of(FRX >= T ? tid : min(tid, FRX - 1))];
+        if constexpr (CPT > 1) f1 = src[src_of(min(tid + T, FRX - 1))];
+    };
+    auto put_frag = [&](int l, const uint4& f0, const uint4& f1) {
+        uint4* dst = fr + (size_t)(l & 1) * FRX;
+        if (FRX >= T || tid < FRX) dst[tid] = f0;
+        if constexpr (CPT > 1) if (tid + T < FRX) dst[tid + T] = f1;
+    };
+    // the next update's inputs: the lane's own four values (from the register queue), the
+    // y-upwind values and the level's r_q and weight (its (cx, cy) come from LDS)
+    struct Ahead {
+        float v[4], y[4];
+        float rq;
+        double w;
+    };
+    auto fetch_ahead = [&](int l, Ahead& ah) {
+        const __amdgpu_buffer_rsrc_t r = level_rsrc(a.psi + (size_t)l * lvl_floats);
+        const int q0 = l * A;
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+            ah.y[o] = load_plane(r, yoff + (uint32_t)o * pb);
+        }
+        ah.rq = rdk[q0];
+        ah.w = qk[q0].w;
+    };
+
+    // n_az not a multiple of 32: the last k-step reads azimuths past n_az, which the ring
+    // holds at zero (the A operands' wrapped values there multiply zeros)
+    if constexpr (A % 32 != 0) {
+        uint4* z = reinterpret_cast<uint4*>(xr);
+        constexpr int NZ = NS * TERMS * XSLOT * 2 / 16;
+        for (int t = tid; t < NZ; t += T) z[t] = make_uint4(0u, 0u, 0u, 0u);
+        lds_barrier();
+    }
+    // The level loop runs one level behind in its update: pass i contracts level i and
+    // updates level i - 1 with the products of the pass before, two independent streams
+    // (LDS reads and MFMA; VALU, DPP and stores) interleaved in one schedule.  The edge
+    // ring is reach + 3 levels deep: a level's edges stay until its lagging update has
+    // read them.
+    // the lane's own unrounded values of the levels in the ring ahead of the update
+    // (levels i + 1 .. i + R + 1 at the end of pass i)
+    float fifo[R + 1][4];
+    {   // prologue: levels 0 .. R into the ring and the queue, level 0's operands
+        Fill f;
+#pragma unroll
+        for (int l = 0; l <= R; ++l) {
+            fetch(min(l, L - 1), f);
+            if (l < L) put(l, f);
+#pragma unroll
+            for (int o = 0; o < 4; ++o) fifo[l][o] = f.v[o];
+        }
+        uint4 g0, g1;
+        fetch_frag(0, g0, g1);
+        put_frag(0, g0, g1);
+    }
+    Fill pre;
+    fetch(min(R + 1, L - 1), pre);
+    uint4 fp0, fp1;
+    fetch_frag(1, fp0, fp1);
+    Ahead ah;
+    lds_barrier();
+
+    double phacc = 0.0, ypacc = 0.0, defect = 0.0, outflow = 0.0;
+    float mx = 0.f;
+    const int mtk0 = ((0 - mt) % MT + MT) % MT;   // fragment of k-step 0: offset (32 kt - 16 mt) mod A
+    // B operand of k-step kt: chunk g + 4 kt of the lane's cell (16 lanes of a row read
+    // 256 contiguous bytes)
+    const uint16_t* xl = xr + (g * kBandCells + cc) * 8;
+    static_assert(KC * kBandCells * 8 == XSLOT, "ring slot layout");
+    static_assert(A * 256 <= NS * TERMS * XSLOT * 2, "the final partials fit in the ring");
+    // level i's products: every pair slot, k-steps of 32 azimuths, operand terms
+    struct Ops {
+        uint4 a[KS], b[KS];
+        const uint16_t* xs;
+    };
+    struct Pass {
+        uint32_t kcodes;
+        int sb;
+        const uint4* fl;
+    };
+    auto pass_of = [&](int i) {
+        Pass ps;
+        ps.kcodes = ldesc[2 * i].z;
+        ps.fl = fr + (size_t)(i & 1) * FRX + lane;
+        // ring slot of level i - RE (k = 0); a pair's partner i - RE + k sits k slots on
+        ps.sb = ((i - RE) % NS + NS) % NS;
+        return ps;
+    };
+    // a pair's A operands and its first operand term; the second term (BF16) is read
+    // into the same registers after the first term's products
+    auto load_pair = [&](const Pass& ps, int p, Ops& op) {
+        int sl = ps.sb + (int)((ps.kcodes >> (4 * p)) & 15u);
+        sl = sl >= NS ? sl - NS : sl;
+        op.xs = xl + (size_t)sl * TERMS * XSLOT;
+#pragma unroll
+        for (int kt = 0; kt < KS; ++kt) op.a[kt] = ps.fl[(p * MT + (mtk0 + 2 * kt) % MT) * 64];
+#pragma unroll
+        for (int kt = 0; kt < KS; ++kt)
+            op.b[kt] = *reinterpret_cast<const uint4*>(op.xs + 4 * kBandCells * 8 * kt);
+    };
+    auto load_term = [&](int t, Ops& op) {
+#pragma unroll
+        for (int kt = 0; kt < KS; ++kt)
+            op.b[kt] = *reinterpret_cast<const uint4*>(op.xs + t * XSLOT + 4 * kBandCells * 8 * kt);
+    };
+    auto mul_term = [&](const Ops& op, f32x4& acc) {
+#pragma unroll
+        for (int kt = 0; kt < KS; ++kt) acc = mfma_lp<DT>(op.a[kt], op.b[kt], acc);
+    };
+    auto mul_pair = [&](Ops& op, f32x4& acc) {   // (no overlap with other work)
+        mul_term(op, acc);
+#pragma unroll
+        for (int t = 1; t < TERMS; ++t) {
+            load_term(t, op);
+            mul_term(op, acc);
+        }
+    };
+    // the update of the lane's four outputs of level j (as the fused reduced-precision form):
+    //   v = psi^ + delta, dev = psi^ - iso^, Y^ - iso^ = s_out acc + r_q dev
+    //   col = gs ((iso^ + Y^ - iso^) - psi^) + bs (iso^ - psi^)
+    //   new = v - cx (v - ux) - cy (v - uy) - aa v + col + ss
+    // (the look-ahead values hold level j)
+    struct Upd {
+        __amdgpu_buffer_rsrc_t ro;
+        const float* es;   // the level's edge slot at the lane's tile and azimuths
+        const float2* cxy;   // the level's (cx, cy) at the lane's azimuths
+        float colsum, yas;
+        double ph;
+    };
+    auto upd_begin = [&](int j, Upd& u) {
+        u.es = edge + (size_t)(j % NE) * 2 * NT * A + nt * A + a0;
+        u.cxy = reinterpret_cast<const float2*>(fr + (size_t)((j + 1) & 1) * FRX + FR) + a0;
+        u.ro = level_rsrc(a.psi_new + (size_t)j * lvl_floats);
+        u.colsum = 0.f;
+        u.yas = 0.f;
+        u.ph = 0.0;
+    };
+    auto upd_out = [&](int o, const f32x4& acc, Upd& u) {
+        const float vh = ah.v[o];
+        const float v = vh + dv;
+        // the row shifts run in every lane (a lane whose neighbour is inactive would read
+        // 0), then the row's edge lanes (0 and 15) take the edge ring's value
+        const float dl = dpp_from_left(v), dr = dpp_from_right(v);
+        const float left = cl == 0 ? u.es[o] : dl;
+        const float right = cl == 15 ? u.es[NT * A + o] : dr;
+        const float ux = tl[o] ? left : (tr[o] ? right : 0.f);
+        const float uy = ah.y[o] + ydl;
+        const float dev = vh - ihv;
+        const float ya = s_out * acc[o] + ah.rq * dev;
+        const float col = cf.z * ((ihv + ya) - vh) + cf.y * (ihv - vh);
+        // a padding cell (not in) has psi^ = delta = iso^ = 0, zero coefficients, zero
+        // operands and ghosts: its update is 0 without a select
+        const float2 c = u.cxy[o];
+        const float nv = v - c.x * (v - ux) - c.y * (v - uy) - cf.x * v + col + cf.w;
+        // a wave writes half of each 128-byte line, a sibling wave the other half: the L2
+        // joins them (non-temporal stores wrote 1.4x the bytes)
+        store_plane(nv, u.ro, off0 + (uint32_t)o * pb);
+        u.ph += (double)nv;
+        u.yas += ya;
+        u.colsum += col;
+        mx = fmaxf(mx, fabsf(nv));
+    };
+    auto upd_end = [&](const Upd& u) {
+        phacc += ah.w * u.ph;
+        // sum over the four outputs of Y^ = iso^ + delta + (Y^ - iso^); the deviations,
+        // small against iso^, summed in FP32
+        ypacc += ah.w * ((in ? 4.0 * (double)(ihv + dv) : 0.0) + (double)u.yas);
+        defect += ah.w * (double)u.colsum;
+    };
+    // the outflow of the level just updated (the look-ahead values still hold it)
+    auto outflow_of = [&](const Upd& u) {
+        if (wedge) {
+            float ob = 0.f;
+#pragma unroll
+            for (int o = 0; o < 4; ++o) {
+                const float v = ah.v[o] + dv;
+                const float2 c = u.cxy[o];
+                ob += (ox[o] ? c.x * v : 0.f) + (oy[o] ? c.y * v : 0.f);
+            }
+            outflow += ah.w * (double)ob;
+        }
+    };
+    // the end of pass i: level i + R + 1 goes into the ring slot level i - R - 1 held and
+    // the queue, level i leaves the queue for the next pass's update, loads for the next
+    // passes
+    auto advance = [&](int i) {
+        if (i + R + 1 < L) put(i + R + 1, pre);
+        fetch_ahead(i, ah);
+#pragma unroll
+        for (int o = 0; o < 4; ++o) ah.v[o] = fifo[0][o];
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+#pragma unroll
+            for (int o = 0; o < 4; ++o) fifo[q][o] = fifo[q + 1][o];
+#pragma unroll
+        for (int o = 0; o < 4; ++o) fifo[R][o] = pre.v[o];
+        fetch(min(i + R + 2, L - 1), pre);
+        lds_barrier();
+    };
+
+    f32x4 accp = {0.f, 0.f, 0.f, 0.f};
+    {   // pass 0: products only
+        put_frag(1, fp0, fp1);
+        fetch_frag(min(2, L), fp0, fp1);
+        const Pass ps = pass_of(0);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            Ops op;
+            load_pair(ps, p, op);
+            mul_pair(op, accp);
+        }
+        advance(0);
+    }
+    for (int i = 1; i < L; ++i) {
+        // block i + 1 of the operand table (its buffer's last readers passed the barrier)
+        put_frag(i + 1, fp0, fp1);
+        fetch_frag(min(i + 2, L), fp0, fp1);
+        // pass i in chunks the scheduler may not merge: chunk p reads pair p's operands,
+        // updates output p of level i - 1 while they arrive, then multiplies pair p (the
+        // MFMAs run on while the next chunk issues)
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        const Pass ps = pass_of(i);
+        Upd u;
+        upd_begin(i - 1, u);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            __builtin_amdgcn_sched_barrier(0);
+            Ops op;
+            load_pair(ps, p, op);
+            if (p < 4) upd_out(p, accp, u);
+            mul_term(op, acc);
+#pragma unroll
+            for (int t = 1; t < TERMS; ++t) {
+                load_term(t, op);
+                mul_term(op, acc);
+            }
+        }
+#pragma unroll
+        for (int o = NP; o < 4; ++o) upd_out(o, accp, u);
+        __builtin_amdgcn_sched_barrier(0);
+        upd_end(u);
+        accp = acc;
+        outflow_of(u);
+        advance(i);
+    }
+    {
+        Upd u;
+        upd_begin(L - 1, u);
+#pragma unroll
+        for (int o = 0; o < 4; ++o) upd_out(o, accp, u);
+        upd_end(u);
+        outflow_of(u);
+    }
+
+    // per cell Phi^ and sum_q w_q Y^: the (n_az / 4) lane groups' partials in a fixed order
+    double* red = reinterpret_cast<double*>(lds_raw);
+    red[(4 * mt + g) * kBandCells + cc] = phacc;
+    red[(A / 4 + 4 * mt + g) * kBandCells + cc] = ypacc;
+    lds_barrier();
+    if (tid < kBandCells) {
+        const int c = local * kBandCells + tid;
+        if (c < C) {
+            double s = red[tid], sy = red[(A / 4) * kBandCells + tid];
+#pragma unroll
+            for (int k = 1; k < A / 4; ++k) {
+                s += red[k * kBandCells + tid];
+                sy += red[(A / 4 + k) * kBandCells + tid];
+            }
+            gp(a.phi_part)[c] = s;
+            gp(a.ypart)[c] = sy;
+        }
+    }
+    // block max |psi^{n+1}| of the next operand scale: the block's cells lie in one block
+    const unsigned mbits = wave_max_u32(__float_as_uint(mx));
+    if (lane == 0 && mbits) atomicMax(&a.bmax_next[(local * kBandCells) >> a.sb_log], mbits);
+    double sums[2] = {defect, outflow};
+    block_sum_waves<NW, 2>(sums, gp(a.blk_part) + 2 * (size_t)local);
+}
+
+// ---------------------------------------------------------------------------
+// 7. Step for any ordinate set whose K is sparse and whose values at 64 cells fit LDS
 //    (forward Euler; FP32 Heun).
 //    A K with 13 % nonzeros (162 ordinates of the icosahedron: 21 a row) leaves the matrix cores
 //    nearly all zeros whatever the tile, and few ordinates leave most of a 128-row tile empty.
@@ -2802,7 +3261,7 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void sparse_step_kernel(BatchA
 static inline unsigned div_up(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
 void blocks_per_kind(const StepArgs& a, int out[KT_COUNT]) {
-    const bool banded = a.band != nullptr;
+    const bool banded = a.band != nullptr || a.bfrag != nullptr;
     out[KT_GEMM] = banded ? 0 : (a.Qp / kGemmBM) * (int)(a.P / kGemmBN);
     out[KT_FIX] = (a.dtype != 0 && !a.fused) ? a.fin_blocks : 0;
     out[KT_SC] = (a.fused && !banded) ? 0 : a.tiles_x * a.tiles_y * a.G;
@@ -2839,6 +3298,42 @@ static hipError_t with_banded(int az, int dtype, int reach, int heun, F&& f) {
     if (reach <= 1) return f(BandedInstance<1, 1024, 2, 0>{});
     if (reach == 2) return f(BandedInstance<2, 1024, 2, 0>{});
     return small ? f(BandedInstance<3, 512, 2, 0>{}) : f(BandedInstance<3, 1024, 2, 0>{});
+}
+
+// The same of the banded step on the matrix cores.
+template <int A, int DT, int R>
+struct BandedLpInstance {
+    static constexpr auto kernel = banded_lp_kernel<A, DT, R>;
+    static void name(char* out, size_t n) { std::snprintf(out, n, "banded_lp_kernel<%d, %d, %d>", A, DT, R); }
+};
+template <int A, int DT, typename F>
+static hipError_t with_banded_lp_a(int reach, F&& f) {
+    switch (reach) {
+        case 0: return f(BandedLpInstance<A, DT, 0>{});
+        case 1: return f(BandedLpInstance<A, DT, 1>{});
+        case 2: return f(BandedLpInstance<A, DT, 2>{});
+        case 3: return f(BandedLpInstance<A, DT, 3>{});
+        default: return hipErrorInvalidValue;
+    }
+}
+template <typename F>
+static hipError_t with_banded_lp(int az, int dtype, int reach, F&& f) {
+    if (az == 32) return dtype == 1 ? with_banded_lp_a<32, 1>(reach, f) : with_banded_lp_a<32, 2>(reach, f);
+    if (az == 48) return dtype == 1 ? with_banded_lp_a<48, 1>(reach, f) : with_banded_lp_a<48, 2>(reach, f);
+    if (az == 64) return dtype == 1 ? with_banded_lp_a<64, 1>(reach, f) : with_banded_lp_a<64, 2>(reach, f);
+    return hipErrorInvalidValue;
+}
+static hipError_t launch_banded_lp(const BatchArgs& b, int blocks, int az, int dtype, hipStream_t s, int reach) {
+    return with_banded_lp(az, dtype, reach, [&](auto i) {
+        i.kernel<<<blocks, band_lp_threads(az), band_lp_lds_bytes(az, reach, dtype), s>>>(b);
+        return hipSuccess;
+    });
+}
+hipError_t prepare_banded_lp(int az, int dtype, int reach) {
+    return with_banded_lp(az, dtype, reach, [&](auto i) {
+        return hipFuncSetAttribute((const void*)i.kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)band_lp_lds_bytes(az, reach, dtype));
+    });
 }
 
 // heun: 0, or the pass.
@@ -2897,8 +3392,9 @@ hipError_t prepare_sparse(int waves, int dtype, bool heun) {
 
 // Stencil kinds of a pass: 0 donor-cell strips, 1 / 2 Heun stages (strips), 3 donor-cell
 // flat chunks, 4 / 5 Heun stages (flat chunks), kStencilBanded the banded Euler step and + 1,
-// + 2 the banded Heun passes (contraction and stencil in one kernel), kStencilSparse likewise.
-constexpr int kStencilBanded = 16, kStencilSparse = 32;
+// + 2 the banded Heun passes (contraction and stencil in one kernel), kStencilSparse likewise,
+// kStencilBandedLp the banded step on the matrix cores (in one kernel too, then finalize and budget).
+constexpr int kStencilBanded = 16, kStencilSparse = 32, kStencilBandedLp = 64;
 
 // One pass: contraction, stencil, finalize, budget.
 static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, int stencil,
@@ -2908,6 +3404,17 @@ static hipError_t launch_pass(const BatchArgs& b, const int* grid, int dtype, in
     auto mark = [&](int k) {
         if (ev && e == hipSuccess) e = hipEventRecord(ev[k], s);
     };
+    if (stencil == kStencilBandedLp) {
+        mark(0);
+        e = launch_banded_lp(b, grid[KT_SC], band_az, dtype, s, band_reach);
+        mark(1);
+        mark(2);
+        if (e == hipSuccess) finalize_kernel<<<grid[KT_FIN], 256, 0, s>>>(b, 0);
+        mark(3);
+        if (e == hipSuccess) budget_kernel<<<b.n, kBudgetThreads, 0, s>>>(b, bud, false);
+        mark(4);
+        return e != hipSuccess ? e : hipGetLastError();
+    }
     if (stencil >= kStencilBanded) {   // contraction and stencil in one kernel
         mark(0);
         e = stencil >= kStencilSparse
@@ -2968,6 +3475,8 @@ hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int schem
     if (scheme == SCHEME_EULER_BANDED || scheme == SCHEME_EULER_SPARSE)
         return launch_pass(b, grid, dtype, scheme == SCHEME_EULER_SPARSE ? kStencilSparse : kStencilBanded,
                            BUD_STEP, s, ev, band_az, band_lds, band_reach);
+    if (scheme == SCHEME_EULER_BANDED_LP)
+        return launch_pass(b, grid, dtype, kStencilBandedLp, BUD_STEP, s, ev, band_az, band_lds, band_reach);
     if (passes_per_step(scheme) == 1)
         return launch_pass(b, grid, dtype, scheme == SCHEME_EULER_FLAT ? 3 : 0, BUD_STEP, s, ev);
     // stencil of the first pass
@@ -2991,6 +3500,8 @@ void contraction_kernel(int dtype, int scheme, bool fused, int band_az, int band
     };
     if (scheme == SCHEME_EULER_BANDED || scheme == SCHEME_HEUN_BANDED)
         (void)with_banded(band_az, dtype, band_reach, heun, name);
+    else if (scheme == SCHEME_EULER_BANDED_LP)
+        (void)with_banded_lp(band_az, dtype, band_reach, name);
     else if (scheme == SCHEME_EULER_SPARSE || scheme == SCHEME_HEUN_SPARSE)
         (void)with_sparse(band_az / kBandO, dtype, heun, name);
     else if (dtype == 0)
@@ -3000,7 +3511,7 @@ void contraction_kernel(int dtype, int scheme, bool fused, int band_az, int band
 }
 
 hipError_t launch_last_budget(const BatchArgs& b, int n_steps, int scheme, hipStream_t s) {
-    if (scheme < SCHEME_EULER_BANDED || n_steps < 1) return hipSuccess;
+    if (scheme < SCHEME_EULER_BANDED || scheme == SCHEME_EULER_BANDED_LP || n_steps < 1) return hipSuccess;
     const bool heun = passes_per_step(scheme) == 2;
     BatchArgs l = b;
     l.step = n_steps - 1;

@@ -88,6 +88,33 @@ inline size_t band_lds_bytes(int az, int dtype, bool heun) {
     return (size_t)(dtype == 0 ? 2 : 4) * az * band_row(heun) * 4;
 }
 
+// The banded BF16 / FP16 step on the matrix cores (MFMA 16x16x32, FP32 accumulate): a block owns
+// kBandCells consecutive cells and every ordinate; wave (m, n) produces azimuths 16 m .. 16 m + 15
+// of cells 16 n .. 16 n + 15.  Per level pair (i, j) the circulant block of the stored K is
+// multiplied as A operands of 16 x 32 (one per 16-azimuth offset, built on the host:
+// band_lp_fragments) with the quantised partner level as B operand.
+constexpr int SCHEME_EULER_BANDED_LP = 9;
+// k-steps of 32 azimuths a level pair takes (48 azimuths: two, the second half-padded)
+__host__ __device__ constexpr int band_lp_ksteps(int az) { return (az + 31) / 32; }
+__host__ __device__ constexpr int band_lp_threads(int az) { return (az / 16) * (kBandCells / 16) * 64; }
+// 16-bit elements of a slot of the quantised-level ring (one level, one operand term): the
+// 8-azimuth chunks of every k-step (the padding past n_az held at zero), each chunk the
+// block's cells in a row ([chunk][cell][8]: 16 lanes reading one chunk of 16 cells read
+// 256 contiguous bytes)
+__host__ __device__ constexpr int band_lp_slot(int az) { return 4 * band_lp_ksteps(az) * kBandCells * 8; }
+// Dynamic LDS of its block (at most 152 KB, for any reach that band_supported takes): the ring of
+// 2 reach + 2 quantised levels (two operand terms for BF16), two buffers of a level's A operands (at
+// most 2 reach + 1 pairs, n_az / 16 fragments of 1 KiB each, and the previous level's (cx, cy)), the
+// ring of tile-edge values (reach + 3 levels).
+inline size_t band_lp_lds_bytes(int az, int reach, int dtype) {
+    const int terms = dtype == 1 ? 2 : 1, mt = az / 16, nt = kBandCells / 16;
+    return (size_t)(2 * reach + 2) * terms * band_lp_slot(az) * 2 +
+           (size_t)2 * ((2 * reach + 1) * mt * 1024 + az * 8) + (size_t)(reach + 3) * 2 * nt * az * 4;
+}
+// uint4 of a level's block in its operand table: 2 kBandMaxReach + 1 pair slots, the (cx, cy) of
+// the level before.
+inline size_t band_lp_block(int az) { return (size_t)(2 * kBandMaxReach + 1) * (az / 16) * 64 + az / 2; }
+
 // A step's form for any ordinate set with a sparse K, also one kernel a pass (Heun: FP32).  A block
 // owns kBandCells cells and every ordinate, whose values (BF16 / FP16: rounded operands) are all in
 // LDS, a row each, so their number is bounded by it.  Tables: sparse_form (asn_host.hpp).
@@ -199,6 +226,12 @@ struct StepArgs {
     const float* bcoef7;
     const float2* bcxy;
     int n_lev, n_az, reach;
+    // on the matrix cores (then `band` is not set): per level and one more, two uint4 {pairs, first
+    // uint4 of its block in bfrag, the level offsets k of its pair slots (4 bits each), 0}; per level
+    // pair and 16-azimuth offset the A operand of MFMA 16x16x32 as 64 lanes x 8 16-bit values
+    // (band_lp_fragments)
+    const uint4* bpairs;
+    const uint4* bfrag;
     // sparse step (then also `band` is set and n_az such that the budget's fold has its threads):
     // groups of ordinates, per position in them what the step takes of an ordinate, LDS byte
     // offsets of the sources' rows and their coefficients, kBandO a source
@@ -249,7 +282,8 @@ hipError_t launch_step(const BatchArgs& b, const int* grid, int dtype, int schem
 // and reach, to the most that any problem of that instance takes (a limit set for one problem
 // would hold for a larger one that is still alive).
 hipError_t prepare_banded(int band_az, int dtype, int reach, bool heun);
-// The same of the sparse kernel of so many waves.
+// The same of the banded kernel on the matrix cores and of the sparse kernel of so many waves.
+hipError_t prepare_banded_lp(int band_az, int dtype, int reach);
 hipError_t prepare_sparse(int waves, int dtype, bool heun);
 // Passes per step of a scheme.
 inline int passes_per_step(int scheme) {
