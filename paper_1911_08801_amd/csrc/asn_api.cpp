@@ -94,6 +94,41 @@ int64_t plane_pitch(int64_t C, int azim) {
 // 137), 78 sources 144 (196; BF16 150 and 149), 177 sources 251 (235).  Up to 170 ordinates it is the
 // faster one at a dense K too (200^2 x 162 70 and 86, BF16 73 and 77; x 92 28 and 45).
 int sparse_sources(int Q) { return Q <= 170 ? Q : 64; }
+// ... and at most in a large problem, where the tiled contraction's launches and its last wave of
+// blocks no longer count: there the matrix cores are faster at a dense K.  A step of 1 M
+// cell-ordinates takes the sparse kernel about 1.8 us (2.4 and 3.0 with two and one block a CU) and
+// 0.033 to 0.042 for each source, the tiled one 4.4 to 7 us by its nonzero blocks (tiles: columns of
+// K that a tile of 128 rows multiplies, mean; pad: of rows, 128 at a time).  Sparse over tiled time
+// of a step at 5, 16, 31 and 80 M cell-ordinates (the fused form, square grids):
+//   128 ordinates, dense: FP32 0.77 1.01 1.01 1.07, BF16 0.88 1.19 1.33 1.31, Heun 0.81 1.06 0.99 0.87
+//   76 sources of 128: FP32 0.59 0.76 0.74 0.81, BF16 0.64 0.85 0.99 0.98
+//   92 ordinates, dense: FP32 0.80 0.75 0.88 0.92, BF16 0.70 0.83 1.02 1.02
+//   162 ordinates, dense: FP32 0.91 0.88 0.87 0.86, BF16 0.95 1.16 1.14 1.17, FP16 0.94 1.20 1.18 1.20
+//   256, 60 sources, 192 columns: BF16 0.75 0.84 0.95 1.02; 252, 55, 224: 0.72 0.74 0.86 0.90
+//   512, 45 sources, 224 columns: BF16 0.62 0.77 0.91 0.98 (1.04 at 128 M), 58: 0.70 0.87 1.01 1.09
+//   492, 50 sources, 304 columns: BF16 0.67 0.69 0.79 0.85; 362, FP16, 31, 235: 0.45 0.77 0.98 0.94
+double sparse_sources_large(int Q, int dtype, bool heun, int64_t cells, double tiles) {
+    const double m = 1e-6 * (double)cells * Q, pad = (double)round_up(Q, asn::kGemmBM) / Q;
+    const double any = (double)round_up(sparse_sources(Q), asn::kSparseChunk);
+    if (dtype == ASN_GEMM_F32) return Q <= 170 && m > 12.0 && (!heun || m <= 28.0) ? std::min(any, 118.0 * pad) : any;
+    if (Q <= 170) return m > 8.0 ? std::min(any, 75.0 * pad) : any;
+    const bool bf16 = dtype == ASN_GEMM_BF16;
+    const double per_column = asn::sparse_waves(Q) == 8 ? (bf16 ? 0.29 : 0.26) : (bf16 ? 0.196 : 0.16);
+    return m > 64.0 ? std::min(any, per_column * tiles * pad) : any;
+}
+// Columns of K that a 128-row tile of the reduced-precision contraction multiplies, 32 at a time, mean.
+double tile_columns(int Q, const std::vector<float>& K32) {
+    const int bm = asn::kGemmBM, bk = asn::kBK_LP;
+    int64_t n = 0;
+    for (int q0 = 0; q0 < Q; q0 += bm)
+        for (int k0 = 0; k0 < Q; k0 += bk) {
+            bool any = false;
+            for (int q = q0; q < std::min(Q, q0 + bm) && !any; ++q)
+                for (int k = k0; k < std::min(Q, k0 + bk) && !any; ++k) any = K32[(size_t)q * Q + k] != 0.f;
+            n += any;
+        }
+    return (double)(n * bk) / (double)(round_up(Q, bm) / bm);
+}
 // Groups of the sparse step, and the chunks of sources it takes at most (the larger its K's
 // unions, the less it is worth), with the one that the kernel loads beyond the last.
 size_t sparse_groups(int Q) { return ((size_t)Q + asn::kBandO - 1) / asn::kBandO; }
@@ -711,7 +746,10 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         for (int q = 0; banded && !matrix && p->dtype != ASN_GEMM_F32 && q < Q; ++q)
             rdef[(size_t)q] = (float)((double)rdef[(size_t)q] - gain[(size_t)(q / quad->n_azim)]);
         sparse = sparse && !banded &&
-                 asn::sparse_form(Q, K32.data(), asn::kBandO, asn::kSparseChunk, sparse_chunks(Q) - 1, sf);
+                 asn::sparse_form(Q, K32.data(), asn::kBandO, asn::kSparseChunk, sparse_chunks(Q) - 1, sf) &&
+                 (double)sf.first.back() * asn::kSparseChunk <=
+                     (double)sparse_groups(Q) * sparse_sources_large(Q, p->dtype, p->scheme == ASN_SCHEME_HEUN, C,
+                                                                     tile_columns(Q, K32));
     }
     if (opt.step_form == ASN_FORM_BANDED && !banded) {
         delete p;

@@ -108,3 +108,40 @@ def test_larger_problem_steps_after_a_smaller_one_is_created(large, small, dtype
     assert np.array_equal(asn.asn_get_state(p), state)
     p.close()
     q.close()
+
+
+@pytest.mark.parametrize("n,n_polar,n_azim,ico,beta,dtype,scheme,kernel", [
+    (200, 2, 64, 0, 80.0, "bf16", "euler", "sparse"), (500, 2, 64, 0, 80.0, "bf16", "euler", "gemm_lp_kernel<1, true>"),
+    (500, 2, 64, 0, 80.0, "f32", "euler", "gemm_f32_kernel<true>"), (500, 2, 64, 0, 4.5, "bf16", "euler", "sparse"),
+    (200, 1, 4, 5, 80.0, "f16", "euler", "sparse"), (500, 1, 4, 5, 80.0, "f16", "euler", "gemm_lp_kernel<2, true>"),
+    (500, 1, 4, 5, 80.0, "f32", "euler", "sparse"), (500, 1, 4, 5, 10.0, "bf16", "euler", "sparse"),
+    (200, 16, 32, 0, 7.0, "bf16", "euler", "sparse"), (500, 16, 32, 0, 7.0, "bf16", "euler", "gemm_lp_kernel<1, true>"),
+    (500, 16, 32, 0, 7.0, "f32", "euler", "sparse"), (500, 8, 64, 0, 13.0, "f16", "euler", "gemm_lp_kernel<2, true>"),
+    (500, 1, 4, 8, 7.0, "bf16", "euler", "sparse"), (400, 4, 32, 0, 40.0, "f32", "heun", "gemm_f32_kernel<false>"),
+    (800, 4, 32, 0, 40.0, "f32", "heun", "sparse")])
+def test_the_faster_kernel_is_taken(n, n_polar, n_azim, ico, beta, dtype, scheme, kernel):
+    # both measured, 3 to 30 % apart: large problems with a K that is dense for their ordinates
+    # go to the tiled contraction
+    spec = wl.random_problem(3, n, n, n_polar=n_polar, n_azim=n_azim, beta=beta)
+    spec.ico_order = ico
+    p = asn.from_spec(spec, dtype=dtype, scheme=scheme, form="fused", set_initial_state=False)
+    assert asn.asn_step_kernel(p).startswith(kernel)
+    p.close()
+
+
+def test_batch_of_sizes_that_take_different_kernels_equals_alone_bitwise():
+    specs = [_spec(nx, ny, 2, 64, 0, 80.0)[0] for nx, ny in ((20, 9), (330, 330), (64, 3))]
+    kw = dict(dtype="bf16", form="fused")
+    alone = []
+    for spec in specs:
+        p = asn.from_spec(spec, **kw)
+        asn.asn_step(p, 3)
+        alone.append((asn.asn_get_state(p), asn.asn_mass_budget(p)))
+        p.close()
+    probs = [asn.from_spec(s, **kw) for s in specs]
+    assert [asn.asn_step_kernel(p)[:6] for p in probs] == ["sparse", "gemm_l", "sparse"]
+    asn.asn_step_batch(probs, 3)
+    for p, (state, bud) in zip(probs, alone):
+        assert np.array_equal(asn.asn_get_state(p), state)
+        assert asn.asn_mass_budget(p) == bud
+        p.close()
