@@ -548,6 +548,19 @@ bool band_candidate(int dtype, int scheme, int form, const asn_quadrature* q, in
            q->q_custom == 0 && q->icosahedron_order == 0 && q->n_polar >= 1;
 }
 
+// Whether the Heun passes of a product set of few levels leave the banded kernel, which takes two
+// levels' time beyond the set's and whose blocks of n_azim / 4 waves leave a CU's 16 wave slots empty
+// (24, 40 to 56 azimuths) or start and end at once (64), to the sparse one: from 2 M cell-ordinates on
+// that is the faster one, and the banded one slower than separate kernels at large grids.  Us a step
+// banded, sparse, separate: 2 x 64, 400^2, beta 4.5 240, 138, 209, beta 20 324, 247, 252; 800^2 dense
+// 1343, 973, 1110; 2 x 40 dense, 800^2 842, 481, 683; 1 x 24, 800^2 288, 153, 202; 3 x 40 dense, 800^2
+// 1189, 884, 1044.  2 x 32 (dense, 800^2 435, 366, 544), 3 x 32 (596, 618, 805), 3 x 48 (1351, 1166, 1641)
+// and more levels stay banded.
+bool heun_few_levels(const asn_quadrature* q, int64_t C) {
+    const int l = q->n_polar, az = q->n_azim;
+    return (double)C * l * az >= 2e6 && az >= 24 && (l == 1 || (l == 2 && az != 32) || (l == 3 && az == 40));
+}
+
 // Bytes that either layout of the banded step needs.
 size_t band_layouts(const asn_grid& g, const asn_quadrature& q, int Q, int dtype, int scheme) {
     size_t bytes = make_layout(g.nx, g.ny, Q, dtype, scheme, false, q.n_polar, q.n_azim).total;
@@ -715,7 +728,8 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
     std::vector<double> gain;
     asn::SparseForm sf;
     bool sparse = sparse_candidate(p->dtype, p->scheme, opt.step_form, Q, C);
-    const bool may_band = band_candidate(p->dtype, p->scheme, opt.step_form, quad, C);
+    const bool may_band = band_candidate(p->dtype, p->scheme, opt.step_form, quad, C) &&
+                          !(p->scheme == ASN_SCHEME_HEUN && heun_few_levels(quad, C));
     const int Qp = (int)round_up(Q, asn::kGemmBM);
     std::vector<uint16_t> Klp;   // BF16 / FP16 K and its row defects
     std::vector<float> rdef((size_t)Qp, 0.f);
