@@ -89,6 +89,19 @@ int64_t plane_pitch(int64_t C, int azim) {
     return (pad ? v : u) * asn::kScaleBlock;
 }
 
+// Columns of K that a 128-row tile of the reduced-precision contraction multiplies, 32 at a time, mean.
+double tile_columns(int Q, const std::vector<float>& K32) {
+    const int bm = asn::kGemmBM, bk = asn::kBK_LP;
+    int64_t n = 0;
+    for (int q0 = 0; q0 < Q; q0 += bm)
+        for (int k0 = 0; k0 < Q; k0 += bk) {
+            bool any = false;
+            for (int q = q0; q < std::min(Q, q0 + bm) && !any; ++q)
+                for (int k = k0; k < std::min(Q, k0 + bk) && !any; ++k) any = K32[(size_t)q * Q + k] != 0.f;
+            n += any;
+        }
+    return (double)(n * bk) / (double)(round_up(Q, bm) / bm);
+}
 // Mean sources of a group of the sparse step at most.  Its time goes with their number, the tiled
 // contraction's with its nonzero blocks: 200^2 x 492, us a step, 33 sources 96 (tiled 155; BF16 96 and
 // 137), 78 sources 144 (196; BF16 150 and 149), 177 sources 251 (235).  Up to 170 ordinates it is the
@@ -107,27 +120,14 @@ int sparse_sources(int Q) { return Q <= 170 ? Q : 64; }
 //   256, 60 sources, 192 columns: BF16 0.75 0.84 0.95 1.02; 252, 55, 224: 0.72 0.74 0.86 0.90
 //   512, 45 sources, 224 columns: BF16 0.62 0.77 0.91 0.98 (1.04 at 128 M), 58: 0.70 0.87 1.01 1.09
 //   492, 50 sources, 304 columns: BF16 0.67 0.69 0.79 0.85; 362, FP16, 31, 235: 0.45 0.77 0.98 0.94
-double sparse_sources_large(int Q, int dtype, bool heun, int64_t cells, double tiles) {
+double sparse_sources_large(int Q, int dtype, bool heun, int64_t cells, const std::vector<float>& K32) {
     const double m = 1e-6 * (double)cells * Q, pad = (double)round_up(Q, asn::kGemmBM) / Q;
     const double any = (double)round_up(sparse_sources(Q), asn::kSparseChunk);
     if (dtype == ASN_GEMM_F32) return Q <= 170 && m > 12.0 && (!heun || m <= 28.0) ? std::min(any, 118.0 * pad) : any;
     if (Q <= 170) return m > 8.0 ? std::min(any, 75.0 * pad) : any;
     const bool bf16 = dtype == ASN_GEMM_BF16;
     const double per_column = asn::sparse_waves(Q) == 8 ? (bf16 ? 0.29 : 0.26) : (bf16 ? 0.196 : 0.16);
-    return m > 64.0 ? std::min(any, per_column * tiles * pad) : any;
-}
-// Columns of K that a 128-row tile of the reduced-precision contraction multiplies, 32 at a time, mean.
-double tile_columns(int Q, const std::vector<float>& K32) {
-    const int bm = asn::kGemmBM, bk = asn::kBK_LP;
-    int64_t n = 0;
-    for (int q0 = 0; q0 < Q; q0 += bm)
-        for (int k0 = 0; k0 < Q; k0 += bk) {
-            bool any = false;
-            for (int q = q0; q < std::min(Q, q0 + bm) && !any; ++q)
-                for (int k = k0; k < std::min(Q, k0 + bk) && !any; ++k) any = K32[(size_t)q * Q + k] != 0.f;
-            n += any;
-        }
-    return (double)(n * bk) / (double)(round_up(Q, bm) / bm);
+    return m > 64.0 ? std::min(any, per_column * tile_columns(Q, K32) * pad) : any;
 }
 // Groups of the sparse step, and the chunks of sources it takes at most (the larger its K's
 // unions, the less it is worth), with the one that the kernel loads beyond the last.
@@ -762,8 +762,7 @@ asn_status asn_create(const asn_grid* grid, const asn_quadrature* quad, const fl
         sparse = sparse && !banded &&
                  asn::sparse_form(Q, K32.data(), asn::kBandO, asn::kSparseChunk, sparse_chunks(Q) - 1, sf) &&
                  (double)sf.first.back() * asn::kSparseChunk <=
-                     (double)sparse_groups(Q) * sparse_sources_large(Q, p->dtype, p->scheme == ASN_SCHEME_HEUN, C,
-                                                                     tile_columns(Q, K32));
+                     (double)sparse_groups(Q) * sparse_sources_large(Q, p->dtype, p->scheme == ASN_SCHEME_HEUN, C, K32);
     }
     if (opt.step_form == ASN_FORM_BANDED && !banded) {
         delete p;

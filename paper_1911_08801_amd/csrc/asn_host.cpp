@@ -405,11 +405,24 @@ bool sparse_form(int Q, const float* K32, int width, int chunk, size_t max_chunk
     std::vector<uint64_t> bits(words * Q, 0);   // sources of each ordinate
     size_t nz = 0;
     for (int q = 0; q < Q; ++q)
-        for (int k = 0; k < Q; ++k)
-            if (K32[(size_t)q * Q + k] != 0.f) {
-                bits[q * words + k / 64] |= 1ull << (k % 64);
-                ++nz;
+        for (size_t w = 0; w < words; ++w) {
+            const float* row = K32 + (size_t)q * Q + 64 * w;
+            const int n = std::min<int>(64, Q - 64 * (int)w);
+            uint8_t set[64] = {};
+            for (int k = 0; k < n; ++k) set[k] = row[k] != 0.f;
+            uint64_t b = 0;
+            for (int k = 0; k < 64; k += 8) {   // eight flags to eight bits
+                uint64_t f;
+                std::memcpy(&f, set + k, 8);
+                b |= f * 0x0102040810204080ull >> 56 << k;
             }
+            bits[q * words + w] = b;
+            if (b) nz += __builtin_popcountll(b);
+        }
+    auto each = [&](const uint64_t* row, auto&& f) {   // set bits, ascending
+        for (size_t w = 0; w < words; ++w)
+            for (uint64_t b = row[w]; b; b &= b - 1) f((int)(64 * w) + __builtin_ctzll(b));
+    };
     if (nz > max_chunks * chunk * width) return false;
     out = SparseForm();
     out.first.push_back(0);
@@ -426,7 +439,7 @@ bool sparse_form(int Q, const float* K32, int width, int chunk, size_t max_chunk
                 if (taken[q]) return;
                 int c = 0;
                 for (size_t w = 0; w < words; ++w)
-                    c += __builtin_popcountll(bits[q * words + w] & ~have[w]);
+                    if (const uint64_t b = bits[q * words + w] & ~have[w]) c += __builtin_popcountll(b);
                 if (best < 0 || c < cost) {
                     best = q;
                     cost = c;
@@ -434,9 +447,7 @@ bool sparse_form(int Q, const float* K32, int width, int chunk, size_t max_chunk
             };
             if (n == 0) best = next;
             else {
-                const float* row = K32 + (size_t)out.order[at] * Q;
-                for (int q = 0; q < Q; ++q)
-                    if (row[q] != 0.f) consider(q);
+                each(&bits[out.order[at] * words], consider);
                 for (int q = next; best < 0 && q < Q; ++q)
                     if (!taken[q]) best = q;
             }
@@ -447,8 +458,7 @@ bool sparse_form(int Q, const float* K32, int width, int chunk, size_t max_chunk
         }
         while ((int)(out.order.size() - at) < width) out.order.push_back(out.order[at]);
         const size_t base = out.src.size();
-        for (int k = 0; k < Q; ++k)
-            if (have[k / 64] >> (k % 64) & 1) out.src.push_back(k);
+        each(have.data(), [&](int k) { out.src.push_back(k); });
         while ((out.src.size() - base) % chunk) out.src.push_back(out.src[base]);
         out.first.push_back((int)(out.src.size() / chunk));
         if (out.src.size() > max_chunks * chunk) return false;

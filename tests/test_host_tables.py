@@ -37,3 +37,14 @@ BANDED = [(1, 8, "f32", 4.5), (2, 8, "f32", 2.0), (4, 8, "f32", 40.0), (8, 16, "
 def test_row_defect_of_the_coefficients_multiplied(tables, n_polar, n_azim, dtype, beta):
     # c(-d) one number of the operand type above c(d), of which the kernel multiplies the latter
     assert tables("defect", n_polar, n_azim, DTYPES[dtype], beta) == ""
+
+
+# (n_polar, n_azim, icosahedron order, operand type, beta): ordinates that fill the last group or
+# not, and the last 64-ordinate word or not; a sparse and a dense K
+SPARSE = [(1, 2, 0, "f32", 4.5), (5, 10, 0, "bf16", 4.5), (8, 16, 0, "f16", 9.0), (1, 4, 2, "f32", 4.5),
+          (1, 4, 3, "f16", 4.5), (1, 4, 5, "f32", 4.5), (1, 4, 5, "f32", 80.0), (1, 4, 7, "bf16", 4.5)]
+
+
+@pytest.mark.parametrize("n_polar,n_azim,ico,dtype,beta", SPARSE)
+def test_sparse_tables_give_the_stored_kernel_back(tables, n_polar, n_azim, ico, dtype, beta):
+    assert tables("sparse", n_polar, n_azim, ico, DTYPES[dtype], beta, 4, 8) == ""
