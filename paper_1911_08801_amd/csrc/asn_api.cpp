@@ -1658,7 +1658,7 @@ asn_status asn_band_expand(int32_t n_polar, int32_t n_azim, const double* k_in, 
     asn::BandForm bf;
     if (!asn::band_form(n_polar, n_azim, K32.data(), asn::kBandMaxReach, asn::kBandNarrow, bf))
         return fail(ASN_E_UNSUPPORTED, "K has no banded form");
-    // decode the per-level descriptors the kernel reads
+    // decode the per-level runs that the kernels' tables are made of
     std::fill(k_out, k_out + (size_t)Q * Q, 0.f);
     auto put_run = [&](int i, int k, int lo, int len, int first) {
         const int j = i + k - bf.reach;

@@ -39,6 +39,12 @@ def test_row_defect_of_the_coefficients_multiplied(tables, n_polar, n_azim, dtyp
     assert tables("defect", n_polar, n_azim, DTYPES[dtype], beta) == ""
 
 
+@pytest.mark.parametrize("n_polar,n_azim,dtype,beta", BANDED)
+def test_banded_tables_give_the_stored_kernel_back(tables, n_polar, n_azim, dtype, beta):
+    # from each reach's table, by its offsets, flags and step counts, +-d one coefficient
+    assert tables("band", n_polar, n_azim, DTYPES[dtype], beta) == ""
+
+
 # (n_polar, n_azim, icosahedron order, operand type, beta): ordinates that fill the last group or
 # not, and the last 64-ordinate word or not; a sparse and a dense K
 SPARSE = [(1, 2, 0, "f32", 4.5), (5, 10, 0, "bf16", 4.5), (8, 16, 0, "f16", 9.0), (1, 4, 2, "f32", 4.5),
