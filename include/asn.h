@@ -105,7 +105,7 @@ enum { ASN_DT_STREAMING = 0, ASN_DT_STIFF = 1 };
  *                    levels is circulant along the azimuth, and K couples only nearby
  *                    levels (forward peak, Section 3.5 notes S_as^+ is sparse).  One kernel
  *                    per step applies K as short circular convolutions on the vector units
- *                    and the update, reading psi^n once.  FP32: n_azim in {8, 16, ..., 64}.
+ *                    and the update in one pass over psi^n.  FP32: n_azim in {8, 16, ..., 64}.
  *                    BF16 / FP16: the rounded operands and the rounded K (the same rounding
  *                    recipe and pending per-cell correction as ASN_FORM_FUSED), n_azim 32,
  *                    48 or 64; where K is wide, each coupled pair's circulant block on the
@@ -274,8 +274,8 @@ asn_status asn_iteration_counts(asn_problem p, int64_t* sweeps, int64_t* matvecs
  * duration per step of kernel k: 0 the ordinate contraction Y = K Psi, 1 stream
  * + collide, 2 moment finalize, 3 budget fold (for ASN_SCHEME_HEUN, the sum over
  * its two passes; the steps of banded_euler_kernel and sparse_step_kernel, see
- * asn_step_kernel, do all of it in kernel 0, but for the last step's fold); kernel_ms[4] the average span of a whole step.  Measurement
- * support for benchmarks; results equal asn_step.
+ * asn_step_kernel, do all of it in kernel 0, but for the last step's fold); kernel_ms[4] the
+ * average span of a whole step.  Measurement support for benchmarks; results equal asn_step.
  * Errors: ASN_E_INVALID (n_steps < 1), ASN_E_HIP. */
 asn_status asn_step_timed(asn_problem p, int64_t n_steps, double kernel_ms[5]);
 

@@ -532,7 +532,7 @@ bool use_fused(int dtype, int scheme, int form, int nx, int ny, int Q) {
 
 // Whether a problem may take the banded step: forward Euler, or Heun in FP32 unless separate
 // kernels were asked for (its form is reported as separate either way), on a product set whose
-// azimuth count has a kernel instance (FP32: 8 .. 64 in steps of 8; BF16 / FP16: 32 or
+// azimuth count has a kernel instance (FP32: 8 .. 64 in steps of 8; BF16 / FP16: 32, 48 or
 // 64) (ASN_FORM_AUTO or ASN_FORM_BANDED); the stored K must then also have the banded
 // form (band_form).
 bool band_candidate(int dtype, int scheme, int form, const asn_quadrature* q, int64_t C) {

@@ -364,7 +364,6 @@ bool band_form(int levels, int azim, const float* K32, int max_reach, int narrow
     out.levels = levels;
     out.azim = azim;
     out.reach = reach;
-    out.cmax = 0;
     out.desc.assign((size_t)levels * 8, 0u);
     out.range.assign((size_t)levels * 2, 0);
     out.coef.clear();
@@ -395,7 +394,6 @@ bool band_form(int levels, int azim, const float* K32, int max_reach, int narrow
         out.range[2 * (size_t)i] = base;
         out.range[2 * (size_t)i + 1] = (int)out.coef.size() - base;
         if ((int)out.coef.size() - base > 508) return false;
-        out.cmax = std::max(out.cmax, (int)out.coef.size() - base);
     }
     return true;
 }

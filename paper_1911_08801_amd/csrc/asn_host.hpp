@@ -44,10 +44,10 @@ bool kernel_matrix(int Q, const double* omega, const double* w, double eps, int 
 //   bits 0-5   s (azim / 2 for a whole ring)       bit 6  wide: whole ring or s > narrow_max
 //   bit 7      whole ring                          bits 8-10  k
 //   bits 11-17 the run's start within the level, in units of 4 coefficients.
-// cmax is the largest coefficient count of a level; reach the largest |i - j| with a
-// nonzero.
+// reach is the largest |i - j| with a nonzero.  The padding and bit 6 are what asn_contraction_work
+// counts an FP32 banded step by; the kernels' tables are made of the runs alone.
 struct BandForm {
-    int levels = 0, azim = 0, reach = 0, cmax = 0;
+    int levels = 0, azim = 0, reach = 0;
     std::vector<uint32_t> desc;
     std::vector<int32_t> range;
     std::vector<float> coef;

@@ -1984,10 +1984,13 @@ __global__ __launch_bounds__(256) void broadcast_kernel(float* psi, const float*
 //    What bounds it: memory and VALU issue together.  At 1024^2 x 2048 the pass without its
 //    loads and stores takes 3.7 ms (203 VALU instructions a wave and level, half of them in
 //    the four levels at either pole, which couple up to the whole ring), without its
-//    convolution 4.4 ms, as a whole 5.2 ms (3.3 TB/s on 8 B per update; a 4 GiB copy
-//    reaches 4.9); 400^2 x 512 0.172 ms (3.8 TB/s), 700^2 x 1152 1.36 ms.  The direct form
-//    (gathering per output level, all levels within reach in LDS) took 6.85, 0.289 and
-//    2.23 ms.  Two levels of loads in flight, flags between neighbouring waves instead of
+//    convolution 4.4 ms, as a whole 5.2 ms (all three before the planes' pitch was padded, 5.0 ms
+//    with that: 3.4 TB/s on 8 B per update; a 4 GiB copy reaches 4.9, and the y-upwind rows, which
+//    the L2 no longer holds at this width, make it 10.0 B moved: 4.3 TB/s); 400^2 x 512 0.172 ms
+//    (3.8 TB/s), 700^2 x 1152 1.36 ms.  The direct form (gathering per output level, all levels
+//    within reach in LDS) took 6.85, 0.289 and 2.23 ms.  The instances of reach 3 for more than 32
+//    azimuths spill, 13 registers in FP32 and 43 in FP16: 32 x 64 azimuths beta 9, 256^2 cells, FP32
+//    554 us (reach 2 at beta 4.5: 319; the direct form 884 and 441).  Two levels of loads in flight, flags between neighbouring waves instead of
 //    the barrier, and loads issued at the start of a pass instead of its end were all
 //    slower: what they add in registers and instructions costs more than they hide.
 //    BF16 / FP16 operands: the recipe of the fused reduced-precision form (the state is
@@ -3308,13 +3311,12 @@ struct BandedLpInstance {
 };
 template <int A, int DT, typename F>
 static hipError_t with_banded_lp_a(int reach, F&& f) {
-    switch (reach) {
-        case 0: return f(BandedLpInstance<A, DT, 0>{});
-        case 1: return f(BandedLpInstance<A, DT, 1>{});
-        case 2: return f(BandedLpInstance<A, DT, 2>{});
-        case 3: return f(BandedLpInstance<A, DT, 3>{});
-        default: return hipErrorInvalidValue;
-    }
+    if (reach < 0 || !band_supported(A, DT, reach, false)) return hipErrorInvalidValue;
+    if (reach == 0) return f(BandedLpInstance<A, DT, 0>{});
+    if (reach == 1) return f(BandedLpInstance<A, DT, 1>{});
+    if (reach == 2) return f(BandedLpInstance<A, DT, 2>{});
+    if constexpr (DT == 2 || A == 32) return f(BandedLpInstance<A, DT, 3>{});
+    return hipErrorInvalidValue;
 }
 template <typename F>
 static hipError_t with_banded_lp(int az, int dtype, int reach, F&& f) {

@@ -70,7 +70,7 @@ constexpr int kBandO = 4;
 // (Heun passes: two neighbours on either side)
 __host__ __device__ constexpr int band_row(bool heun) { return kBandCells + (heun ? 4 : 2); }
 constexpr int kBandMaxReach = 3;
-// Largest half-width of the pair codes marked narrow by band_form (asn_host.hpp).
+// Largest half-width of the pair codes that band_form (asn_host.hpp) marks narrow.
 constexpr int kBandNarrow = 8;
 // Azimuth counts the step takes: FP32 8 .. 64 in steps of 8, BF16 / FP16 32, 48 or 64; BF16
 // at 48 or 64 azimuths couples levels at most 2 apart.
@@ -213,7 +213,7 @@ struct StepArgs {
                             // of the stored state and phi64 the true Phi
     float* delta_next;      // [P] banded: that of the new state (delta follows the psi buffer)
     unsigned* bmax_cur;     // block max |psi^n| (read by the GEMM), follows the psi buffer; per
-                            // scale block, banded: per 64 cells
+                            // scale block, banded and sparse: per 64 cells
     unsigned* bmax_next;    // block max |psi^{n+1}| (written by the stencil)
     double* rec;
     // banded step (product ordinate sets): n_lev levels of n_az azimuths, coupling
