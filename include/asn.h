@@ -117,9 +117,10 @@ enum { ASN_DT_STREAMING = 0, ASN_DT_STIFF = 1 };
  *                    fuses smaller problems, the faster forms on MI355X at the sizes
  *                    measured.  asn_workspace_size covers every form AUTO may take.
  * AUTO and FUSED: where one block holds every ordinate (up to 632) and K is sparse (or there
- * are few ordinates), one kernel that multiplies K's nonzeros takes the place of the fused or
- * separate kernels, whose form it reports; FP32 Heun passes likewise, and banded on product
- * sets with an azimuth count above. */
+ * are few ordinates; the larger the problem, the sparser), one kernel that multiplies K's
+ * nonzeros takes the place of the fused or separate kernels, whose form it reports; FP32 Heun
+ * passes likewise, and banded on product sets with an azimuth count above (of more than a few
+ * levels at large grids).  asn_step_kernel names the kernel. */
 enum { ASN_FORM_AUTO = 0, ASN_FORM_SEPARATE = 1, ASN_FORM_FUSED = 2, ASN_FORM_BANDED = 3 };
 
 #define ASN_BUDGET_LEN 8

@@ -86,9 +86,9 @@ bool band_scatter_tables(const BandForm& bf, int dtype, std::vector<uint32_t>& d
 // operands wait in LDS, and with fewer azimuths, of which the tables sum fewer; lower up to 32 M
 // cell-ordinates, where both states stay in the 256 MB cache, which the tables' kernel writes past;
 // higher below about 15 M, where the matrix form's two further launches and its start count.  Us a
-// step, tables and matrix: BF16 4 x 64 azimuths, 400^2 cells, 21 products 161 and 154, 33: 172 and
-// 164, 51: 206 and 168, 101: 294 and 195; 8 x 64, 200^2, 19: 73 and 87, 66: 120 and 99; 16 x 32,
-// 400^2, 22: 207 and 250, 50: 384 and 377; FP16 4 x 64, 400^2, 147 (reach 3): 385 and 191.
+// step, tables and matrix: BF16 4 x 64 azimuths, 400^2 cells, 21 products 161 and 154, 33: 177 and
+// 170, 51: 215 and 177, 101: 294 and 205; 8 x 64, 200^2, 19: 75 and 90, 66: 123 and 106; 16 x 32,
+// 400^2, 22: 217 and 263, 50: 384 and 378; FP16 4 x 64, 400^2, 147 (reach 3): 385 and 201.
 bool band_on_matrix_cores(const BandForm& bf, const std::vector<uint32_t>& desc, int64_t cells);
 // The A operands of MFMA 16x16x32 for pair `pair` of level `level` of a banded form of
 // the BF16 (dtype 1) or FP16 (dtype 2) K: the pair's circulant block C[a][a'] =

@@ -2589,10 +2589,10 @@ __global__ __launch_bounds__(T) void banded_euler_kernel(BatchArgs B) {
 //    halo loads) fill at the same time.  Outputs as the fused form:
 //    psi^{n+1} without its correction, per cell Phi^ and sum_q w_q Y^, budget partials,
 //    block maxima of the next operand scale; finalize and budget kernels follow.
-//    Its time hardly depends on K's width: BF16 4 x 64, 400^2, 151 us with one level coupled and
-//    195 with a whole ring of five (294 by the tables of the kernel above), 2 x 64, dense 114 (152),
-//    4 x 32, dense 123 (174), 8 x 64, 200^2, a fifth of K 99 (120); FP16 4 x 64, 400^2, dense 191
-//    (385).  What bounds it: each B operand is read from LDS by n_az / 16 waves.
+//    Its time hardly depends on K's width: BF16 4 x 64, 400^2, 154 us with one level coupled and
+//    205 with whole rings of three to four (294 by the tables of the kernel above), 2 x 64, dense 116
+//    (152), 4 x 32, dense 122 (174), 8 x 64, 200^2, a fifth of K 106 (123); FP16 4 x 64, 400^2, dense
+//    201 (385).  What bounds it: each B operand is read from LDS by n_az / 16 waves.
 // ---------------------------------------------------------------------------
 // (lanes at the row's edge get 0; the kernel takes their value from the edge ring)
 __device__ __forceinline__ float dpp_from_left(float v) {   // lane l gets lane l - 1 (row of 16)
@@ -3036,7 +3036,7 @@ __global__ __launch_bounds__(band_lp_threads(A)) void banded_lp_kernel(BatchArgs
 //    sources (sparse_form: 32 for those four) and multiplies the union of their rows' nonzeros:
 //    an LDS value serves four outputs, coefficients are scalar.  The neighbours' values are loaded
 //    beside the products, from L2.  The rest of the step as in the banded kernel.
-//    What bounds it: 280^2 x 162 takes 43 us (2.4 TB/s on 8 B per update); without the products
+//    What bounds it: 280^2 x 162 takes 46 us (2.2 TB/s on 8 B per update); without the products
 //    26 us, without scalar misses the products alone would be 21 us of VALU issue.  The two
 //    overlap only between a CU's blocks (three at 162 ordinates), which start together.  A chunk
 //    of eight sources a trip to the scalar tables instead of four: 55 -> 47 us; ten waves a block
